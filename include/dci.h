@@ -15,7 +15,7 @@
  *    there and are read by zero-copy on a cache miss (Section IV, framework paragraph).
  *  - The library allocates no device memory.  Temporary device memory comes from the workspace
  *    handed to dci_create(); the dci_*_workspace_bytes() queries say how much each call needs.
- *    (A context owns a few HIP events and 64 bytes of pinned host memory; dci_timing_enable
+ *    (A context owns a few dozen HIP events and 128 bytes of pinned host memory; dci_timing_enable
  *    creates events on first use.)
  *  - Calls enqueue work on the context's HIP stream and return without waiting, except
  *    dci_fill_caches(), which waits for completion because the cache sizes it reports are
@@ -240,7 +240,7 @@ enum {
   DCI_K_LINEAR_IN = 6,   /* first layer (input features): dense layer (matrix cores) */
   DCI_K_MEAN = 7,        /* later layers: neighbour mean                            */
   DCI_K_LINEAR = 8,      /* later layers: dense layer                               */
-  DCI_K_COUNT_NODES = 9, /* pre-sampling: visits of the input nodes                 */
+  DCI_K_COUNT_NODES = 9, /* pre-sampling: visits of the input nodes (counted by the closing kernel: no launches of its own) */
   DCI_K_COUNT = 10
 };
 #define DCI_TIMING_MAX_LAUNCHES 8192

@@ -79,7 +79,8 @@ int32_t dci_create(dci_ctx** out, int32_t device, void* hip_stream, void* worksp
   if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
   if (e == hipSuccess) {
     ctx->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    for (int i = 0; i < 3 && e == hipSuccess; ++i) e = hipEventCreate(&ctx->ev[i]);
+    for (hipEvent_t& ev : ctx->ev)
+      if (e == hipSuccess) e = hipEventCreate(&ev);
   }
   if (e == hipSuccess) {
     void* p = nullptr;
@@ -88,15 +89,16 @@ int32_t dci_create(dci_ctx** out, int32_t device, void* hip_stream, void* worksp
   }
   if (e == hipSuccess) {
     void* p = nullptr;
-    e = hipHostMalloc(&p, 64, hipHostMallocDefault);
+    e = hipHostMalloc(&p, 128, hipHostMallocDefault);
     if (e == hipSuccess) {
       ctx->host_flag = static_cast<unsigned*>(p);
+      ctx->host_scal = reinterpret_cast<unsigned long long*>(static_cast<char*>(p) + 64);
       *ctx->host_flag = 0u;
     }
   }
   if (e != hipSuccess) {
-    for (int i = 0; i < 3; ++i)
-      if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
+    for (hipEvent_t ev : ctx->ev)
+      if (ev) (void)hipEventDestroy(ev);
     if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
     delete ctx;
     return DCI_ERR_HIP;
@@ -124,8 +126,8 @@ int32_t dci_set_workspace(dci_ctx* ctx, void* workspace, size_t workspace_bytes)
 void dci_destroy(dci_ctx* ctx) {
   if (!ctx) return;
   if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
-  for (int i = 0; i < 3; ++i)
-    if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
+  for (hipEvent_t ev : ctx->ev)
+    if (ev) (void)hipEventDestroy(ev);
   if (ctx->t_events) {
     for (int i = 0; i < 2 * DCI_TIMING_MAX_LAUNCHES; ++i)
       if (ctx->t_events[i]) (void)hipEventDestroy(ctx->t_events[i]);

@@ -108,27 +108,68 @@ static int32_t device_scan(dci_ctx* ctx, long long n, In in, Out out, u64* tile_
 static inline long long scan_tiles_for(long long n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
 // ---- reductions -----------------------------------------------------------------------------
-// scal[0] += sum(count), scal[1] = max(scal[1], max(count)), scal[3] += number of non-zero counts
-__global__ __launch_bounds__(kFillBlock) void k_sum_max(const u32* __restrict__ count, long long n, u64* scal) {
-  u64 s = 0, nz = 0;
-  u32 m = 0;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    const u32 c = count[i];
-    s += c;
-    nz += c != 0;
-    m = c > m ? c : m;
-  }
-  s = wave_sum_u64(s);
-  nz = wave_sum_u64(nz);
+// Sum, maximum and number of non-zero values of one or two counter arrays (blockIdx.y picks the array).  Bound by
+// the read of the counters (4 bytes per node).  The workgroups leave one triple each and k_count_fold, one
+// workgroup per array, adds them up: with atomics on three words instead, 16,384 wavefronts queue on one L2 line
+// (2.4 M nodes: 581 us for 10 MB; this pair takes 8 us).
+struct CountTotals {
+  u64 sum, max, nonzero;
+};
+constexpr int kCountBlocks = 1024;  // most workgroups per array: four per compute unit keep enough loads in flight
+
+__device__ __forceinline__ void block_fold_counts(CountTotals& t) {
+  __shared__ CountTotals part[kFillBlock / kWave];
+  t.sum = wave_sum_u64(t.sum);
+  t.nonzero = wave_sum_u64(t.nonzero);
 #pragma unroll
   for (int d = kWave / 2; d >= 1; d >>= 1) {
-    const u32 o = __shfl_down(m, d, kWave);
-    m = o > m ? o : m;
+    const u64 o = __shfl_down(t.max, d, kWave);
+    t.max = o > t.max ? o : t.max;
   }
-  if (lane_id() == 0) {
-    if (s) atomicAdd(&scal[0], s);
-    if (m) atomicMax(&scal[1], (u64)m);
-    if (nz) atomicAdd(&scal[3], nz);
+  if (lane_id() == 0) part[threadIdx.x / kWave] = t;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < kFillBlock / kWave; ++w) {
+      t.sum += part[w].sum;
+      t.nonzero += part[w].nonzero;
+      t.max = part[w].max > t.max ? part[w].max : t.max;
+    }
+}
+
+__global__ __launch_bounds__(kFillBlock) void k_count_totals(const u32* __restrict__ count0, const u32* __restrict__ count1,
+                                                             long long n, CountTotals* __restrict__ parts) {
+  const u32* __restrict__ count = blockIdx.y ? count1 : count0;
+  CountTotals t = {0, 0, 0};
+  const long long stride = (long long)gridDim.x * kFillBlock;
+  for (long long i = blockIdx.x * (long long)kFillBlock + threadIdx.x; i < n; i += 4 * stride) {
+    u32 c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = i + k * stride < n ? count[i + k * stride] : 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      t.sum += c[k];
+      t.nonzero += c[k] != 0;
+      t.max = c[k] > t.max ? c[k] : t.max;
+    }
+  }
+  block_fold_counts(t);
+  if (threadIdx.x == 0) parts[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = t;
+}
+
+// totals[blockIdx.x] on the device (the scans read the sum there) and in pinned host memory
+__global__ __launch_bounds__(kFillBlock) void k_count_fold(const CountTotals* __restrict__ parts, int n_parts,
+                                                           CountTotals* __restrict__ totals, CountTotals* host_totals) {
+  CountTotals t = {0, 0, 0};
+  for (int i = (int)threadIdx.x; i < n_parts; i += kFillBlock) {
+    const CountTotals p = parts[(size_t)blockIdx.x * n_parts + i];
+    t.sum += p.sum;
+    t.nonzero += p.nonzero;
+    t.max = p.max > t.max ? p.max : t.max;
+  }
+  block_fold_counts(t);
+  if (threadIdx.x == 0) {
+    totals[blockIdx.x] = t;
+    host_totals[blockIdx.x] = t;
   }
 }
 
@@ -332,10 +373,10 @@ static int32_t resort_by_key(dci_ctx* ctx, const int* ids_in, const u32* key_by_
 
 struct AboveIn {
   const u32* count;
-  const u64* scal;  // [0] = total
+  const CountTotals* totals;
   u64 n;
   __device__ __forceinline__ u64 operator()(long long v) const {
-    return ((u64)count[v] * n > scal[0]) ? 1u : 0u;  // count < 2^32 and n < 2^31: no overflow
+    return ((u64)count[v] * n > totals->sum) ? 1u : 0u;  // count < 2^32 and n < 2^31: no overflow
   }
 };
 struct MeanRemapOut {
@@ -398,43 +439,94 @@ struct AdjOut {
   int* remap;
   long long* c_indptr;  // start of the region reserved for it (N+1 entries available)
   u64 c_adj;
-  u64* scal;  // [2] = number of cached nodes, written by the last cached position
+  u64* cached;  // pinned host memory: [0] cached nodes, [1] their elements, written by the last cached position
   const u32* deg;
   long long n;
   __device__ __forceinline__ void operator()(long long s, u64 excl, u64 cost) const {
     const u64 P = 8ull + excl + cost;
     const bool in = P <= c_adj;
     remap[order[s]] = in ? (int)s : -1;
+    if (s == 0) c_indptr[0] = 0;
     if (in) {
-      c_indptr[s + 1] = (long long)((P - 8ull - 8ull * (u64)(s + 1)) / 8ull);
+      const u64 elements = (P - 8ull - 8ull * (u64)(s + 1)) / 8ull;
+      c_indptr[s + 1] = (long long)elements;
       const bool next_in = s + 1 < n && P + 8ull * deg[order[s + 1]] + 8ull <= c_adj;
-      if (!next_in) scal[2] = (u64)(s + 1);
+      if (!next_in) {
+        cached[0] = (u64)(s + 1);
+        cached[1] = elements;
+      }
     }
   }
 };
 
-// One wavefront per cached slot s0 <= s < K copies the cached (leading) part of its node's list.
+// Copies the cached (leading) parts of the lists of slots s0 <= s < K.  Bound by the read of the lists (over the
+// host link where the graph lives there).  Every workgroup copies an equal share of the elements, whatever lists
+// they belong to: the cached nodes are the hottest ones, in order, and with a wavefront per list the few hubs at the
+// front decide how long it takes (5.5 M elements in HBM: 370 us, with equal shares 30; 4.5 M elements over the link:
+// 1,116 us, with equal shares 660 = 55 GB/s, the link's streaming rate).  The lists that a share of kListChunk elements touches are staged in LDS, at most
+// kListSlots at a time - where each begins in the share and how far its source is from its destination - and a
+// lane finds its element's list there by bisection.
+constexpr int kListChunk = 4096, kListSlots = 2048;
+
 __global__ __launch_bounds__(kFillBlock) void k_copy_lists(const int* __restrict__ order, long long s0, long long K,
                                                            const long long* __restrict__ indptr,
                                                            const long long* __restrict__ indices,
                                                            const long long* __restrict__ c_indptr,
                                                            long long* __restrict__ c_indices) {
-  const int lane = lane_id();
-  const long long wave0 = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / kWave;
-  const long long n_waves = (long long)gridDim.x * blockDim.x / kWave;
-  for (long long s = s0 + wave0; s < K; s += n_waves) {
-    const long long v = order ? order[s] : s;
-    const long long src0 = indptr[v], dst0 = c_indptr[s], len = c_indptr[s + 1] - dst0;
-    long long e = lane;
-    for (; e + 3 * kWave < len; e += 4 * kWave) {
-      const long long a = indices[src0 + e], b = indices[src0 + e + kWave], c = indices[src0 + e + 2 * kWave],
-                      d = indices[src0 + e + 3 * kWave];
-      c_indices[dst0 + e] = a;
-      c_indices[dst0 + e + kWave] = b;
-      c_indices[dst0 + e + 2 * kWave] = c;
-      c_indices[dst0 + e + 3 * kWave] = d;
+  __shared__ int s_begin[kListSlots];         // first element of the staged list within the share (-1: before it)
+  __shared__ long long s_shift[kListSlots];   // source position minus destination position
+  const long long first = c_indptr[s0], last = c_indptr[K];
+  const int tid = (int)threadIdx.x;
+  for (long long e0 = first + (long long)blockIdx.x * kListChunk; e0 < last; e0 += (long long)gridDim.x * kListChunk) {
+    const long long e1 = e0 + kListChunk < last ? e0 + kListChunk : last;
+    // the slots of the share's first and last element: the last slot that begins at or before it, by a search in 256 parts
+    long long lo[2] = {s0, s0}, hi[2] = {K, K};
+    while (hi[0] - lo[0] > 1 || hi[1] - lo[1] > 1) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const long long step = (hi[k] - lo[k] + kFillBlock - 1) / kFillBlock;
+        const long long at = lo[k] + tid * step;
+        const int n_le = __syncthreads_count(at < hi[k] && c_indptr[at] <= (k ? e1 - 1 : e0));
+        lo[k] += (n_le - 1) * step;  // the probe at lo itself always holds
+        if (lo[k] + step < hi[k]) hi[k] = lo[k] + step;
+      }
     }
-    for (; e < len; e += kWave) c_indices[dst0 + e] = indices[src0 + e];
+    long long s = lo[0];
+    const long long s_end = lo[1] + 1;
+    for (long long e = e0; e < e1;) {
+      const int n = (int)(s_end - s < kListSlots ? s_end - s : kListSlots);
+      __syncthreads();  // the previous round is done with the staged lists
+      for (int k = tid; k < n; k += kFillBlock) {
+        const long long dst0 = c_indptr[s + k];
+        s_begin[k] = dst0 < e0 ? -1 : (int)(dst0 - e0);
+        s_shift[k] = indptr[order[s + k]] - dst0;
+      }
+      __syncthreads();
+      const long long staged = s + n < s_end ? c_indptr[s + n] : e1;
+      const long long stop = staged < e1 ? staged : e1;
+      constexpr int kPer = kListChunk / kFillBlock;
+      long long v[kPer];
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const long long x = e + k * kFillBlock + tid;
+        if (x < stop) {
+          const int rel = (int)(x - e0);
+          int l = 0, h = n;
+          while (h - l > 1) {
+            const int mid = (l + h) / 2;
+            if (s_begin[mid] <= rel) l = mid; else h = mid;
+          }
+          v[k] = indices[x + s_shift[l]];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const long long x = e + k * kFillBlock + tid;
+        if (x < stop) c_indices[x] = v[k];
+      }
+      e = stop;
+      s += n;
+    }
   }
 }
 
@@ -551,20 +643,29 @@ static void carve_elem_ws(Arena& ar, long long n_nodes, long long n_elems, ElemW
 }
 
 struct FillWs {
-  u64* scal;  // [0] sum, [1] max, [2] cached-node counter, [3] spare
+  CountTotals* totals;  // [2]
+  CountTotals* parts;   // [2 * kCountBlocks]
   u32* deg;
   SortWs sort;
 };
 
 static void carve_fill_ws(Arena& ar, long long n, FillWs* ws) {
-  ws->scal = ar.take<u64>(8);
+  ws->totals = ar.take<CountTotals>(2);
+  ws->parts = ar.take<CountTotals>(2 * kCountBlocks);
   ws->deg = ar.take<u32>((size_t)n);
   carve_sort_ws(ar, n, &ws->sort);
 }
 
-static int32_t read_scal(dci_ctx* ctx, const u64* dev, u64* host, int n) {
-  DCI_HIP(ctx, hipMemcpyAsync(host, dev, sizeof(u64) * n, hipMemcpyDeviceToHost, ctx->stream));
-  DCI_HIP(ctx, hipStreamSynchronize(ctx->stream));
+// Enqueues the totals of count0 (and, unless null, count1), n values each, to ws.totals and to the pinned `host`.
+static int32_t count_totals(dci_ctx* ctx, const u32* count0, const u32* count1, long long n, const FillWs& ws, CountTotals* host) {
+  long long blocks = (n + 4 * kFillBlock - 1) / (4 * kFillBlock);
+  if (blocks > kCountBlocks) blocks = kCountBlocks;
+  const unsigned arrays = count1 ? 2 : 1;
+  hipLaunchKernelGGL(k_count_totals, dim3((unsigned)blocks, arrays), dim3(kFillBlock), 0, ctx->stream, count0, count1, n, ws.parts);
+  DCI_LAUNCH_CHECK(ctx);
+  hipLaunchKernelGGL(k_count_fold, dim3(arrays), dim3(kFillBlock), 0, ctx->stream, (const CountTotals*)ws.parts, (int)blocks,
+                     ws.totals, host);
+  DCI_LAUNCH_CHECK(ctx);
   return DCI_OK;
 }
 
@@ -648,25 +749,32 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
   int32_t rc;
   auto aligned = [](const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; };
 
-  // 2. feature cache
-  if ((rc = fill_bytes(ctx, ws.scal, 64, 0u)) != DCI_OK) return rc;
-  hipLaunchKernelGGL(k_sum_max, dim3(grid_1d(ctx, N)), dim3(kFillBlock), 0, ctx->stream, feat_count, N, ws.scal);
-  DCI_LAUNCH_CHECK(ctx);
-  if (feat_policy == DCI_FEAT_POLICY_PAPER_MEAN) {
-    AboveIn in{feat_count, ws.scal, (u64)N};
+  // What the host has to know: the counters' totals (the sort's passes follow from the maximum), then how many lists
+  // fit.  The kernels write both into the context's pinned memory; the host waits for the first right away and for
+  // the second only after the copy of the feature rows, the longest step, has been enqueued behind it.
+  CountTotals* const host_totals = reinterpret_cast<CountTotals*>(ctx->host_scal);
+  u64* const host_cached = ctx->host_scal + 6;
+  static_assert(sizeof(CountTotals) * 2 == 6 * sizeof(u64), "layout of the pinned words");
+  const bool topk = feat_policy == DCI_FEAT_POLICY_TOPK;
+  const bool adj_all = adj_total <= c_adj, adj_none = !adj_all && c_adj < 16 && !elements, adj_sort = !adj_all && !adj_none;
+  if ((rc = count_totals(ctx, feat_count, adj_sort ? adj_count : nullptr, N, ws, host_totals)) != DCI_OK) return rc;
+  if (topk || adj_sort) DCI_HIP(ctx, hipStreamSynchronize(ctx->stream));
+
+  // 2. feature cache: which rows
+  if (!topk) {
+    AboveIn in{feat_count, ws.totals, (u64)N};
     u64* tiles = ws.sort.tile_sums;
     MeanRemapOut o{feat_remap, tiles + (scan_tiles_for(N) - 1), k};
     if ((rc = device_scan(ctx, N, in, o, tiles)) != DCI_OK) return rc;
   } else {
-    u64 h[2];
-    if ((rc = read_scal(ctx, ws.scal, h, 2)) != DCI_OK) return rc;
     const int* order = nullptr;
-    if ((rc = sort_by_count_desc(ctx, feat_count, N, (u32)h[1], ws.sort, &order)) != DCI_OK) return rc;
+    if ((rc = sort_by_count_desc(ctx, feat_count, N, (u32)host_totals[0].max, ws.sort, &order)) != DCI_OK) return rc;
     hipLaunchKernelGGL(k_remap_from_order, dim3(grid_1d(ctx, N)), dim3(kFillBlock), 0, ctx->stream, order, N, k,
                        feat_remap);
     DCI_LAUNCH_CHECK(ctx);
   }
-  if (k > 0) {
+  auto copy_feature_rows = [&]() -> int32_t {
+    if (k == 0) return DCI_OK;
     int V = 1;
     if (F % 4 == 0 && aligned(g->feat, 16)) V = 4;
     else if (F % 2 == 0 && aligned(g->feat, 8)) V = 2;
@@ -684,51 +792,48 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
       hipLaunchKernelGGL((k_copy_rows<1>), dim3(grid), dim3(kFillBlock), 0, ctx->stream, (const int*)feat_remap, N,
                          g->feat, F, lpr_log2, feat_cache);
     DCI_LAUNCH_CHECK(ctx);
-  }
+    return DCI_OK;
+  };
 
   // 3. adjacency cache
   long long K = 0, M = 0, partial_node = -1, partial_deg = 0;
   const long long* indptr = reinterpret_cast<const long long*>(g->indptr);
   const long long* indices = reinterpret_cast<const long long*>(g->indices);
   long long* c_indices = nullptr;
-  if (adj_total <= c_adj) {
+  if (adj_all) {
     K = N;
     M = E;
     c_indices = c_indptr + (K + 1);
+    if ((rc = copy_feature_rows()) != DCI_OK) return rc;
     hipLaunchKernelGGL(k_iota_i32, dim3(grid_1d(ctx, N)), dim3(kFillBlock), 0, ctx->stream, adj_remap, N);
     DCI_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_copy_i64, dim3(grid_1d(ctx, N + 1)), dim3(kFillBlock), 0, ctx->stream, indptr, N + 1, c_indptr);
     DCI_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_copy_i64, dim3(grid_1d(ctx, E)), dim3(kFillBlock), 0, ctx->stream, indices, E, c_indices);
     DCI_LAUNCH_CHECK(ctx);
-  } else if (c_adj < 16 && !elements) {
+  } else if (adj_none) {
     // not even an empty list fits: nothing is cached
+    if ((rc = copy_feature_rows()) != DCI_OK) return rc;
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_1d(ctx, N)), dim3(kFillBlock), 0, ctx->stream, adj_remap, N, -1);
     DCI_LAUNCH_CHECK(ctx);
   } else {
-    if ((rc = fill_bytes(ctx, ws.scal, 64, 0u)) != DCI_OK) return rc;
-    hipLaunchKernelGGL(k_sum_max, dim3(grid_1d(ctx, N)), dim3(kFillBlock), 0, ctx->stream, adj_count, N, ws.scal);
-    DCI_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_degrees, dim3(grid_1d(ctx, N)), dim3(kFillBlock), 0, ctx->stream, indptr, N, ws.deg);
     DCI_LAUNCH_CHECK(ctx);
-    u64 h[4];
-    if ((rc = read_scal(ctx, ws.scal, h, 4)) != DCI_OK) return rc;
-    const long long n_nz = (long long)h[3];  // nodes with a non-zero total: the first n_nz of the order
+    const long long n_nz = (long long)host_totals[1].nonzero;  // nodes with a non-zero total: the first n_nz of the order
     const int* order = nullptr;
-    if ((rc = sort_by_count_desc(ctx, adj_count, N, (u32)h[1], ws.sort, &order)) != DCI_OK) return rc;
+    if ((rc = sort_by_count_desc(ctx, adj_count, N, (u32)host_totals[1].max, ws.sort, &order)) != DCI_OK) return rc;
     if (c_adj >= 16) {
+      host_cached[0] = host_cached[1] = 0;
       CostIn in{order, ws.deg};
-      AdjOut o{order, adj_remap, c_indptr, c_adj, ws.scal, ws.deg, N};
+      AdjOut o{order, adj_remap, c_indptr, c_adj, host_cached, ws.deg, N};
       if ((rc = device_scan(ctx, N, in, o, ws.sort.tile_sums)) != DCI_OK) return rc;
-      u64 hk[3];
-      if ((rc = read_scal(ctx, ws.scal, hk, 3)) != DCI_OK) return rc;
-      K = (long long)hk[2];
-      // c_indptr[0] = 0, then read M = c_indptr[K]
-      long long zero = 0;
-      DCI_HIP(ctx, hipMemcpyAsync(c_indptr, &zero, sizeof(zero), hipMemcpyHostToDevice, ctx->stream));
-      DCI_HIP(ctx, hipMemcpyAsync(&M, c_indptr + K, sizeof(M), hipMemcpyDeviceToHost, ctx->stream));
-      DCI_HIP(ctx, hipStreamSynchronize(ctx->stream));
+      DCI_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
+      if ((rc = copy_feature_rows()) != DCI_OK) return rc;
+      DCI_HIP(ctx, hipEventSynchronize(ctx->ev[0]));
+      K = (long long)host_cached[0];
+      M = (long long)host_cached[1];
     } else {
+      if ((rc = copy_feature_rows()) != DCI_OK) return rc;
       hipLaunchKernelGGL(k_fill_i32, dim3(grid_1d(ctx, N)), dim3(kFillBlock), 0, ctx->stream, adj_remap, N, -1);
       DCI_LAUNCH_CHECK(ctx);
     }
@@ -787,14 +892,10 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
         hipLaunchKernelGGL(k_gather_elems, dim3(grid_1d(ctx, n_nz, wpb)), dim3(kFillBlock), 0, ctx->stream, order, n_nz,
                            indptr, indices, edge_count, (const long long*)ew.off, ew.vals, ew.cnt, ew.seg);
         DCI_LAUNCH_CHECK(ctx);
-        if ((rc = fill_bytes(ctx, ws.scal, 64, 0u)) != DCI_OK) return rc;
-        hipLaunchKernelGGL(k_sum_max, dim3(grid_1d(ctx, e_nz)), dim3(kFillBlock), 0, ctx->stream, (const u32*)ew.cnt, e_nz,
-                           ws.scal);
-        DCI_LAUNCH_CHECK(ctx);
-        u64 he[2];
-        if ((rc = read_scal(ctx, ws.scal, he, 2)) != DCI_OK) return rc;
+        if ((rc = count_totals(ctx, (const u32*)ew.cnt, nullptr, e_nz, ws, host_totals)) != DCI_OK) return rc;
+        DCI_HIP(ctx, hipStreamSynchronize(ctx->stream));
         const int* by_count = nullptr;
-        if ((rc = sort_by_count_desc(ctx, ew.cnt, e_nz, (u32)he[1], ew.sort, &by_count)) != DCI_OK) return rc;
+        if ((rc = sort_by_count_desc(ctx, ew.cnt, e_nz, (u32)host_totals[0].max, ew.sort, &by_count)) != DCI_OK) return rc;
         const int* sorted = by_count;
         int seg_bits = 0;
         while (seg_bits < 32 && ((u64)(n_nz - 1) >> seg_bits) != 0) ++seg_bits;
@@ -809,8 +910,7 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
     }
     if (K > first_plain) {
       // Entries of c_indptr beyond K+1 were never written; the lists start right after entry K.
-      const long long waves_per_block = kFillBlock / kWave;
-      hipLaunchKernelGGL(k_copy_lists, dim3(grid_1d(ctx, K - first_plain, (int)waves_per_block)), dim3(kFillBlock), 0,
+      hipLaunchKernelGGL(k_copy_lists, dim3(grid_1d(ctx, M, kListChunk)), dim3(kFillBlock), 0,
                          ctx->stream, order, first_plain, K, indptr, indices, (const long long*)c_indptr, c_indices);
       DCI_LAUNCH_CHECK(ctx);
     }

@@ -85,7 +85,9 @@ __device__ __forceinline__ void copy_rows(const long long* __restrict__ ids, lon
 // Hit / miss / copied totals leave a gather kernel as one triple per workgroup and are folded by a second,
 // tiny kernel: thousands of atomics on one counter serialise in L2 for longer than the copy takes
 // (measured: +30 us for 4096 workgroups).
-__device__ __forceinline__ void store_partials(GatherCounts cnt, unsigned long long* __restrict__ partials) {
+// (`add`: on top of what the workgroup of the same number of an earlier launch left, so that a run of launches is
+// folded once.)
+__device__ __forceinline__ void store_partials(GatherCounts cnt, unsigned long long* __restrict__ partials, bool add = false) {
   __shared__ unsigned long long s_h[kGatherBlock / kWave], s_m[kGatherBlock / kWave], s_c[kGatherBlock / kWave];
   const unsigned long long hits = wave_sum_u64(cnt.hits), misses = wave_sum_u64(cnt.misses), copied = wave_sum_u64(cnt.copied);
   if (lane_id() == 0) {
@@ -101,9 +103,10 @@ __device__ __forceinline__ void store_partials(GatherCounts cnt, unsigned long l
       m += s_m[w];
       c += s_c[w];
     }
-    partials[3 * blockIdx.x] = h;
-    partials[3 * blockIdx.x + 1] = m;
-    partials[3 * blockIdx.x + 2] = c;
+    unsigned long long* const p = partials + 3 * blockIdx.x;
+    p[0] = h + (add ? p[0] : 0);
+    p[1] = m + (add ? p[1] : 0);
+    p[2] = c + (add ? p[2] : 0);
   }
 }
 
@@ -114,12 +117,12 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather(const long long* __rest
                                                          const float* __restrict__ cache,
                                                          const float* __restrict__ feat, int F, int lpr_log2,
                                                          float* __restrict__ out,
-                                                         unsigned long long* __restrict__ partials) {
+                                                         unsigned long long* __restrict__ partials, int add) {
   long long n = n_dev ? *n_dev : n_max;
   if (n > n_max) n = n_max;
   GatherCounts cnt;
   copy_rows<V>(ids, n, remap, cache, feat, F, lpr_log2, out, nullptr, (int)blockIdx.x, (int)gridDim.x, cnt);
-  if (partials) store_partials(cnt, partials);
+  if (partials) store_partials(cnt, partials, add != 0);
 }
 
 // The selective gather of dci_gather_forward: every row's cache slot (or -1) is noted in rowref[i]; the
@@ -257,7 +260,7 @@ size_t gather_partials_bytes(const dci_ctx* ctx) {
 
 int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* ids, int64_t n_max,
                       const int64_t* n_dev, float* out, uint64_t* stats, void* partials_buf, int32_t* rowref,
-                      const int64_t* n_dense_dev, int64_t n_dense_max) {
+                      const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials, bool fold_partials) {
   const int F = g->feat_dim;
   const float* fcache = cache ? cache->feat_cache : nullptr;
   const int* remap = cache ? cache->feat_remap : nullptr;
@@ -302,16 +305,16 @@ int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, 
                            (long long)n_max, nd_, remap, fcache, g->feat, F, lpr_log2, out, st, rowref, dn_);
     } else if (V == 4)
       hipLaunchKernelGGL((k_gather<4>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max,
-                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st);
+                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0);
     else if (V == 2)
       hipLaunchKernelGGL((k_gather<2>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max,
-                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st);
+                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0);
     else
       hipLaunchKernelGGL((k_gather<1>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max,
-                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st);
+                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0);
   }
   DCI_LAUNCH_CHECK(ctx);
-  if (stats) {
+  if (stats && fold_partials) {
     hipLaunchKernelGGL(k_fold_gather_stats, dim3(1), dim3(kGatherBlock), 0, ctx->stream,
                        reinterpret_cast<const unsigned long long*>(partials_buf), (int)blocks,
                        (unsigned long long)F * 4ull, reinterpret_cast<unsigned long long*>(stats));

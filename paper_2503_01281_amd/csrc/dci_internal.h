@@ -11,6 +11,8 @@
 
 #include "dci.h"
 
+constexpr int kPresampleRun = 16;  // batches that dci_presample_count times between two waits for the GPU
+
 struct dci_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -18,7 +20,7 @@ struct dci_ctx {
   size_t ws_bytes = 0;
   char* static_scratch = nullptr;  // this GPU's copy of the library's static scratch array (DCI_STATIC_SCRATCH_BYTES)
   int num_cus = 256;
-  hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
+  hipEvent_t ev[2 * kPresampleRun + 1] = {nullptr};  // dci_presample_count's stage times (dci_fill_caches uses the first)
   char err[512] = {0};
   // optional per-kernel-class timing
   uint32_t timing_mask = 0;
@@ -26,6 +28,7 @@ struct dci_ctx {
   int8_t* t_class = nullptr;
   int t_used = 0;
   unsigned* host_flag = nullptr;  // pinned host word (64 bytes): a kernel raises it when a batch had to be voided
+  unsigned long long* host_scal = nullptr;  // eight pinned words behind it: what dci_fill_caches reads back
   unsigned relabel_spin_limit = 1u << 24;  // DCI_OPT_RELABEL_SPIN_LIMIT
   unsigned test_first_ticket = 0;          // DCI_OPT_TEST_RELABEL_FIRST_TICKET
   // what the last call that returned DCI_ERR_CAPACITY needed (dci_last_required)
@@ -152,9 +155,12 @@ int32_t check_device_flag(dci_ctx* ctx);
 // partials_buf: gather_partials_bytes(ctx) bytes of device scratch, needed when stats != NULL
 // rowref / n_dense_dev: nullptr for the plain gather; otherwise the selective form (see k_gather_select),
 // n_dense_max bounding *n_dense_dev
+// add_partials / fold_partials (plain gather only): several launches of one n_max that are folded into stats once - the
+// first starts the partial sums, later ones add to them, the last folds them
 int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* ids,
                       int64_t n_max, const int64_t* n_dev, float* out, uint64_t* stats, void* partials_buf,
-                      int32_t* rowref, const int64_t* n_dense_dev, int64_t n_dense_max);
+                      int32_t* rowref, const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials = false,
+                      bool fold_partials = true);
 size_t gather_partials_bytes(const dci_ctx* ctx);
 
 }  // namespace dci

@@ -208,7 +208,8 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
                                                       const long long* blk_indptr, const HashEntry* table,
                                                       int* blk_src, long long* counts_host, StatFold sf,
                                                       const unsigned* batch_flag, long long* counts_rw,
-                                                      unsigned* host_flag) {
+                                                      unsigned* host_flag, const long long* nodes, int n_hops,
+                                                      unsigned* feat_count) {
   if (*batch_flag != kBatchOk) {
     // A relabel tile timed out: the batch is void.  Its sizes are zeroed so that whatever consumes the
     // batch next (gather, forward) finds nothing to do, and the context's host flag is raised for dci_sync.
@@ -221,6 +222,11 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
   }
   write_block_sources(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, blk_src, (int)blockIdx.x,
                       (int)gridDim.x);
+  if (feat_count) {  // pre-sampling: one visit for every input node
+    const long long n = counts[n_hops];
+    for (long long i = blockIdx.x * (long long)kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
+      atomicAdd(&feat_count[nodes[i]], 1u);
+  }
   if (counts_host && blockIdx.x == 0 && threadIdx.x < 2 * DCI_MAX_HOPS + 1)
     counts_host[threadIdx.x] = counts[threadIdx.x];  // pinned host memory, visible once the stream is idle
   if (sf.stats && blockIdx.x == gridDim.x - 1) {
@@ -708,14 +714,6 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_count_input_nodes(const long long* __restrict__ nodes,
-                                                              const long long* __restrict__ counts, int n_hops,
-                                                              unsigned* __restrict__ feat_count) {
-  const long long n = counts[n_hops];
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    atomicAdd(&feat_count[nodes[i]], 1u);
-}
-
 __global__ void k_add_u64(unsigned long long* p, unsigned long long v) { atomicAdd(p, v); }
 
 // ---- host side ----------------------------------------------------------------------------------
@@ -939,16 +937,9 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
                        (const long long*)counts, h, fanouts[h], (const int*)ws.row_cnt[h & 1],
                        (const int*)ws.tmp_slot[h & 1], reinterpret_cast<const long long*>(out->blk_indptr[h]),
                        (const HashEntry*)ws.table, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
-                       (const unsigned*)ws.batch_flag, counts, ctx->host_flag);
+                       (const unsigned*)ws.batch_flag, counts, ctx->host_flag, (const long long*)nodes, n_hops, feat_count);
   }
   DCI_LAUNCH_CHECK(ctx);
-  if (feat_count) {
-    int grid = grid_for_rows(ctx, out->cap_nodes, kBlock);
-    Timed t(ctx, DCI_K_COUNT_NODES);
-    hipLaunchKernelGGL(k_count_input_nodes, dim3(grid), dim3(kBlock), 0, ctx->stream, (const long long*)nodes,
-                       (const long long*)counts, n_hops, feat_count);
-    DCI_LAUNCH_CHECK(ctx);
-  }
   return DCI_OK;
 }
 
@@ -1090,29 +1081,39 @@ int32_t dci_presample_count(dci_ctx* ctx, const dci_graph* graph, const dci_cach
   void* gather_partials = ar.take<char>(gather_partials_bytes(ctx));
   if (!ar.ok())
     return fail(ctx, DCI_ERR_CAPACITY, "workspace holds %zu bytes, pre-sampling needs %zu", ctx->ws_bytes, ar.off);
+  // The batches run back to back: the stage times come from events between them, read once per kPresampleRun batches
+  // (a wait after every batch left the GPU idle for the length of the host's round trip), and the gather's
+  // statistics are folded once per run.
   double ms_sample = 0.0, ms_feature = 0.0;
-  for (int64_t k = 0; k < n_batches; ++k) {
+  int64_t batches = (n_seeds + batch_size - 1) / batch_size - first_batch;  // those that have seeds
+  if (batches > n_batches) batches = n_batches;
+  int in_run = 0;
+  for (int64_t k = 0; k < batches; ++k) {
     const int64_t lo = (first_batch + k) * batch_size;
-    if (lo >= n_seeds) break;
     const int64_t hi = lo + batch_size < n_seeds ? lo + batch_size : n_seeds;
-    if (feat_scratch) DCI_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
+    if (feat_scratch && in_run == 0) DCI_HIP(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
     rc = sample_batch(ctx, graph, cache, seeds + lo, hi - lo, rng_batch0 + (uint64_t)k, fanouts, n_hops, rng_seed,
                       &blk, ws, stats, feat_count, adj_count, edge_count);
     if (rc != DCI_OK) return rc;
-    if (feat_scratch) {
-      DCI_HIP(ctx, hipEventRecord(ctx->ev[1], ctx->stream));
-      rc = gather_launch(ctx, graph, cache, blk.nodes, cap_nodes[n_hops], blk.counts + n_hops, feat_scratch, stats,
-                         gather_partials, nullptr, nullptr, 0);
-      if (rc != DCI_OK) return rc;
-      DCI_HIP(ctx, hipEventRecord(ctx->ev[2], ctx->stream));
-      DCI_HIP(ctx, hipEventSynchronize(ctx->ev[2]));
-      if ((rc = check_device_flag(ctx)) != DCI_OK) return rc;
+    if (!feat_scratch) continue;
+    const bool last = in_run + 1 == kPresampleRun || k + 1 == batches;
+    DCI_HIP(ctx, hipEventRecord(ctx->ev[2 * in_run + 1], ctx->stream));
+    rc = gather_launch(ctx, graph, cache, blk.nodes, cap_nodes[n_hops], blk.counts + n_hops, feat_scratch, stats,
+                       gather_partials, nullptr, nullptr, 0, in_run > 0, last);
+    if (rc != DCI_OK) return rc;
+    DCI_HIP(ctx, hipEventRecord(ctx->ev[2 * in_run + 2], ctx->stream));
+    ++in_run;
+    if (!last) continue;
+    DCI_HIP(ctx, hipEventSynchronize(ctx->ev[2 * in_run]));
+    if ((rc = check_device_flag(ctx)) != DCI_OK) return rc;
+    for (int j = 0; j < in_run; ++j) {
       float a = 0.f, b = 0.f;
-      DCI_HIP(ctx, hipEventElapsedTime(&a, ctx->ev[0], ctx->ev[1]));
-      DCI_HIP(ctx, hipEventElapsedTime(&b, ctx->ev[1], ctx->ev[2]));
+      DCI_HIP(ctx, hipEventElapsedTime(&a, ctx->ev[2 * j], ctx->ev[2 * j + 1]));
+      DCI_HIP(ctx, hipEventElapsedTime(&b, ctx->ev[2 * j + 1], ctx->ev[2 * j + 2]));
       ms_sample += a;
       ms_feature += b;
     }
+    in_run = 0;
   }
   if (feat_scratch && stats) {
     unsigned long long* st = reinterpret_cast<unsigned long long*>(stats);

@@ -1,0 +1,56 @@
+"""Kernels whose work split has edges of its own, at the sizes where a split can go wrong, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import paper_2503_01281_amd as dci
+    from tests import gpu_util as gu
+    return dict(dci=dci, gu=gu, ctx=dci.Context(0))
+
+
+# The list copy of the adjacency cache takes shares of 4,096 elements and stages at most 2,048 lists of a share at a time:
+# one list over many shares, shares made of thousands of empty lists, lists that begin or end on a share's edge.
+@pytest.mark.parametrize("lengths", [[20_001] + [0] * 5_000 + [1, 4_095, 4_096, 4_097], [1] * 4_097 + [0] * 2_050 + [3] * 700,
+                                     [4_096, 8_192, 0, 1], [0] * 6_000 + [5]])
+@pytest.mark.parametrize("share", [0.999, 0.4])
+def test_list_copy_of_the_adjacency_cache(env, lengths, share):
+    dci, gu, ctx = env["dci"], env["gu"], env["ctx"]
+    rng = np.random.default_rng(len(lengths))
+    indptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    N, E = len(lengths), int(indptr[-1])
+    indices = rng.integers(0, N, E).astype(np.int64)
+    count = np.arange(N, 0, -1).astype(np.uint32) if lengths[0] else rng.integers(0, 9, N).astype(np.uint32)
+    c_adj = int(share * 8 * (N + 1 + E))
+    remap, c_indptr, c_indices = oracle.fill_adj(indptr, indices, count, c_adj)
+    g = gu.make_graph(indptr, indices, np.zeros((N, 1), dtype=np.float32))
+    cache = dci.dci_fill_caches(ctx, g, gu.dev(np.zeros(N, dtype=np.int32)), gu.dev(count.view(np.int32)), c_adj, 1, 0,
+                                dci.DCI_FILL_STRICT_SPLIT)
+    K, M = cache.adj_nodes, cache.adj_edges
+    assert (K, M) == (len(c_indptr) - 1, len(c_indices))
+    assert np.array_equal(cache.adj_remap.cpu().numpy(), remap)
+    words = cache.buf[cache.buf_offset:cache.buf_offset + 8 * (K + 1 + M)].view(torch.int64).cpu().numpy()
+    assert np.array_equal(words[:K + 1], c_indptr) and np.array_equal(words[K + 1:], c_indices)
+
+
+# The totals of the counters: fewer nodes than one workgroup's lanes, a remainder behind whole strides, and counters whose
+# sum needs more than 32 bits (the paper's rule compares count * N with it).
+@pytest.mark.parametrize("N", [1, 255, 1_025, 70_001])
+def test_counter_totals_decide_the_feature_rows(env, N):
+    dci, gu, ctx = env["dci"], env["gu"], env["ctx"]
+    rng = np.random.default_rng(N)
+    count = rng.integers(0, 2**32 - 1, N, dtype=np.uint32)
+    feat = rng.standard_normal((N, 3)).astype(np.float32)
+    g = gu.make_graph(np.minimum(np.arange(N + 1), 1).astype(np.int64), np.zeros(1, dtype=np.int64), feat)
+    for policy in (0, 1):
+        remap, rows, k = oracle.fill_feat(count, feat, 12 * (N // 3 + 1), policy)
+        cache = dci.dci_fill_caches(ctx, g, gu.dev(count.view(np.int32)), gu.dev(np.zeros(N, dtype=np.int32)), 12 * (N // 3 + 1), 0, 1,
+                                    policy | dci.DCI_FILL_STRICT_SPLIT)
+        assert cache.feat_rows == k and np.array_equal(cache.feat_remap.cpu().numpy(), remap)
