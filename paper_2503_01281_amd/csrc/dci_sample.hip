@@ -1,14 +1,14 @@
 // Cache-aware multi-hop neighbour sampling, mini-batch block construction and pre-sampling
 // access counting (Section II-C; Section IV; Section IV-B, first and third paragraphs).
 //
-// One batch is one clear of the batch's hash table, two kernels per hop and one closing kernel:
+// One batch is one clear of the batch's node table, two kernels per hop and one closing kernel:
 //   k_sample_hop  - one lane group per frontier node (a whole wavefront for fan-outs above 32, a
 //                   half / quarter / eighth for smaller ones): read the node's list bounds from the
 //                   adjacency cache or the host CSR (a position is served by the cache iff it lies
 //                   below the node's cached length, which is the whole list for every node but the
 //                   one an element-granular fill may have cached in part), draw the positions (Floyd's subset algorithm
 //                   on Philox4x32-10, one lane per slot), read the neighbour ids, store them at the
-//                   padded position row*fanout + slot and register every id in the hash table with
+//                   padded position row*fanout + slot and register every id in the node table with
 //                   an atomic minimum over that padded position.  A row's list bounds are noted for the
 //                   batch's later hops, which sample the same row again and then need neither the slot
 //                   look-up nor - for a miss - a second trip over the host link.  At hop 0 the same kernel turns
@@ -24,9 +24,10 @@
 // Should a tile of the scan ever give up waiting for its predecessors, the batch is voided: a status
 // word makes the batch's remaining kernels return at once, k_write_src zeroes the batch's sizes and
 // raises the context's host flag, and the next dci_sync reports it.
-// A table word holds the node id in its high half and, in its low half, either a final local id
-// (below 2^31) or 2^31 + the smallest padded position seen so far, so one atomic minimum serves
-// both "already in the frontier" and "who came first".
+// A node's value in the table is either a final local id (below 2^31) or 2^31 + the smallest padded
+// position seen so far, so one atomic minimum serves both "already in the frontier" and "who came first".
+// The table is hashed (a 64-bit word per entry, node id in the high half, value in the low half) or direct
+// (a 32-bit value per node of the graph): see table_is_direct.
 #include "dci_internal.h"
 
 namespace dci {
@@ -54,11 +55,13 @@ constexpr int kHostLineLog2 = 7;  // the host link moves 128-byte lines: smaller
 // else = a relabel tile gave up waiting for its predecessors, the batch's outputs are void.
 constexpr unsigned kBatchOk = 0xFFFFFFFFu;
 
-__device__ __forceinline__ unsigned entry_val(const HashEntry* table, unsigned slot) {
-  return reinterpret_cast<const unsigned*>(table)[2 * (size_t)slot];  // low half (little endian)
+// The value of a slot: the low half (little endian) of a hashed table's word, the word itself of a direct one
+// (entries == 0; the slot is the node's id).
+__device__ __forceinline__ unsigned entry_val(const HashEntry* table, unsigned entries, unsigned slot) {
+  return reinterpret_cast<const unsigned*>(table)[(size_t)slot << (entries ? 1 : 0)];
 }
-__device__ __forceinline__ void entry_set_val(HashEntry* table, unsigned slot, unsigned v) {
-  reinterpret_cast<unsigned*>(table)[2 * (size_t)slot] = v;
+__device__ __forceinline__ void entry_set_val(HashEntry* table, unsigned entries, unsigned slot, unsigned v) {
+  reinterpret_cast<unsigned*>(table)[(size_t)slot << (entries ? 1 : 0)] = v;
 }
 
 // ---- Philox4x32-10 (Salmon et al., SC'11), counter-based ---------------------------------
@@ -87,16 +90,26 @@ __device__ __forceinline__ unsigned long long uniform_below(unsigned k0, unsigne
   return __umul64hi(u, m);
 }
 
-// ---- hash table -----------------------------------------------------------------------------
-// Finds or creates the entry of node u (open addressing, linear probing) and lowers its value to
+// ---- node table -----------------------------------------------------------------------------
+// Direct (entries == 0): the node's word is looked at and, if v is smaller, lowered by an atomic minimum whose
+// result nobody waits for; one dependent access per edge where the hashed table has two or more (look, claim,
+// probe on).  An id outside the graph stays inside the table (its last word).
+// Hashed: finds or creates the entry of node u (open addressing, linear probing) and lowers its value to
 // v if v is smaller; returns the slot and, in *candidate, whether v may have become the entry's
 // value (the slot was empty, or held a larger value when it was looked at).  A call for which that
 // is false can never be the node's first appearance; the reverse need not hold.
 // For an entry that already holds u, key and value move as one word, so a single 64-bit atomic
 // minimum does it; an empty slot is claimed by compare-and-swap.  Values only decrease and keys
 // never change, so a stale read costs a redundant atomic at most.
-__device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned entries, long long u,
-                                                     unsigned v, bool* candidate) {
+__device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned entries, unsigned last_node,
+                                                     long long u, unsigned v, bool* candidate) {
+  if (entries == 0) {
+    const unsigned own = (unsigned long long)u < last_node ? (unsigned)u : last_node;
+    unsigned* const word = reinterpret_cast<unsigned*>(table) + own;
+    *candidate = __atomic_load_n(word, __ATOMIC_RELAXED) > v;
+    if (*candidate) atomicMin(word, v);
+    return own;
+  }
   // multiplicative hash, its high 32 bits scaled to [0, entries): the table need not be a power of two
   unsigned slot = __umulhi((unsigned)(((unsigned long long)u * 0x9E3779B97F4A7C15ull) >> 32), entries);
   const HashEntry mine = ((HashEntry)u << 32) | v;
@@ -154,7 +167,8 @@ struct HopArgs {
   int* tmp_slot;
   int* row_cnt;
   HashEntry* table;
-  unsigned entries;  // of the table
+  unsigned entries;    // of a hashed table; 0: direct
+  unsigned last_node;  // the graph's last node id
   unsigned* adj_count;
   unsigned* edge_count;
   // previous hop, whose edges get their local ids at the start of this kernel (hop >= 1)
@@ -178,7 +192,8 @@ struct HopArgs {
 __device__ __forceinline__ void write_block_sources(long long n_rows, int fanout, const int* __restrict__ row_cnt,
                                                     const int* __restrict__ tmp_slot,
                                                     const long long* __restrict__ blk_indptr,
-                                                    const HashEntry* table, int* __restrict__ blk_src,
+                                                    const HashEntry* table, unsigned entries,
+                                                    int* __restrict__ blk_src,
                                                     int block, int n_blocks) {
   const long long total = n_rows * fanout;
   for (long long q = block * (long long)blockDim.x + threadIdx.x; q < total; q += (long long)n_blocks * blockDim.x) {
@@ -186,7 +201,7 @@ __device__ __forceinline__ void write_block_sources(long long n_rows, int fanout
     const int s = (int)(q - i * fanout);
     if (s < (row_cnt[i] & kRowCntMask)) {
       const int ts = tmp_slot[q];
-      if (ts != kSlotDone) blk_src[blk_indptr[i] + s] = (int)entry_val(table, slot_of(ts));
+      if (ts != kSlotDone) blk_src[blk_indptr[i] + s] = (int)entry_val(table, entries, slot_of(ts));
     }
   }
 }
@@ -206,7 +221,7 @@ struct StatFold {
 __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, int hop, int fanout,
                                                       const int* row_cnt, const int* tmp_slot,
                                                       const long long* blk_indptr, const HashEntry* table,
-                                                      int* blk_src, long long* counts_host, StatFold sf,
+                                                      unsigned entries, int* blk_src, long long* counts_host, StatFold sf,
                                                       const unsigned* batch_flag, long long* counts_rw,
                                                       unsigned* host_flag, const long long* nodes, int n_hops,
                                                       unsigned* feat_count) {
@@ -220,7 +235,7 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
     }
     return;
   }
-  write_block_sources(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, blk_src, (int)blockIdx.x,
+  write_block_sources(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, entries, blk_src, (int)blockIdx.x,
                       (int)gridDim.x);
   if (feat_count) {  // pre-sampling: one visit for every input node
     const long long n = counts[n_hops];
@@ -298,7 +313,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
   } else if ((int)blockIdx.x < a.n_write_blocks) {
     // the first few workgroups finish the previous hop while the others sample this one
     write_block_sources(a.counts[a.hop - 1], a.prev_fanout, a.prev_row_cnt, a.prev_tmp_slot, a.prev_blk_indptr,
-                        a.table, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
+                        a.table, a.entries, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
     return;
   }
   const int block = (int)blockIdx.x - (INIT ? 0 : a.n_write_blocks);
@@ -322,7 +337,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
         if (gl == 0) {
           a.nodes[i] = v;
           bool ignored;
-          (void)table_insert_min(a.table, a.entries, v, (unsigned)i, &ignored);
+          (void)table_insert_min(a.table, a.entries, a.last_node, v, (unsigned)i, &ignored);
         }
       } else {
         v = a.nodes[i];
@@ -404,8 +419,8 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
       const long long u = *src;
       const int p = (int)(i * f + gl);
       bool candidate;
-      const unsigned slot = table_insert_min(a.table, a.entries, u, kTentative | (unsigned)p, &candidate);
-      a.tmp_u[p] = u;
+      const unsigned slot = table_insert_min(a.table, a.entries, a.last_node, u, kTentative | (unsigned)p, &candidate);
+      if (a.entries) a.tmp_u[p] = u;  // (a direct table's slot is the id)
       a.tmp_slot[p] = candidate ? (int)slot : -2 - (int)slot;  // the relabel kernel looks at the candidates only
       if (COUNT && a.edge_count) {
         const long long host_start = hit ? a.indptr[v] : start;
@@ -453,6 +468,7 @@ struct RelabelArgs {
   const long long* tmp_u;
   int* tmp_slot;  // read; the first appearances are marked kSlotDone
   HashEntry* table;
+  unsigned entries;  // of a hashed table; 0: direct
   long long* nodes;
   long long* blk_indptr;
   int* blk_src;   // the first appearances' local ids are written here, the other edges' by the next kernel
@@ -525,7 +541,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
     slot[it] = (i < n_rows && gl < f) ? a.tmp_slot[i * f + gl] : -1;  // -1 where the row has no edge
   }
 #pragma unroll
-  for (int it = 0; it < kTileIters; ++it) val[it] = slot[it] >= 0 ? entry_val(a.table, (unsigned)slot[it]) : 0u;
+  for (int it = 0; it < kTileIters; ++it) val[it] = slot[it] >= 0 ? entry_val(a.table, a.entries, (unsigned)slot[it]) : 0u;
   unsigned first_bits = 0;
   long long new_u[kTileIters];
   unsigned long long hit_rows = 0, hit_edges = 0, host_lines = 0, bound_lines = 0;
@@ -539,7 +555,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
     if (first) first_bits |= 1u << it;
     // the ids of the first appearances are only needed once the tile knows its offsets; asked for here, they
     // arrive while the tile scans and looks back
-    new_u[it] = first ? a.tmp_u[(row0 + r) * f + gl] : 0;
+    new_u[it] = !first ? 0 : a.entries ? a.tmp_u[(row0 + r) * f + gl] : (long long)slot[it];
     if (gl == 0) {
       s_c[r] = c;
       s_f[r] = __popcll(bits);
@@ -682,7 +698,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
   for (int it = 0; it < kTileIters; ++it)
     if (new_id[it] >= 0) {
       a.nodes[new_id[it]] = new_u[it];
-      entry_set_val(a.table, (unsigned)slot[it], (unsigned)new_id[it]);
+      entry_set_val(a.table, a.entries, (unsigned)slot[it], (unsigned)new_id[it]);
       // this edge's local id is known right here: write it (the row's edges sit at its sampled slots
       // 0 .. c-1, and s_c holds the row's inclusive edge count within the tile), and spare the edge-id pass
       // the table look-up
@@ -720,7 +736,7 @@ __global__ void k_add_u64(unsigned long long* p, unsigned long long v) { atomicA
 
 struct SampleWs {
   HashEntry* table;        // the table, the tile status words and the tickets are one region,
-  uint64_t table_entries;  // cleared with a single all-ones fill per batch
+  uint64_t table_entries;  // cleared with a single all-ones fill per batch (0 entries: direct table)
   unsigned long long* status[DCI_MAX_HOPS];
   unsigned* ticket;        // [DCI_MAX_HOPS]
   unsigned* batch_flag;    // one word after the tickets, also in the cleared region
@@ -737,6 +753,17 @@ struct SampleWs {
 static uint64_t table_entries_for(int64_t cap_nodes_last) {
   uint64_t want = (uint64_t)(cap_nodes_last > 0 ? cap_nodes_last : 1) * 2;
   return want < 1024 ? 1024 : want;
+}
+
+// Direct table: 4 bytes per node of the graph, where that is no more to clear than the hashed table's 8 bytes for
+// each of twice the bound on the batch's nodes.  At equal bytes the direct one is the quicker of the two (no
+// claim to wait for, no probing, no second copy of the ids); a graph many times the batch's bound would pay
+// for its clear with more than that.  Slots double as negative codes in tmp_slot, hence the limit of 2^30.
+// Hashed -> direct: eight 4,096-seed batches of a 2.4 M-node graph on four lanes 2,002 -> 1,917 us (clear 39 -> 10 MB a
+// batch); an 8,192-seed batch of two hops on 4.0 M nodes 353 -> 346 us; 4,096 seeds on 1.6 M nodes 366 -> 357 us; 1,024 seeds
+// on 233 k nodes, a table that either way stays in L2, 331 -> 333 us.
+static bool table_is_direct(int64_t num_nodes, uint64_t hashed_bytes) {
+  return num_nodes < ((int64_t)1 << 30) && 4 * (uint64_t)num_nodes <= hashed_bytes;
 }
 
 static int group_for(int fanout) { return fanout <= 8 ? 8 : fanout <= 16 ? 16 : fanout <= 32 ? 32 : 64; }
@@ -756,8 +783,8 @@ static int tile_iters_for(const dci_ctx* ctx, int64_t cap_rows, int fanout) {
   return kTileItersMax;
 }
 
-static void carve_sample_ws(Arena& ar, const int64_t* cap_nodes, const int64_t* cap_edges, const int32_t* fanouts,
-                            int32_t n_hops, SampleWs* ws) {
+static void carve_sample_ws(Arena& ar, int64_t num_nodes, const int64_t* cap_nodes, const int64_t* cap_edges,
+                            const int32_t* fanouts, int32_t n_hops, SampleWs* ws) {
   int64_t max_edges = 1, max_rows = 1;
   size_t status_words = 0;
   for (int32_t h = 0; h < n_hops; ++h) {
@@ -766,9 +793,13 @@ static void carve_sample_ws(Arena& ar, const int64_t* cap_nodes, const int64_t* 
     status_words += (size_t)tiles_for(cap_nodes[h], fanouts[h], kTileItersMin);
   }
   ws->table_entries = table_entries_for(cap_nodes[n_hops]);
-  const size_t table_bytes = ws->table_entries * sizeof(HashEntry);
+  size_t table_bytes = ws->table_entries * sizeof(HashEntry);
   const size_t sync_bytes = align_up(status_words * 8 + (DCI_MAX_HOPS + 1) * 4, 16);
-  char* region = ar.take<char>(table_bytes + sync_bytes);
+  char* region = ar.take<char>(table_bytes + sync_bytes);  // the hashed table's size either way
+  if (table_is_direct(num_nodes, table_bytes)) {
+    ws->table_entries = 0;
+    table_bytes = align_up(4 * (size_t)num_nodes, 16);  // both are multiples of 16: at most the hashed table's bytes
+  }
   ws->table = reinterpret_cast<HashEntry*>(region);
   unsigned long long* st = reinterpret_cast<unsigned long long*>(region + table_bytes);
   for (int32_t h = 0; h < n_hops; ++h) {
@@ -882,6 +913,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ha.row_cnt = ws.row_cnt[h & 1];
     ha.table = ws.table;
     ha.entries = (unsigned)ws.table_entries;
+    ha.last_node = (unsigned)(g->num_nodes - 1);
     ha.adj_count = adj_count;
     ha.edge_count = edge_count;
     ha.prev_fanout = h > 0 ? fanouts[h - 1] : 1;
@@ -902,6 +934,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ra.tmp_u = ws.tmp_u;
     ra.tmp_slot = ws.tmp_slot[h & 1];
     ra.table = ws.table;
+    ra.entries = (unsigned)ws.table_entries;
     ra.nodes = nodes;
     ra.blk_indptr = reinterpret_cast<long long*>(out->blk_indptr[h]);
     ra.blk_src = out->blk_src[h];
@@ -936,7 +969,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     hipLaunchKernelGGL(k_write_src, dim3(grid_for_rows(ctx, positions, kBlock)), dim3(kBlock), 0, ctx->stream,
                        (const long long*)counts, h, fanouts[h], (const int*)ws.row_cnt[h & 1],
                        (const int*)ws.tmp_slot[h & 1], reinterpret_cast<const long long*>(out->blk_indptr[h]),
-                       (const HashEntry*)ws.table, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
+                       (const HashEntry*)ws.table, (unsigned)ws.table_entries, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
                        (const unsigned*)ws.batch_flag, counts, ctx->host_flag, (const long long*)nodes, n_hops, feat_count);
   }
   DCI_LAUNCH_CHECK(ctx);
@@ -976,7 +1009,7 @@ size_t dci_sample_workspace_bytes(int64_t num_nodes, int64_t n_seeds, const int3
   Arena ar(nullptr, 0);
   SampleWs ws;
   dci_blocks b;
-  carve_sample_ws(ar, cap_nodes, cap_edges, fanouts, n_hops, &ws);
+  carve_sample_ws(ar, num_nodes, cap_nodes, cap_edges, fanouts, n_hops, &ws);
   carve_blocks(ar, cap_nodes, cap_edges, n_hops, &b);
   (void)ar.take<char>(256 * 1024);  // room for the gather statistics of the pre-sampling pass
   return ar.off;
@@ -999,7 +1032,7 @@ static int32_t sample_khop_in(dci_ctx* ctx, const dci_graph* graph, const dci_ca
   {  // remembered for dci_last_required, should one of the capacity checks below fail
     Arena probe(nullptr, 0);
     SampleWs unused;
-    carve_sample_ws(probe, cap_nodes, cap_edges, fanouts, n_hops, &unused);
+    carve_sample_ws(probe, graph->num_nodes, cap_nodes, cap_edges, fanouts, n_hops, &unused);
     std::memset(ctx->req_nodes, 0, sizeof(ctx->req_nodes));
     std::memset(ctx->req_edges, 0, sizeof(ctx->req_edges));
     for (int32_t h = 0; h <= n_hops; ++h) ctx->req_nodes[h] = cap_nodes[h];
@@ -1018,7 +1051,7 @@ static int32_t sample_khop_in(dci_ctx* ctx, const dci_graph* graph, const dci_ca
   }
   Arena ar(ws_base, ws_bytes);
   SampleWs ws;
-  carve_sample_ws(ar, cap_nodes, cap_edges, fanouts, n_hops, &ws);
+  carve_sample_ws(ar, graph->num_nodes, cap_nodes, cap_edges, fanouts, n_hops, &ws);
   if (!ar.ok())
     return fail(ctx, DCI_ERR_CAPACITY, "%s holds %zu bytes, sampling a batch of these bounds needs %zu", ws_name,
                 ws_bytes, ar.off);
@@ -1052,7 +1085,7 @@ size_t dci_sample_khop_scratch_bytes(int64_t num_nodes, int64_t n_seeds, const i
   if (dci_blocks_bounds(num_nodes, n_seeds, fanouts, n_hops, cap_nodes, cap_edges) != DCI_OK) return 0;
   Arena ar(nullptr, 0);
   SampleWs ws;
-  carve_sample_ws(ar, cap_nodes, cap_edges, fanouts, n_hops, &ws);
+  carve_sample_ws(ar, num_nodes, cap_nodes, cap_edges, fanouts, n_hops, &ws);
   return ar.off;
 }
 
@@ -1076,7 +1109,7 @@ int32_t dci_presample_count(dci_ctx* ctx, const dci_graph* graph, const dci_cach
   Arena ar(ctx->ws, ctx->ws_bytes);
   SampleWs ws;
   dci_blocks blk;
-  carve_sample_ws(ar, cap_nodes, cap_edges, fanouts, n_hops, &ws);
+  carve_sample_ws(ar, graph->num_nodes, cap_nodes, cap_edges, fanouts, n_hops, &ws);
   carve_blocks(ar, cap_nodes, cap_edges, n_hops, &blk);
   void* gather_partials = ar.take<char>(gather_partials_bytes(ctx));
   if (!ar.ok())

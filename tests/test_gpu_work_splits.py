@@ -54,3 +54,23 @@ def test_counter_totals_decide_the_feature_rows(env, N):
         cache = dci.dci_fill_caches(ctx, g, gu.dev(count.view(np.int32)), gu.dev(np.zeros(N, dtype=np.int32)), 12 * (N // 3 + 1), 0, 1,
                                     policy | dci.DCI_FILL_STRICT_SPLIT)
         assert cache.feat_rows == k and np.array_equal(cache.feat_remap.cpu().numpy(), remap)
+
+
+# The sampler's node table is direct up to four nodes of the graph per node of the batch's bound, and hashed beyond: both sides
+# of that line (768 nodes' bound; the smallest table, of 1,024 words), sizes that leave the cleared region a remainder, the
+# first and last node ids, duplicate seeds and lists that repeat a hub.
+@pytest.mark.parametrize("N,n_seeds", [(1, 5), (3, 2), (2_047, 3), (2_048, 3), (2_049, 3), (3_071, 64), (3_072, 64), (3_073, 64)])
+def test_node_table_direct_and_hashed(env, N, n_seeds):
+    dci, gu, ctx = env["dci"], env["gu"], env["ctx"]
+    rng = np.random.default_rng(N)
+    degree = rng.integers(0, 9, N)
+    indptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    indices = np.where(rng.random(indptr[-1]) < 0.5, N - 1, rng.integers(0, N, indptr[-1])).astype(np.int64)
+    seeds = rng.integers(0, N, n_seeds).astype(np.int64)
+    seeds[0], seeds[-1] = N - 1, 0
+    g = gu.make_graph(indptr, indices, None)
+    blk = dci.Blocks(ctx, N, n_seeds, (3, 2))
+    for batch in range(2):  # the second batch meets what the first left in the table
+        for sample in (dci.dci_sample_khop, dci.dci_sample_khop_static):
+            sample(ctx, g, None, gu.dev(seeds), batch, (3, 2), 7, blk)
+            gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), oracle.sample_khop(indptr, indices, seeds, batch, (3, 2), 7))
