@@ -74,3 +74,20 @@ def test_node_table_direct_and_hashed(env, N, n_seeds):
         for sample in (dci.dci_sample_khop, dci.dci_sample_khop_static):
             sample(ctx, g, None, gu.dev(seeds), batch, (3, 2), 7, blk)
             gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), oracle.sample_khop(indptr, indices, seeds, batch, (3, 2), 7))
+
+
+# Floyd's chain takes its slots four at a time: fan-outs at the edges of the fours and of the lane groups, lists one longer than
+# the fan-out (where collisions are the rule) and long ones.
+@pytest.mark.parametrize("fanout", [1, 2, 4, 5, 6, 8, 9, 16, 17, 31, 32, 33, 62, 64])
+def test_draw_chain_at_the_edges_of_its_steps(env, fanout):
+    dci, gu, ctx = env["dci"], env["gu"], env["ctx"]
+    N = 200
+    rng = np.random.default_rng(fanout)
+    degree = rng.choice([fanout - 1, fanout, fanout + 1, fanout + 2, 5 * fanout], N)
+    indptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    indices = rng.integers(0, N, indptr[-1]).astype(np.int64)
+    seeds = rng.permutation(N)[:101].astype(np.int64)
+    g = gu.make_graph(indptr, indices, None)
+    blk = dci.Blocks(ctx, N, len(seeds), (fanout,))
+    dci.dci_sample_khop(ctx, g, None, gu.dev(seeds), 3, (fanout,), 11, blk)
+    gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), oracle.sample_khop(indptr, indices, seeds, 3, (fanout,), 11))
