@@ -55,13 +55,13 @@ constexpr int kHostLineLog2 = 7;  // the host link moves 128-byte lines: smaller
 // else = a relabel tile gave up waiting for its predecessors, the batch's outputs are void.
 constexpr unsigned kBatchOk = 0xFFFFFFFFu;
 
-// The value of a slot: the low half (little endian) of a hashed table's word, the word itself of a direct one
-// (entries == 0; the slot is the node's id).
-__device__ __forceinline__ unsigned entry_val(const HashEntry* table, unsigned entries, unsigned slot) {
-  return reinterpret_cast<const unsigned*>(table)[(size_t)slot << (entries ? 1 : 0)];
+// The value of a slot: the low half (little endian) of a hashed table's word (shift 1), or the first of the 2^shift
+// 32-bit words that a direct table has per node (its slot is the node's id).
+__device__ __forceinline__ unsigned entry_val(const HashEntry* table, unsigned shift, unsigned slot) {
+  return reinterpret_cast<const unsigned*>(table)[(size_t)slot << shift];
 }
-__device__ __forceinline__ void entry_set_val(HashEntry* table, unsigned entries, unsigned slot, unsigned v) {
-  reinterpret_cast<unsigned*>(table)[(size_t)slot << (entries ? 1 : 0)] = v;
+__device__ __forceinline__ void entry_set_val(HashEntry* table, unsigned shift, unsigned slot, unsigned v) {
+  reinterpret_cast<unsigned*>(table)[(size_t)slot << shift] = v;
 }
 
 // ---- Philox4x32-10 (Salmon et al., SC'11), counter-based ---------------------------------
@@ -109,11 +109,11 @@ __device__ __forceinline__ unsigned uniform_below_32(unsigned k0, unsigned k1, l
 // For an entry that already holds u, key and value move as one word, so a single 64-bit atomic
 // minimum does it; an empty slot is claimed by compare-and-swap.  Values only decrease and keys
 // never change, so a stale read costs a redundant atomic at most.
-__device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned entries, unsigned last_node,
+__device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned entries, unsigned shift, unsigned last_node,
                                                      long long u, unsigned v, bool* candidate) {
   if (entries == 0) {
     const unsigned own = (unsigned long long)u < last_node ? (unsigned)u : last_node;
-    unsigned* const word = reinterpret_cast<unsigned*>(table) + own;
+    unsigned* const word = reinterpret_cast<unsigned*>(table) + ((size_t)own << shift);
     *candidate = __atomic_load_n(word, __ATOMIC_RELAXED) > v;
     if (*candidate) atomicMin(word, v);
     return own;
@@ -176,6 +176,7 @@ struct HopArgs {
   int* row_cnt;
   HashEntry* table;
   unsigned entries;    // of a hashed table; 0: direct
+  unsigned shift;      // of a slot, to its 32-bit word
   unsigned last_node;  // the graph's last node id
   unsigned* adj_count;
   unsigned* edge_count;
@@ -200,7 +201,7 @@ struct HopArgs {
 __device__ __forceinline__ void write_block_sources(long long n_rows, int fanout, const int* __restrict__ row_cnt,
                                                     const int* __restrict__ tmp_slot,
                                                     const long long* __restrict__ blk_indptr,
-                                                    const HashEntry* table, unsigned entries,
+                                                    const HashEntry* table, unsigned shift,
                                                     int* __restrict__ blk_src,
                                                     int block, int n_blocks) {
   const long long total = n_rows * fanout;
@@ -209,7 +210,7 @@ __device__ __forceinline__ void write_block_sources(long long n_rows, int fanout
     const int s = (int)(q - i * fanout);
     if (s < (row_cnt[i] & kRowCntMask)) {
       const int ts = tmp_slot[q];
-      if (ts != kSlotDone) blk_src[blk_indptr[i] + s] = (int)entry_val(table, entries, slot_of(ts));
+      if (ts != kSlotDone) blk_src[blk_indptr[i] + s] = (int)entry_val(table, shift, slot_of(ts));
     }
   }
 }
@@ -229,7 +230,7 @@ struct StatFold {
 __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, int hop, int fanout,
                                                       const int* row_cnt, const int* tmp_slot,
                                                       const long long* blk_indptr, const HashEntry* table,
-                                                      unsigned entries, int* blk_src, long long* counts_host, StatFold sf,
+                                                      unsigned shift, int* blk_src, long long* counts_host, StatFold sf,
                                                       const unsigned* batch_flag, long long* counts_rw,
                                                       unsigned* host_flag, const long long* nodes, int n_hops,
                                                       unsigned* feat_count) {
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
     }
     return;
   }
-  write_block_sources(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, entries, blk_src, (int)blockIdx.x,
+  write_block_sources(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, shift, blk_src, (int)blockIdx.x,
                       (int)gridDim.x);
   if (feat_count) {  // pre-sampling: one visit for every input node
     const long long n = counts[n_hops];
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
   } else if ((int)blockIdx.x < a.n_write_blocks) {
     // the first few workgroups finish the previous hop while the others sample this one
     write_block_sources(a.counts[a.hop - 1], a.prev_fanout, a.prev_row_cnt, a.prev_tmp_slot, a.prev_blk_indptr,
-                        a.table, a.entries, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
+                        a.table, a.shift, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
     return;
   }
   const int block = (int)blockIdx.x - (INIT ? 0 : a.n_write_blocks);
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
         if (gl == 0) {
           a.nodes[i] = v;
           bool ignored;
-          (void)table_insert_min(a.table, a.entries, a.last_node, v, (unsigned)i, &ignored);
+          (void)table_insert_min(a.table, a.entries, a.shift, a.last_node, v, (unsigned)i, &ignored);
         }
       } else {
         v = a.nodes[i];
@@ -451,7 +452,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
       const long long u = *src;
       const int p = (int)(i * f + gl);
       bool candidate;
-      const unsigned slot = table_insert_min(a.table, a.entries, a.last_node, u, kTentative | (unsigned)p, &candidate);
+      const unsigned slot = table_insert_min(a.table, a.entries, a.shift, a.last_node, u, kTentative | (unsigned)p, &candidate);
       if (a.entries) a.tmp_u[p] = u;  // (a direct table's slot is the id)
       a.tmp_slot[p] = candidate ? (int)slot : -2 - (int)slot;  // the relabel kernel looks at the candidates only
       if (COUNT && a.edge_count) {
@@ -501,6 +502,7 @@ struct RelabelArgs {
   int* tmp_slot;  // read; the first appearances are marked kSlotDone
   HashEntry* table;
   unsigned entries;  // of a hashed table; 0: direct
+  unsigned shift;    // of a slot, to its 32-bit word
   long long* nodes;
   long long* blk_indptr;
   int* blk_src;   // the first appearances' local ids are written here, the other edges' by the next kernel
@@ -573,7 +575,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
     slot[it] = (i < n_rows && gl < f) ? a.tmp_slot[i * f + gl] : -1;  // -1 where the row has no edge
   }
 #pragma unroll
-  for (int it = 0; it < kTileIters; ++it) val[it] = slot[it] >= 0 ? entry_val(a.table, a.entries, (unsigned)slot[it]) : 0u;
+  for (int it = 0; it < kTileIters; ++it) val[it] = slot[it] >= 0 ? entry_val(a.table, a.shift, (unsigned)slot[it]) : 0u;
   unsigned first_bits = 0;
   long long new_u[kTileIters];
   unsigned long long hit_rows = 0, hit_edges = 0, host_lines = 0, bound_lines = 0;
@@ -730,7 +732,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
   for (int it = 0; it < kTileIters; ++it)
     if (new_id[it] >= 0) {
       a.nodes[new_id[it]] = new_u[it];
-      entry_set_val(a.table, a.entries, (unsigned)slot[it], (unsigned)new_id[it]);
+      entry_set_val(a.table, a.shift, (unsigned)slot[it], (unsigned)new_id[it]);
       // this edge's local id is known right here: write it (the row's edges sit at its sampled slots
       // 0 .. c-1, and s_c holds the row's inclusive edge count within the tile), and spare the edge-id pass
       // the table look-up
@@ -769,6 +771,7 @@ __global__ void k_add_u64(unsigned long long* p, unsigned long long v) { atomicA
 struct SampleWs {
   HashEntry* table;        // the table, the tile status words and the tickets are one region,
   uint64_t table_entries;  // cleared with a single all-ones fill per batch (0 entries: direct table)
+  unsigned table_shift;    // of a slot, to its 32-bit word
   unsigned long long* status[DCI_MAX_HOPS];
   unsigned* ticket;        // [DCI_MAX_HOPS]
   unsigned* batch_flag;    // one word after the tickets, also in the cleared region
@@ -792,10 +795,20 @@ static uint64_t table_entries_for(int64_t cap_nodes_last) {
 // claim to wait for, no probing, no second copy of the ids); a graph many times the batch's bound would pay
 // for its clear with more than that (24 M nodes, bound 4.3 M: direct 3,185 us a pass, hashed 3,168).  Slots double as negative codes in tmp_slot, hence the limit of 2^30.
 // Hashed -> direct: eight 4,096-seed batches of a 2.4 M-node graph on four lanes 2,002 -> 1,917 us (clear 39 -> 10 MB a
-// batch); an 8,192-seed batch of two hops on 4.0 M nodes 353 -> 346 us; 4,096 seeds on 1.6 M nodes 366 -> 357 us; 1,024 seeds
-// on 233 k nodes, a table that either way stays in L2, 331 -> 333 us.
+// batch); an 8,192-seed batch of two hops on 4.0 M nodes 353 -> 346 us; 4,096 seeds on 1.6 M nodes 366 -> 357 us.
 static bool table_is_direct(int64_t num_nodes, uint64_t hashed_bytes) {
   return num_nodes < ((int64_t)1 << 30) && 4 * (uint64_t)num_nodes <= hashed_bytes;
+}
+
+// A small direct table is spread out, up to four words per node, as long as it stays within 4 MB (cleared in 2 us) and
+// the hashed table's bytes: packed 32 to a 128-byte line, the nodes of a dense graph queue for their line.
+// 1,024 seeds on 233 k nodes of 490 neighbours: hashed 331, direct packed 333, direct spread 330 us.
+constexpr size_t kSpreadBytes = (size_t)4 << 20;
+static unsigned direct_shift(int64_t num_nodes, size_t hashed_bytes) {
+  const size_t limit = hashed_bytes < kSpreadBytes ? hashed_bytes : kSpreadBytes;
+  unsigned shift = 0;
+  while (shift < 2 && ((size_t)4 * (size_t)num_nodes << (shift + 1)) <= limit) ++shift;
+  return shift;
 }
 
 static int group_for(int fanout) { return fanout <= 8 ? 8 : fanout <= 16 ? 16 : fanout <= 32 ? 32 : 64; }
@@ -828,9 +841,12 @@ static void carve_sample_ws(Arena& ar, int64_t num_nodes, const int64_t* cap_nod
   size_t table_bytes = ws->table_entries * sizeof(HashEntry);
   const size_t sync_bytes = align_up(status_words * 8 + (DCI_MAX_HOPS + 1) * 4, 16);
   char* region = ar.take<char>(table_bytes + sync_bytes);  // the hashed table's size either way
+  ws->table_shift = 1;
   if (table_is_direct(num_nodes, table_bytes)) {
     ws->table_entries = 0;
-    table_bytes = align_up(4 * (size_t)num_nodes, 16);  // both are multiples of 16: at most the hashed table's bytes
+    ws->table_shift = direct_shift(num_nodes, table_bytes);
+    // both are multiples of 16: at most the hashed table's bytes
+    table_bytes = align_up((size_t)4 * (size_t)num_nodes << ws->table_shift, 16);
   }
   ws->table = reinterpret_cast<HashEntry*>(region);
   unsigned long long* st = reinterpret_cast<unsigned long long*>(region + table_bytes);
@@ -945,6 +961,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ha.row_cnt = ws.row_cnt[h & 1];
     ha.table = ws.table;
     ha.entries = (unsigned)ws.table_entries;
+    ha.shift = ws.table_shift;
     ha.last_node = (unsigned)(g->num_nodes - 1);
     ha.adj_count = adj_count;
     ha.edge_count = edge_count;
@@ -967,6 +984,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ra.tmp_slot = ws.tmp_slot[h & 1];
     ra.table = ws.table;
     ra.entries = (unsigned)ws.table_entries;
+    ra.shift = ws.table_shift;
     ra.nodes = nodes;
     ra.blk_indptr = reinterpret_cast<long long*>(out->blk_indptr[h]);
     ra.blk_src = out->blk_src[h];
@@ -1001,7 +1019,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     hipLaunchKernelGGL(k_write_src, dim3(grid_for_rows(ctx, positions, kBlock)), dim3(kBlock), 0, ctx->stream,
                        (const long long*)counts, h, fanouts[h], (const int*)ws.row_cnt[h & 1],
                        (const int*)ws.tmp_slot[h & 1], reinterpret_cast<const long long*>(out->blk_indptr[h]),
-                       (const HashEntry*)ws.table, (unsigned)ws.table_entries, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
+                       (const HashEntry*)ws.table, ws.table_shift, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
                        (const unsigned*)ws.batch_flag, counts, ctx->host_flag, (const long long*)nodes, n_hops, feat_count);
   }
   DCI_LAUNCH_CHECK(ctx);
