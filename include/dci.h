@@ -334,7 +334,7 @@ int32_t dci_presample_count(dci_ctx* ctx, const dci_graph* graph, const dci_cach
  * cache_buf: device, 256-byte aligned, at least budget_bytes + 256 bytes; the cache arrays are
  * carved from it (feature rows first).  adj_remap, feat_remap: device int32 [N], written in
  * full.  edge_count is only read with DCI_FILL_ADJ_ELEMENTS (may be NULL otherwise).  *out is
- * filled on return; this call waits for the GPU. */
+ * filled on return; this call waits for the GPU, also where it returns an error. */
 int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* graph, const uint32_t* feat_count,
                         const uint32_t* adj_count, const uint32_t* edge_count, uint64_t budget_bytes,
                         uint64_t t_sample_ns, uint64_t t_feature_ns, int32_t feat_policy, void* cache_buf,

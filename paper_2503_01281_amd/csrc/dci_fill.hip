@@ -746,6 +746,16 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
   const size_t adj_off = (size_t)((u64)k * (u64)F * 4ull + 7ull) / 8 * 8;
   long long* c_indptr = reinterpret_cast<long long*>(buf + adj_off);
 
+  // A failed call leaves the stream idle as well: the row copy is enqueued ahead of checks that can still fail (how many
+  // elements there are is only known on the GPU), and a caller that got an error may free cache_buf.
+  struct Drain {
+    hipStream_t stream;
+    bool failed = true;
+    ~Drain() {
+      if (failed) (void)hipStreamSynchronize(stream);
+    }
+  } drain{ctx->stream};
+
   int32_t rc;
   auto aligned = [](const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; };
 
@@ -916,6 +926,7 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
     }
   }
   DCI_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  drain.failed = false;
 
   std::memset(out, 0, sizeof(*out));
   out->adj_nodes = K;
