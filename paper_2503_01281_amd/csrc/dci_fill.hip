@@ -644,27 +644,29 @@ static void carve_elem_ws(Arena& ar, long long n_nodes, long long n_elems, ElemW
 
 struct FillWs {
   CountTotals* totals;  // [2]
-  CountTotals* parts;   // [2 * kCountBlocks]
   u32* deg;
   SortWs sort;
 };
 
 static void carve_fill_ws(Arena& ar, long long n, FillWs* ws) {
   ws->totals = ar.take<CountTotals>(2);
-  ws->parts = ar.take<CountTotals>(2 * kCountBlocks);
   ws->deg = ar.take<u32>((size_t)n);
   carve_sort_ws(ar, n, &ws->sort);
 }
 
-// Enqueues the totals of count0 (and, unless null, count1), n values each, to ws.totals and to the pinned `host`.
-static int32_t count_totals(dci_ctx* ctx, const u32* count0, const u32* count1, long long n, const FillWs& ws, CountTotals* host) {
+// Enqueues the totals of count0 (and, unless null, count1), n values each, to `totals` and to the pinned `host`.  The
+// workgroups' triples lie in the first key buffer of `sort`, scratch for n values that no sort uses yet: 48 bytes per 1,024
+// values in a buffer of 4 bytes per value, rounded up to 256.
+static int32_t count_totals(dci_ctx* ctx, const u32* count0, const u32* count1, long long n, const SortWs& sort,
+                            CountTotals* totals, CountTotals* host) {
+  CountTotals* const parts = reinterpret_cast<CountTotals*>(sort.keys[0]);
   long long blocks = (n + 4 * kFillBlock - 1) / (4 * kFillBlock);
   if (blocks > kCountBlocks) blocks = kCountBlocks;
   const unsigned arrays = count1 ? 2 : 1;
-  hipLaunchKernelGGL(k_count_totals, dim3((unsigned)blocks, arrays), dim3(kFillBlock), 0, ctx->stream, count0, count1, n, ws.parts);
+  hipLaunchKernelGGL(k_count_totals, dim3((unsigned)blocks, arrays), dim3(kFillBlock), 0, ctx->stream, count0, count1, n, parts);
   DCI_LAUNCH_CHECK(ctx);
-  hipLaunchKernelGGL(k_count_fold, dim3(arrays), dim3(kFillBlock), 0, ctx->stream, (const CountTotals*)ws.parts, (int)blocks,
-                     ws.totals, host);
+  hipLaunchKernelGGL(k_count_fold, dim3(arrays), dim3(kFillBlock), 0, ctx->stream, (const CountTotals*)parts, (int)blocks,
+                     totals, host);
   DCI_LAUNCH_CHECK(ctx);
   return DCI_OK;
 }
@@ -767,7 +769,7 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
   static_assert(sizeof(CountTotals) * 2 == 6 * sizeof(u64), "layout of the pinned words");
   const bool topk = feat_policy == DCI_FEAT_POLICY_TOPK;
   const bool adj_all = adj_total <= c_adj, adj_none = !adj_all && c_adj < 16 && !elements, adj_sort = !adj_all && !adj_none;
-  if ((rc = count_totals(ctx, feat_count, adj_sort ? adj_count : nullptr, N, ws, host_totals)) != DCI_OK) return rc;
+  if ((rc = count_totals(ctx, feat_count, adj_sort ? adj_count : nullptr, N, ws.sort, ws.totals, host_totals)) != DCI_OK) return rc;
   if (topk || adj_sort) DCI_HIP(ctx, hipStreamSynchronize(ctx->stream));
 
   // 2. feature cache: which rows
@@ -902,7 +904,7 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
         hipLaunchKernelGGL(k_gather_elems, dim3(grid_1d(ctx, n_nz, wpb)), dim3(kFillBlock), 0, ctx->stream, order, n_nz,
                            indptr, indices, edge_count, (const long long*)ew.off, ew.vals, ew.cnt, ew.seg);
         DCI_LAUNCH_CHECK(ctx);
-        if ((rc = count_totals(ctx, (const u32*)ew.cnt, nullptr, e_nz, ws, host_totals)) != DCI_OK) return rc;
+        if ((rc = count_totals(ctx, (const u32*)ew.cnt, nullptr, e_nz, ew.sort, ws.totals, host_totals)) != DCI_OK) return rc;
         DCI_HIP(ctx, hipStreamSynchronize(ctx->stream));
         const int* by_count = nullptr;
         if ((rc = sort_by_count_desc(ctx, ew.cnt, e_nz, (u32)host_totals[0].max, ew.sort, &by_count)) != DCI_OK) return rc;

@@ -55,6 +55,18 @@ def test_workspace_queries_grow_with_the_problem(lib):
     assert need >= 67584 * 602 * 4 + 2 * 67584 * 256 * 4
 
 
+def test_fill_workspace_stays_what_its_arrays_take(lib):
+    """Five arrays of a word per node, the sort's histograms and scan sums, two counter totals: nothing of a size of its
+    own, so a workspace that a caller sized once keeps being enough."""
+    up = lambda n: -(-n // 256) * 256
+    sort = lambda n: 4 * up(4 * n) + up(1024 * -(-n // 4096)) + up(8 * (-(-max(n, 256 * -(-n // 4096)) // 2048) + 1))
+    for n in (1, 1_000, 2_449_029):
+        fill = 256 + up(4 * n) + sort(n)
+        assert lib.dci_fill_workspace_bytes(n) == fill
+        e = 10 * n
+        assert lib.dci_fill_elements_workspace_bytes(n, e) == fill + up(8 * (n + 1)) + up(8 * e) + 2 * up(4 * e) + sort(e)
+
+
 def test_static_scratch_size_query(lib):
     """The no-allocation sampler's size query (host arithmetic only): a Medium-sized batch fits the
     static array, a Large-sized one does not, invalid fan-outs give 0."""
