@@ -460,13 +460,15 @@ struct AdjOut {
 };
 
 // Copies the cached (leading) parts of the lists of slots s0 <= s < K.  Bound by the read of the lists (over the
-// host link where the graph lives there).  Every workgroup copies an equal share of the elements, whatever lists
-// they belong to: the cached nodes are the hottest ones, in order, and with a wavefront per list the few hubs at the
-// front decide how long it takes (5.5 M elements in HBM: 370 us, with equal shares 30; 4.5 M elements over the link:
-// 1,116 us, with equal shares 660 = 55 GB/s, the link's streaming rate).  The lists that a share of kListChunk elements touches are staged in LDS, at most
-// kListSlots at a time - where each begins in the share and how far its source is from its destination - and a
-// lane finds its element's list there by bisection.
-constexpr int kListChunk = 4096, kListSlots = 2048;
+// host link where the graph lives there).  Every workgroup takes equal shares of the slots and elements together (a
+// slot's unit, then its elements), whatever lists they belong to.  The cached nodes are the hottest ones, in order: with a
+// wavefront per list the few hubs at the front decide how long it takes (5.5 M elements in HBM: 370 us, with equal
+// shares 30; 4.5 M elements over the link: 1,116 us, with equal shares 660 = 55 GB/s, the link's streaming rate).  And
+// nodes without neighbours come in runs: counted by elements alone one share holds all of a run (6 M of them between two
+// lists: a fill of 14.4 ms, with the slots shared out as well 0.48).
+// The lists that a share touches are staged in LDS, at most kListSlots at a time - where each begins in the share and how
+// far its source is from its destination - and a lane finds its element's list there by bisection.
+constexpr int kListShare = 4096, kListSlots = 2048;
 
 __global__ __launch_bounds__(kFillBlock) void k_copy_lists(const int* __restrict__ order, long long s0, long long K,
                                                            const long long* __restrict__ indptr,
@@ -475,22 +477,26 @@ __global__ __launch_bounds__(kFillBlock) void k_copy_lists(const int* __restrict
                                                            long long* __restrict__ c_indices) {
   __shared__ int s_begin[kListSlots];         // first element of the staged list within the share (-1: before it)
   __shared__ long long s_shift[kListSlots];   // source position minus destination position
-  const long long first = c_indptr[s0], last = c_indptr[K];
+  const long long first = c_indptr[s0], units = K - s0 + c_indptr[K] - first;
   const int tid = (int)threadIdx.x;
-  for (long long e0 = first + (long long)blockIdx.x * kListChunk; e0 < last; e0 += (long long)gridDim.x * kListChunk) {
-    const long long e1 = e0 + kListChunk < last ? e0 + kListChunk : last;
-    // the slots of the share's first and last element: the last slot that begins at or before it, by a search in 256 parts
+  for (long long p0 = (long long)blockIdx.x * kListShare; p0 < units; p0 += (long long)gridDim.x * kListShare) {
+    const long long p1 = p0 + kListShare < units ? p0 + kListShare : units;
+    // the slots of the share's first and last unit: the last slot whose own unit lies at or before it, by a search in
+    // 256 parts
     long long lo[2] = {s0, s0}, hi[2] = {K, K};
     while (hi[0] - lo[0] > 1 || hi[1] - lo[1] > 1) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const long long step = (hi[k] - lo[k] + kFillBlock - 1) / kFillBlock;
         const long long at = lo[k] + tid * step;
-        const int n_le = __syncthreads_count(at < hi[k] && c_indptr[at] <= (k ? e1 - 1 : e0));
+        const int n_le = __syncthreads_count(at < hi[k] && at - s0 + c_indptr[at] - first <= (k ? p1 - 1 : p0));
         lo[k] += (n_le - 1) * step;  // the probe at lo itself always holds
         if (lo[k] + step < hi[k]) hi[k] = lo[k] + step;
       }
     }
+    // the share's elements: p units from the start are those of the slots up to there less the slots themselves
+    const long long e0 = first + p0 - (lo[0] - s0) - (lo[0] - s0 + c_indptr[lo[0]] - first < p0 ? 1 : 0);
+    const long long e1 = first + p1 - 1 - (lo[1] - s0);
     long long s = lo[0];
     const long long s_end = lo[1] + 1;
     for (long long e = e0; e < e1;) {
@@ -499,12 +505,12 @@ __global__ __launch_bounds__(kFillBlock) void k_copy_lists(const int* __restrict
       for (int k = tid; k < n; k += kFillBlock) {
         const long long dst0 = c_indptr[s + k];
         s_begin[k] = dst0 < e0 ? -1 : (int)(dst0 - e0);
-        s_shift[k] = indptr[order[s + k]] - dst0;
+        if (c_indptr[s + k + 1] != dst0) s_shift[k] = indptr[order[s + k]] - dst0;
       }
       __syncthreads();
       const long long staged = s + n < s_end ? c_indptr[s + n] : e1;
       const long long stop = staged < e1 ? staged : e1;
-      constexpr int kPer = kListChunk / kFillBlock;
+      constexpr int kPer = kListShare / kFillBlock;
       long long v[kPer];
 #pragma unroll
       for (int k = 0; k < kPer; ++k) {
@@ -922,7 +928,7 @@ int32_t dci_fill_caches(dci_ctx* ctx, const dci_graph* g, const uint32_t* feat_c
     }
     if (K > first_plain) {
       // Entries of c_indptr beyond K+1 were never written; the lists start right after entry K.
-      hipLaunchKernelGGL(k_copy_lists, dim3(grid_1d(ctx, M, kListChunk)), dim3(kFillBlock), 0,
+      hipLaunchKernelGGL(k_copy_lists, dim3(grid_1d(ctx, K - first_plain + M, kListShare)), dim3(kFillBlock), 0,
                          ctx->stream, order, first_plain, K, indptr, indices, (const long long*)c_indptr, c_indices);
       DCI_LAUNCH_CHECK(ctx);
     }
