@@ -240,7 +240,8 @@ enum {
   DCI_K_LINEAR_IN = 6,   /* first layer (input features): dense layer (matrix cores) */
   DCI_K_MEAN = 7,        /* later layers: neighbour mean                            */
   DCI_K_LINEAR = 8,      /* later layers: dense layer                               */
-  DCI_K_COUNT_NODES = 9, /* pre-sampling: visits of the input nodes (counted by the closing kernel: no launches of its own) */
+  DCI_K_COUNT_NODES = 9, /* pre-sampling: what DCI_K_WRITE_SRC is elsewhere, and the
+                            visits of the input nodes (one kernel)                */
   DCI_K_COUNT = 10
 };
 #define DCI_TIMING_MAX_LAUNCHES 8192

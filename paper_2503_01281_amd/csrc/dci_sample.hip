@@ -1015,7 +1015,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
       sf.part[k] = k < n_hops ? ws.stat_part[k] : nullptr;
       sf.tile_rows[k] = k < n_hops ? (kBlock / group_for(fanouts[k])) * tile_iters_for(ctx, out->cap_rows[k], fanouts[k]) : 1;
     }
-    Timed t(ctx, DCI_K_WRITE_SRC);
+    Timed t(ctx, feat_count ? DCI_K_COUNT_NODES : DCI_K_WRITE_SRC);
     hipLaunchKernelGGL(k_write_src, dim3(grid_for_rows(ctx, positions, kBlock)), dim3(kBlock), 0, ctx->stream,
                        (const long long*)counts, h, fanouts[h], (const int*)ws.row_cnt[h & 1],
                        (const int*)ws.tmp_slot[h & 1], reinterpret_cast<const long long*>(out->blk_indptr[h]),

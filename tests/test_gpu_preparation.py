@@ -76,3 +76,23 @@ def test_run_of_empty_lists_is_shared_out(env):
     _, few = fill_adjacency(env, indptr, indices, count, 8 * 5_010)
     print(f"fill of {K} lists {ms:.2f} ms, of a few {few:.2f} ms")
     assert ms < 3 * few + 1
+
+
+# The closing kernel of a pre-sampled batch counts the visits of the input nodes and is billed as that; a batch that is
+# only sampled has none to count.
+def test_visit_counting_has_its_timing_class(env):
+    dci, gu = env["dci"], env["gu"]
+    N, fanouts = 500, (3, 2)
+    rng = np.random.default_rng(1)
+    indptr = np.arange(0, 6 * N + 1, 6, dtype=np.int64)
+    g = gu.make_graph(indptr, rng.integers(0, N, 6 * N), None)
+    seeds = gu.dev(rng.permutation(N)[:100])
+    ctx = dci.Context(0)
+    counts = [torch.zeros(N, dtype=torch.int32, device="cuda") for _ in range(2)]
+    ctx.timing_enable(["write_src", "count_nodes"])
+    dci.dci_presample_count(ctx, g, None, seeds, 20, 0, 5, 0, fanouts, 7, *counts)
+    t = ctx.timing_read()
+    assert t["count_nodes"][1] == 5 and t["count_nodes"][0] > 0 and t["write_src"] == (0.0, 0)
+    dci.dci_sample_khop(ctx, g, None, seeds, 0, fanouts, 7, dci.Blocks(ctx, N, 100, fanouts))
+    t = ctx.timing_read()
+    assert t["write_src"][1] == 1 and t["write_src"][0] > 0 and t["count_nodes"] == (0.0, 0)
