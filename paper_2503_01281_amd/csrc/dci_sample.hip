@@ -90,14 +90,6 @@ __device__ __forceinline__ unsigned long long uniform_below(unsigned k0, unsigne
   return __umul64hi(u, m);
 }
 
-// The same draw for m < 2^32: u m / 2^64 from two 32-bit products, exactly.
-__device__ __forceinline__ unsigned uniform_below_32(unsigned k0, unsigned k1, long long node, unsigned batch, int hop,
-                                                     int slot, unsigned m) {
-  const unsigned long long u = philox_u64((unsigned)(unsigned long long)node, (unsigned)((unsigned long long)node >> 32),
-                                          batch, ((unsigned)hop << 24) | (unsigned)slot, k0, k1);
-  return (unsigned)(((u >> 32) * m + (((u & 0xFFFFFFFFull) * m) >> 32)) >> 32);
-}
-
 // ---- node table -----------------------------------------------------------------------------
 // Direct (entries == 0): the node's word is looked at and, if v is smaller, lowered by an atomic minimum whose
 // result nobody waits for; one dependent access per edge where the hashed table has two or more (look, claim,
@@ -385,41 +377,17 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
     if (__ballot(floyd) != 0ull) {
       // slot s draws t_s below j_s + 1, j_s = d - f + s; it keeps t_s unless an earlier slot
       // already holds that value, in which case it takes j_s.
-      // The chain over the slots is serial, and on long frontiers its instructions are a good part of the kernel's
-      // time.  Lists of fewer than 2^32 - 1 elements (in practice all; uniform over the wavefront) take it in
-      // 32 bits, four broadcasts at a time: those do not depend on the chain.  The slots at and above f that the last four
-      // may run over belong to lanes that hold no slot.
-      // Before -> now: 8,192 seeds, two hops of 10 and 25, 4.0 M nodes 346 -> 343 us; 256 seeds, hops of 5 and 10 76.2 -> 75.7 us.
-      if (__ballot(floyd && d >= 0xFFFFFFFFll) == 0ull) {
-        const unsigned j = (unsigned)(d - f) + (unsigned)gl;
-        unsigned t = 0;
-        if (floyd && gl < f) t = uniform_below_32(a.k0, a.k1, v, a.batch, a.hop, gl, j + 1u);
-        unsigned S = t;
-        constexpr int kAhead = 4;
-        for (int s0 = 1; s0 < f; s0 += kAhead) {
-          unsigned ts[kAhead];
-#pragma unroll
-          for (int k = 0; k < kAhead; ++k) ts[k] = __shfl(t, (s0 + k) & (G - 1), G);
-#pragma unroll
-          for (int k = 0; k < kAhead; ++k) {
-            const bool any = group_bits<G>(__ballot(gl < s0 + k && S == ts[k]), grp_in_wave) != 0ull;
-            if (gl == s0 + k && any) S = j;
-          }
-        }
-        if (floyd) pos = S;
-      } else {
-        const long long j = d - f + gl;
-        long long t = 0;
-        if (floyd && gl < f) t = (long long)uniform_below(a.k0, a.k1, v, a.batch, a.hop, gl, (unsigned long long)(j + 1));
-        long long S = t;
-        for (int s = 1; s < f; ++s) {
-          const long long ts = __shfl(t, s, G);
-          const bool match = floyd && gl < s && S == ts;
-          const bool any = group_bits<G>(__ballot(match), grp_in_wave) != 0ull;
-          if (gl == s && any) S = j;
-        }
-        if (floyd) pos = S;
+      const long long j = d - f + gl;
+      long long t = 0;
+      if (floyd && gl < f) t = (long long)uniform_below(a.k0, a.k1, v, a.batch, a.hop, gl, (unsigned long long)(j + 1));
+      long long S = t;
+      for (int s = 1; s < f; ++s) {
+        const long long ts = __shfl(t, s, G);
+        const bool match = floyd && gl < s && S == ts;
+        const bool any = group_bits<G>(__ballot(match), grp_in_wave) != 0ull;
+        if (gl == s && any) S = j;
       }
+      if (floyd) pos = S;
     }
     const bool active = row_ok && gl < c;
     // position p of a node with a slot is served by the cache iff p < cached length (Section IV-B, third
@@ -793,7 +761,8 @@ static uint64_t table_entries_for(int64_t cap_nodes_last) {
 // Direct table: 4 bytes per node of the graph, where that is no more to clear than the hashed table's 8 bytes for
 // each of twice the bound on the batch's nodes.  At equal bytes the direct one is the quicker of the two (no
 // claim to wait for, no probing, no second copy of the ids); a graph many times the batch's bound would pay
-// for its clear with more than that (24 M nodes, bound 4.3 M: direct 3,185 us a pass, hashed 3,168).  Slots double as negative codes in tmp_slot, hence the limit of 2^30.
+// for its clear with more than that (24 M nodes, bound 4.3 M: direct 3,185 us a pass, hashed 3,168).  Slots double as
+// negative codes in tmp_slot, hence the limit of 2^30.
 // Hashed -> direct: eight 4,096-seed batches of a 2.4 M-node graph on four lanes 2,002 -> 1,917 us (clear 39 -> 10 MB a
 // batch); an 8,192-seed batch of two hops on 4.0 M nodes 353 -> 346 us; 4,096 seeds on 1.6 M nodes 366 -> 357 us.
 static bool table_is_direct(int64_t num_nodes, uint64_t hashed_bytes) {

@@ -76,7 +76,7 @@ def test_node_table_direct_and_hashed(env, N, n_seeds):
             gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), oracle.sample_khop(indptr, indices, seeds, batch, (3, 2), 7))
 
 
-# Floyd's chain takes its slots four at a time: fan-outs at the edges of the fours and of the lane groups, lists one longer than
+# Floyd's chain over the slots of a lane group: fan-outs at the edges of the groups and between them, lists one longer than
 # the fan-out (where collisions are the rule) and long ones.
 @pytest.mark.parametrize("fanout", [1, 2, 4, 5, 6, 8, 9, 16, 17, 31, 32, 33, 62, 64])
 def test_draw_chain_at_the_edges_of_its_steps(env, fanout):
