@@ -55,13 +55,17 @@ constexpr int kHostLineLog2 = 7;  // the host link moves 128-byte lines: smaller
 // else = a relabel tile gave up waiting for its predecessors, the batch's outputs are void.
 constexpr unsigned kBatchOk = 0xFFFFFFFFu;
 
-// The value of a slot: the low half (little endian) of a hashed table's word (shift 1), or the first of the 2^shift
-// 32-bit words that a direct table has per node (its slot is the node's id).
+// The value of a slot: the low half (little endian) of a hashed table's word, or the first of the 2^shift 32-bit words
+// that a direct table has per node (its slot is the node's id).  The kind is a template parameter throughout: the kernels of
+// small batches are bound by latency, code fetch included, and with the kind as a branch at run time the hashed ones were a
+// third longer (six batches of 27 seeds 486 us, as a template 479; 485 seeds 117.2 and 115.3).
+template <bool DIRECT>
 __device__ __forceinline__ unsigned entry_val(const HashEntry* table, unsigned shift, unsigned slot) {
-  return reinterpret_cast<const unsigned*>(table)[(size_t)slot << shift];
+  return reinterpret_cast<const unsigned*>(table)[(size_t)slot << (DIRECT ? shift : 1u)];
 }
+template <bool DIRECT>
 __device__ __forceinline__ void entry_set_val(HashEntry* table, unsigned shift, unsigned slot, unsigned v) {
-  reinterpret_cast<unsigned*>(table)[(size_t)slot << shift] = v;
+  reinterpret_cast<unsigned*>(table)[(size_t)slot << (DIRECT ? shift : 1u)] = v;
 }
 
 // ---- Philox4x32-10 (Salmon et al., SC'11), counter-based ---------------------------------
@@ -91,7 +95,7 @@ __device__ __forceinline__ unsigned long long uniform_below(unsigned k0, unsigne
 }
 
 // ---- node table -----------------------------------------------------------------------------
-// Direct (entries == 0): the node's word is looked at and, if v is smaller, lowered by an atomic minimum whose
+// Direct: the node's word is looked at and, if v is smaller, lowered by an atomic minimum whose
 // result nobody waits for; one dependent access per edge where the hashed table has two or more (look, claim,
 // probe on).  An id outside the graph stays inside the table (its last word).
 // Hashed: finds or creates the entry of node u (open addressing, linear probing) and lowers its value to
@@ -101,9 +105,10 @@ __device__ __forceinline__ unsigned long long uniform_below(unsigned k0, unsigne
 // For an entry that already holds u, key and value move as one word, so a single 64-bit atomic
 // minimum does it; an empty slot is claimed by compare-and-swap.  Values only decrease and keys
 // never change, so a stale read costs a redundant atomic at most.
+template <bool DIRECT>
 __device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned entries, unsigned shift, unsigned last_node,
                                                      long long u, unsigned v, bool* candidate) {
-  if (entries == 0) {
+  if (DIRECT) {
     const unsigned own = (unsigned long long)u < last_node ? (unsigned)u : last_node;
     unsigned* const word = reinterpret_cast<unsigned*>(table) + ((size_t)own << shift);
     *candidate = __atomic_load_n(word, __ATOMIC_RELAXED) > v;
@@ -167,9 +172,9 @@ struct HopArgs {
   int* tmp_slot;
   int* row_cnt;
   HashEntry* table;
-  unsigned entries;    // of a hashed table; 0: direct
-  unsigned shift;      // of a slot, to its 32-bit word
-  unsigned last_node;  // the graph's last node id
+  unsigned entries;    // of a hashed table
+  unsigned shift;      // of a direct table's slot, to its 32-bit word
+  unsigned last_node;  // the graph's last node id (direct table)
   unsigned* adj_count;
   unsigned* edge_count;
   // previous hop, whose edges get their local ids at the start of this kernel (hop >= 1)
@@ -190,6 +195,7 @@ struct HopArgs {
 
 // blk_src of a finished hop: every edge reads the (by now final) local id of its source.
 // One thread per padded position row * fanout + slot.
+template <bool DIRECT>
 __device__ __forceinline__ void write_block_sources(long long n_rows, int fanout, const int* __restrict__ row_cnt,
                                                     const int* __restrict__ tmp_slot,
                                                     const long long* __restrict__ blk_indptr,
@@ -202,7 +208,7 @@ __device__ __forceinline__ void write_block_sources(long long n_rows, int fanout
     const int s = (int)(q - i * fanout);
     if (s < (row_cnt[i] & kRowCntMask)) {
       const int ts = tmp_slot[q];
-      if (ts != kSlotDone) blk_src[blk_indptr[i] + s] = (int)entry_val(table, shift, slot_of(ts));
+      if (ts != kSlotDone) blk_src[blk_indptr[i] + s] = (int)entry_val<DIRECT>(table, shift, slot_of(ts));
     }
   }
 }
@@ -219,6 +225,7 @@ struct StatFold {
   int n_hops;
 };
 
+template <bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, int hop, int fanout,
                                                       const int* row_cnt, const int* tmp_slot,
                                                       const long long* blk_indptr, const HashEntry* table,
@@ -236,8 +243,8 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
     }
     return;
   }
-  write_block_sources(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, shift, blk_src, (int)blockIdx.x,
-                      (int)gridDim.x);
+  write_block_sources<DIRECT>(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, shift, blk_src, (int)blockIdx.x,
+                              (int)gridDim.x);
   if (feat_count) {  // pre-sampling: one visit for every input node
     const long long n = counts[n_hops];
     for (long long i = blockIdx.x * (long long)kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
@@ -303,7 +310,7 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
 // i in the table; an atomic minimum, so it also wins against a neighbour lane that registered
 // the same node a moment earlier).  Otherwise the kernel starts by finishing the previous hop
 // (write_block_sources), which only needs values that are already final.
-template <int G, bool COUNT, bool INIT>
+template <int G, bool COUNT, bool INIT, bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
   const long long n_rows = INIT ? a.n_seeds : a.counts[a.hop];
   const long long n_noted = INIT ? 0 : a.counts[a.hop - 1];  // rows below this were rows of the previous hop as well
@@ -313,8 +320,8 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
     return;  // an earlier relabel tile gave up: the closing kernel voids the batch
   } else if ((int)blockIdx.x < a.n_write_blocks) {
     // the first few workgroups finish the previous hop while the others sample this one
-    write_block_sources(a.counts[a.hop - 1], a.prev_fanout, a.prev_row_cnt, a.prev_tmp_slot, a.prev_blk_indptr,
-                        a.table, a.shift, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
+    write_block_sources<DIRECT>(a.counts[a.hop - 1], a.prev_fanout, a.prev_row_cnt, a.prev_tmp_slot, a.prev_blk_indptr,
+                                a.table, a.shift, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
     return;
   }
   const int block = (int)blockIdx.x - (INIT ? 0 : a.n_write_blocks);
@@ -338,7 +345,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
         if (gl == 0) {
           a.nodes[i] = v;
           bool ignored;
-          (void)table_insert_min(a.table, a.entries, a.shift, a.last_node, v, (unsigned)i, &ignored);
+          (void)table_insert_min<DIRECT>(a.table, a.entries, a.shift, a.last_node, v, (unsigned)i, &ignored);
         }
       } else {
         v = a.nodes[i];
@@ -420,8 +427,9 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
       const long long u = *src;
       const int p = (int)(i * f + gl);
       bool candidate;
-      const unsigned slot = table_insert_min(a.table, a.entries, a.shift, a.last_node, u, kTentative | (unsigned)p, &candidate);
-      if (a.entries) a.tmp_u[p] = u;  // (a direct table's slot is the id)
+      const unsigned slot =
+          table_insert_min<DIRECT>(a.table, a.entries, a.shift, a.last_node, u, kTentative | (unsigned)p, &candidate);
+      if (!DIRECT) a.tmp_u[p] = u;  // (a direct table's slot is the id)
       a.tmp_slot[p] = candidate ? (int)slot : -2 - (int)slot;  // the relabel kernel looks at the candidates only
       if (COUNT && a.edge_count) {
         const long long host_start = hit ? a.indptr[v] : start;
@@ -469,8 +477,7 @@ struct RelabelArgs {
   const long long* tmp_u;
   int* tmp_slot;  // read; the first appearances are marked kSlotDone
   HashEntry* table;
-  unsigned entries;  // of a hashed table; 0: direct
-  unsigned shift;    // of a slot, to its 32-bit word
+  unsigned shift;  // of a direct table's slot, to its 32-bit word
   long long* nodes;
   long long* blk_indptr;
   int* blk_src;   // the first appearances' local ids are written here, the other edges' by the next kernel
@@ -482,7 +489,7 @@ struct RelabelArgs {
   unsigned first_ticket;  // tiles are numbered from here (0 except under the failure-handling test hook)
 };
 
-template <int G, int kTileIters>
+template <int G, int kTileIters, bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
   constexpr int kGroups = kBlock / G;
   constexpr int TR = kGroups * kTileIters;  // rows per tile, at most kBlock
@@ -543,7 +550,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
     slot[it] = (i < n_rows && gl < f) ? a.tmp_slot[i * f + gl] : -1;  // -1 where the row has no edge
   }
 #pragma unroll
-  for (int it = 0; it < kTileIters; ++it) val[it] = slot[it] >= 0 ? entry_val(a.table, a.shift, (unsigned)slot[it]) : 0u;
+  for (int it = 0; it < kTileIters; ++it) val[it] = slot[it] >= 0 ? entry_val<DIRECT>(a.table, a.shift, (unsigned)slot[it]) : 0u;
   unsigned first_bits = 0;
   long long new_u[kTileIters];
   unsigned long long hit_rows = 0, hit_edges = 0, host_lines = 0, bound_lines = 0;
@@ -557,7 +564,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
     if (first) first_bits |= 1u << it;
     // the ids of the first appearances are only needed once the tile knows its offsets; asked for here, they
     // arrive while the tile scans and looks back
-    new_u[it] = !first ? 0 : a.entries ? a.tmp_u[(row0 + r) * f + gl] : (long long)slot[it];
+    new_u[it] = !first ? 0 : DIRECT ? (long long)slot[it] : a.tmp_u[(row0 + r) * f + gl];
     if (gl == 0) {
       s_c[r] = c;
       s_f[r] = __popcll(bits);
@@ -700,7 +707,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
   for (int it = 0; it < kTileIters; ++it)
     if (new_id[it] >= 0) {
       a.nodes[new_id[it]] = new_u[it];
-      entry_set_val(a.table, a.shift, (unsigned)slot[it], (unsigned)new_id[it]);
+      entry_set_val<DIRECT>(a.table, a.shift, (unsigned)slot[it], (unsigned)new_id[it]);
       // this edge's local id is known right here: write it (the row's edges sit at its sampled slots
       // 0 .. c-1, and s_c holds the row's inclusive edge count within the tile), and spare the edge-id pass
       // the table look-up
@@ -738,8 +745,9 @@ __global__ void k_add_u64(unsigned long long* p, unsigned long long v) { atomicA
 
 struct SampleWs {
   HashEntry* table;        // the table, the tile status words and the tickets are one region,
-  uint64_t table_entries;  // cleared with a single all-ones fill per batch (0 entries: direct table)
-  unsigned table_shift;    // of a slot, to its 32-bit word
+  uint64_t table_entries;  // cleared with a single all-ones fill per batch
+  bool direct;             // which kind of table
+  unsigned table_shift;    // of a direct table's slot, to its 32-bit word
   unsigned long long* status[DCI_MAX_HOPS];
   unsigned* ticket;        // [DCI_MAX_HOPS]
   unsigned* batch_flag;    // one word after the tickets, also in the cleared region
@@ -810,9 +818,9 @@ static void carve_sample_ws(Arena& ar, int64_t num_nodes, const int64_t* cap_nod
   size_t table_bytes = ws->table_entries * sizeof(HashEntry);
   const size_t sync_bytes = align_up(status_words * 8 + (DCI_MAX_HOPS + 1) * 4, 16);
   char* region = ar.take<char>(table_bytes + sync_bytes);  // the hashed table's size either way
-  ws->table_shift = 1;
-  if (table_is_direct(num_nodes, table_bytes)) {
-    ws->table_entries = 0;
+  ws->direct = table_is_direct(num_nodes, table_bytes);
+  ws->table_shift = 0;
+  if (ws->direct) {
     ws->table_shift = direct_shift(num_nodes, table_bytes);
     // both are multiples of 16: at most the hashed table's bytes
     table_bytes = align_up((size_t)4 * (size_t)num_nodes << ws->table_shift, 16);
@@ -859,21 +867,21 @@ static int grid_for_rows(const dci_ctx* ctx, int64_t rows, int groups_per_block)
   return (int)blocks;
 }
 
-template <int G>
+template <int G, bool DIRECT>
 static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra, bool count, int64_t cap_rows) {
   const int grid = grid_for_rows(ctx, cap_rows, kBlock / G) + (ha.hop > 0 ? ha.n_write_blocks : 0);
   {
     Timed t(ctx, DCI_K_SAMPLE);
     if (ha.hop == 0) {
       if (count)
-        hipLaunchKernelGGL((k_sample_hop<G, true, true>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
+        hipLaunchKernelGGL((k_sample_hop<G, true, true, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
       else
-        hipLaunchKernelGGL((k_sample_hop<G, false, true>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
+        hipLaunchKernelGGL((k_sample_hop<G, false, true, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
     } else {
       if (count)
-        hipLaunchKernelGGL((k_sample_hop<G, true, false>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
+        hipLaunchKernelGGL((k_sample_hop<G, true, false, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
       else
-        hipLaunchKernelGGL((k_sample_hop<G, false, false>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
+        hipLaunchKernelGGL((k_sample_hop<G, false, false, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
     }
   }
   DCI_LAUNCH_CHECK(ctx);
@@ -882,11 +890,11 @@ static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra
     const int iters = tile_iters_for(ctx, cap_rows, ha.fanout);
     const dim3 grid_r((unsigned)tiles_for(cap_rows, ha.fanout, iters));
     if (iters == 2)
-      hipLaunchKernelGGL((k_relabel_hop<G, 2>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
+      hipLaunchKernelGGL((k_relabel_hop<G, 2, DIRECT>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
     else if (iters == 4)
-      hipLaunchKernelGGL((k_relabel_hop<G, 4>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
+      hipLaunchKernelGGL((k_relabel_hop<G, 4, DIRECT>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
     else
-      hipLaunchKernelGGL((k_relabel_hop<G, 8>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
+      hipLaunchKernelGGL((k_relabel_hop<G, 8, DIRECT>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
   }
   DCI_LAUNCH_CHECK(ctx);
   return DCI_OK;
@@ -952,7 +960,6 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ra.tmp_u = ws.tmp_u;
     ra.tmp_slot = ws.tmp_slot[h & 1];
     ra.table = ws.table;
-    ra.entries = (unsigned)ws.table_entries;
     ra.shift = ws.table_shift;
     ra.nodes = nodes;
     ra.blk_indptr = reinterpret_cast<long long*>(out->blk_indptr[h]);
@@ -967,10 +974,10 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     // runs so that the (empty) sizes get written
     const int64_t rows = out->cap_rows[h];
     switch (group_for(fanouts[h])) {
-      case 8: rc = launch_hop<8>(ctx, ha, ra, count, rows); break;
-      case 16: rc = launch_hop<16>(ctx, ha, ra, count, rows); break;
-      case 32: rc = launch_hop<32>(ctx, ha, ra, count, rows); break;
-      default: rc = launch_hop<64>(ctx, ha, ra, count, rows); break;
+      case 8: rc = (ws.direct ? launch_hop<8, true> : launch_hop<8, false>)(ctx, ha, ra, count, rows); break;
+      case 16: rc = (ws.direct ? launch_hop<16, true> : launch_hop<16, false>)(ctx, ha, ra, count, rows); break;
+      case 32: rc = (ws.direct ? launch_hop<32, true> : launch_hop<32, false>)(ctx, ha, ra, count, rows); break;
+      default: rc = (ws.direct ? launch_hop<64, true> : launch_hop<64, false>)(ctx, ha, ra, count, rows); break;
     }
     if (rc != DCI_OK) return rc;
   }
@@ -985,7 +992,8 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
       sf.tile_rows[k] = k < n_hops ? (kBlock / group_for(fanouts[k])) * tile_iters_for(ctx, out->cap_rows[k], fanouts[k]) : 1;
     }
     Timed t(ctx, feat_count ? DCI_K_COUNT_NODES : DCI_K_WRITE_SRC);
-    hipLaunchKernelGGL(k_write_src, dim3(grid_for_rows(ctx, positions, kBlock)), dim3(kBlock), 0, ctx->stream,
+    hipLaunchKernelGGL(ws.direct ? k_write_src<true> : k_write_src<false>, dim3(grid_for_rows(ctx, positions, kBlock)),
+                       dim3(kBlock), 0, ctx->stream,
                        (const long long*)counts, h, fanouts[h], (const int*)ws.row_cnt[h & 1],
                        (const int*)ws.tmp_slot[h & 1], reinterpret_cast<const long long*>(out->blk_indptr[h]),
                        (const HashEntry*)ws.table, ws.table_shift, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
