@@ -15,8 +15,8 @@
  *    there and are read by zero-copy on a cache miss (Section IV, framework paragraph).
  *  - The library allocates no device memory.  Temporary device memory comes from the workspace
  *    handed to dci_create(); the dci_*_workspace_bytes() queries say how much each call needs.
- *    (A context owns a few dozen HIP events and 128 bytes of pinned host memory; dci_timing_enable
- *    creates events on first use.)
+ *    (A context owns a few HIP events and 128 bytes of pinned host memory; dci_timing_enable and
+ *    dci_presample_count, where it loads features, create more events on first use.)
  *  - Calls enqueue work on the context's HIP stream and return without waiting, except
  *    dci_fill_caches(), which waits for completion because the cache sizes it reports are
  *    computed on the GPU.  Device outputs, and host outputs marked "valid after dci_sync", may be
@@ -193,7 +193,8 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *       `counts` (and counts_host) are zeroed so that a following gather / forward finds no rows, and the
  *       next dci_sync (or dci_timing_read, or the waiting dci_presample_count) on the context returns
  *       DCI_ERR_HIP with the message "relabel scan timed out ...".  Pre-sampling counters updated by a
- *       voided batch are unspecified. */
+ *       voided batch are unspecified; the waiting dci_presample_count looks once per 16 batches, so up to
+ *       15 batches behind a voided one have been counted when it returns. */
 #define DCI_OPT_RELABEL_SPIN_LIMIT 3
 /*   DCI_OPT_TEST_RELABEL_FIRST_TICKET  test hook for that failure path, off (0) by default: the scan numbers
  *       its tiles from this value, so the tiles below it never run or publish and the first real tile must

@@ -79,8 +79,7 @@ int32_t dci_create(dci_ctx** out, int32_t device, void* hip_stream, void* worksp
   if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
   if (e == hipSuccess) {
     ctx->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    for (hipEvent_t& ev : ctx->ev)
-      if (e == hipSuccess) e = hipEventCreate(&ev);
+    for (int i = 0; i < 3 && e == hipSuccess; ++i) e = hipEventCreate(&ctx->ev[i]);
   }
   if (e == hipSuccess) {
     void* p = nullptr;

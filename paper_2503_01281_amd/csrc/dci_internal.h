@@ -20,7 +20,7 @@ struct dci_ctx {
   size_t ws_bytes = 0;
   char* static_scratch = nullptr;  // this GPU's copy of the library's static scratch array (DCI_STATIC_SCRATCH_BYTES)
   int num_cus = 256;
-  hipEvent_t ev[2 * kPresampleRun + 1] = {nullptr};  // dci_presample_count's stage times (dci_fill_caches uses the first)
+  hipEvent_t ev[2 * kPresampleRun + 1] = {nullptr};  // dci_presample_count's stage times; it makes those beyond the first three
   char err[512] = {0};
   // optional per-kernel-class timing
   uint32_t timing_mask = 0;

@@ -1147,6 +1147,8 @@ int32_t dci_presample_count(dci_ctx* ctx, const dci_graph* graph, const dci_cach
   double ms_sample = 0.0, ms_feature = 0.0;
   int64_t batches = (n_seeds + batch_size - 1) / batch_size - first_batch;  // those that have seeds
   if (batches > n_batches) batches = n_batches;
+  for (int64_t i = 0; feat_scratch && i <= 2 * (batches < kPresampleRun ? batches : kPresampleRun); ++i)
+    if (!ctx->ev[i]) DCI_HIP(ctx, hipEventCreate(&ctx->ev[i]));
   int in_run = 0;
   for (int64_t k = 0; k < batches; ++k) {
     const int64_t lo = (first_batch + k) * batch_size;
