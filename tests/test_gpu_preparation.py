@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+from tests.test_gpu_parity import _expected_sampler_traffic
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +97,61 @@ def test_visit_counting_has_its_timing_class(env):
     dci.dci_sample_khop(ctx, g, None, seeds, 0, fanouts, 7, dci.Blocks(ctx, N, 100, fanouts))
     t = ctx.timing_read()
     assert t["write_src"][1] == 1 and t["write_src"][0] > 0 and t["count_nodes"] == (0.0, 0)
+
+
+# With features loaded, pre-sampling waits and folds the gather's statistics once per 16 batches: whole runs, one batch over
+# them, a last run of one, and a last batch that is short; all statistics against the oracle's batches.
+@pytest.mark.parametrize("n_batches", [1, 15, 16, 17, 33])
+def test_presampling_over_its_runs_of_batches(env, n_batches):
+    dci, gu = env["dci"], env["gu"]
+    N, F, batch, fanouts = 900, 5, 7, (3, 2)
+    rng = np.random.default_rng(n_batches)
+    indptr = np.concatenate([[0], np.cumsum(rng.integers(0, 9, N))]).astype(np.int64)
+    indices = rng.integers(0, N, int(indptr[-1])).astype(np.int64)
+    feat = rng.standard_normal((N, F)).astype(np.float32)
+    g = gu.make_graph(indptr, indices, feat)
+    seeds = rng.permutation(N)[:batch * n_batches - 3].astype(np.int64)
+    weight = rng.integers(0, 9, N).astype(np.uint32)
+    adj_remap, c_indptr, c_indices = oracle.fill_adj(indptr, indices, weight, 4 * (N + len(indices)))
+    feat_remap, rows, _ = oracle.fill_feat(weight, feat, 2 * F * N, 1)
+    cache = gu.upload_cache(adj_remap, c_indptr, c_indices, feat_remap, rows)
+    ctx, stats = dci.Context(0), gu.new_stats()  # (a new context: its events are made by this call)
+    counts = [torch.zeros(N, dtype=torch.int32, device="cuda") for _ in range(2)]
+    scratch = torch.zeros(dci.blocks_bounds(N, batch, fanouts)[0][-1], F, device="cuda")
+    dci.dci_presample_count(ctx, g, cache, gu.dev(seeds), batch, 0, n_batches + 2, 50, fanouts, 7, *counts, feat_scratch=scratch,
+                            stats=stats)
+    st = gu.stats_dict(ctx, stats)
+    want = [oracle.sample_khop(indptr, indices, seeds[b * batch:(b + 1) * batch], 50 + b, fanouts, 7) for b in range(n_batches)]
+    traffic = [_expected_sampler_traffic(b, fanouts, indptr, adj_remap, g.indptr.data_ptr(), g.indices.data_ptr()) for b in want]
+    n_in = sum(len(b.nodes) for b in want)
+    hits = sum(int((feat_remap[b.nodes] >= 0).sum()) for b in want)
+    assert 0 < hits < n_in
+    assert (st["feat_hits"], st["feat_misses"], st["rows_copied"], st["input_nodes"]) == (hits, n_in - hits, n_in, n_in)
+    assert st["edges_sampled"] == sum(int(b.n_edges.sum()) for b in want)
+    assert (st["bytes_hbm"], st["bytes_host"]) == (sum(t[0] for t in traffic) + 4 * F * hits,
+                                                   sum(t[1] for t in traffic) + 4 * F * (n_in - hits))
+    assert (st["lines_bounds"], st["lines_ids"]) == (sum(t[2] for t in traffic), sum(t[3] for t in traffic))
+    assert st["t_sample_ns"] > 0 and st["t_feature_ns"] > 0
+    assert np.array_equal(scratch[:len(want[-1].nodes)].cpu().numpy(), feat[want[-1].nodes])
+    f, a, _, _ = oracle.presample_count(indptr, indices, seeds, batch, n_batches, fanouts, 7, 50)
+    assert all(np.array_equal(got.cpu().numpy().view(np.uint32), w) for got, w in zip(counts, (f, a)))
+
+
+def test_presampling_reports_a_voided_batch_at_the_end_of_its_run(env):
+    dci, gu = env["dci"], env["gu"]
+    N, batch, fanouts = 900, 7, (3, 2)
+    g = gu.make_graph(np.arange(N + 1, dtype=np.int64), np.arange(N, dtype=np.int64), np.ones((N, 2), dtype=np.float32))
+    seeds = gu.dev(np.arange(20 * batch))
+    ctx, stats = dci.Context(0), gu.new_stats()
+    counts = [torch.zeros(N, dtype=torch.int32, device="cuda") for _ in range(2)]
+    scratch = torch.zeros(dci.blocks_bounds(N, batch, fanouts)[0][-1], 2, device="cuda")
+    ctx.set_option(dci.DCI_OPT_RELABEL_SPIN_LIMIT, 200)
+    ctx.set_option(dci.DCI_OPT_TEST_RELABEL_FIRST_TICKET, 1)
+    with pytest.raises(dci.DciError) as e:
+        dci.dci_presample_count(ctx, g, None, seeds, batch, 0, 20, 0, fanouts, 7, *counts, feat_scratch=scratch, stats=stats)
+    assert e.value.code == -3 and "relabel scan timed out" in str(e.value)
+    ctx.sync()  # reported once
+    assert not counts[0].any() and not stats.any()  # every batch was voided: no input node was visited
+    ctx.set_option(dci.DCI_OPT_TEST_RELABEL_FIRST_TICKET, 0)
+    dci.dci_presample_count(ctx, g, None, seeds, batch, 0, 20, 0, fanouts, 7, *counts, feat_scratch=scratch, stats=stats)
+    assert gu.stats_dict(ctx, stats)["input_nodes"] == int(counts[0].sum()) > 0
