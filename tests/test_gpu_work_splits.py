@@ -54,6 +54,8 @@ def test_counter_totals_decide_the_feature_rows(env, N):
         cache = dci.dci_fill_caches(ctx, g, gu.dev(count.view(np.int32)), gu.dev(np.zeros(N, dtype=np.int32)), 12 * (N // 3 + 1), 0, 1,
                                     policy | dci.DCI_FILL_STRICT_SPLIT)
         assert cache.feat_rows == k and np.array_equal(cache.feat_remap.cpu().numpy(), remap)
+        got = cache.buf[cache.buf_offset:cache.buf_offset + cache.feat_bytes].view(torch.float32).cpu().numpy()
+        assert np.array_equal(got.reshape(k, 3), rows)
 
 
 # The sampler's node table is direct up to four nodes of the graph per node of the batch's bound, and hashed beyond: both sides
