@@ -62,7 +62,7 @@ typedef struct dci_ctx dci_ctx;
  * sparse column form of the paper with the target node as the column: the in-neighbours of
  * node v are indices[indptr[v] .. indptr[v+1]).  Unweighted, so there is no Values array. */
 typedef struct {
-  int64_t num_nodes;      /* N, 1 .. 2^31-1                                   */
+  int64_t num_nodes;      /* N, 1 .. 2^31-1; every id in indices is below N   */
   int64_t num_edges;      /* E = indptr[N]                                    */
   int32_t feat_dim;       /* F >= 1                                           */
   const int64_t* indptr;  /* [N+1] mapped, borrowed                           */
@@ -231,7 +231,7 @@ int32_t dci_set_option(dci_ctx* ctx, int32_t option, int64_t value);
  * up the elapsed time and the number of recorded launches per class into total_ms[DCI_K_COUNT]
  * and launches[DCI_K_COUNT], and starts over.  class_mask = 0 switches timing off (the default). */
 enum {
-  DCI_K_TABLE_CLEAR = 0, /* clearing the batch's hash table and scan status words   */
+  DCI_K_TABLE_CLEAR = 0, /* clearing the batch's node table and scan status words   */
   DCI_K_SAMPLE = 1,      /* per hop: draw positions, read neighbours, register ids
                             (also writes the previous hop's edge local ids)        */
   DCI_K_RELABEL = 2,     /* per hop: first appearances, row offsets, new local ids  */
@@ -358,7 +358,7 @@ int32_t dci_sample_khop(dci_ctx* ctx, const dci_graph* graph, const dci_cache* c
 
 /* dci_sample_khop for callers that cannot allocate device memory or hand over a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
- * kernels and the same result as dci_sample_khop, but the temporaries (hash table, scan status
+ * kernels and the same result as dci_sample_khop, but the temporaries (node table, scan status
  * words, padded per-hop arrays) live in an array of DCI_STATIC_SCRATCH_BYTES bytes that is part of
  * the library's device code: every GPU the library runs on holds its own copy until the process
  * ends, and the context's workspace is neither needed nor touched.  The call allocates nothing.

@@ -111,7 +111,8 @@ static inline long long scan_tiles_for(long long n) { return (n + kScanTile - 1)
 // Sum, maximum and number of non-zero values of one or two counter arrays (blockIdx.y picks the array).  Bound by
 // the read of the counters (4 bytes per node).  The workgroups leave one triple each and k_count_fold, one
 // workgroup per array, adds them up: with atomics on three words instead, 16,384 wavefronts queue on one L2 line
-// (2.4 M nodes: 581 us for 10 MB; this pair takes 8 us).
+// (2.4 M nodes: 581 us for 10 MB; this pair takes 11 us,
+// 14 for two arrays).
 struct CountTotals {
   u64 sum, max, nonzero;
 };
@@ -462,8 +463,8 @@ struct AdjOut {
 // Copies the cached (leading) parts of the lists of slots s0 <= s < K.  Bound by the read of the lists (over the
 // host link where the graph lives there).  Every workgroup takes equal shares of the slots and elements together (a
 // slot's unit, then its elements), whatever lists they belong to.  The cached nodes are the hottest ones, in order: with a
-// wavefront per list the few hubs at the front decide how long it takes (5.5 M elements in HBM: 370 us, with equal
-// shares 30; 4.5 M elements over the link: 1,116 us, with equal shares 660 = 55 GB/s, the link's streaming rate).  And
+// wavefront per list the few hubs at the front decide how long it takes (5.6 M elements in HBM: 370 us, with equal
+// shares 33; 4.6 M elements over the link: 1,116 us, with equal shares 661 = 55 GB/s, the link's streaming rate).  And
 // nodes without neighbours come in runs: counted by elements alone one share holds all of a run (6 M of them between two
 // lists: a fill of 14.4 ms, with the slots shared out as well 0.48).
 // The lists that a share touches are staged in LDS, at most kListSlots at a time - where each begins in the share and how

@@ -19,8 +19,8 @@
 //                   appearances over all rows (chained scan with decoupled look-back), appends the
 //                   first appearances to the frontier in (row, slot) order, publishes their
 //                   local ids in the table and writes them as those edges' ids.
-//   k_write_src   - the last hop's remaining edge ids, the batch sizes for the host, and the totals of
-//                   the batch's statistics.
+//   k_write_src   - the last hop's remaining edge ids, the batch sizes for the host, in pre-sampling the visits of the
+//                   input nodes, and the totals of the batch's statistics.
 // Should a tile of the scan ever give up waiting for its predecessors, the batch is voided: a status
 // word makes the batch's remaining kernels return at once, k_write_src zeroes the batch's sizes and
 // raises the context's host flag, and the next dci_sync reports it.
@@ -771,15 +771,17 @@ static uint64_t table_entries_for(int64_t cap_nodes_last) {
 // claim to wait for, no probing, no second copy of the ids); a graph many times the batch's bound would pay
 // for its clear with more than that (24 M nodes, bound 4.3 M: direct 3,185 us a pass, hashed 3,168).  Slots double as
 // negative codes in tmp_slot, hence the limit of 2^30.
-// Hashed -> direct: eight 4,096-seed batches of a 2.4 M-node graph on four lanes 2,002 -> 1,917 us (clear 39 -> 10 MB a
-// batch); an 8,192-seed batch of two hops on 4.0 M nodes 353 -> 346 us; 4,096 seeds on 1.6 M nodes 366 -> 357 us.
+// Both measured, hashed / direct: eight 4,096-seed batches of a 2.4 M-node graph on four lanes 2,002 / 1,917 us (clear 39 /
+// 10 MB a batch); an 8,192-seed batch of two hops on 4.0 M nodes 353 / 346 us; 4,096 seeds on 1.6 M nodes 366 / 357 us.
 static bool table_is_direct(int64_t num_nodes, uint64_t hashed_bytes) {
   return num_nodes < ((int64_t)1 << 30) && 4 * (uint64_t)num_nodes <= hashed_bytes;
 }
 
 // A small direct table is spread out, up to four words per node, as long as it stays within 4 MB (cleared in 2 us) and
-// the hashed table's bytes: packed 32 to a 128-byte line, the nodes of a dense graph queue for their line.
-// 1,024 seeds on 233 k nodes of 490 neighbours: hashed 331, direct packed 333, direct spread 330 us.
+// the hashed table's bytes: packed 32 to a 128-byte line, the nodes of a dense graph queue for their line.  1,024 seeds on
+// 233 k nodes of 490 neighbours: packed 334 us, spread 331 (hashed 331; runs of one kind differ by 0.3 %).  Other graphs gain
+// nothing from it and lose nothing: of 28 cases no other changed by more than its own runs differ, nor did any with 16 MB in
+// the place of 4.
 constexpr size_t kSpreadBytes = (size_t)4 << 20;
 static unsigned direct_shift(int64_t num_nodes, size_t hashed_bytes) {
   const size_t limit = hashed_bytes < kSpreadBytes ? hashed_bytes : kSpreadBytes;
