@@ -1085,7 +1085,8 @@ struct FuseArgs {
 
 template <int NS>
 __global__ __launch_bounds__(kResThreads, 1) void k_sage_input_res(LinearArgs a, FuseArgs fa, int g_n) {
-  static_assert(NS >= 4 && NS <= kResMaxSlabs, "slab count");
+  // a slab has room for three of a block's 32 slots (DCI_F_SLAB): with fewer than eleven slabs some would never be taken
+  static_assert((kFuseSlots + NS - 1) / NS <= 3 && NS <= kResMaxSlabs, "slab count");
   // slots in flight per lane: eight where the registers allow it (the weights of the longest contraction take 128)
   constexpr int kFuseAhead = NS > 13 ? 4 : 8;
   __shared__ __attribute__((aligned(1024))) char lds[kResBufs * kResTileBytes];
@@ -1869,11 +1870,7 @@ static int32_t forward_in(dci_ctx* ctx, const dci_blocks* blocks, const float* x
       const dim3 grid_f((unsigned)(g_f * la.n_tiles_n));
       {
         Timed timed(ctx, DCI_K_LINEAR_IN);
-        if (slabs <= 4)
-          hipLaunchKernelGGL(k_sage_input_res<4>, grid_f, dim3(kResThreads), 0, ctx->stream, la, fa, g_f);
-        else if (slabs <= 8)
-          hipLaunchKernelGGL(k_sage_input_res<8>, grid_f, dim3(kResThreads), 0, ctx->stream, la, fa, g_f);
-        else if (slabs <= 13)
+        if (slabs <= 13)
           hipLaunchKernelGGL(k_sage_input_res<13>, grid_f, dim3(kResThreads), 0, ctx->stream, la, fa, g_f);
         else
           hipLaunchKernelGGL(k_sage_input_res<16>, grid_f, dim3(kResThreads), 0, ctx->stream, la, fa, g_f);
