@@ -169,7 +169,11 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
 /* Tuning options of a context.  None changes what is computed (the dense-layer kernels differ only
  * in the order of the floating-point sums).  DCI_ERR_INVALID_ARG for an unknown option or value.
  *   DCI_OPT_LINEAR_KERNEL  which dense-layer kernel dci_sage_forward / dci_gnn_forward launch:
- *       0  by shape (default): the kernel that keeps the weights in registers when the whole contraction
+ *       0  by shape (default): aggregation and dense layer as one kernel, its products on the bf16 matrix
+ *          instructions with every fp32 operand as a sum of three bf16 parts (an error against 64-bit sums no
+ *          larger than that of the fp32 instructions), unless DCI_OPT_INPUT_LAYER is set, a layer's input has
+ *          fewer than four columns or the parts of the weights do not fit where the aggregated rows would be.
+ *          Then: the kernel that keeps the weights in registers when the whole contraction
  *          is at most 256 long (two operands of up to 128 columns, or GCN's one of up to 256), the input width
  *          a multiple of 4, the output width a multiple of 256 and the layer at least 98304 rows tall by
  *          capacity; else the wide kernel (128-column tiles, one workgroup per compute unit)
@@ -179,7 +183,7 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *          input width even and the contraction not split, through registers otherwise
  *       1  always the 64x64 tile kernel that stages its operands through registers
  *       2  the wide kernel whenever width and alignment allow it, whatever the row count
- *       3  like 0 without the wide and the weights-in-registers kernels
+ *       3  the 64x64 tile kernels, chosen as under 0
  *       4  the weights-in-registers kernel whenever widths and alignment allow it, whatever the row count;
  *          other layers as under 1 */
 #define DCI_OPT_LINEAR_KERNEL 1
@@ -210,7 +214,7 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *       the frontier's size, or 2, 4, 8.  Tuning only: the result does not depend on it. */
 #define DCI_OPT_RELABEL_TILE_ITERS 6
 /*   DCI_OPT_INPUT_LAYER  how the forward pass runs its first layer (two operands of at most 128 columns, mean or
- *       sum aggregator).  There are two one-kernel forms that keep the aggregated rows out of device memory:
+ *       sum aggregator) where DCI_OPT_LINEAR_KERNEL 0 does not make it one kernel.  There are two one-kernel forms that keep the aggregated rows out of device memory:
  *       "registers" - the aggregation runs inside the weights-in-registers dense kernel (needs what that kernel
  *       needs, see DCI_OPT_LINEAR_KERNEL) - and "tiles" - half of each workgroup aggregates 64 rows into LDS while
  *       the other half multiplies the 64 rows before (needs a width that is a multiple of 16, at least 32, an
@@ -238,7 +242,8 @@ enum {
   DCI_K_WRITE_SRC = 3,   /* last hop: local id of every edge, batch sizes to host   */
   DCI_K_GATHER = 4,      /* feature gather                                          */
   DCI_K_MEAN_IN = 5,     /* first layer (input features): neighbour mean            */
-  DCI_K_LINEAR_IN = 6,   /* first layer (input features): dense layer (matrix cores) */
+  DCI_K_LINEAR_IN = 6,   /* first layer (input features): dense layer (matrix cores), or
+                            the whole layer where it is one kernel                  */
   DCI_K_MEAN = 7,        /* later layers: neighbour mean                            */
   DCI_K_LINEAR = 8,      /* later layers: dense layer                               */
   DCI_K_COUNT_NODES = 9, /* pre-sampling: what DCI_K_WRITE_SRC is elsewhere, and the
@@ -390,7 +395,8 @@ int32_t dci_gather_features(dci_ctx* ctx, const dci_graph* graph, const dci_cach
  *   y_i = x_i W_self[l] + m_i W_neigh[l] + bias[l], ReLU on all layers but the last.
  * x_in: device [n_nodes[L], dims[0]]; w_self[l], w_neigh[l]: device [dims[l], dims[l+1]]
  * row-major; bias[l]: device [dims[l+1]]; logits: device [cap_rows[0], dims[n_layers]].
- * n_layers must equal blocks->n_hops.  fp32 storage, fp32 accumulation on the matrix cores. */
+ * n_layers must equal blocks->n_hops.  fp32 storage, fp32 accumulation on the matrix cores (products of
+ * fp32 accuracy whichever kernel makes them, see DCI_OPT_LINEAR_KERNEL). */
 int32_t dci_sage_forward(dci_ctx* ctx, const dci_blocks* blocks, const float* x_in, int32_t n_layers,
                          const int32_t* dims, const float* const* w_self, const float* const* w_neigh,
                          const float* const* bias, float* logits);

@@ -163,6 +163,38 @@ int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, 
                       bool fold_partials = true);
 size_t gather_partials_bytes(const dci_ctx* ctx);
 
+// One layer of the forward pass in one kernel (dci_layer.hip)
+struct LayerArgs {
+  const long long* counts;  // rows = counts[hop]
+  int hop;
+  const long long* blk_indptr;
+  const int* blk_src;
+  const float* x;      // [*, D] rows of the layer's input
+  const int* rowref;   // not nullptr: the row of source s is cache[rowref[s]] where that is not negative, else x[s]
+  const float* cache;
+  const float* w_self;   // [D, N] row-major (not read for GCN)
+  const float* w_neigh;  // [D, N]
+  const float* bias;     // [N]
+  float* y;              // [rows, N]
+  int D, N, relu;
+  int mode;  // DCI_MODEL_*
+  int n_col_groups;
+  long long cap_rows;     // bound on the rows
+  const void* w_split;    // the weights as parts (k_sage_layer)
+};
+struct LayerPlan {
+  int D, N, C;  // C: 0 k_sage_layer_small, else k_sage_layer with 16 C columns per wavefront
+  int64_t cap_rows;
+  void* w_split;
+};
+// Plans every layer of a forward pass; scratch is where the weights' parts may go.  false: one of the layers is not for these
+// kernels, or the scratch is too small.
+bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int64_t* cap_rows, void* scratch,
+                 size_t scratch_bytes, LayerPlan* plans);
+int32_t layers_split_weights(dci_ctx* ctx, int32_t model, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,
+                             const float* const* w_neigh);
+int32_t layer_launch(dci_ctx* ctx, const LayerPlan& plan, const LayerArgs& args);
+
 }  // namespace dci
 
 #endif  // DCI_INTERNAL_H_

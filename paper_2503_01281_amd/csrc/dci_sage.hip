@@ -1,7 +1,9 @@
 // Forward pass over the blocks of one mini-batch: GraphSAGE with the mean aggregator, and the two
 // models of Table III (GraphSAGE with the sum aggregator, GCN with the averaging one).
 //
-// Per layer:
+// Per layer, by default, one kernel of dci_layer.hip (k_sage_layer, k_sage_layer_small).  The kernels of this file are what
+// DCI_OPT_LINEAR_KERNEL and DCI_OPT_INPUT_LAYER ask for, and run where those of dci_layer.hip cannot (inputs of fewer than
+// four columns):
 //   k_sage_mean        - m_i = mean (or sum; for GCN the mean over the row itself and its sources) of
 //                        x[src] over row i of the block; bandwidth bound: one lane group per
 //                        destination row, consecutive lanes on consecutive chunks of the row;
@@ -1679,6 +1681,7 @@ __global__ __launch_bounds__(kTileInThreads, 1) void k_sage_input_tile(LinearArg
 
 struct SageWs {
   float* m;
+  size_t m_bytes;
   float* y[2];
   float* part;         // partial sums of split dense layers
 };
@@ -1716,6 +1719,7 @@ static void carve_sage_ws(Arena& ar, const int64_t* cap_rows, int32_t n_layers, 
     }
   }
   ws->m = ar.take<float>(max_m);
+  ws->m_bytes = max_m * sizeof(float);
   ws->y[0] = ar.take<float>(max_y);
   ws->y[1] = ar.take<float>(max_y);
   ws->part = ar.take<float>(max_part);
@@ -1770,13 +1774,51 @@ static int32_t forward_in(dci_ctx* ctx, const dci_blocks* blocks, const float* x
   const long long* counts = reinterpret_cast<const long long*>(blocks->counts);
   const float* x = x_in;
   auto aligned = [](const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; };
+  // A layer in one kernel (dci_layer.hip) unless an option asks for one of the kernels here; the parts of the weights go where
+  // the aggregated rows' matrix would be.
+  LayerPlan plans[DCI_MAX_HOPS];
+  const bool planned = ctx->linear_kernel == 0 && ctx->input_layer == 0 &&
+                       layers_plan(model, n_layers, dims, blocks->cap_rows, ws.m, ws.m_bytes, plans);
+  bool split = false;  // the weights' parts are made
   for (int32_t l = 0; l < n_layers; ++l) {
     const int32_t h = n_layers - 1 - l;
     const int D = dims[l], Do = dims[l + 1];
     const int64_t cap = blocks->cap_rows[h] > 0 ? blocks->cap_rows[h] : 1;
     float* y = l == n_layers - 1 ? logits : ws.y[l & 1];
-    // Input layer in one kernel (aggregation inside the weights-in-registers dense layer) where the layer qualifies
     const bool ref_l = l == 0 && rowref != nullptr;
+    // ... and except for the input layers of 9 to 13 slabs that the weights-in-registers kernel takes whole: it moves fewer bytes
+    // (rows in one piece each), which counts when batches share the card.  Eight 4,096-seed batches of 2 x 100 x 256 on four
+    // lanes 1,819 us a pass, k_sage_layer 1,874; four on one lane 1,093 either way; 2 x 64 x 256 on one lane 939 and 921.
+    const int slabs_l = (2 * ((D / 4 + 1) & ~1) + 3) / 4;
+    const bool whole_rows = l == 0 && !gcn && Do % kResCols == 0 && D % 4 == 0 && slabs_l > 8 && slabs_l <= 13 && cap >= kResMinRows &&
+                            ctx->num_cus >= Do / kResCols && aligned(x, 16) && (!ref_l || aligned(feat_cache, 16));
+    if (planned && !whole_rows) {
+      LayerArgs na;
+      na.counts = counts;
+      na.hop = h;
+      na.blk_indptr = reinterpret_cast<const long long*>(blocks->blk_indptr[h]);
+      na.blk_src = blocks->blk_src[h];
+      na.x = x;
+      na.rowref = l == 0 ? rowref : nullptr;
+      na.cache = feat_cache;
+      na.w_self = gcn ? w_neigh[l] : w_self[l];
+      na.w_neigh = w_neigh[l];
+      na.bias = bias[l];
+      na.y = y;
+      na.relu = l != n_layers - 1;
+      na.mode = model;
+      Timed timed(ctx, l == 0 ? DCI_K_LINEAR_IN : DCI_K_LINEAR);
+      int32_t rc = DCI_OK;
+      if (plans[l].C > 0 && !split) {
+        rc = layers_split_weights(ctx, model, n_layers, plans, w_self, w_neigh);
+        split = true;
+      }
+      if (rc == DCI_OK) rc = layer_launch(ctx, plans[l], na);
+      if (rc != DCI_OK) return rc;
+      x = y;
+      continue;
+    }
+    // Input layer in one kernel (aggregation inside the weights-in-registers dense layer) where the layer qualifies
     bool fuse_in = false;
     if (l == 0 && !gcn && ctx->input_layer != 1 && (ctx->linear_kernel == 0 || ctx->linear_kernel == 4)) {
       const int n_tiles_f = Do / kResCols;
