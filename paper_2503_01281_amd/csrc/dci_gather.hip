@@ -2,6 +2,10 @@
 // a row comes from the HBM feature cache when feat_remap[id] >= 0 and from the host feature
 // matrix (zero-copy over the host link) otherwise.
 //
+// The weights of a following forward pass are laid out as bf16 parts by the first workgroups of the same launch where the caller
+// wants that: a kernel of its own for it takes 6 - 7 us of launch and latency, beside the copy it takes none (4,096 seeds
+// on 716 k nodes: a pass 241 us with it, 232 without; three batches of 1,001 seeds 280 and 265).
+//
 // The copy is bandwidth bound.  A row is handled by a group of lanes (a whole wavefront for
 // rows of 64 or more 16-byte chunks, a fraction for narrow rows); consecutive lanes move
 // consecutive 16-byte chunks, up to four loads in flight per lane before the first store, and the
@@ -9,6 +13,7 @@
 // only 4-byte alignment: gfx950 global memory takes under-aligned 16-byte accesses, and the
 // F % 4 trailing floats are moved one per lane.
 #include "dci_internal.h"
+#include "dci_parts.h"
 
 namespace dci {
 
@@ -87,7 +92,7 @@ __device__ __forceinline__ void copy_rows(const long long* __restrict__ ids, lon
 // (measured: +30 us for 4096 workgroups).
 // (`add`: on top of what the workgroup of the same number of an earlier launch left, so that a run of launches is
 // folded once.)
-__device__ __forceinline__ void store_partials(GatherCounts cnt, unsigned long long* __restrict__ partials, bool add = false) {
+__device__ __forceinline__ void store_partials(GatherCounts cnt, unsigned long long* __restrict__ partials, int block, bool add = false) {
   __shared__ unsigned long long s_h[kGatherBlock / kWave], s_m[kGatherBlock / kWave], s_c[kGatherBlock / kWave];
   const unsigned long long hits = wave_sum_u64(cnt.hits), misses = wave_sum_u64(cnt.misses), copied = wave_sum_u64(cnt.copied);
   if (lane_id() == 0) {
@@ -103,26 +108,38 @@ __device__ __forceinline__ void store_partials(GatherCounts cnt, unsigned long l
       m += s_m[w];
       c += s_c[w];
     }
-    unsigned long long* const p = partials + 3 * blockIdx.x;
+    unsigned long long* const p = partials + 3 * block;
     p[0] = h + (add ? p[0] : 0);
     p[1] = m + (add ? p[1] : 0);
     p[2] = c + (add ? p[2] : 0);
   }
 }
 
-template <int V>
+// The weights to lay out beside the copy: none, where the launch is for the copy alone (360 bytes of arguments are half a
+// microsecond of a small launch).
+struct NoSplit {
+  static constexpr int wgs = 0;
+};
+__device__ __forceinline__ void split_weights(const NoSplit&, int) {}
+
+template <int V, class Split>
 __global__ __launch_bounds__(kGatherBlock) void k_gather(const long long* __restrict__ ids, long long n_max,
                                                          const long long* __restrict__ n_dev,
                                                          const int* __restrict__ remap,
                                                          const float* __restrict__ cache,
                                                          const float* __restrict__ feat, int F, int lpr_log2,
                                                          float* __restrict__ out,
-                                                         unsigned long long* __restrict__ partials, int add) {
+                                                         unsigned long long* __restrict__ partials, int add, Split split) {
+  if ((int)blockIdx.x < split.wgs) {
+    split_weights(split, (int)blockIdx.x);
+    return;
+  }
+  const int block = (int)blockIdx.x - split.wgs, n_blocks = (int)gridDim.x - split.wgs;
   long long n = n_dev ? *n_dev : n_max;
   if (n > n_max) n = n_max;
   GatherCounts cnt;
-  copy_rows<V>(ids, n, remap, cache, feat, F, lpr_log2, out, nullptr, (int)blockIdx.x, (int)gridDim.x, cnt);
-  if (partials) store_partials(cnt, partials, add != 0);
+  copy_rows<V>(ids, n, remap, cache, feat, F, lpr_log2, out, nullptr, block, n_blocks, cnt);
+  if (partials) store_partials(cnt, partials, block, add != 0);
 }
 
 // The selective gather of dci_gather_forward: every row's cache slot (or -1) is noted in rowref[i]; the
@@ -134,7 +151,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather(const long long* __rest
 // rest with one lane per row - 64 dependent id -> remap chains in flight per wavefront instead of one per
 // lane group, because most of these rows are only looked up - and the rows among them that missed are then
 // listed in LDS and copied a lane group per row, two rows per group in flight.
-template <int V>
+template <int V, class Split>
 __global__ __launch_bounds__(kGatherBlock) void k_gather_select(const long long* __restrict__ ids, long long n_max,
                                                                 const long long* __restrict__ n_dev,
                                                                 const int* __restrict__ remap,
@@ -143,9 +160,14 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_select(const long long*
                                                                 float* __restrict__ out,
                                                                 unsigned long long* __restrict__ partials,
                                                                 int* __restrict__ rowref,
-                                                                const long long* __restrict__ n_dense_dev) {
+                                                                const long long* __restrict__ n_dense_dev, Split split) {
   typedef typename GVec<V>::reg reg_t;
   typedef typename GVec<V>::mem mem_t;
+  if ((int)blockIdx.x < split.wgs) {
+    split_weights(split, (int)blockIdx.x);
+    return;
+  }
+  const int block = (int)blockIdx.x - split.wgs;
   long long n = *n_dev;
   if (n > n_max) n = n_max;
   long long n_dense = *n_dense_dev;
@@ -155,7 +177,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_select(const long long*
   // spread.  nd follows the work: 8F bytes per dense row - but no less than 2 KB, since narrow rows are bound by
   // the latency of their id -> slot -> row chain, not by their bytes - against about 160 bytes per looked-up row
   // (id, a sector of the remap, the slot note).
-  const long long G = (long long)gridDim.x, b = (long long)blockIdx.x;
+  const long long G = (long long)gridDim.x - split.wgs, b = (long long)block;
   long long nd;
   {
     const double dense_bytes = (double)n_dense * (8.0 * F > 2048.0 ? 8.0 * F : 2048.0), look_bytes = (double)(n - n_dense) * 160.0;
@@ -216,7 +238,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_select(const long long*
       __syncthreads();  // the list is rewritten in the next round
     }
   }
-  if (partials) store_partials(cnt, partials);
+  if (partials) store_partials(cnt, partials, block);
 }
 
 __global__ __launch_bounds__(kGatherBlock) void k_fold_gather_stats(const unsigned long long* __restrict__ partials,
@@ -260,7 +282,7 @@ size_t gather_partials_bytes(const dci_ctx* ctx) {
 
 int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* ids, int64_t n_max,
                       const int64_t* n_dev, float* out, uint64_t* stats, void* partials_buf, int32_t* rowref,
-                      const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials, bool fold_partials) {
+                      const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials, bool fold_partials, const SplitArgs* split) {
   const int F = g->feat_dim;
   const float* fcache = cache ? cache->feat_cache : nullptr;
   const int* remap = cache ? cache->feat_remap : nullptr;
@@ -281,6 +303,7 @@ int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, 
     return b < 1 ? (int64_t)1 : b;
   };
   int64_t blocks = blocks_for(n_max, rows_per_block);
+  const SplitArgs sp = split ? *split : SplitArgs();
   {
     Timed timed(ctx, DCI_K_GATHER);
     const long long* ids_ = reinterpret_cast<const long long*>(ids);
@@ -294,24 +317,30 @@ int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, 
       blocks = blocks_for(n_dense_max, rows_per_block) + blocks_for(n_max, kGatherBlock);
       if (blocks > cap) blocks = cap;
       if (blocks < 2) blocks = 2;
-      if (V == 4)
-        hipLaunchKernelGGL((k_gather_select<4>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_,
-                           (long long)n_max, nd_, remap, fcache, g->feat, F, lpr_log2, out, st, rowref, dn_);
-      else if (V == 2)
-        hipLaunchKernelGGL((k_gather_select<2>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_,
-                           (long long)n_max, nd_, remap, fcache, g->feat, F, lpr_log2, out, st, rowref, dn_);
-      else
-        hipLaunchKernelGGL((k_gather_select<1>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_,
-                           (long long)n_max, nd_, remap, fcache, g->feat, F, lpr_log2, out, st, rowref, dn_);
-    } else if (V == 4)
-      hipLaunchKernelGGL((k_gather<4>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max,
-                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0);
-    else if (V == 2)
-      hipLaunchKernelGGL((k_gather<2>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max,
-                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0);
-    else
-      hipLaunchKernelGGL((k_gather<1>), dim3((int)blocks), dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max,
-                         nd_, remap, fcache, g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0);
+#define DCI_SELECT(V_, S_, s_)                                                                                                 \
+  hipLaunchKernelGGL((k_gather_select<V_, S_>), grid, dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max, nd_, remap, \
+                     fcache, g->feat, F, lpr_log2, out, st, rowref, dn_, s_)
+#define DCI_GATHER(V_, S_, s_)                                                                                                 \
+  hipLaunchKernelGGL((k_gather<V_, S_>), grid, dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max, nd_, remap, fcache, \
+                     g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0, s_)
+#define DCI_BY_SPLIT(WHAT_, V_)                    \
+  do {                                             \
+    if (sp.wgs) WHAT_(V_, SplitArgs, sp);          \
+    else WHAT_(V_, NoSplit, NoSplit());            \
+  } while (0)
+      const dim3 grid((unsigned)(blocks + sp.wgs));
+      if (V == 4) DCI_BY_SPLIT(DCI_SELECT, 4);
+      else if (V == 2) DCI_BY_SPLIT(DCI_SELECT, 2);
+      else DCI_BY_SPLIT(DCI_SELECT, 1);
+    } else {
+      const dim3 grid((unsigned)(blocks + sp.wgs));
+      if (V == 4) DCI_BY_SPLIT(DCI_GATHER, 4);
+      else if (V == 2) DCI_BY_SPLIT(DCI_GATHER, 2);
+      else DCI_BY_SPLIT(DCI_GATHER, 1);
+    }
+#undef DCI_BY_SPLIT
+#undef DCI_GATHER
+#undef DCI_SELECT
   }
   DCI_LAUNCH_CHECK(ctx);
   if (stats && fold_partials) {
@@ -323,21 +352,27 @@ int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, 
   return DCI_OK;
 }
 
+int32_t check_gather(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* node_ids, int64_t n_max, const float* out) {
+  if (!ctx) return DCI_ERR_INVALID_ARG;
+  if (!graph || !graph->feat || graph->feat_dim < 1 || graph->num_nodes < 1)
+    return fail(ctx, DCI_ERR_INVALID_ARG, "graph: feature matrix missing or feat_dim < 1");
+  if (n_max < 0 || (n_max > 0 && (!node_ids || !out)))
+    return fail(ctx, DCI_ERR_INVALID_ARG, "node_ids / out: null or negative count");
+  if (cache && (!cache->feat_remap || (cache->feat_rows > 0 && !cache->feat_cache)))
+    return fail(ctx, DCI_ERR_INVALID_ARG, "cache: null feature arrays");
+  if ((reinterpret_cast<uintptr_t>(graph->feat) | reinterpret_cast<uintptr_t>(out) |
+       (cache ? reinterpret_cast<uintptr_t>(cache->feat_cache) : 0)) & 3)
+    return fail(ctx, DCI_ERR_INVALID_ARG, "feature arrays must be 4-byte aligned");
+  return DCI_OK;
+}
+
 }  // namespace dci
 
 extern "C" int32_t dci_gather_features(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache,
                                        const int64_t* node_ids, int64_t n_max, const int64_t* n_dev, float* out,
                                        uint64_t* stats) {
-  if (!ctx) return DCI_ERR_INVALID_ARG;
-  if (!graph || !graph->feat || graph->feat_dim < 1 || graph->num_nodes < 1)
-    return dci::fail(ctx, DCI_ERR_INVALID_ARG, "graph: feature matrix missing or feat_dim < 1");
-  if (n_max < 0 || (n_max > 0 && (!node_ids || !out)))
-    return dci::fail(ctx, DCI_ERR_INVALID_ARG, "node_ids / out: null or negative count");
-  if (cache && (!cache->feat_remap || (cache->feat_rows > 0 && !cache->feat_cache)))
-    return dci::fail(ctx, DCI_ERR_INVALID_ARG, "cache: null feature arrays");
-  if ((reinterpret_cast<uintptr_t>(graph->feat) | reinterpret_cast<uintptr_t>(out) |
-       (cache ? reinterpret_cast<uintptr_t>(cache->feat_cache) : 0)) & 3)
-    return dci::fail(ctx, DCI_ERR_INVALID_ARG, "feature arrays must be 4-byte aligned");
+  const int32_t rc = dci::check_gather(ctx, graph, cache, node_ids, n_max, out);
+  if (rc != DCI_OK) return rc;
   if (n_max == 0) return DCI_OK;
   void* partials = nullptr;
   if (stats) {

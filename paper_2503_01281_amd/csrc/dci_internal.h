@@ -157,11 +157,19 @@ int32_t check_device_flag(dci_ctx* ctx);
 // n_dense_max bounding *n_dense_dev
 // add_partials / fold_partials (plain gather only): several launches of one n_max that are folded into stats once - the
 // first starts the partial sums, later ones add to them, the last folds them
+// split (nullable): weights to be laid out as parts by workgroups of their own in the same launch
+struct SplitArgs;
 int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* ids,
                       int64_t n_max, const int64_t* n_dev, float* out, uint64_t* stats, void* partials_buf,
                       int32_t* rowref, const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials = false,
-                      bool fold_partials = true);
+                      bool fold_partials = true, const SplitArgs* split = nullptr);
 size_t gather_partials_bytes(const dci_ctx* ctx);
+// dci_gather_features' checks
+int32_t check_gather(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* node_ids, int64_t n_max, const float* out);
+// dci_gather_features of a whole batch and dci_gnn_forward on its rows, in one call
+int32_t gather_all_forward(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const dci_blocks* blocks, float* x,
+                           int32_t n_layers, const int32_t* dims, int32_t model, const float* const* w_self,
+                           const float* const* w_neigh, const float* const* bias, float* logits);
 
 // One layer of the forward pass in one kernel (dci_layer.hip)
 struct LayerArgs {
@@ -191,8 +199,9 @@ struct LayerPlan {
 // kernels, or the scratch is too small.
 bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int64_t* cap_rows, void* scratch,
                  size_t scratch_bytes, LayerPlan* plans);
-int32_t layers_split_weights(dci_ctx* ctx, int32_t model, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,
-                             const float* const* w_neigh);
+SplitArgs layers_split_args(int32_t model, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,
+                            const float* const* w_neigh);
+int32_t layers_split_weights(dci_ctx* ctx, const SplitArgs& args);
 int32_t layer_launch(dci_ctx* ctx, const LayerPlan& plan, const LayerArgs& args);
 
 }  // namespace dci

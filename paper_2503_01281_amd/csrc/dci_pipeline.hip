@@ -42,6 +42,9 @@ extern "C" int32_t dci_infer_batches(const dci_lane* lanes, int32_t n_lanes, con
     if (rc == DCI_OK && ctx->fused_input) {
       rc = dci_gather_forward(ctx, graph, cache, lane.blocks, lane.x, n_hops, dims, model, w_self, w_neigh, bias,
                               logits + lo * width, stats);
+    } else if (rc == DCI_OK && !stats) {
+      rc = dci::gather_all_forward(ctx, graph, cache, lane.blocks, lane.x, n_hops, dims, model, w_self, w_neigh, bias,
+                                   logits + lo * width);
     } else {
       if (rc == DCI_OK)
         rc = dci_gather_features(ctx, graph, cache, lane.blocks->nodes, lane.blocks->cap_nodes,

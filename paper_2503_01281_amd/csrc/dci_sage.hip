@@ -23,6 +23,7 @@
 // Row counts come from the block's device-side `counts`, so no host round trip is needed; the
 // grids are sized for the capacities and surplus workgroups leave at once.
 #include "dci_internal.h"
+#include "dci_parts.h"
 
 #include <type_traits>
 
@@ -1745,13 +1746,18 @@ int32_t dci_sage_forward(dci_ctx* ctx, const dci_blocks* blocks, const float* x_
   return dci_gnn_forward(ctx, blocks, x_in, n_layers, dims, DCI_MODEL_SAGE_MEAN, w_self, w_neigh, bias, logits);
 }
 
-// Shared body of dci_gnn_forward and dci_gather_forward.  rowref != nullptr: the input layer's aggregation
-// reads the row of source s from feat_cache[rowref[s]] when rowref[s] >= 0 and from x_in[s] otherwise.
-// ws_off: bytes at the start of the workspace that the caller keeps for itself.
-static int32_t forward_in(dci_ctx* ctx, const dci_blocks* blocks, const float* x_in, int32_t n_layers,
-                          const int32_t* dims, int32_t model, const float* const* w_self,
-                          const float* const* w_neigh, const float* const* bias, float* logits,
-                          const int32_t* rowref, const float* feat_cache, size_t ws_off) {
+// How a forward pass will run.  The layers are one kernel each (dci_layer.hip) unless an option asks for one of the kernels here;
+// the parts of their weights go where the aggregated rows' matrix would be.
+struct ForwardPlan {
+  SageWs ws;
+  bool planned;
+  LayerPlan layers[DCI_MAX_HOPS];
+};
+
+// Checks a forward pass's arguments and plans it.  ws_off: bytes at the start of the workspace that the caller keeps for itself.
+static int32_t plan_forward(dci_ctx* ctx, const dci_blocks* blocks, const float* x_in, int32_t n_layers, const int32_t* dims,
+                            int32_t model, const float* const* w_self, const float* const* w_neigh, const float* const* bias,
+                            const float* logits, size_t ws_off, ForwardPlan* plan) {
   if (!ctx) return DCI_ERR_INVALID_ARG;
   if (model != DCI_MODEL_SAGE_MEAN && model != DCI_MODEL_SAGE_SUM && model != DCI_MODEL_GCN_AVG)
     return fail(ctx, DCI_ERR_INVALID_ARG, "gnn_forward: unknown model %d", model);
@@ -1767,26 +1773,35 @@ static int32_t forward_in(dci_ctx* ctx, const dci_blocks* blocks, const float* x
       return fail(ctx, DCI_ERR_INVALID_ARG, "sage_forward: null weight or block array at layer %d", l);
   Arena ar(ctx->ws, ctx->ws_bytes);
   if (ws_off) (void)ar.take<char>(ws_off);
-  SageWs ws;
-  carve_sage_ws(ar, blocks->cap_rows, n_layers, dims, &ws);
+  carve_sage_ws(ar, blocks->cap_rows, n_layers, dims, &plan->ws);
   if (!ar.ok())
     return fail(ctx, DCI_ERR_CAPACITY, "workspace holds %zu bytes, the forward pass needs %zu", ctx->ws_bytes, ar.off);
+  plan->planned = ctx->linear_kernel == 0 && ctx->input_layer == 0 &&
+                  layers_plan(model, n_layers, dims, blocks->cap_rows, plan->ws.m, plan->ws.m_bytes, plan->layers);
+  return DCI_OK;
+}
+
+// Shared body of the calls that run the model, planned beforehand.  rowref != nullptr: the input layer's aggregation
+// reads the row of source s from feat_cache[rowref[s]] when rowref[s] >= 0 and from x_in[s] otherwise.
+// split: the weights' parts are made already.
+static int32_t forward_in(dci_ctx* ctx, const ForwardPlan& plan, const dci_blocks* blocks, const float* x_in, int32_t n_layers,
+                          const int32_t* dims, int32_t model, const float* const* w_self,
+                          const float* const* w_neigh, const float* const* bias, float* logits,
+                          const int32_t* rowref, const float* feat_cache, bool split) {
+  const bool gcn = model == DCI_MODEL_GCN_AVG;
+  const SageWs& ws = plan.ws;
+  const bool planned = plan.planned;
+  const LayerPlan* const plans = plan.layers;
   const long long* counts = reinterpret_cast<const long long*>(blocks->counts);
   const float* x = x_in;
   auto aligned = [](const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; };
-  // A layer in one kernel (dci_layer.hip) unless an option asks for one of the kernels here; the parts of the weights go where
-  // the aggregated rows' matrix would be.
-  LayerPlan plans[DCI_MAX_HOPS];
-  const bool planned = ctx->linear_kernel == 0 && ctx->input_layer == 0 &&
-                       layers_plan(model, n_layers, dims, blocks->cap_rows, ws.m, ws.m_bytes, plans);
-  bool split = false;  // the weights' parts are made
   for (int32_t l = 0; l < n_layers; ++l) {
     const int32_t h = n_layers - 1 - l;
     const int D = dims[l], Do = dims[l + 1];
     const int64_t cap = blocks->cap_rows[h] > 0 ? blocks->cap_rows[h] : 1;
     float* y = l == n_layers - 1 ? logits : ws.y[l & 1];
     const bool ref_l = l == 0 && rowref != nullptr;
-    // ... and except for the input layers of 9 to 13 slabs that the weights-in-registers kernel takes whole: it moves fewer bytes
+    // One kernel of dci_layer.hip, except for the input layers of 9 to 13 slabs that the weights-in-registers kernel takes whole: it moves fewer bytes
     // (rows in one piece each), which counts when batches share the card.  Eight 4,096-seed batches of 2 x 100 x 256 on four
     // lanes 1,819 us a pass, k_sage_layer 1,874; four on one lane 1,093 either way; 2 x 64 x 256 on one lane 939 and 921.
     const int slabs_l = (2 * ((D / 4 + 1) & ~1) + 3) / 4;
@@ -1810,7 +1825,7 @@ static int32_t forward_in(dci_ctx* ctx, const dci_blocks* blocks, const float* x
       Timed timed(ctx, l == 0 ? DCI_K_LINEAR_IN : DCI_K_LINEAR);
       int32_t rc = DCI_OK;
       if (plans[l].C > 0 && !split) {
-        rc = layers_split_weights(ctx, model, n_layers, plans, w_self, w_neigh);
+        rc = layers_split_weights(ctx, layers_split_args(model, n_layers, plans, w_self, w_neigh));
         split = true;
       }
       if (rc == DCI_OK) rc = layer_launch(ctx, plans[l], na);
@@ -2066,7 +2081,10 @@ static int32_t forward_in(dci_ctx* ctx, const dci_blocks* blocks, const float* x
 int32_t dci_gnn_forward(dci_ctx* ctx, const dci_blocks* blocks, const float* x_in, int32_t n_layers,
                         const int32_t* dims, int32_t model, const float* const* w_self,
                         const float* const* w_neigh, const float* const* bias, float* logits) {
-  return forward_in(ctx, blocks, x_in, n_layers, dims, model, w_self, w_neigh, bias, logits, nullptr, nullptr, 0);
+  ForwardPlan plan;
+  const int32_t rc = plan_forward(ctx, blocks, x_in, n_layers, dims, model, w_self, w_neigh, bias, logits, 0, &plan);
+  if (rc != DCI_OK) return rc;
+  return forward_in(ctx, plan, blocks, x_in, n_layers, dims, model, w_self, w_neigh, bias, logits, nullptr, nullptr, false);
 }
 
 static size_t gather_forward_prefix_bytes(const dci_ctx* ctx, int64_t cap_nodes, size_t* partials_off) {
@@ -2106,13 +2124,40 @@ int32_t dci_gather_forward(dci_ctx* ctx, const dci_graph* graph, const dci_cache
   if (prefix > ctx->ws_bytes || !ctx->ws)
     return fail(ctx, DCI_ERR_CAPACITY, "workspace holds %zu bytes, gather_forward needs more than %zu", ctx->ws_bytes, prefix);
   int32_t* rowref = reinterpret_cast<int32_t*>(ctx->ws);
+  ForwardPlan plan;
+  int32_t rc = plan_forward(ctx, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, prefix, &plan);
+  if (rc != DCI_OK) return rc;
+  SplitArgs split;
+  if (plan.planned) split = layers_split_args(model, n_layers, plan.layers, w_self, w_neigh);
   // the rows the dense layer of the input layer reads as a matrix: F_{L-1}, a prefix of the input nodes
   const int64_t* n_dense = blocks->counts + (n_layers - 1);
-  int32_t rc = gather_launch(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, blocks->counts + n_layers, x, stats,
-                             ctx->ws + partials_off, rowref, n_dense, blocks->cap_rows[n_layers - 1]);
+  rc = gather_launch(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, blocks->counts + n_layers, x, stats,
+                     ctx->ws + partials_off, rowref, n_dense, blocks->cap_rows[n_layers - 1], false, true, &split);
   if (rc != DCI_OK) return rc;
-  return forward_in(ctx, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, rowref,
-                    cache ? cache->feat_cache : nullptr, prefix);
+  return forward_in(ctx, plan, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, rowref,
+                    cache ? cache->feat_cache : nullptr, true);
 }
 
 }  // extern "C"
+
+namespace dci {
+
+int32_t gather_all_forward(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const dci_blocks* blocks, float* x,
+                           int32_t n_layers, const int32_t* dims, int32_t model, const float* const* w_self,
+                           const float* const* w_neigh, const float* const* bias, float* logits) {
+  int32_t rc = check_gather(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, x);
+  if (rc != DCI_OK) return rc;
+  ForwardPlan plan;
+  rc = plan_forward(ctx, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, 0, &plan);
+  if (rc != DCI_OK) return rc;
+  SplitArgs split;
+  if (plan.planned) split = layers_split_args(model, n_layers, plan.layers, w_self, w_neigh);
+  if (blocks->cap_nodes > 0)
+    rc = gather_launch(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, blocks->counts + n_layers, x, nullptr, nullptr, nullptr,
+                       nullptr, 0, false, true, &split);
+  if (rc != DCI_OK) return rc;
+  return forward_in(ctx, plan, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, nullptr, nullptr,
+                    blocks->cap_nodes > 0);
+}
+
+}  // namespace dci
