@@ -43,6 +43,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3
+THREE_PART_PEAK_TFLOPS = 2500.0 / 6  # fp32 products as six bf16 ones (k_sage_layer)
 PIN_LIMIT_BYTES = 60 * 10**9     # the GPU machines refuse page-locked allocations beyond 64 GiB in total
 
 
@@ -74,8 +75,8 @@ def main() -> int:
     ap.add_argument("--model", default="sage-mean", choices=["sage-mean", "sage-sum", "gcn-avg"],
                     help="GNN of the forward pass (Table III); the headline configuration is sage-mean")
     ap.add_argument("--linear-kernel", type=int, default=0, choices=[0, 1, 2, 3, 4],
-                    help="dense-layer kernel of the single-stream regions: 0 by shape (default), 1 register-staged tile "
-                         "kernel, 2 wide kernel, 3 by shape without the wide and the weights-in-registers kernels, "
+                    help="kernel of the layers in the single-stream regions: 0 by shape (default: a layer is one kernel), "
+                         "1 register-staged tile kernel, 2 wide kernel, 3 the tile kernels by shape, "
                          "4 weights in registers where the shape allows")
     ap.add_argument("--pipelined-linear-kernel", type=int, default=1, choices=[0, 1, 2, 3, 4],
                     help="dense-layer kernel of the pipelined regions (the statically partitioned wide kernel loses "
@@ -351,13 +352,16 @@ def main() -> int:
             if l == 1 and L > 2:       # the later layers share one class: add them up
                 mb = sum(4 * w.dims[j] * (int(hop_edges[L - 1 - j]) + int(hop_nodes[L - 1 - j])) for j in range(1, L))
             fl = flops_layer[0] if l == 0 else float(flops_layer[1:].sum())
-            one_kernel = l == 0 and timing_all[cls_m][1] == 0 and timing_all[cls_l][1] > 0
-            if one_kernel:
-                # the input layer ran as one kernel (aggregation inside the dense layer): it answers to both bounds
-                rooflines[cls_l] = entry("k_sage_input_res / k_sage_input_tile (aggregation inside the dense layer)", cls_l,
-                                         {"hbm": mb / hbm_bw, "mfma": fl / (FP32_MFMA_PEAK_TFLOPS * 1e12)},
+            if timing_all[cls_m][1] == 0 and timing_all[cls_l][1] > 0:
+                # the layer ran as one kernel: it answers to both bounds (input layers of 65 to 104 columns stay with the
+                # kernel that keeps fp32 weights in registers)
+                fp32 = args.linear_kernel or args.input_layer or (l == 0 and model != 2 and 64 < w.dims[0] <= 104 and w.dims[1] % 256 == 0)
+                peak = FP32_MFMA_PEAK_TFLOPS if fp32 else THREE_PART_PEAK_TFLOPS
+                name = "k_sage_input_res / k_sage_input_tile" if fp32 else "k_sage_layer / k_sage_layer_small"
+                rooflines[cls_l] = entry(f"{name} (aggregation and dense layer)", cls_l,
+                                         {"hbm": mb / hbm_bw, "mfma": fl / (peak * 1e12)},
                                          {"hbm": mb / GB, "mfma": fl / 1e12},
-                                         {"hbm": HBM_PEAK_GBPS, "mfma": FP32_MFMA_PEAK_TFLOPS}, unit_hbm,
+                                         {"hbm": HBM_PEAK_GBPS, "mfma": round(peak, 1)}, unit_hbm,
                                          bytes_per_step=round(mb / K), flops_per_step=round(fl / K))
                 continue
             rooflines[cls_m] = entry("k_sage_mean", cls_m, {"hbm": mb / hbm_bw}, {"hbm": mb / GB}, {"hbm": HBM_PEAK_GBPS},
