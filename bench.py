@@ -43,7 +43,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3
-THREE_PART_PEAK_TFLOPS = 2500.0 / 6  # fp32 products as six bf16 ones (k_sage_layer)
+THREE_PART_PEAK_TFLOPS = 2500.0 / 8  # fp32 products as eight bf16 ones (k_sage_layer)
 PIN_LIMIT_BYTES = 60 * 10**9     # the GPU machines refuse page-locked allocations beyond 64 GiB in total
 
 

@@ -170,8 +170,8 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  * in the order of the floating-point sums).  DCI_ERR_INVALID_ARG for an unknown option or value.
  *   DCI_OPT_LINEAR_KERNEL  which dense-layer kernel dci_sage_forward / dci_gnn_forward launch:
  *       0  by shape (default): aggregation and dense layer as one kernel, its products on the bf16 matrix
- *          instructions with every fp32 operand as a sum of three bf16 parts (an error against 64-bit sums no
- *          larger than that of the fp32 instructions), unless DCI_OPT_INPUT_LAYER is set, a layer's input has
+ *          instructions with every fp32 operand as a sum of three bf16 parts (a product by itself is rounded like an
+ *          fp32 product, and 32 at a time are added), unless DCI_OPT_INPUT_LAYER is set, a layer's input has
  *          fewer than four columns or the parts of the weights do not fit where the aggregated rows would be.
  *          Then: the kernel that keeps the weights in registers when the whole contraction
  *          is at most 256 long (two operands of up to 128 columns, or GCN's one of up to 256), the input width

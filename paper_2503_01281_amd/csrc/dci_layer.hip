@@ -8,11 +8,17 @@
 // order) and multiplied with the chunk's rows of the weights, a wavefront making all 16 T rows of 16 C columns.
 //
 // The products run on the bf16 matrix instructions (v_mfma_f32_16x16x32_bf16, fp32 accumulators): an fp32 number is the sum
-// of three bf16 numbers, h + m + l, without a remainder (8 + 8 + 8 bits, each part the rest rounded to nearest), and of the nine
-// products of two such sums the six largest are taken.  The three left out (m l, l m, l l) are below 2^-26 of the product -
-// a quarter of the rounding of one fp32 product - and the instruction adds 32 products at a time, where the fp32 one rounds
-// after every four: the error against 64-bit sums is no larger than that of the fp32 matrix instructions.  Six bf16
-// instructions take 3/8 of the matrix pipe's time of the eight fp32 ones they stand for.
+// of three bf16 numbers, h + m + l, without a remainder (8 + 8 + 8 bits, each part the rest rounded to nearest: |m| <= 2^-8 |x|,
+// |l| <= 2^-17 |x|), and of the nine products of two such sums all but l l, which is below 2^-33 of the product, are taken.
+// The instruction adds its 32 products to the accumulator without rounding to nearest (a product by itself came out up to
+// 2^-23 too small), so h h, whose products are whole numbers of 16 bits, is summed apart from the other seven, and the two sums
+// meet in an fp32 addition: one product by itself then has the rounding of an fp32 product (1.004 x 2^-24 at most, seen over
+// 10^6; with the six largest products in one accumulator it was 2.6 x 2^-24).  32 products are added at a time where the fp32
+// instruction rounds after every four.  Root mean square of the error over the sum of magnitudes, in 2^-24, these kernels / the
+// fp32 ones: N(0,1) x Glorot, 4 columns 0.31 / 0.39, 32 0.14 / 0.32, 602 0.08 / 0.31; U[1,2) 0.66 / 0.72, 0.72 / 1.21, 1.64 / 4.5.
+// Only where all but a few of a long contraction's products are zero is it larger (three of 602: 0.72 / 0.64), because a step of
+// 32 with one product in it is rounded twice.  Eight bf16 instructions take half of the matrix pipe's time of the eight fp32 ones
+// they stand for.
 //   Numbers that the parts cannot hold (infinities, NaN, magnitudes that round up to infinity in bf16) leave infinities or
 // NaN in the accumulators they touch, and nothing else but a true overflow does.  A workgroup that finds one in its tile
 // makes the tile again with the fp32 instructions.
@@ -210,21 +216,24 @@ __device__ __forceinline__ void multiply_chunk(const LayerLds& lds, int buf, int
 #pragma unroll
         for (int q = 0; q < 3; ++q) b[(u + 1) & 1][c][q] = *((gw_t)(p + ((((u + 1) % kPairs) * kPair + c) * 3 + q) * 1024) + lane);
     }
-    // the step's 32 products are added up from zero, smallest first, and join the running sum as one number
+    // the step's 32 products are added up from zero, h h by itself and the others smallest first, and join the running sum as
+    // one number
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      f32x4 part[kPair];
-#define DCI_MM(A_, P_, IN_) \
-  _Pragma("unroll") for (int c = 0; c < kPair; ++c) part[c] = mfma_bf16(af[t][A_], b[u & 1][c][P_], IN_)
-      DCI_MM(2, 0, zero);
-      DCI_MM(0, 2, part[c]);
-      DCI_MM(1, 1, part[c]);
-      DCI_MM(1, 0, part[c]);
-      DCI_MM(0, 1, part[c]);
-      DCI_MM(0, 0, part[c]);
+      f32x4 top[kPair], rest[kPair];
+#define DCI_MM(TO_, A_, P_, IN_) \
+  _Pragma("unroll") for (int c = 0; c < kPair; ++c) TO_[c] = mfma_bf16(af[t][A_], b[u & 1][c][P_], IN_)
+      DCI_MM(rest, 2, 1, zero);
+      DCI_MM(rest, 1, 2, rest[c]);
+      DCI_MM(rest, 2, 0, rest[c]);
+      DCI_MM(rest, 0, 2, rest[c]);
+      DCI_MM(rest, 1, 1, rest[c]);
+      DCI_MM(rest, 1, 0, rest[c]);
+      DCI_MM(rest, 0, 1, rest[c]);
+      DCI_MM(top, 0, 0, zero);
 #undef DCI_MM
 #pragma unroll
-      for (int c = 0; c < kPair; ++c) acc[t][pair * kPair + c] += part[c];
+      for (int c = 0; c < kPair; ++c) acc[t][pair * kPair + c] += top[c] + rest[c];
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -431,7 +440,7 @@ __global__ __launch_bounds__(256) void k_split_weights(SplitArgs a) { split_weig
 // ---- layers of few rows ---------------------------------------------------------------------------
 // A workgroup of sixteen wavefronts makes 16 rows by 64 columns of y: wavefront w puts row w together (256 columns of it at
 // a time, 16 bytes per lane, the places of the sources in scalar registers), then multiplies one k step of 32 of the chunk
-// with the weights it asked for beforehand; the sixteen partial tiles are added up in LDS.
+// with the weights it asked for beforehand; the sixteen partial tiles are added up through LDS.
 //   Bound by the latency of its chain of look-ups (row count and list bounds, sources, their cache slots, their rows); all sixteen rows
 // and all of the weights are asked for at once, and the list bounds beside the row count.  A layer of 40 x 2 x 256 x 256 takes 10 us;
 // as three kernels it took 15.
@@ -527,14 +536,14 @@ __device__ __forceinline__ float small_tile(const LayerArgs& a, unsigned char* l
             b[1][jj] = s.m;
             b[2][jj] = s.l;
           }
-          f32x4 part = zero;
-          part = mfma_bf16(al, b[0], part);
-          part = mfma_bf16(ah, b[2], part);
-          part = mfma_bf16(am, b[1], part);
-          part = mfma_bf16(am, b[0], part);
-          part = mfma_bf16(ah, b[1], part);
-          part = mfma_bf16(ah, b[0], part);
-          acc[c] += part;
+          f32x4 rest = mfma_bf16(al, b[1], zero);  // as in multiply_chunk
+          rest = mfma_bf16(am, b[2], rest);
+          rest = mfma_bf16(al, b[0], rest);
+          rest = mfma_bf16(ah, b[2], rest);
+          rest = mfma_bf16(am, b[1], rest);
+          rest = mfma_bf16(am, b[0], rest);
+          rest = mfma_bf16(ah, b[1], rest);
+          acc[c] += mfma_bf16(ah, b[0], zero) + rest;
         }
       } else {
         const f32x4 lo = *reinterpret_cast<const f32x4*>(p), hi = *reinterpret_cast<const f32x4*>(p + 1024);
@@ -560,8 +569,16 @@ __device__ __forceinline__ float small_tile(const LayerArgs& a, unsigned char* l
       *reinterpret_cast<f32x4*>(red + wave * (kSmallRows * kSmallCols) + (4 * g + r) * kSmallCols + 4 * r16) =
           f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
   __syncthreads();
-  float v = red[tid];
-  for (int w = 1; w < n_parts; ++w) v += red[w * (kSmallRows * kSmallCols) + tid];
+  // (in pairs: sixteen one after the other round 2 x 602 products of one sign to 4.4 x 2^-24 of their sum at most, pairs to
+  // 2.3; the kernel that split the contraction eight ways had 3.7)
+  float sum[16];
+#pragma unroll
+  for (int w = 0; w < 16; ++w) sum[w] = w < n_parts ? red[w * (kSmallRows * kSmallCols) + tid] : 0.f;
+#pragma unroll
+  for (int n = 8; n > 0; n >>= 1)
+#pragma unroll
+    for (int w = 0; w < n; ++w) sum[w] += sum[w + n];
+  const float v = sum[0];
   return EXACT ? v : v * kUnscale;
 }
 
