@@ -191,15 +191,16 @@ struct LayerArgs {
   const void* w_split;    // the weights as parts (k_sage_layer)
 };
 struct LayerPlan {
-  int D, N, C;  // C: 0 k_sage_layer_small, else k_sage_layer with 16 C columns per wavefront
+  int D, N, C;  // C: -1 not one of these kernels, 0 k_sage_layer_small, else k_sage_layer with 16 C columns per wavefront
   int64_t cap_rows;
   void* w_split;
 };
-// Plans every layer of a forward pass; scratch is where the weights' parts may go.  false: one of the layers is not for these
-// kernels, or the scratch is too small.
-bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int64_t* cap_rows, void* scratch,
+// Plans every layer of a forward pass; input_apart: the input layer is not for these kernels; scratch is where the weights' parts may
+// go.  false: none of the layers is for these kernels, because an input is too narrow or the scratch too small.
+bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int64_t* cap_rows, bool input_apart, void* scratch,
                  size_t scratch_bytes, LayerPlan* plans);
-SplitArgs layers_split_args(int32_t model, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,
+// The parts to lay out for the layers from `first` on
+SplitArgs layers_split_args(int32_t model, int32_t first, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,
                             const float* const* w_neigh);
 int32_t layers_split_weights(dci_ctx* ctx, const SplitArgs& args);
 int32_t layer_launch(dci_ctx* ctx, const LayerPlan& plan, const LayerArgs& args);

@@ -632,8 +632,8 @@ static size_t split_bytes(const LayerPlan& p, int ops) {
   return (size_t)ops * ((p.D + 31) / 32) * ((p.N + 64 * p.C - 1) / (64 * p.C)) * 4 * p.C * 3 * 1024;
 }
 
-bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int64_t* cap_rows, void* scratch, size_t scratch_bytes,
-                 LayerPlan* plans) {
+bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int64_t* cap_rows, bool input_apart, void* scratch,
+                 size_t scratch_bytes, LayerPlan* plans) {
   const int ops = model == DCI_MODEL_GCN_AVG ? 1 : 2;
   Arena ar(reinterpret_cast<char*>(scratch), scratch_bytes);
   for (int32_t l = 0; l < n_layers; ++l) {
@@ -641,10 +641,14 @@ bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int
     p.D = dims[l];
     p.N = dims[l + 1];
     p.cap_rows = cap_rows[n_layers - 1 - l];
+    p.w_split = nullptr;
     if (p.D < 4 || p.cap_rows < 1) return false;
+    if (l == 0 && input_apart) {
+      p.C = -1;
+      continue;
+    }
     const int64_t small_wgs = (p.cap_rows + kSmallRows - 1) / kSmallRows * ((p.N + kSmallCols - 1) / kSmallCols);
     p.C = 0;
-    p.w_split = nullptr;
     if (p.N >= 4 && small_wgs <= kSmallMax) continue;
     if (p.cap_rows >= kWideFrom) p.C = p.N > 128 ? 4 : p.N > 64 ? 2 : 1;
     else p.C = (p.N + 63) / 64 % 2 ? 1 : (p.N + 63) / 64 % 4 ? 2 : 4;
@@ -653,13 +657,13 @@ bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int
   return ar.ok();
 }
 
-SplitArgs layers_split_args(int32_t model, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,
+SplitArgs layers_split_args(int32_t model, int32_t first, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,
                             const float* const* w_neigh) {
   const bool gcn = model == DCI_MODEL_GCN_AVG;
   SplitArgs sa;
-  for (int32_t l = 0; l < n_layers; ++l) {
+  for (int32_t l = first; l < n_layers; ++l) {
     const LayerPlan& p = plans[l];
-    if (p.C == 0) continue;
+    if (p.C <= 0) continue;
     sa.first[sa.n] = sa.wgs;
     sa.w[sa.n][0] = gcn ? w_neigh[l] : w_self[l];
     sa.w[sa.n][1] = w_neigh[l];

@@ -1746,18 +1746,46 @@ int32_t dci_sage_forward(dci_ctx* ctx, const dci_blocks* blocks, const float* x_
   return dci_gnn_forward(ctx, blocks, x_in, n_layers, dims, DCI_MODEL_SAGE_MEAN, w_self, w_neigh, bias, logits);
 }
 
-// How a forward pass will run.  The layers are one kernel each (dci_layer.hip) unless an option asks for one of the kernels here;
-// the parts of their weights go where the aggregated rows' matrix would be.
+static bool aligned(const void* p, size_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
+
+// Slabs of 16 of the two operands side by side (k_sage_input_res, k_sage_linear_res)
+static int input_slabs(int D) { return (2 * ((D / 4 + 1) & ~1) + 3) / 4; }
+
+// Which kernel of this file runs an input layer: aggregation and dense layer apart, or one of the two that do both.
+// feat_cache: where rows are read in place (nullptr: nowhere).
+enum class InputKernel { Apart, Registers, Tiles };
+static InputKernel input_kernel(const dci_ctx* ctx, int32_t model, int D, int Do, int64_t cap, const float* x, const float* feat_cache,
+                                const float* w_self, const float* w_neigh, const float* bias, const float* y) {
+  if (model == DCI_MODEL_GCN_AVG || ctx->input_layer == 1 || (ctx->linear_kernel != 0 && ctx->linear_kernel != 4)) return InputKernel::Apart;
+  if (D > 128 || !aligned(x, 16) || !aligned(feat_cache, 16)) return InputKernel::Apart;
+  const bool many = ctx->linear_kernel == 0 && cap >= kResMinRows;
+  // By default only where it was measured ahead of the two kernels: up to 13 slabs (large's 2 x 100 columns: 107 us
+  // against 60 + 64).  With all 16 slabs (huge's 2 x 128) the weights leave room for four slots in flight per
+  // lane, the loads no longer keep up, and the kernel takes as long as the two it replaces (160 us).
+  if (Do % kResCols == 0 && D % 4 == 0 && ctx->num_cus >= Do / kResCols && (ctx->input_layer == 2 || (many && input_slabs(D) <= 13)))
+    return InputKernel::Registers;
+  if ((ctx->input_layer == 3 || (ctx->input_layer == 0 && many)) && Do % TN == 0 && D % TK == 0 && D >= 2 * TK && aligned(w_self, 16) &&
+      aligned(w_neigh, 16) && aligned(y, 16) && aligned(bias, 16) && (cap + TM - 1) / TM < ((int64_t)1 << 31))
+    return InputKernel::Tiles;
+  return InputKernel::Apart;
+}
+
+// How a forward pass will run.  A layer is one kernel of dci_layer.hip unless an option asks for one of the kernels here or the
+// layer is planned to be apart (LayerPlan); the parts of the weights go where the aggregated rows' matrix would be.
 struct ForwardPlan {
   SageWs ws;
   bool planned;
   LayerPlan layers[DCI_MAX_HOPS];
+  InputKernel input;  // of an input layer that runs here
+  // whether the parts can be laid out before the input layer runs: nothing writes the matrix of aggregated rows before they are read
+  bool parts_first() const { return planned && (layers[0].C >= 0 || input != InputKernel::Apart); }
 };
 
-// Checks a forward pass's arguments and plans it.  ws_off: bytes at the start of the workspace that the caller keeps for itself.
+// Checks a forward pass's arguments and plans it.  feat_cache: where the input layer reads rows in place.  ws_off: bytes at the
+// start of the workspace that the caller keeps for itself.
 static int32_t plan_forward(dci_ctx* ctx, const dci_blocks* blocks, const float* x_in, int32_t n_layers, const int32_t* dims,
                             int32_t model, const float* const* w_self, const float* const* w_neigh, const float* const* bias,
-                            const float* logits, size_t ws_off, ForwardPlan* plan) {
+                            const float* logits, const float* feat_cache, size_t ws_off, ForwardPlan* plan) {
   if (!ctx) return DCI_ERR_INVALID_ARG;
   if (model != DCI_MODEL_SAGE_MEAN && model != DCI_MODEL_SAGE_SUM && model != DCI_MODEL_GCN_AVG)
     return fail(ctx, DCI_ERR_INVALID_ARG, "gnn_forward: unknown model %d", model);
@@ -1776,8 +1804,19 @@ static int32_t plan_forward(dci_ctx* ctx, const dci_blocks* blocks, const float*
   carve_sage_ws(ar, blocks->cap_rows, n_layers, dims, &plan->ws);
   if (!ar.ok())
     return fail(ctx, DCI_ERR_CAPACITY, "workspace holds %zu bytes, the forward pass needs %zu", ctx->ws_bytes, ar.off);
+  const int64_t cap_in = blocks->cap_rows[n_layers - 1] > 0 ? blocks->cap_rows[n_layers - 1] : 1;
+  auto input = [&](const float* in_place) {
+    return input_kernel(ctx, model, dims[0], dims[1], cap_in, x_in, in_place, model == DCI_MODEL_GCN_AVG ? nullptr : w_self[0], w_neigh[0],
+                        bias[0], n_layers == 1 ? logits : plan->ws.y[0]);
+  };
+  plan->input = input(feat_cache);
+  // Input layers of 9 to 13 slabs stay with the weights-in-registers kernel, which moves fewer bytes (rows in one piece each); that
+  // counts when batches share the card.  Eight 4,096-seed batches of 2 x 100 x 256 on four lanes 1,819 us a pass, k_sage_layer 1,874;
+  // four on one lane 1,093 either way; 2 x 64 x 256 on one lane 939 and 921.  Where the cache's alignment rules that kernel out for rows read
+  // in place, the layer's two kernels are taken, whose results are the same to the bit: DCI_OPT_FUSED_INPUT changes no logits.
+  const bool input_apart = input_slabs(dims[0]) > 8 && input(nullptr) == InputKernel::Registers;
   plan->planned = ctx->linear_kernel == 0 && ctx->input_layer == 0 &&
-                  layers_plan(model, n_layers, dims, blocks->cap_rows, plan->ws.m, plan->ws.m_bytes, plan->layers);
+                  layers_plan(model, n_layers, dims, blocks->cap_rows, input_apart, plan->ws.m, plan->ws.m_bytes, plan->layers);
   return DCI_OK;
 }
 
@@ -1794,20 +1833,13 @@ static int32_t forward_in(dci_ctx* ctx, const ForwardPlan& plan, const dci_block
   const LayerPlan* const plans = plan.layers;
   const long long* counts = reinterpret_cast<const long long*>(blocks->counts);
   const float* x = x_in;
-  auto aligned = [](const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; };
   for (int32_t l = 0; l < n_layers; ++l) {
     const int32_t h = n_layers - 1 - l;
     const int D = dims[l], Do = dims[l + 1];
     const int64_t cap = blocks->cap_rows[h] > 0 ? blocks->cap_rows[h] : 1;
     float* y = l == n_layers - 1 ? logits : ws.y[l & 1];
     const bool ref_l = l == 0 && rowref != nullptr;
-    // One kernel of dci_layer.hip, except for the input layers of 9 to 13 slabs that the weights-in-registers kernel takes whole: it moves fewer bytes
-    // (rows in one piece each), which counts when batches share the card.  Eight 4,096-seed batches of 2 x 100 x 256 on four
-    // lanes 1,819 us a pass, k_sage_layer 1,874; four on one lane 1,093 either way; 2 x 64 x 256 on one lane 939 and 921.
-    const int slabs_l = (2 * ((D / 4 + 1) & ~1) + 3) / 4;
-    const bool whole_rows = l == 0 && !gcn && Do % kResCols == 0 && D % 4 == 0 && slabs_l > 8 && slabs_l <= 13 && cap >= kResMinRows &&
-                            ctx->num_cus >= Do / kResCols && aligned(x, 16) && (!ref_l || aligned(feat_cache, 16));
-    if (planned && !whole_rows) {
+    if (planned && plans[l].C >= 0) {
       LayerArgs na;
       na.counts = counts;
       na.hop = h;
@@ -1825,7 +1857,7 @@ static int32_t forward_in(dci_ctx* ctx, const ForwardPlan& plan, const dci_block
       Timed timed(ctx, l == 0 ? DCI_K_LINEAR_IN : DCI_K_LINEAR);
       int32_t rc = DCI_OK;
       if (plans[l].C > 0 && !split) {
-        rc = layers_split_weights(ctx, layers_split_args(model, n_layers, plans, w_self, w_neigh));
+        rc = layers_split_weights(ctx, layers_split_args(model, l, n_layers, plans, w_self, w_neigh));
         split = true;
       }
       if (rc == DCI_OK) rc = layer_launch(ctx, plans[l], na);
@@ -1833,26 +1865,8 @@ static int32_t forward_in(dci_ctx* ctx, const ForwardPlan& plan, const dci_block
       x = y;
       continue;
     }
-    // Input layer in one kernel (aggregation inside the weights-in-registers dense layer) where the layer qualifies
-    bool fuse_in = false;
-    if (l == 0 && !gcn && ctx->input_layer != 1 && (ctx->linear_kernel == 0 || ctx->linear_kernel == 4)) {
-      const int n_tiles_f = Do / kResCols;
-      const bool shape_ok = Do % kResCols == 0 && D % 4 == 0 && D <= 128 && n_tiles_f > 0 && ctx->num_cus / n_tiles_f >= 1 &&
-                            aligned(x, 16) && (!ref_l || aligned(feat_cache, 16));
-      // By default only where it was measured ahead of the two kernels: up to 13 slabs (large's 2 x 100 columns: 107 us
-      // against 60 + 64).  With all 16 slabs (huge's 2 x 128) the weights leave room for four slots in flight per
-      // lane, the loads no longer keep up, and the kernel takes as long as the two it replaces (160 us).
-      const int slabs_f = (2 * ((D / 4 + 1) & ~1) + 3) / 4;
-      fuse_in = shape_ok && (ctx->input_layer == 2 || (ctx->linear_kernel == 0 && cap >= kResMinRows && slabs_f <= 13));
-    }
-    // The 64-row-tile form of the same: aggregate into LDS, then multiply (k_sage_input_tile)
-    bool tile_in = false;
-    if (l == 0 && !gcn && !fuse_in && (ctx->input_layer == 3 || ctx->input_layer == 0) && (ctx->linear_kernel == 0 || ctx->linear_kernel == 4)) {
-      const bool shape_ok = Do % TN == 0 && D % TK == 0 && D >= 2 * TK && D <= 128 && aligned(x, 16) && (!ref_l || aligned(feat_cache, 16)) &&
-                            aligned(w_self[l], 16) && aligned(w_neigh[l], 16) && aligned(y, 16) && aligned(bias[l], 16) && (cap + TM - 1) / TM < ((int64_t)1 << 31);
-      tile_in = shape_ok && (ctx->input_layer == 3 || (ctx->linear_kernel == 0 && cap >= kResMinRows));
-    }
-    if (tile_in) {
+    // The input layer in one kernel of its 64-row tiles: aggregate into LDS, then multiply
+    if (l == 0 && plan.input == InputKernel::Tiles) {
       LinearArgs la;
       la.counts = counts;
       la.hop = h;
@@ -1896,7 +1910,8 @@ static int32_t forward_in(dci_ctx* ctx, const ForwardPlan& plan, const dci_block
       x = y;
       continue;
     }
-    if (fuse_in) {
+    // The input layer in one kernel: the aggregation inside the weights-in-registers dense layer
+    if (l == 0 && plan.input == InputKernel::Registers) {
       LinearArgs la;
       la.counts = counts;
       la.hop = h;
@@ -1923,7 +1938,7 @@ static int32_t forward_in(dci_ctx* ctx, const ForwardPlan& plan, const dci_block
       fa.x_src = x;
       fa.mode = model;
       const int g_f = ctx->num_cus / la.n_tiles_n;
-      const int slabs = (2 * ((D / 4 + 1) & ~1) + 3) / 4;
+      const int slabs = input_slabs(D);
       const dim3 grid_f((unsigned)(g_f * la.n_tiles_n));
       {
         Timed timed(ctx, DCI_K_LINEAR_IN);
@@ -1936,7 +1951,8 @@ static int32_t forward_in(dci_ctx* ctx, const ForwardPlan& plan, const dci_block
       x = y;
       continue;
     }
-    // mean aggregation
+    // mean aggregation (into the place of the parts of the layers to come)
+    split = false;
     int V = 1;
     const bool cache_al16 = !(l == 0 && rowref) || aligned(feat_cache, 16), cache_al8 = !(l == 0 && rowref) || aligned(feat_cache, 8);
     if (D % 4 == 0 && aligned(x, 16) && cache_al16) V = 4;
@@ -2082,7 +2098,7 @@ int32_t dci_gnn_forward(dci_ctx* ctx, const dci_blocks* blocks, const float* x_i
                         const int32_t* dims, int32_t model, const float* const* w_self,
                         const float* const* w_neigh, const float* const* bias, float* logits) {
   ForwardPlan plan;
-  const int32_t rc = plan_forward(ctx, blocks, x_in, n_layers, dims, model, w_self, w_neigh, bias, logits, 0, &plan);
+  const int32_t rc = plan_forward(ctx, blocks, x_in, n_layers, dims, model, w_self, w_neigh, bias, logits, nullptr, 0, &plan);
   if (rc != DCI_OK) return rc;
   return forward_in(ctx, plan, blocks, x_in, n_layers, dims, model, w_self, w_neigh, bias, logits, nullptr, nullptr, false);
 }
@@ -2125,17 +2141,18 @@ int32_t dci_gather_forward(dci_ctx* ctx, const dci_graph* graph, const dci_cache
     return fail(ctx, DCI_ERR_CAPACITY, "workspace holds %zu bytes, gather_forward needs more than %zu", ctx->ws_bytes, prefix);
   int32_t* rowref = reinterpret_cast<int32_t*>(ctx->ws);
   ForwardPlan plan;
-  int32_t rc = plan_forward(ctx, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, prefix, &plan);
+  const float* const feat_cache = cache ? cache->feat_cache : nullptr;
+  int32_t rc = plan_forward(ctx, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, feat_cache, prefix, &plan);
   if (rc != DCI_OK) return rc;
   SplitArgs split;
-  if (plan.planned) split = layers_split_args(model, n_layers, plan.layers, w_self, w_neigh);
+  if (plan.parts_first()) split = layers_split_args(model, 0, n_layers, plan.layers, w_self, w_neigh);
   // the rows the dense layer of the input layer reads as a matrix: F_{L-1}, a prefix of the input nodes
   const int64_t* n_dense = blocks->counts + (n_layers - 1);
   rc = gather_launch(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, blocks->counts + n_layers, x, stats,
                      ctx->ws + partials_off, rowref, n_dense, blocks->cap_rows[n_layers - 1], false, true, &split);
   if (rc != DCI_OK) return rc;
   return forward_in(ctx, plan, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, rowref,
-                    cache ? cache->feat_cache : nullptr, true);
+                    feat_cache, plan.parts_first());
 }
 
 }  // extern "C"
@@ -2148,16 +2165,16 @@ int32_t gather_all_forward(dci_ctx* ctx, const dci_graph* graph, const dci_cache
   int32_t rc = check_gather(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, x);
   if (rc != DCI_OK) return rc;
   ForwardPlan plan;
-  rc = plan_forward(ctx, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, 0, &plan);
+  rc = plan_forward(ctx, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, nullptr, 0, &plan);
   if (rc != DCI_OK) return rc;
   SplitArgs split;
-  if (plan.planned) split = layers_split_args(model, n_layers, plan.layers, w_self, w_neigh);
+  if (plan.parts_first()) split = layers_split_args(model, 0, n_layers, plan.layers, w_self, w_neigh);
   if (blocks->cap_nodes > 0)
     rc = gather_launch(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, blocks->counts + n_layers, x, nullptr, nullptr, nullptr,
                        nullptr, 0, false, true, &split);
   if (rc != DCI_OK) return rc;
   return forward_in(ctx, plan, blocks, x, n_layers, dims, model, w_self, w_neigh, bias, logits, nullptr, nullptr,
-                    blocks->cap_nodes > 0);
+                    blocks->cap_nodes > 0 && plan.parts_first());
 }
 
 }  // namespace dci
