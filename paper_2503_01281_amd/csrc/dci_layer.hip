@@ -59,14 +59,17 @@ __device__ __forceinline__ f32x4 shifted(f32x4 v, int shift) {
 // it 129 and 200.  The products alone take 37 and 72 us.
 //   Why this shape: wavefronts of their own for the two kinds of work, because a wavefront's vector and matrix instructions
 // take turns (one role after the other in every wavefront: 121 us where this takes 94); 32 rows, so that two workgroups fit
-// on a compute unit and the rounds of tiles are short; two rounds of loads on their way at any time (one at a time: 98 us).
-constexpr int kLayerThreads = 512, kLayerRows = 32, kLayerChunk = 64, kLayerSlots = 32, kLayerPerCu = 2, kLayerFlags = 64;
+// on a compute unit and the rounds of tiles are short; two rounds of loads on their way at any time (one at a time: 98 us); places for
+// as many sources as a fan-out can have, because those beyond them are read one after the other (12 k rows of 64 sources x 2 x 256 x
+// 256: 120 us, with 32 places 248; x 2 x 602 x 256: 380, 644).
+constexpr int kLayerThreads = 512, kLayerRows = 32, kLayerChunk = 64, kLayerSlots = 64, kLayerPerCu = 2, kLayerFlags = 64;
 
 struct LayerLds {
   // [buffer][operand][k step of 32][row tile][part]: 64 lanes' fragments of 8 bf16; lane (g, r) = (l / 16, l % 16) holds
   // columns 8g .. 8g+7 of row r, in the place (r + 4g) % 16 of its group so that the writes of a row spread over the banks
   __attribute__((aligned(16))) unsigned char a[2][2][2][2][3][1024];
-  const float* src[kLayerRows][kLayerSlots];  // where a row's first sources are
+  const float* src[kLayerRows][kLayerSlots];  // where a row's first sources are (all of them, in batches of dci_sample_khop)
+  static_assert(kLayerSlots >= DCI_MAX_FANOUT, "a list of the longest fan-out");
   int again[kLayerFlags];                     // tiles to make again with the fp32 instructions
 };
 
@@ -283,12 +286,6 @@ __global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
         e0[t] = ok[t] ? a.blk_indptr[row0 + i] : 0;
         deg[t] = ok[t] ? (int)(a.blk_indptr[row0 + i + 1] - e0[t]) : 0;
       }
-      // (written and read by one group of lanes; places without a source hold the row itself)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int s = 0; s < kLayerSlots; s += 16)
-          lds.src[16 * t + grp][s + gl] = s + gl < deg[t] ? source_row(a, e0[t] + s + gl) : own[t];
       // A row's sources come in rounds of eight loads; two rounds are on their way at any time, across rows and chunks: a
       // place is asked for again, two rounds on, as soon as it has been added.
       int rounds[2];  // of the wavefront's row with the most
@@ -302,6 +299,12 @@ __global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
         n = __builtin_amdgcn_readfirstlane(n);
         rounds[t] = n > 8 ? (n + 7) / 8 : 1;
       }
+      // (written and read by one group of lanes; places without a source, up to the last that a round asks for, hold the row itself)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int s = 0; s < kLayerSlots; s += 16)
+          if (s < 8 * rounds[t]) lds.src[16 * t + grp][s + gl] = s + gl < deg[t] ? source_row(a, e0[t] + s + gl) : own[t];
       f32x4 v0[8], v1[8], own0, own1;
       int n_k = 0, n_t = 0, n_r = 0;  // the round to ask for next
       auto ask = [&](f32x4 (&v)[8], f32x4& own_v) {

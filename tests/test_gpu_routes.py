@@ -99,3 +99,38 @@ def test_rows_read_in_place_from_an_unaligned_cache_give_the_same_logits(env, F,
     assert bool(((out[0].double() - want).abs() <= size * 2.0 ** -24 * (sum(dims) + 30)).all())
     for o in out[1:]:
         assert o.numpy().tobytes() == out[0].numpy().tobytes()
+
+
+def _one_layer(env, M, cap, fan, D, N, model, seed, deg=None):
+    """One layer through dci_gather_forward on gathered rows: (result, 64-bit result, sum of magnitudes, launches per kernel class)"""
+    dci, ctx = env["dci"], env["ctx"]
+    n_in = M + 7
+    blk, host = _blocks(env, cap, (min(fan, 64),), (M, n_in), 10**7, seed)
+    if deg is not None:
+        src = np.random.default_rng(seed).integers(0, n_in, deg.sum()).astype(np.int32)
+        blk.blk_indptr[0][:M + 1] = torch.from_numpy(np.concatenate([[0], deg.cumsum()])).cuda()
+        blk.blk_src[0][:len(src)] = torch.from_numpy(src).cuda()
+        host = [(deg, src)]
+    feat = torch.randn(n_in, D, generator=torch.Generator().manual_seed(seed))
+    g = dci.Graph(torch.zeros(n_in + 1, dtype=torch.int64).cuda(), torch.zeros(1, dtype=torch.int64).cuda(), feat.cuda())
+    ws, wn, bs = _weights((D, N), seed + 1)
+    x = torch.zeros(blk.cap_nodes[-1], D, dtype=torch.float32, device="cuda")
+    y = torch.full((blk.cap_nodes[0], N), float("nan"), dtype=torch.float32, device="cuda")
+    ctx.timing_enable(dci.KERNEL_CLASSES)
+    dci.dci_gather_forward(ctx, g, None, blk, x, model, None if model == 2 else ws, wn, bs, y)
+    n = {k: v[1] for k, v in ctx.timing_read().items()}
+    ctx.timing_enable([])
+    assert bool(torch.isnan(y[M:]).all()), "rows beyond the batch were written"
+    want, size = _model64(model, host, feat, ws, wn, bs)
+    return y[:M].cpu(), want, size, n
+
+
+@pytest.mark.parametrize("model", [0, 1, 2])
+@pytest.mark.parametrize("M,cap,D,N", [(70, 40000, 128, 64), (70, 40000, 160, 200), (70, 20000, 96, 100)])
+def test_lists_as_long_as_the_places_for_their_sources(env, model, M, cap, D, N):
+    """Rows with 0, 1, 31 to 33, 63 to 65 and 100 sources, next to each other, in tiles of many rows."""
+    deg = np.random.default_rng(D).choice([0, 1, 8, 9, 31, 32, 33, 40, 63, 64, 65, 100], M)
+    deg[:3] = (64, 65, 0)
+    got, want, size, n = _one_layer(env, M, cap, 64, D, N, model, D + N, deg)
+    assert n["mean_in"] == 0 and n["linear_in"] == 1        # one kernel
+    assert bool(((got.double() - want).abs() <= size * 2.0 ** -24 * (100 + D / 4 + 8)).all())
