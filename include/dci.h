@@ -166,14 +166,20 @@ const char* dci_last_error(const dci_ctx* ctx);
  * numbers come from dci_blocks_bounds and the *_workspace_bytes queries before a call. */
 int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_edges, size_t* workspace_bytes);
 
-/* Tuning options of a context.  None changes what is computed (the dense-layer kernels differ only
- * in the order of the floating-point sums).  DCI_ERR_INVALID_ARG for an unknown option or value.
- *   DCI_OPT_LINEAR_KERNEL  which dense-layer kernel dci_sage_forward / dci_gnn_forward launch:
+/* Tuning options of a context.  None changes what is computed: the kernels of a layer differ in the order of the floating-point
+ * sums and, for DCI_OPT_LINEAR_KERNEL 0 with DCI_OPT_INPUT_LAYER 0, in how a product of two fp32 numbers is put together (from three
+ * bf16 parts of each, rounded like an fp32 product).  DCI_ERR_INVALID_ARG for an unknown option or value.
+ *   DCI_OPT_LINEAR_KERNEL  which kernels dci_sage_forward / dci_gnn_forward launch for a layer:
  *       0  by shape (default): aggregation and dense layer as one kernel, its products on the bf16 matrix
  *          instructions with every fp32 operand as a sum of three bf16 parts (a product by itself is rounded like an
- *          fp32 product, and 32 at a time are added), unless DCI_OPT_INPUT_LAYER is set, a layer's input has
- *          fewer than four columns or the parts of the weights do not fit where the aggregated rows would be.
- *          Then: the kernel that keeps the weights in registers when the whole contraction
+ *          fp32 product, and 32 at a time are added).  A layer is aggregation and dense layer apart where that is faster: lists
+ *          (cap_edges / cap_rows of its block) of more than 20 sources or so where input rows are not a multiple of 128 bytes, or of
+ *          more than 42 where the output has more than 256 columns; 257 to 384 outputs.  An input layer of 65 to 104 columns and
+ *          256 outputs, or of 112 or 128 columns and a multiple of 256 outputs above that, lists of 11 to 16 sources, at least
+ *          98304 rows by capacity, is one kernel with fp32 instructions (the default forms under DCI_OPT_INPUT_LAYER).  The whole pass
+ *          is as with two kernels a layer where DCI_OPT_INPUT_LAYER is set, an input has fewer than four columns or the parts of
+ *          the weights do not fit where the aggregated rows would be.
+ *          The dense layer of two: the kernel that keeps the weights in registers when the whole contraction
  *          is at most 256 long (two operands of up to 128 columns, or GCN's one of up to 256), the input width
  *          a multiple of 4, the output width a multiple of 256 and the layer at least 98304 rows tall by
  *          capacity; else the wide kernel (128-column tiles, one workgroup per compute unit)
@@ -185,7 +191,8 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *       2  the wide kernel whenever width and alignment allow it, whatever the row count
  *       3  the 64x64 tile kernels, chosen as under 0
  *       4  the weights-in-registers kernel whenever widths and alignment allow it, whatever the row count;
- *          other layers as under 1 */
+ *          other layers as under 1
+ *       (1 to 4: aggregation and dense layer apart, or the input layer as DCI_OPT_INPUT_LAYER asks for it) */
 #define DCI_OPT_LINEAR_KERNEL 1
 /*   DCI_OPT_LINEAR_SPLIT   upper limit on the workgroups that share one output tile of the 64x64 kernel
  *       (the contraction is split between them and a second kernel adds the partial sums in a fixed order):
@@ -214,12 +221,15 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *       the frontier's size, or 2, 4, 8.  Tuning only: the result does not depend on it. */
 #define DCI_OPT_RELABEL_TILE_ITERS 6
 /*   DCI_OPT_INPUT_LAYER  how the forward pass runs its first layer (two operands of at most 128 columns, mean or
- *       sum aggregator) where DCI_OPT_LINEAR_KERNEL 0 does not make it one kernel.  There are two one-kernel forms that keep the aggregated rows out of device memory:
+ *       sum aggregator) where DCI_OPT_LINEAR_KERNEL 0 does not make it one kernel with three-part products; 1, 2 or 3
+ *       take every layer of the pass off those kernels.  There are two one-kernel forms with fp32 instructions that
+ *       keep the aggregated rows out of device memory:
  *       "registers" - the aggregation runs inside the weights-in-registers dense kernel (needs what that kernel
  *       needs, see DCI_OPT_LINEAR_KERNEL) - and "tiles" - half of each workgroup aggregates 64 rows into LDS while
  *       the other half multiplies the 64 rows before (needs a width that is a multiple of 16, at least 32, an
  *       output width that is a multiple of 64, 16-byte aligned rows, weights, bias and output).
- *       0 (default): for layers of at least 98,304 rows (capacity) the registers form if the two operands together
+ *       0 (default): where no layer of the pass has three-part products, for layers of at least 98,304 rows
+ *       (capacity) the registers form if the two operands together
  *       are at most 208 columns (13 slabs of 16: beyond that the weights leave too few registers for the loads in
  *       flight), else the tiles form if the shape allows it, else two kernels;  1: always the aggregation kernel
  *       followed by a dense kernel;  2: the registers form whenever widths and alignment allow it, whatever the

@@ -622,40 +622,61 @@ __global__ __launch_bounds__(kSmallThreads) void k_sage_layer_small(LayerArgs a)
   }
 }
 
-// Which kernel, by the layer's bound on its rows (batches fill a fifth of it to all of it):
+// Which kernel, by the bounds on the layer's rows and on the length of their lists (batches fill a fifth of the rows' bound to all
+// of it; f: sources of every row):
 //   * the one for few rows up to 1,024 workgroups of it, four to a compute unit.  Three layers of 16 - 289 rows (request of 16
 //     seeds): a pass 79 us against 94 with aggregation, dense layer and sum of the split contraction as kernels of their own;
 //     1,171 x 2 x 130 x 130 in 12.3 us, the other kernel 14.7; 18.6 k x 2 x 602 x 256 in 459 us, the other kernel 165.
-//   * above it, columns per wavefront: as many as the layer has from 32,768 rows on, where putting a tile's rows together is
-//     what takes the time (18.6 k rows x 2 x 602 x 256: 64 columns 166 us, 32 columns 170, 16 columns 265); below, no more
-//     than keep the padding small (3.1 k rows x 2 x 75 x 130: 16 columns 15.8, 32 columns 17.6, 64 columns 21.0).
-constexpr int64_t kSmallMax = 1024, kWideFrom = 32768;
+//   * above it, the fewest columns per wavefront with which every tile has a compute unit to itself, all of the bound taken for the
+//     rows of the seeds' block, half of it for the next one's and a quarter for those behind: 1 k rows x 2 x 256 x 512, f = 10, with
+//     16 columns 20.7 us, 64 columns 26.5; 6 k x 2 x 602 x 192 with 64 columns 56 us, 16 columns, which put the rows together three
+//     times on more tiles than there are compute units, 78.
+//   * where there are more tiles than that, as many columns as the layer has, up to 64, because putting a tile's rows together is
+//     what takes the time: 18.6 k x 2 x 602 x 256, f = 10, with 64 columns 166 us, 32 columns 162, 16 columns 251.
+//   * none of them where the lists are long and every column group puts the same rows together again, or rows are no whole 128-byte
+//     lines, so that a piece of 256 bytes touches three.  The aggregation reads them once and in one piece, and the dense
+//     layer follows.  18.6 k x 2 x D x N, this kernel / the two: f = 64, 602 x 256 624 us / 534, 602 x 1,024 1,668 / 832, 256 x 256
+//     0.83 of the two, 256 x 1,024 1.05; f = 25, 602 x 256 297 / 286, 602 x 1,024 691 / 575, 256 x 256 0.78, 100 x 1,024 1.08; f = 15,
+//     602 x 256 0.87, 602 x 512 0.88, 300 x 768 0.78 (60 k rows 1.03).  2 k x 2 x 602 x 256: f = 10 0.88, f = 25 1.11.
+//     Where they are even the two are taken: with four lanes they are 5 % ahead (batches of two hops, f = 10 and 25, 68 columns, 144
+//     us a batch against 151; on one lane 176 either way).  For the same reason 257 to 384 columns, a second group of 256 for less
+//     than half of its columns, are not for these kernels: three layers of 256, 300, 300 and 47 columns, 2,048 seeds, on four lanes 263 us a batch,
+//     285 with them, on one lane 305 and 297; from 100 columns 190 and 218, 225 and 230.
+constexpr int64_t kSmallMax = 1024;
 
 static size_t split_bytes(const LayerPlan& p, int ops) {
   return (size_t)ops * ((p.D + 31) / 32) * ((p.N + 64 * p.C - 1) / (64 * p.C)) * 4 * p.C * 3 * 1024;
 }
 
-bool layers_plan(int32_t model, int32_t n_layers, const int32_t* dims, const int64_t* cap_rows, bool input_apart, void* scratch,
+// Columns per wavefront / 16 of k_sage_layer, or -1.  rows: about what a batch has.
+static int columns_for(const dci_ctx* ctx, const LayerPlan& p, int64_t rows, int64_t fan) {
+  const bool lines = p.D % 32 == 0;  // rows are whole 128-byte lines
+  auto groups = [&](int C) -> int64_t { return (p.N + 64 * C - 1) / (64 * C); };
+  for (int C = 1; C <= 4; C *= 2)
+    if (rows * groups(C) <= (int64_t)ctx->num_cus * kLayerRows) return fan * groups(C) <= (lines ? 100 : 80) ? C : -1;
+  if (p.N > 256 && p.N <= 384) return -1;
+  const int C = p.N <= 64 ? 1 : p.N <= 128 ? 2 : 4;
+  const int64_t g = groups(C);
+  return lines ? (fan * (g + 1) <= 128 ? C : -1) : (fan * (g < 3 ? 3 : g) <= 60 ? C : -1);
+}
+
+bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, const int32_t* dims, bool input_apart, void* scratch,
                  size_t scratch_bytes, LayerPlan* plans) {
-  const int ops = model == DCI_MODEL_GCN_AVG ? 1 : 2;
+  const int ops = model == DCI_MODEL_GCN_AVG ? 1 : 2, n_layers = blocks->n_hops;
   Arena ar(reinterpret_cast<char*>(scratch), scratch_bytes);
   for (int32_t l = 0; l < n_layers; ++l) {
     LayerPlan& p = plans[l];
+    const int h = n_layers - 1 - l;
     p.D = dims[l];
     p.N = dims[l + 1];
-    p.cap_rows = cap_rows[n_layers - 1 - l];
+    p.cap_rows = blocks->cap_rows[h];
     p.w_split = nullptr;
     if (p.D < 4 || p.cap_rows < 1) return false;
-    if (l == 0 && input_apart) {
-      p.C = -1;
-      continue;
-    }
     const int64_t small_wgs = (p.cap_rows + kSmallRows - 1) / kSmallRows * ((p.N + kSmallCols - 1) / kSmallCols);
-    p.C = 0;
-    if (p.N >= 4 && small_wgs <= kSmallMax) continue;
-    if (p.cap_rows >= kWideFrom) p.C = p.N > 128 ? 4 : p.N > 64 ? 2 : 1;
-    else p.C = (p.N + 63) / 64 % 2 ? 1 : (p.N + 63) / 64 % 4 ? 2 : 4;
-    p.w_split = ar.take<char>(split_bytes(p, ops));
+    if (l == 0 && input_apart) p.C = -1;
+    else if (p.N >= 4 && small_wgs <= kSmallMax) p.C = 0;
+    else p.C = columns_for(ctx, p, p.cap_rows >> (h < 2 ? h : 2), (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
+    if (p.C > 0) p.w_split = ar.take<char>(split_bytes(p, ops));
   }
   return ar.ok();
 }

@@ -1810,13 +1810,21 @@ static int32_t plan_forward(dci_ctx* ctx, const dci_blocks* blocks, const float*
                         bias[0], n_layers == 1 ? logits : plan->ws.y[0]);
   };
   plan->input = input(feat_cache);
-  // Input layers of 9 to 13 slabs stay with the weights-in-registers kernel, which moves fewer bytes (rows in one piece each); that
-  // counts when batches share the card.  Eight 4,096-seed batches of 2 x 100 x 256 on four lanes 1,819 us a pass, k_sage_layer 1,874;
-  // four on one lane 1,093 either way; 2 x 64 x 256 on one lane 939 and 921.  Where the cache's alignment rules that kernel out for rows read
-  // in place, the layer's two kernels are taken, whose results are the same to the bit: DCI_OPT_FUSED_INPUT changes no logits.
-  const bool input_apart = input_slabs(dims[0]) > 8 && input(nullptr) == InputKernel::Registers;
+  // Input layers of 65 to 104 columns and 256 outputs stay with the weights-in-registers kernel for lists of 11 to 16 sources: it moves
+  // fewer bytes (rows in one piece each), which counts when batches share the card, but its pipeline holds 16 sources and no more.
+  // Eight 4,096-seed batches of 2 x 100 x 256, 15 sources, on four lanes 1,819 us a pass, k_sage_layer 1,874; four on one lane
+  // 1,093 either way; 60 k rows x 2 x 100 x 256 with 5, 15 and 25 sources 101, 125 and 259 us, k_sage_layer 93, 144 and 199.  Input
+  // layers of 112 or 128 columns and 512 outputs or more stay with k_sage_input_tile for the same lists, since k_sage_layer puts their
+  // rows together more than once: 60 k x 2 x 128 x 512 180, 196 and 390 us, k_sage_layer 160, 211 and 268.
+  //   Where the cache's alignment rules such a kernel out for rows read in place, the layer's two kernels are taken, whose results are
+  // the same to the bit where the outputs are a multiple of 256: DCI_OPT_FUSED_INPUT changes no logits.
+  const int64_t fan = (blocks->cap_edges[n_layers - 1] + cap_in - 1) / cap_in;
+  const InputKernel whole = input(nullptr);
+  const bool input_here = fan > 10 && fan <= 16 && input_slabs(dims[0]) > 8 && dims[1] % kResCols == 0 &&
+                          whole == (dims[1] == kResCols ? InputKernel::Registers : InputKernel::Tiles);
   plan->planned = ctx->linear_kernel == 0 && ctx->input_layer == 0 &&
-                  layers_plan(model, n_layers, dims, blocks->cap_rows, input_apart, plan->ws.m, plan->ws.m_bytes, plan->layers);
+                  layers_plan(ctx, blocks, model, dims, input_here, plan->ws.m, plan->ws.m_bytes, plan->layers);
+  if (plan->planned && !input_here) plan->input = InputKernel::Apart;
   return DCI_OK;
 }
 

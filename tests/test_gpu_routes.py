@@ -101,28 +101,35 @@ def test_rows_read_in_place_from_an_unaligned_cache_give_the_same_logits(env, F,
         assert o.numpy().tobytes() == out[0].numpy().tobytes()
 
 
-def _one_layer(env, M, cap, fan, D, N, model, seed, deg=None):
-    """One layer through dci_gather_forward on gathered rows: (result, 64-bit result, sum of magnitudes, launches per kernel class)"""
+def _forward(env, cap, fanouts, rows, dims, model, seed, deg=None):
+    """dci_gather_forward on gathered rows: (result, 64-bit result, sum of magnitudes, launches per kernel class).  deg: list
+    lengths of the input layer's block."""
     dci, ctx = env["dci"], env["ctx"]
-    n_in = M + 7
-    blk, host = _blocks(env, cap, (min(fan, 64),), (M, n_in), 10**7, seed)
+    blk, host = _blocks(env, cap, fanouts, rows, 10**7, seed)
     if deg is not None:
-        src = np.random.default_rng(seed).integers(0, n_in, deg.sum()).astype(np.int32)
-        blk.blk_indptr[0][:M + 1] = torch.from_numpy(np.concatenate([[0], deg.cumsum()])).cuda()
-        blk.blk_src[0][:len(src)] = torch.from_numpy(src).cuda()
-        host = [(deg, src)]
-    feat = torch.randn(n_in, D, generator=torch.Generator().manual_seed(seed))
-    g = dci.Graph(torch.zeros(n_in + 1, dtype=torch.int64).cuda(), torch.zeros(1, dtype=torch.int64).cuda(), feat.cuda())
-    ws, wn, bs = _weights((D, N), seed + 1)
-    x = torch.zeros(blk.cap_nodes[-1], D, dtype=torch.float32, device="cuda")
-    y = torch.full((blk.cap_nodes[0], N), float("nan"), dtype=torch.float32, device="cuda")
+        h = len(fanouts) - 1
+        src = np.random.default_rng(seed).integers(0, rows[-1], deg.sum()).astype(np.int32)
+        blk.blk_indptr[h][:rows[h] + 1] = torch.from_numpy(np.concatenate([[0], deg.cumsum()])).cuda()
+        blk.blk_src[h][:len(src)] = torch.from_numpy(src).cuda()
+        host[h] = (deg, src)
+    n = rows[-1]
+    feat = torch.randn(n, dims[0], generator=torch.Generator().manual_seed(seed))
+    g = dci.Graph(torch.zeros(n + 1, dtype=torch.int64).cuda(), torch.zeros(1, dtype=torch.int64).cuda(), feat.cuda())
+    ws, wn, bs = _weights(dims, seed + 1)
+    x = torch.zeros(blk.cap_nodes[-1], dims[0], dtype=torch.float32, device="cuda")
+    y = torch.full((blk.cap_nodes[0], dims[-1]), float("nan"), dtype=torch.float32, device="cuda")
     ctx.timing_enable(dci.KERNEL_CLASSES)
     dci.dci_gather_forward(ctx, g, None, blk, x, model, None if model == 2 else ws, wn, bs, y)
-    n = {k: v[1] for k, v in ctx.timing_read().items()}
+    launches = {k: v[1] for k, v in ctx.timing_read().items()}
     ctx.timing_enable([])
-    assert bool(torch.isnan(y[M:]).all()), "rows beyond the batch were written"
+    assert bool(torch.isnan(y[rows[0]:]).all()), "rows beyond the batch were written"
     want, size = _model64(model, host, feat, ws, wn, bs)
-    return y[:M].cpu(), want, size, n
+    return y[:rows[0]].cpu().double(), want, size, launches
+
+
+def _close(got, want, size, fanouts, dims):
+    # a mean of f rows is off by f 2^-24 of their magnitudes, a contraction of 2 D products by less than D / 4, layer after layer
+    return bool(((got - want).abs() <= size * 2.0 ** -24 * (sum(fanouts) + sum(dims) / 4 + 8)).all())
 
 
 @pytest.mark.parametrize("model", [0, 1, 2])
@@ -131,6 +138,101 @@ def test_lists_as_long_as_the_places_for_their_sources(env, model, M, cap, D, N)
     """Rows with 0, 1, 31 to 33, 63 to 65 and 100 sources, next to each other, in tiles of many rows."""
     deg = np.random.default_rng(D).choice([0, 1, 8, 9, 31, 32, 33, 40, 63, 64, 65, 100], M)
     deg[:3] = (64, 65, 0)
-    got, want, size, n = _one_layer(env, M, cap, 64, D, N, model, D + N, deg)
+    got, want, size, n = _forward(env, cap, (64,), (M, M + 7), (D, N), model, D + N, deg)
     assert n["mean_in"] == 0 and n["linear_in"] == 1        # one kernel
-    assert bool(((got.double() - want).abs() <= size * 2.0 ** -24 * (100 + D / 4 + 8)).all())
+    assert _close(got, want, size, (100,), (D, N))
+
+
+@pytest.mark.parametrize("cap,fan,D,N,kernels", [
+    # by an estimate of the rows (a quarter of the bound, 4 cap) every tile has a compute unit to itself: with 16, 32, 64 columns to
+    # a wavefront, in one column group and in several
+    (2000, 7, 96, 192, 1), (2000, 7, 33, 256, 1), (1500, 5, 68, 300, 1), (2000, 5, 40, 300, 1), (2000, 5, 64, 512, 1),
+    (4000, 9, 31, 257, 1), (8000, 9, 36, 193, 1),
+    # more tiles than that
+    (10_000, 6, 48, 64, 1), (10_000, 6, 48, 65, 1), (10_000, 6, 48, 129, 1), (10_000, 2, 64, 257, 2), (10_000, 2, 64, 384, 2),
+    (10_000, 2, 64, 385, 1), (10_000, 5, 31, 1030, 1),
+    # lists as long as they may be, and longer
+    (2000, 33, 128, 192, 1), (2000, 34, 128, 192, 2), (2000, 26, 75, 192, 1), (2000, 27, 75, 192, 2),
+    (10_000, 20, 100, 256, 1), (10_000, 21, 100, 256, 2), (10_000, 15, 100, 1024, 1), (10_000, 16, 100, 1024, 2),
+    (10_000, 64, 128, 256, 1), (10_000, 42, 128, 512, 1), (10_000, 43, 128, 512, 2), (10_000, 25, 300, 256, 2)])
+def test_kernels_of_an_input_layer(env, cap, fan, D, N, kernels):
+    fanouts, dims = (1, 1, fan), (D, N, 8, 5)
+    got, want, size, n = _forward(env, cap, fanouts, (100, 170, 300, 1000), dims, 0, cap + D + N)
+    assert n["mean_in"] + n["linear_in"] == kernels
+    assert _close(got, want, size, fanouts, dims)
+
+
+@pytest.mark.parametrize("cap,kernels", [(8000, 1), (5000, 2)])
+def test_parts_fit_where_the_aggregated_rows_would_be_or_not(env, cap, kernels):
+    """98,304 bytes of parts of 2 x 4 x 256 weights, 16 bytes to a row."""
+    got, want, size, n = _forward(env, cap, (3,), (3000, 3007), (4, 256), 0, cap)
+    assert n["mean_in"] + n["linear_in"] == kernels
+    assert _close(got, want, size, (3,), (4, 256))
+
+
+@pytest.mark.parametrize("model", [0, 2])
+@pytest.mark.parametrize("N,cap,rows", [(64, 10_000, 20_011), (100, 10_000, 20_011), (600, 10_000, 20_011),   # 16, 32, 64 columns
+                                        (256, 2000, 8000), (500, 2000, 8000)])                             # 16, 32
+def test_more_tiles_than_workgroups_in_several_column_groups(env, model, N, cap, rows):
+    """Several tiles to a workgroup: the next tile's weights are asked for while the last one is multiplied, and they are another
+    column group's."""
+    fanouts, dims = (1, 1, 3), (36, N, 8, 5)
+    got, want, size, n = _forward(env, cap, fanouts, (100, 170, rows, rows + 7), dims, model, N)
+    assert n["mean_in"] == 0
+    assert _close(got, want, size, fanouts, dims)
+
+
+def test_more_tiles_than_flags(env):
+    """More than 64 tiles to a workgroup: tiles share the flag that has one made again, and are made again with it."""
+    dci, ctx = env["dci"], env["ctx"]
+    M, D, N = 1_300_003, 4, 64
+    blk = dci.Blocks(ctx, 10**7, M, (1,))
+    blk.counts.zero_()
+    blk.counts[0] = blk.counts[1] = M
+    blk.blk_indptr[0][:M + 1] = torch.arange(M + 1).cuda()
+    src = torch.randperm(M, generator=torch.Generator().manual_seed(3))
+    blk.blk_src[0][:M] = src.int().cuda()
+    x = torch.randn(M, D, generator=torch.Generator().manual_seed(4))
+    x[7, 1], x[M - 5, 2] = float("inf"), 1e33
+    x_dev = torch.zeros(blk.cap_nodes[1], D, dtype=torch.float32, device="cuda")
+    x_dev[:M] = x.cuda()
+    ws, wn, bs = _weights((D, N), 5)
+    y = torch.empty(blk.cap_nodes[0], N, dtype=torch.float32, device="cuda")
+    dci.dci_gnn_forward(ctx, blk, x_dev, 0, ws, wn, bs, y)
+    ctx.sync()
+    a, c, b = (t[0].double().cpu() for t in (ws, wn, bs))
+    xd = x.double()
+    want = xd @ a + xd[src] @ c + b
+    size = xd.abs() @ a.abs() + xd.abs()[src] @ c.abs() + b.abs()
+    got = y[:M].cpu().double()
+    fin = torch.isfinite(want)
+    assert int((~fin).sum()) == 2 * N and bool((got[~fin] == want[~fin]).all())
+    assert bool(((got - want).abs()[fin] <= (size * 2.0 ** -24 * 12)[fin]).all())
+
+
+def test_parts_are_laid_out_again_after_a_layer_that_takes_their_place(env):
+    """Three layers: one kernel, aggregation and dense layer apart (its aggregated rows go where the parts of the weights were), one
+    kernel.  Gathered rows and rows read in place give the same logits."""
+    dci, ctx = env["dci"], env["ctx"]
+    dims, fanouts, rows = (64, 100, 128, 65), (2, 40, 2), (500, 1400, 5000, 9000)
+    n = rows[-1]
+    feat = torch.randn(n, dims[0], generator=torch.Generator().manual_seed(1))
+    g = dci.Graph(torch.zeros(n + 1, dtype=torch.int64).cuda(), torch.zeros(1, dtype=torch.int64).cuda(), feat.cuda())
+    blk, host = _blocks(env, 12_000, fanouts, rows, 10**7, 6)
+    ws, wn, bs = _weights(dims, 7)
+    remap = torch.arange(n, dtype=torch.int32)
+    cache = dci.Cache.from_arrays(torch.full((n,), -1, dtype=torch.int32).cuda(), torch.zeros(1, dtype=torch.int64).cuda(),
+                                  torch.zeros(0, dtype=torch.int64).cuda(), remap.cuda(), feat.cuda())
+    x = torch.zeros(blk.cap_nodes[-1], dims[0], dtype=torch.float32, device="cuda")
+    y = [torch.full((blk.cap_nodes[0], dims[-1]), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+    ctx.timing_enable(dci.KERNEL_CLASSES)
+    dci.dci_gather_forward(ctx, g, cache, blk, x, 0, ws, wn, bs, y[0])
+    launches = {k: v[1] for k, v in ctx.timing_read().items()}
+    ctx.timing_enable([])
+    assert launches["mean_in"] == 0 and launches["mean"] == 1 and launches["linear"] == 2
+    dci.dci_gather_features(ctx, g, cache, blk.nodes, blk.cap_nodes[-1], x, n_dev=blk.n_input_dev())
+    dci.dci_gnn_forward(ctx, blk, x, 0, ws, wn, bs, y[1])
+    ctx.sync()
+    want, size = _model64(0, host, feat, ws, wn, bs)
+    assert bool(((y[0][:500].double().cpu() - want).abs() <= size * 2.0 ** -24 * (sum(dims) + sum(fanouts))).all())
+    assert y[0][:500].cpu().numpy().tobytes() == y[1][:500].cpu().numpy().tobytes()
