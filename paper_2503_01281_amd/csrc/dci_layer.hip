@@ -727,7 +727,10 @@ int32_t layer_launch(dci_ctx* ctx, const LayerPlan& plan, const LayerArgs& args)
   a.n_col_groups = (a.N + 64 * plan.C - 1) / (64 * plan.C);
   const int64_t row_tiles = (plan.cap_rows + kLayerRows - 1) / kLayerRows;
   int64_t n = (row_tiles + 7) / 8 * 8 * a.n_col_groups;
-  if (n > (int64_t)ctx->num_cus * kLayerPerCu) n = (int64_t)ctx->num_cus * kLayerPerCu;
+  // (a multiple of eight: a workgroup's tiles are then all of one XCD's, and once one is past the last row tile so are those behind it,
+  // which the weights fetched ahead rely on)
+  const int64_t most = (int64_t)ctx->num_cus * kLayerPerCu / 8 * 8;
+  if (n > most) n = most > 8 ? most : 8;
   const dim3 grid((unsigned)n);
 #define DCI_LAYER(C_) \
   hipLaunchKernelGGL((gcn ? k_sage_layer<C_, true> : k_sage_layer<C_, false>), grid, dim3(kLayerThreads), 0, ctx->stream, a)
