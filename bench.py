@@ -78,9 +78,8 @@ def main() -> int:
                     help="kernel of the layers in the single-stream regions: 0 by shape (default: a layer is one kernel), "
                          "1 register-staged tile kernel, 2 wide kernel, 3 the tile kernels by shape, "
                          "4 weights in registers where the shape allows")
-    ap.add_argument("--pipelined-linear-kernel", type=int, default=1, choices=[0, 1, 2, 3, 4],
-                    help="dense-layer kernel of the pipelined regions (the statically partitioned wide kernel loses "
-                         "when other streams share the compute units)")
+    ap.add_argument("--pipelined-linear-kernel", type=int, default=0, choices=[0, 1, 2, 3, 4],
+                    help="the same for the pipelined regions")
     ap.add_argument("--fused-input", type=int, default=1, choices=[0, 1],
                     help="1 (default): the input layer reads cached neighbour rows in place (dci_gather_forward: only "
                          "missed rows and the rows of F_{L-1} are copied); 0: dci_gather_features then dci_gnn_forward")
@@ -353,9 +352,12 @@ def main() -> int:
                 mb = sum(4 * w.dims[j] * (int(hop_edges[L - 1 - j]) + int(hop_nodes[L - 1 - j])) for j in range(1, L))
             fl = flops_layer[0] if l == 0 else float(flops_layer[1:].sum())
             if timing_all[cls_m][1] == 0 and timing_all[cls_l][1] > 0:
-                # the layer ran as one kernel: it answers to both bounds (input layers of 65 to 104 columns stay with the
-                # kernel that keeps fp32 weights in registers)
-                fp32 = args.linear_kernel or args.input_layer or (l == 0 and model != 2 and 64 < w.dims[0] <= 104 and w.dims[1] % 256 == 0)
+                # the layer ran as one kernel: it answers to both bounds (some input layers stay with the kernels of fp32
+                # instructions, as include/dci.h has it at DCI_OPT_LINEAR_KERNEL)
+                D, N, cap = w.dims[0], w.dims[1], blk.cap_nodes[h]
+                stays = l == 0 and model != 2 and cap >= 98304 and 11 <= -(-blk.cap_edges[h] // cap) <= 16 and (
+                    (64 < D <= 104 and D % 4 == 0 and N == 256) or (D in (112, 128) and N % 256 == 0 and N > 256))
+                fp32 = args.linear_kernel or args.input_layer or stays
                 peak = FP32_MFMA_PEAK_TFLOPS if fp32 else THREE_PART_PEAK_TFLOPS
                 name = "k_sage_input_res / k_sage_input_tile" if fp32 else "k_sage_layer / k_sage_layer_small"
                 rooflines[cls_l] = entry(f"{name} (aggregation and dense layer)", cls_l,
