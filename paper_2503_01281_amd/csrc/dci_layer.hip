@@ -62,6 +62,8 @@ __device__ __forceinline__ f32x4 shifted(f32x4 v, int shift) {
 // on a compute unit and the rounds of tiles are short; two rounds of loads on their way at any time (one at a time: 98 us); places for
 // as many sources as a fan-out can have, because those beyond them are read one after the other (12 k rows of 64 sources x 2 x 256 x
 // 256: 120 us, with 32 places 248; x 2 x 602 x 256: 380, 644).
+//   Two workgroups on a compute unit leave a lane 128 registers.  With 64 columns to a wavefront that is 34 too few (27 for GCN), and they
+// go to scratch memory, some of them in the loop over the chunks; 16 and 32 columns fit.
 constexpr int kLayerThreads = 512, kLayerRows = 32, kLayerChunk = 64, kLayerSlots = 64, kLayerPerCu = 2, kLayerFlags = 64;
 
 struct LayerLds {
@@ -625,12 +627,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_sage_layer_small(LayerArgs a)
 // Which kernel, by the bounds on the layer's rows and on the length of their lists (batches fill a fifth of the rows' bound to all
 // of it; f: sources of every row):
 //   * the one for few rows up to 1,024 workgroups of it, four to a compute unit.  Three layers of 16 - 289 rows (request of 16
-//     seeds): a pass 79 us against 94 with aggregation, dense layer and sum of the split contraction as kernels of their own;
-//     1,171 x 2 x 130 x 130 in 12.3 us, the other kernel 14.7; 18.6 k x 2 x 602 x 256 in 459 us, the other kernel 165.
-//   * above it, the fewest columns per wavefront with which every tile has a compute unit to itself, all of the bound taken for the
-//     rows of the seeds' block, half of it for the next one's and a quarter for those behind: 1 k rows x 2 x 256 x 512, f = 10, with
-//     16 columns 20.7 us, 64 columns 26.5; 6 k x 2 x 602 x 192 with 64 columns 56 us, 16 columns, which put the rows together three
-//     times on more tiles than there are compute units, 78.
+//     seeds): a pass 79 us against 94 with aggregation, dense layer and sum of the split contraction as kernels of their own.  On
+//     either side of the line, this kernel / the other: 1 k rows of 4,096 x 2 x 256 x 256 (1,024 workgroups) 14.7 us / 20.0, x 260 23.6 / 20.0;
+//     2 k of 8,192 x 2 x 602 x 128 (1,024), f = 10, 32.0 / 38.2, x 172 53.8 / 38.3.
+//   * above it, the fewest columns per wavefront that make no more than five tiles for four compute units, all of the bound taken for the
+//     rows of the seeds' block, three quarters of it for the next one's and a fifth for those behind: 1 k rows x 2 x 256 x 512, f =
+//     10, with 16 columns 20.7 us, 64 columns 26.5; 3.1 k (fewer than a fifth of 15,015, 291 tiles) x 2 x 75 x 130 with 16 columns 15.8,
+//     32 columns 17.6; 6 k x 2 x 602 x 192 with 64 columns 56 us, 16 columns, which put the rows together three times in 564 tiles, 78.
 //   * where there are more tiles than that, as many columns as the layer has, up to 64, because putting a tile's rows together is
 //     what takes the time: 18.6 k x 2 x 602 x 256, f = 10, with 64 columns 166 us, 32 columns 162, 16 columns 251.
 //   * none of them where the lists are long and every column group puts the same rows together again, or rows are no whole 128-byte
@@ -653,7 +656,7 @@ static int columns_for(const dci_ctx* ctx, const LayerPlan& p, int64_t rows, int
   const bool lines = p.D % 32 == 0;  // rows are whole 128-byte lines
   auto groups = [&](int C) -> int64_t { return (p.N + 64 * C - 1) / (64 * C); };
   for (int C = 1; C <= 4; C *= 2)
-    if (rows * groups(C) <= (int64_t)ctx->num_cus * kLayerRows) return fan * groups(C) <= (lines ? 100 : 80) ? C : -1;
+    if (rows * groups(C) <= (int64_t)ctx->num_cus * kLayerRows * 5 / 4) return fan * groups(C) <= (lines ? 100 : 80) ? C : -1;
   if (p.N > 256 && p.N <= 384) return -1;
   const int C = p.N <= 64 ? 1 : p.N <= 128 ? 2 : 4;
   const int64_t g = groups(C);
@@ -675,7 +678,7 @@ bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, co
     const int64_t small_wgs = (p.cap_rows + kSmallRows - 1) / kSmallRows * ((p.N + kSmallCols - 1) / kSmallCols);
     if (l == 0 && input_apart) p.C = -1;
     else if (p.N >= 4 && small_wgs <= kSmallMax) p.C = 0;
-    else p.C = columns_for(ctx, p, p.cap_rows >> (h < 2 ? h : 2), (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
+    else p.C = columns_for(ctx, p, h == 0 ? p.cap_rows : h == 1 ? p.cap_rows * 3 / 4 : p.cap_rows / 5, (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
     if (p.C > 0) p.w_split = ar.take<char>(split_bytes(p, ops));
   }
   return ar.ok();

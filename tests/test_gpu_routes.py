@@ -144,17 +144,17 @@ def test_lists_as_long_as_the_places_for_their_sources(env, model, M, cap, D, N)
 
 
 @pytest.mark.parametrize("cap,fan,D,N,kernels", [
-    # by an estimate of the rows (a quarter of the bound, 4 cap) every tile has a compute unit to itself: with 16, 32, 64 columns to
-    # a wavefront, in one column group and in several
+    # few tiles, by an estimate of the rows (a fifth of the bound, 4 cap): 16, 32 and 64 columns to a wavefront, one column group and
+    # several
     (2000, 7, 96, 192, 1), (2000, 7, 33, 256, 1), (1500, 5, 68, 300, 1), (2000, 5, 40, 300, 1), (2000, 5, 64, 512, 1),
     (4000, 9, 31, 257, 1), (8000, 9, 36, 193, 1),
     # more tiles than that
-    (10_000, 6, 48, 64, 1), (10_000, 6, 48, 65, 1), (10_000, 6, 48, 129, 1), (10_000, 2, 64, 257, 2), (10_000, 2, 64, 384, 2),
-    (10_000, 2, 64, 385, 1), (10_000, 5, 31, 1030, 1),
+    (14_000, 6, 48, 64, 1), (14_000, 6, 48, 65, 1), (14_000, 6, 48, 129, 1), (14_000, 2, 64, 257, 2), (14_000, 2, 64, 384, 2),
+    (14_000, 2, 64, 385, 1), (14_000, 5, 31, 1030, 1),
     # lists as long as they may be, and longer
     (2000, 33, 128, 192, 1), (2000, 34, 128, 192, 2), (2000, 26, 75, 192, 1), (2000, 27, 75, 192, 2),
-    (10_000, 20, 100, 256, 1), (10_000, 21, 100, 256, 2), (10_000, 15, 100, 1024, 1), (10_000, 16, 100, 1024, 2),
-    (10_000, 64, 128, 256, 1), (10_000, 42, 128, 512, 1), (10_000, 43, 128, 512, 2), (10_000, 25, 300, 256, 2)])
+    (14_000, 20, 100, 256, 1), (14_000, 21, 100, 256, 2), (14_000, 15, 100, 1024, 1), (14_000, 16, 100, 1024, 2),
+    (14_000, 64, 128, 256, 1), (14_000, 42, 128, 512, 1), (14_000, 43, 128, 512, 2), (14_000, 25, 300, 256, 2)])
 def test_kernels_of_an_input_layer(env, cap, fan, D, N, kernels):
     fanouts, dims = (1, 1, fan), (D, N, 8, 5)
     got, want, size, n = _forward(env, cap, fanouts, (100, 170, 300, 1000), dims, 0, cap + D + N)
