@@ -559,10 +559,10 @@ def test_dma_tile_kernel_matches_oracle(env, model, dims, fanouts, n_seeds):
         ctx.set_option(dci.DCI_OPT_LINEAR_SPLIT, 0)
 
 
-@pytest.mark.parametrize("option", [0, 1, 3])
+@pytest.mark.parametrize("option", [0, 1, 2, 3])
 def test_forward_many_rows(env, option):
-    """A layer tall enough for the default choice to take the wide kernel with several row blocks per workgroup
-    (option 0), against the same through the tile kernel (option 1)."""
+    """Three layers with edges, the first of them thousands of rows: one kernel each (option 0), the wide kernel with several
+    row blocks per workgroup (option 2), the tile kernels (options 1 and 3)."""
     n_nodes = _forward_case(env, (192, 256, 128, 16), (8, 8, 8), 2048, 0, option)
     assert n_nodes[2] > 4096      # more than one 32-row block for each of the 128 workgroups of a column tile
 
