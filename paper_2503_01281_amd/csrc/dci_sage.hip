@@ -1,9 +1,9 @@
 // Forward pass over the blocks of one mini-batch: GraphSAGE with the mean aggregator, and the two
 // models of Table III (GraphSAGE with the sum aggregator, GCN with the averaging one).
 //
-// Per layer, by default, one kernel of dci_layer.hip (k_sage_layer, k_sage_layer_small).  The kernels of this file are what
-// DCI_OPT_LINEAR_KERNEL and DCI_OPT_INPUT_LAYER ask for, and run where those of dci_layer.hip cannot (inputs of fewer than
-// four columns):
+// Per layer, by default, one kernel of dci_layer.hip (k_sage_layer, k_sage_layer_small) where that is ahead (columns_for there,
+// input_here in plan_forward).  The kernels of this file run the other layers, inputs of fewer than four columns and what
+// DCI_OPT_LINEAR_KERNEL and DCI_OPT_INPUT_LAYER ask for:
 //   k_sage_mean        - m_i = mean (or sum; for GCN the mean over the row itself and its sources) of
 //                        x[src] over row i of the block; bandwidth bound: one lane group per
 //                        destination row, consecutive lanes on consecutive chunks of the row;
