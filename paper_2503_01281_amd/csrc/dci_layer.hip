@@ -626,14 +626,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_sage_layer_small(LayerArgs a)
 
 // Which kernel, by the bounds on the layer's rows and on the length of their lists (batches fill a fifth of the rows' bound to all
 // of it; f: sources of every row):
-//   * the one for few rows up to 1,024 workgroups of it, four to a compute unit.  Three layers of 16 - 289 rows (request of 16
-//     seeds): a pass 79 us against 94 with aggregation, dense layer and sum of the split contraction as kernels of their own.  On
-//     either side of the line, this kernel / the other: 1 k rows of 4,096 x 2 x 256 x 256 (1,024 workgroups) 14.7 us / 20.0, x 260 23.6 / 20.0;
-//     2 k of 8,192 x 2 x 602 x 128 (1,024), f = 10, 32.0 / 38.2, x 172 53.8 / 38.3.
-//   * above it, the fewest columns per wavefront that make no more than five tiles for four compute units, all of the bound taken for the
-//     rows of the seeds' block, three quarters of it for the next one's and a fifth for those behind: 1 k rows x 2 x 256 x 512, f =
-//     10, with 16 columns 20.7 us, 64 columns 26.5; 3.1 k (fewer than a fifth of 15,015, 291 tiles) x 2 x 75 x 130 with 16 columns 15.8,
-//     32 columns 17.6; 6 k x 2 x 602 x 192 with 64 columns 56 us, 16 columns, which put the rows together three times in 564 tiles, 78.
+//   * the one for few rows while its workgroups have a compute unit each, all of the bound taken for the rows of the seeds' block, half
+//     of it for the next one's (0.5 - 0.7 of it in batches of 256 to 1,024 seeds, fan-outs of 5 to 10) and a fifth for those behind.  Three layers of 16 - 289 rows (request of 16 seeds): a pass
+//     79 us against 94 with aggregation, dense layer and sum of the split contraction as kernels of their own.  On either side
+//     of the line, this kernel / the other: 4,096 rows x 2 x 256 x 64 (256 workgroups), f = 5, 12.3 us / 16.8, x 100 (512) 21.8 / 17.4, x 172
+//     (768) 31.0 / 19.6; 1,024 x 2 x 100 x 256 (256), f = 10, 0.78, 2,048 x 2 x 256 x 256 (512), f = 15, 1.5.
+//   * above it, the fewest columns per wavefront that make no more than four column groups and five tiles for four compute units: 1 k rows
+//     x 2 x 256 x 512, f = 10, with 16 columns (eight groups) 20.7 us, 32 columns 21.8, 64 columns 26.5; 3.1 k (fewer than a fifth of 15,015,
+//     291 tiles) x 2 x 75 x 130 with 16 columns 15.8, 32 columns 17.6; 2 k x 2 x 300 x 320, f = 25, with 16 columns (five groups) 43.7, 32
+//     columns 36.9; 6 k x 2 x 602 x 192, f = 10, with 64 columns 56, 16 columns, which put the rows together three times in 564 tiles, 78.
+//   * neither where lists are long: in few workgroups the lists' latency is not hidden.  With lists of more than 10,000 numbers the
+//     layer's two kernels are ahead (x 256 outputs, one kernel / the two; the two have a launch more, 1 - 2 us).  k_sage_layer_small,
+//     1,024 rows: D = 100, f = 64 0.86; D = 256, f = 25 0.93, f = 40 30.1 us / 26.3, f = 64 43 / 31; D = 300, f = 40 42 / 29; D = 602, f = 15 33.4
+//     / 31.8, f = 25 50 / 36, f = 64 106 / 55.  (Where it has two compute units for every workgroup it is only behind for more
+//     than 64 sources times pieces of 256 columns: 512 x 2 x D x 256, D = 256, f = 64 0.97; D = 300, f = 25 1.00, f = 64 1.26; D = 602, f = 25 1.16.)
+//     k_sage_layer, 2,048 rows: D = 64, f = 64 21.7 / 29.3; D = 256, f = 25 29.8 / 30.5, f = 64 49.6 / 42.6; D = 300, f = 25 35.6 / 36.1, f = 40 43.3
+//     / 40.6; D = 602, f = 25 60 / 53, f = 64 110 / 82.
 //   * where there are more tiles than that, as many columns as the layer has, up to 64, because putting a tile's rows together is
 //     what takes the time: 18.6 k x 2 x 602 x 256, f = 10, with 64 columns 166 us, 32 columns 162, 16 columns 251.
 //   * none of them where the lists are long and every column group puts the same rows together again, or rows are no whole 128-byte
@@ -645,19 +653,23 @@ __global__ __launch_bounds__(kSmallThreads) void k_sage_layer_small(LayerArgs a)
 //     us a batch against 151; on one lane 176 either way).  For the same reason 257 to 384 columns, a second group of 256 for less
 //     than half of its columns, are not for these kernels: three layers of 256, 300, 300 and 47 columns, 2,048 seeds, on four lanes 263 us a batch,
 //     285 with them, on one lane 305 and 297; from 100 columns 190 and 218, 225 and 230.
-constexpr int64_t kSmallMax = 1024;
+constexpr int64_t kSmallReads = 10000;
 
 static size_t split_bytes(const LayerPlan& p, int ops) {
   return (size_t)ops * ((p.D + 31) / 32) * ((p.N + 64 * p.C - 1) / (64 * p.C)) * 4 * p.C * 3 * 1024;
 }
 
-// Columns per wavefront / 16 of k_sage_layer, or -1.  rows: about what a batch has.
-static int columns_for(const dci_ctx* ctx, const LayerPlan& p, int64_t rows, int64_t fan) {
-  const bool lines = p.D % 32 == 0;  // rows are whole 128-byte lines
+// LayerPlan::C.  rows: about what a batch has; fan: the longest list.
+static int kernel_for(const dci_ctx* ctx, const LayerPlan& p, int64_t rows, int64_t fan) {
   auto groups = [&](int C) -> int64_t { return (p.N + 64 * C - 1) / (64 * C); };
+  const bool short_lists = fan * p.D <= kSmallReads;
+  const int64_t wgs = (rows + kSmallRows - 1) / kSmallRows * groups(1);
+  if (p.N >= 4 && wgs <= ctx->num_cus)
+    return short_lists || (2 * wgs <= ctx->num_cus && fan * ((p.D + kSmallChunk - 1) / kSmallChunk) <= 64) ? 0 : -1;
   for (int C = 1; C <= 4; C *= 2)
-    if (rows * groups(C) <= (int64_t)ctx->num_cus * kLayerRows * 5 / 4) return fan * groups(C) <= (lines ? 100 : 80) ? C : -1;
+    if (groups(C) <= 4 && rows * groups(C) <= (int64_t)ctx->num_cus * kLayerRows * 5 / 4) return short_lists ? C : -1;
   if (p.N > 256 && p.N <= 384) return -1;
+  const bool lines = p.D % 32 == 0;  // rows are whole 128-byte lines
   const int C = p.N <= 64 ? 1 : p.N <= 128 ? 2 : 4;
   const int64_t g = groups(C);
   return lines ? (fan * (g + 1) <= 128 ? C : -1) : (fan * (g < 3 ? 3 : g) <= 60 ? C : -1);
@@ -675,10 +687,8 @@ bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, co
     p.cap_rows = blocks->cap_rows[h];
     p.w_split = nullptr;
     if (p.D < 4 || p.cap_rows < 1) return false;
-    const int64_t small_wgs = (p.cap_rows + kSmallRows - 1) / kSmallRows * ((p.N + kSmallCols - 1) / kSmallCols);
-    if (l == 0 && input_apart) p.C = -1;
-    else if (p.N >= 4 && small_wgs <= kSmallMax) p.C = 0;
-    else p.C = columns_for(ctx, p, h == 0 ? p.cap_rows : h == 1 ? p.cap_rows * 3 / 4 : p.cap_rows / 5, (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
+    const int64_t rows = h == 0 ? p.cap_rows : h == 1 ? p.cap_rows / 2 : p.cap_rows / 5;
+    p.C = l == 0 && input_apart ? -1 : kernel_for(ctx, p, rows, (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
     if (p.C > 0) p.w_split = ar.take<char>(split_bytes(p, ops));
   }
   return ar.ok();

@@ -1,7 +1,7 @@
 // Forward pass over the blocks of one mini-batch: GraphSAGE with the mean aggregator, and the two
 // models of Table III (GraphSAGE with the sum aggregator, GCN with the averaging one).
 //
-// Per layer, by default, one kernel of dci_layer.hip (k_sage_layer, k_sage_layer_small) where that is ahead (columns_for there,
+// Per layer, by default, one kernel of dci_layer.hip (k_sage_layer, k_sage_layer_small) where that is ahead (kernel_for there,
 // input_here in plan_forward).  The kernels of this file run the other layers, inputs of fewer than four columns and what
 // DCI_OPT_LINEAR_KERNEL and DCI_OPT_INPUT_LAYER ask for:
 //   k_sage_mean        - m_i = mean (or sum; for GCN the mean over the row itself and its sources) of

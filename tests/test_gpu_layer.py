@@ -76,11 +76,12 @@ def _run(env, M, D, N, fan, model, cap, seed, poke=None, scale=1.0):
     (1, 64, 256, 9, 40000), (31, 63, 256, 16, 40000), (32, 65, 129, 17, 40000), (33, 602, 172, 15, 40000), (1000, 36, 128, 33, 40000),
     (70, 4, 100, 64, 40000), (500, 130, 3, 8, 70000), (65, 96, 64, 40, 70000), (129, 101, 1, 5, 70000),    # many, by their bound
     (4096, 128, 256, 15, 5000), (3000, 4, 256, 3, 5000), (20000, 40, 64, 10, 20000), (17001, 7, 300, 2, 17001),
-    (3000, 4, 256, 3, 8000), (17001, 7, 400, 2, 17001), (70, 4, 100, 20, 40000), (70, 32, 100, 64, 40000), (1000, 32, 128, 33, 40000)])
+    (3000, 4, 256, 3, 8000), (17001, 7, 400, 2, 17001), (70, 4, 100, 20, 40000), (70, 32, 100, 64, 40000), (1000, 32, 128, 33, 40000),
+    (33, 602, 47, 16, 64), (33, 128, 47, 64, 64)])
 def test_layer_at_the_edges_of_its_tiles(env, model, M, D, N, fan, cap):
     got, want, bound = _run(env, M, D, N, fan, model, cap, seed=M + D + N)
-    # two kernels: long lists of rows that are no whole lines, 257 to 384 outputs; parts of two operands' weights that do not fit
-    apart = [(1000, 36, 128, 33, 40000), (70, 4, 100, 64, 40000), (17001, 7, 300, 2, 17001)] + [(3000, 4, 256, 3, 5000)] * (model != 2)
+    # two kernels: long lists of wide rows or of rows that are no whole lines, 257 to 384 outputs; parts of two operands' weights that do not fit
+    apart = [(33, 602, 47, 64, 64), (1000, 36, 128, 33, 40000), (70, 4, 100, 64, 40000), (17001, 7, 300, 2, 17001)] + [(3000, 4, 256, 3, 5000)] * (model != 2)
     assert env["one kernel"] == ((M, D, N, fan, cap) not in apart)
     assert (np.abs(got - want) <= bound).all(), np.max(np.abs(got - want) / bound)
 

@@ -143,6 +143,27 @@ def test_lists_as_long_as_the_places_for_their_sources(env, model, M, cap, D, N)
     assert _close(got, want, size, (100,), (D, N))
 
 
+@pytest.mark.parametrize("model", [0, 1, 2])
+@pytest.mark.parametrize("D", [100, 260])
+def test_lists_of_few_rows_that_are_longer_than_most(env, model, D):
+    """Rows with more sources than the block has room for on average, in a layer of few rows."""
+    deg = np.array([100, 0, 65, 64, 63, 1, 0, 8, 9, 66, 0, 2, 7, 0, 0, 15, 16, 17, 0, 40])
+    got, want, size, n = _forward(env, 64, (10,), (20, 27), (D, 70), model, D, deg)
+    assert n["mean_in"] == 0 and n["linear_in"] == 1
+    assert _close(got, want, size, (100,), (D, 70))
+
+
+@pytest.mark.parametrize("cap,fan,D,N,kernels", [
+    # a workgroup of 16 rows by 64 columns for every compute unit, and one more; short and long lists there
+    (4096, 5, 256, 64, 1), (4112, 5, 256, 64, 1), (4112, 64, 100, 64, 1), (4112, 41, 256, 128, 2), (1024, 39, 256, 256, 1), (1024, 40, 256, 256, 2),
+    (1024, 38, 260, 200, 1), (1024, 39, 260, 200, 2), (1024, 16, 602, 41, 1), (1024, 17, 602, 41, 1),
+    (1024, 21, 602, 41, 1), (1024, 22, 602, 41, 2), (1040, 64, 256, 100, 2), (1024, 64, 256, 100, 1)])
+def test_kernels_of_a_layer_of_few_rows(env, cap, fan, D, N, kernels):
+    got, want, size, n = _forward(env, cap, (fan,), (cap, cap + 100), (D, N), 0, cap + D + N)
+    assert n["mean_in"] + n["linear_in"] == kernels
+    assert _close(got, want, size, (fan,), (D, N))
+
+
 @pytest.mark.parametrize("cap,fan,D,N,kernels", [
     # few tiles, by an estimate of the rows (a fifth of the bound, 4 cap): 16, 32 and 64 columns to a wavefront, one column group and
     # several
@@ -152,7 +173,7 @@ def test_lists_as_long_as_the_places_for_their_sources(env, model, M, cap, D, N)
     (14_000, 6, 48, 64, 1), (14_000, 6, 48, 65, 1), (14_000, 6, 48, 129, 1), (14_000, 2, 64, 257, 2), (14_000, 2, 64, 384, 2),
     (14_000, 2, 64, 385, 1), (14_000, 5, 31, 1030, 1),
     # lists as long as they may be, and longer
-    (2000, 33, 128, 192, 1), (2000, 34, 128, 192, 2), (2000, 26, 75, 192, 1), (2000, 27, 75, 192, 2),
+    (2000, 39, 256, 192, 1), (2000, 40, 256, 192, 2), (2000, 33, 300, 256, 1), (2000, 34, 300, 256, 2),
     (14_000, 20, 100, 256, 1), (14_000, 21, 100, 256, 2), (14_000, 15, 100, 1024, 1), (14_000, 16, 100, 1024, 2),
     (14_000, 64, 128, 256, 1), (14_000, 42, 128, 512, 1), (14_000, 43, 128, 512, 2), (14_000, 25, 300, 256, 2)])
 def test_kernels_of_an_input_layer(env, cap, fan, D, N, kernels):
