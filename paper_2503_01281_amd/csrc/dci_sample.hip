@@ -104,14 +104,14 @@ __device__ __forceinline__ unsigned long long uniform_below(unsigned k0, unsigne
 // is false can never be the node's first appearance; the reverse need not hold.
 // For an entry that already holds u, key and value move as one word, so a single 64-bit atomic
 // minimum does it; an empty slot is claimed by compare-and-swap.  Values only decrease and keys
-// never change, so a stale read costs a redundant atomic at most.
+// never change, so a stale read costs a redundant atomic at most, and any cache may serve it.
 template <bool DIRECT>
 __device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned entries, unsigned shift, unsigned last_node,
                                                      long long u, unsigned v, bool* candidate) {
   if (DIRECT) {
     const unsigned own = (unsigned long long)u < last_node ? (unsigned)u : last_node;
     unsigned* const word = reinterpret_cast<unsigned*>(table) + ((size_t)own << shift);
-    *candidate = __atomic_load_n(word, __ATOMIC_RELAXED) > v;
+    *candidate = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > v;
     if (*candidate) atomicMin(word, v);
     return own;
   }
@@ -120,7 +120,7 @@ __device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned 
   const HashEntry mine = ((HashEntry)u << 32) | v;
   *candidate = false;
   for (;;) {
-    HashEntry w = __atomic_load_n(&table[slot], __ATOMIC_RELAXED);
+    HashEntry w = __hip_atomic_load(&table[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (w == kEmptyEntry) {
       w = atomicCAS(&table[slot], kEmptyEntry, mine);
       if (w == kEmptyEntry) {
@@ -151,6 +151,44 @@ __device__ __forceinline__ unsigned long long group_bits(unsigned long long ball
   return (ballot >> (grp_in_wave * G)) & ((1ull << (G & 63)) - 1ull);
 }
 
+// Lane S of every group of G lanes, for all of the group.  Every lane of the wavefront must be active.
+template <int G, int S>
+__device__ __forceinline__ int group_bcast(int x) {
+  if constexpr (G == 64) return __builtin_amdgcn_readlane(x, S);
+  else if constexpr (G == 16) return __builtin_amdgcn_update_dpp(0, x, 0x150 + S, 0xF, 0xF, false);  // row_newbcast
+  else return __builtin_amdgcn_ds_swizzle(x, (S << 5) | (G == 8 ? 0x18 : 0));                         // (lane & 24 or 0) | S
+}
+
+// Whether an earlier lane of the group has the same 64-bit number.  The comparisons do not depend on one another and the broadcasts need no
+// address.  All lanes take part in every broadcast: nothing here may become a branch.
+template <int G, int S = 0>
+__device__ __forceinline__ void least_difference(unsigned lo, unsigned hi, int gl, unsigned& least) {
+  if constexpr (S + 1 < G) {
+    const unsigned differ = ((unsigned)group_bcast<G, S>((int)lo) ^ lo) | ((unsigned)group_bcast<G, S>((int)hi) ^ hi);
+    const unsigned seen = gl > S ? differ : ~0u;
+    least = seen < least ? seen : least;
+    if constexpr (S % 4 == 3) asm volatile("" : "+v"(least));  // four at a time: all at once would cost wavefronts their registers
+    least_difference<G, S + 1>(lo, hi, gl, least);
+  }
+}
+template <int G>
+__device__ __forceinline__ bool earlier_equal(unsigned long long x, int gl) {
+  unsigned least = ~0u;
+  least_difference<G>((unsigned)x, (unsigned)(x >> 32), gl, least);
+  return least == 0u;
+}
+
+// Inclusive sums over the wavefront on the vector ALU (no trips through LDS).  Every lane must be active.
+__device__ __forceinline__ int wave_scan_dpp(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);   // row_shr:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 to rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 to rows 2 and 3
+  return x;
+}
+
 // ---- kernels ----------------------------------------------------------------------------------
 
 struct HopArgs {
@@ -179,7 +217,6 @@ struct HopArgs {
   unsigned* edge_count;
   // previous hop, whose edges get their local ids at the start of this kernel (hop >= 1)
   int prev_fanout;
-  const int* prev_row_cnt;
   const int* prev_tmp_slot;
   const long long* prev_blk_indptr;
   int* prev_blk_src;
@@ -189,27 +226,25 @@ struct HopArgs {
   // List bounds of the frontier's rows, kept for the batch's later hops (F_h is a prefix of F_{h+1}, and every
   // hop samples all of its frontier): row i -> (start in the array that serves it, length | served-by-cache << 62),
   // or a negative second word for the one node cached in part, whose bounds are looked up again.
-  long long* row_memo;
+  longlong2* row_memo;
   int last_hop;                // no later hop will read what this one would note
+  long long cap_rows;          // bound on the rows: what the arrays have room for
 };
 
 // blk_src of a finished hop: every edge reads the (by now final) local id of its source.
-// One thread per padded position row * fanout + slot.
+// One thread per padded position row * fanout + slot (fewer than 2^31 of them).
 template <bool DIRECT>
-__device__ __forceinline__ void write_block_sources(long long n_rows, int fanout, const int* __restrict__ row_cnt,
-                                                    const int* __restrict__ tmp_slot,
+__device__ __forceinline__ void write_block_sources(long long n_rows, int fanout, const int* __restrict__ tmp_slot,
                                                     const long long* __restrict__ blk_indptr,
                                                     const HashEntry* table, unsigned shift,
                                                     int* __restrict__ blk_src,
                                                     int block, int n_blocks) {
-  const long long total = n_rows * fanout;
-  for (long long q = block * (long long)blockDim.x + threadIdx.x; q < total; q += (long long)n_blocks * blockDim.x) {
-    const long long i = q / fanout;
-    const int s = (int)(q - i * fanout);
-    if (s < (row_cnt[i] & kRowCntMask)) {
-      const int ts = tmp_slot[q];
-      if (ts != kSlotDone) blk_src[blk_indptr[i] + s] = (int)entry_val<DIRECT>(table, shift, slot_of(ts));
-    }
+  const unsigned total = (unsigned)(n_rows * fanout), step = (unsigned)n_blocks * blockDim.x;
+  for (unsigned q = (unsigned)block * blockDim.x + threadIdx.x; q < total; q += step) {
+    const unsigned i = q / (unsigned)fanout;
+    const int ts = tmp_slot[q];
+    const long long first = blk_indptr[i];
+    if (ts != -1 && ts != kSlotDone) blk_src[first + (q - i * fanout)] = (int)entry_val<DIRECT>(table, shift, slot_of(ts));
   }
 }
 
@@ -227,7 +262,7 @@ struct StatFold {
 
 template <bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, int hop, int fanout,
-                                                      const int* row_cnt, const int* tmp_slot,
+                                                      const int* tmp_slot,
                                                       const long long* blk_indptr, const HashEntry* table,
                                                       unsigned shift, int* blk_src, long long* counts_host, StatFold sf,
                                                       const unsigned* batch_flag, long long* counts_rw,
@@ -243,8 +278,7 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
     }
     return;
   }
-  write_block_sources<DIRECT>(counts[hop], fanout, row_cnt, tmp_slot, blk_indptr, table, shift, blk_src, (int)blockIdx.x,
-                              (int)gridDim.x);
+  write_block_sources<DIRECT>(counts[hop], fanout, tmp_slot, blk_indptr, table, shift, blk_src, (int)blockIdx.x, (int)gridDim.x);
   if (feat_count) {  // pre-sampling: one visit for every input node
     const long long n = counts[n_hops];
     for (long long i = blockIdx.x * (long long)kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
@@ -310,57 +344,83 @@ __global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, i
 // i in the table; an atomic minimum, so it also wins against a neighbour lane that registered
 // the same node a moment earlier).  Otherwise the kernel starts by finishing the previous hop
 // (write_block_sources), which only needs values that are already final.
+//   Bound by the length of its chain of dependent reads, and in large frontiers by the number of random reads: the arguments are fetched
+// together; the frontier's sizes, the batch's status, the group's first node and that node's note are asked for together, before it is
+// known whether the row exists (the arrays have room for the bound), and the next row's while this one is sampled.  Microseconds before /
+// after, third hops: 18 k rows 14.7 / 13.7, 53 k rows 32.4 / 29.5.
+struct HopRow {
+  long long v;
+  longlong2 memo;
+};
+
 template <int G, bool COUNT, bool INIT, bool DIRECT>
-__global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
-  const long long n_rows = INIT ? a.n_seeds : a.counts[a.hop];
-  const long long n_noted = INIT ? 0 : a.counts[a.hop - 1];  // rows below this were rows of the previous hop as well
-  if (INIT) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.counts[0] = a.n_seeds;
-  } else if (*a.batch_flag != kBatchOk) {
-    return;  // an earlier relabel tile gave up: the closing kernel voids the batch
-  } else if ((int)blockIdx.x < a.n_write_blocks) {
-    // the first few workgroups finish the previous hop while the others sample this one
-    write_block_sources<DIRECT>(a.counts[a.hop - 1], a.prev_fanout, a.prev_row_cnt, a.prev_tmp_slot, a.prev_blk_indptr,
-                                a.table, a.shift, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
-    return;
-  }
-  const int block = (int)blockIdx.x - (INIT ? 0 : a.n_write_blocks);
-  const int n_blocks = (int)gridDim.x - (INIT ? 0 : a.n_write_blocks);
+__global__ __launch_bounds__(kBlock, 8) void k_sample_hop(HopArgs a) {
   const int lane = lane_id();
   const int gl = lane & (G - 1);
   const int grp_in_wave = lane / G;
   constexpr int kGroups = kBlock / G;
   const int grp_in_block = (int)threadIdx.x / G;
   const int f = a.fanout;
+  const int block = (int)blockIdx.x - (INIT ? 0 : a.n_write_blocks);
+  const int n_blocks = (int)gridDim.x - (INIT ? 0 : a.n_write_blocks);
+  auto read_row = [&](long long i) {
+    HopRow r;
+    if (INIT) {
+      r.v = a.seeds[i];
+    } else {
+      r.v = a.nodes[i];
+      r.memo = a.row_memo[i];
+    }
+    return r;
+  };
+  long long n_rows, n_noted = 0;  // rows below n_noted were rows of the previous hop as well
+  HopRow next = {0, {0, 0}};
+  if (INIT) {
+    n_rows = a.n_seeds;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.counts[0] = n_rows;
+    const long long i = (long long)block * kGroups + grp_in_block;
+    if (i < n_rows) next = read_row(i);
+  } else {
+    asm volatile("" ::"s"(a.tmp_slot), "s"(a.row_cnt), "s"(a.table), "s"(a.indices), "s"(a.c_indices), "s"(a.indptr), "s"(a.k0), "s"(a.k1),
+                 "s"(a.batch), "s"(a.row_memo), "s"(a.nodes), "s"(a.counts), "s"(a.batch_flag), "s"(a.last_node), "s"(a.shift));
+    const unsigned flag = *a.batch_flag;
+    n_rows = a.counts[a.hop];
+    n_noted = a.counts[a.hop - 1];
+    const long long i = (long long)block * kGroups + grp_in_block;
+    if (block >= 0 && i < a.cap_rows) next = read_row(i);
+    asm volatile("" ::"s"(flag), "s"(n_rows), "s"(n_noted), "v"(next.v));  // all of them on their way before the first is waited for
+    if (flag != kBatchOk) return;  // an earlier relabel tile gave up: the closing kernel voids the batch
+    if (block < 0) {
+      // the first few workgroups finish the previous hop while the others sample this one
+      write_block_sources<DIRECT>(n_noted, a.prev_fanout, a.prev_tmp_slot, a.prev_blk_indptr,
+                                  a.table, a.shift, a.prev_blk_src, (int)blockIdx.x, a.n_write_blocks);
+      return;
+    }
+  }
 
-  for (long long base = (long long)block * kGroups; base < n_rows; base += (long long)n_blocks * kGroups) {
+  const long long step = (long long)n_blocks * kGroups;
+  for (long long base = (long long)block * kGroups; base < n_rows; base += step) {
     const long long i = base + grp_in_block;
     const bool row_ok = i < n_rows;
-    long long v = 0, start = 0, d = 0, cached_len = 0;
+    const long long v = next.v;
+    const longlong2 memo = next.memo;
+    if (i + step < n_rows) next = read_row(i + step);
+    long long start = 0, d = 0, cached_len = 0;
     const long long* list = a.indices;
     bool hit = false, noted = false;
     if (row_ok) {
-      if (INIT) {
-        v = a.seeds[i];
-        if (gl == 0) {
-          a.nodes[i] = v;
-          bool ignored;
-          (void)table_insert_min<DIRECT>(a.table, a.entries, a.shift, a.last_node, v, (unsigned)i, &ignored);
-        }
+      if (INIT && gl == 0) {
+        a.nodes[i] = v;
+        bool ignored;
+        (void)table_insert_min<DIRECT>(a.table, a.entries, a.shift, a.last_node, v, (unsigned)i, &ignored);
+      }
+      noted = !INIT && i < n_noted && memo.y >= 0;
+      if (noted) {
+        start = memo.x;
+        hit = (memo.y >> 62) != 0;
+        d = cached_len = memo.y & ((1ll << 62) - 1);
+        if (hit) list = a.c_indices;
       } else {
-        v = a.nodes[i];
-      }
-      if (!INIT && i < n_noted) {
-        const long long m = a.row_memo[2 * i + 1];
-        if (m >= 0) {
-          noted = true;
-          start = a.row_memo[2 * i];
-          hit = (m >> 62) != 0;
-          d = cached_len = m & ((1ll << 62) - 1);
-          if (hit) list = a.c_indices;
-        }
-      }
-      if (!noted) {
         const int r = a.adj_remap ? a.adj_remap[v] : -1;
         hit = r >= 0;
         if (hit) {
@@ -372,29 +432,33 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
           start = a.indptr[v];
           d = a.indptr[v + 1] - start;
         }
-        if (!a.last_hop && gl == 0) {
-          a.row_memo[2 * i] = start;
-          a.row_memo[2 * i + 1] = v == a.partial_node ? -1ll : (d | (hit ? (1ll << 62) : 0ll));
-        }
+        if (!a.last_hop && gl == 0)
+          a.row_memo[i] = longlong2{start, v == a.partial_node ? -1ll : (d | (hit ? (1ll << 62) : 0ll))};
       }
     }
     const int c = d < (long long)f ? (int)d : f;
     long long pos = gl;
     const bool floyd = row_ok && d > (long long)f;
     if (__ballot(floyd) != 0ull) {
-      // slot s draws t_s below j_s + 1, j_s = d - f + s; it keeps t_s unless an earlier slot
-      // already holds that value, in which case it takes j_s.
+      // Slot s draws t_s below j_s + 1, j_s = d - f + s; it keeps t_s unless an earlier slot already holds that value, in which
+      // case it takes j_s.  What earlier slots hold is every earlier t, and j_k of every earlier slot k that took its own: so
+      // slot s takes j_s if an earlier t is the same, or if t_s = j_k and slot k took j_k.
       const long long j = d - f + gl;
       long long t = 0;
       if (floyd && gl < f) t = (long long)uniform_below(a.k0, a.k1, v, a.batch, a.hop, gl, (unsigned long long)(j + 1));
-      long long S = t;
-      for (int s = 1; s < f; ++s) {
-        const long long ts = __shfl(t, s, G);
-        const bool match = floyd && gl < s && S == ts;
-        const bool any = group_bits<G>(__ballot(match), grp_in_wave) != 0ull;
-        if (gl == s && any) S = j;
+      const bool own = floyd && gl < f;
+      bool taken = earlier_equal<G>((unsigned long long)t, gl) && own;
+      const long long k = t - (d - f);
+      const bool depends = own && k >= 0 && k < gl;
+      if (__ballot(depends) != 0ull) {
+        for (;;) {
+          const unsigned long long bits = group_bits<G>(__ballot(taken), grp_in_wave);
+          const bool more = depends && !taken && ((bits >> (k & 63)) & 1ull) != 0ull;
+          if (__ballot(more) == 0ull) break;
+          taken = taken || more;
+        }
       }
-      if (floyd) pos = S;
+      if (floyd) pos = taken ? j : t;
     }
     const bool active = row_ok && gl < c;
     // position p of a node with a slot is served by the cache iff p < cached length (Section IV-B, third
@@ -408,13 +472,9 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
       // the neighbour ids it reads from graph->indices, and the lines its list bounds in graph->indptr lie in.
       const bool host_read = active && (from_host || !hit);
       if (__ballot(host_read) != 0ull) {
-        const unsigned long long line = (unsigned long long)reinterpret_cast<uintptr_t>(src) >> kHostLineLog2;
-        bool leader = host_read;
-        for (int s = 0; s + 1 < f; ++s) {
-          const unsigned long long ls = __shfl(line, s, G);
-          const bool hs = __shfl((int)host_read, s, G) != 0;
-          if (gl > s && hs && ls == line) leader = false;
-        }
+        // (lanes that read nothing there have numbers of their own)
+        const unsigned long long line = host_read ? (unsigned long long)reinterpret_cast<uintptr_t>(src) >> kHostLineLog2 : ~(unsigned long long)gl;
+        const bool leader = host_read & !earlier_equal<G>(line, gl);
         n_lines = __popcll(group_bits<G>(__ballot(leader), grp_in_wave));
       }
       if (row_ok && hit && n_host > 0) n_bound_lines = 1;  // the partly cached node: where its host list starts
@@ -424,7 +484,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
       }
     }
     if (active) {
-      const long long u = *src;
+      const long long u = *(__attribute__((address_space(1))) const long long*)src;
       const int p = (int)(i * f + gl);
       bool candidate;
       const unsigned slot =
@@ -436,7 +496,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
         atomicAdd(&a.edge_count[host_start + pos], 1u);
       }
     } else if (row_ok && gl < f) {
-      a.tmp_slot[(int)(i * f + gl)] = -1;  // no edge here: lets the relabel kernel read the slots without the row count
+      a.tmp_slot[(int)(i * f + gl)] = -1;  // no edge here: lets the later kernels read the slots without the row count
     }
     if (row_ok && gl == 0) {
       // the hit flag rides in bit 30 so that the relabel kernel can total the hit statistics
@@ -461,6 +521,15 @@ __global__ __launch_bounds__(kBlock) void k_sample_hop(HopArgs a) {
 // workgroups to hide the tile's chain of dependent phases behind.  Which wins depends on how many tiles a
 // frontier makes, so the count is picked per hop from the frontier's capacity (tile_iters_for).
 constexpr int kTileItersMax = 8;
+// 512 threads to a tile: the tickets of the chained scan are atomics on one word and serialise (12 - 19 ns each), so larger tiles wait
+// less; but a compute unit takes about three clocks for each of a tile's scattered accesses, so they are longer at them.  Rows of 16 slots
+// per tile / microseconds, direct table: 4 k rows (10 sources) 32 / 6.6, 64 / 6.5, 128 / 7.2, 256 / 8.7; 18 k (15) 32 / 16.2, 64 / 10.7, 128 / 8.5, 256 /
+// 9.1; 53 k (15) 64 / 25, 128 / 17.4, 256 / 13.9, and with 1,024 threads 512 / 15.8.
+constexpr int kRelabelBlock = 512;
+// Up to this many tiles are numbered by their workgroup instead of by tickets.  A tile waits for smaller numbers only, so all of them must
+// get to run; workgroups of other kernels end by themselves, and at least two of these fit on each of 256 compute units (launch bounds), so
+// 16 from each of 32 launches (more than a process has hardware queues) are on the card together.
+constexpr long long kUnticketedTiles = 16;
 constexpr unsigned long long kStInvalid = 3ull, kStAggregate = 1ull, kStInclusive = 2ull;
 // The look-back polls at most dci_ctx::relabel_spin_limit times (default 2^24: far beyond any real wait, ends a wedged launch).
 
@@ -490,34 +559,37 @@ struct RelabelArgs {
 };
 
 template <int G, int kTileIters, bool DIRECT>
-__global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
-  constexpr int kGroups = kBlock / G;
-  constexpr int TR = kGroups * kTileIters;  // rows per tile, at most kBlock
-  constexpr int kWaves = kBlock / kWave;
-  static_assert(TR <= kBlock, "one thread per tile row in the block scan");
-  __shared__ int s_c[TR], s_f[TR];
-  __shared__ int s_wc[kWaves], s_wf[kWaves];
+__global__ __launch_bounds__(kRelabelBlock, 4) void k_relabel_hop(RelabelArgs a) {
+  constexpr int kGroups = kRelabelBlock / G;
+  constexpr int TR = kGroups * kTileIters;  // rows per tile, at most kRelabelBlock
+  constexpr int kWaves = kRelabelBlock / kWave;
+  static_assert(TR <= kRelabelBlock, "one thread per tile row in the block scan");
+  static_assert(TR * G < 65536, "edge and first-appearance counts of a tile share a word");
+  __shared__ unsigned s_cf[TR];  // edges | first appearances << 16
+  __shared__ unsigned s_w[kWaves];
   __shared__ unsigned long long s_hr[kWaves], s_he[kWaves], s_hl[kWaves], s_hb[kWaves];
   __shared__ unsigned s_tile;
   __shared__ long long s_ec;
   __shared__ int s_ef;
   const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int gl = lane & (G - 1), grp_in_wave = lane / G, grp = tid / G;
-  if (*a.batch_flag != kBatchOk) return;  // an earlier hop failed (uniform over the launch: set before it began)
+  const unsigned flag = *a.batch_flag;
   const long long n_rows = a.counts[a.hop];
+  asm volatile("" ::"s"(flag), "s"(n_rows));  // (one trip for both)
+  if (flag != kBatchOk) return;  // an earlier hop failed (uniform over the launch: set before it began)
   // The grid is sized for the frontier's bound; only as many workgroups as the frontier has tiles take a
-  // ticket (the tickets are atomics on one word and serialise, about 25 ns each: left to the whole grid
-  // they were most of this kernel's time).  Which workgroups those are does not matter for progress: a
-  // tile waits only for smaller tickets, and those are held by workgroups that are already running.
-  {
-    const long long n_tiles = (n_rows + TR - 1) / TR;
-    long long takers = n_tiles - (long long)a.first_ticket;
-    if (takers < 1) takers = 1;  // an empty frontier (or a test hook beyond it) still needs one workgroup
-    if ((long long)blockIdx.x >= takers) return;
+  // ticket (left to the whole grid the tickets were most of this kernel's time).  Which workgroups those are does not matter for
+  // progress: a tile waits only for smaller tickets, and those are held by workgroups that are already running.
+  const long long n_tiles = (n_rows + TR - 1) / TR;
+  long long takers = n_tiles - (long long)a.first_ticket;
+  if (takers < 1) takers = 1;  // an empty frontier (or a test hook beyond it) still needs one workgroup
+  if ((long long)blockIdx.x >= takers) return;
+  unsigned tile = blockIdx.x + a.first_ticket;
+  if (takers > kUnticketedTiles) {
+    if (tid == 0) s_tile = atomicAdd(a.ticket, 1u) + 1u + a.first_ticket;
+    __syncthreads();
+    tile = s_tile;
   }
-  if (tid == 0) s_tile = atomicAdd(a.ticket, 1u) + 1u + a.first_ticket;
-  __syncthreads();
-  const unsigned tile = s_tile;
   const long long row0 = (long long)tile * TR;
   if (row0 >= n_rows) {
     // (test hook: when even the first numbered tile lies beyond the frontier nobody would notice the
@@ -553,7 +625,6 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
   for (int it = 0; it < kTileIters; ++it) val[it] = slot[it] >= 0 ? entry_val<DIRECT>(a.table, a.shift, (unsigned)slot[it]) : 0u;
   unsigned first_bits = 0;
   long long new_u[kTileIters];
-  unsigned long long hit_rows = 0, hit_edges = 0, host_lines = 0, bound_lines = 0;
 #pragma unroll
   for (int it = 0; it < kTileIters; ++it) {
     const int r = it * kGroups + grp;
@@ -565,72 +636,66 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
     // the ids of the first appearances are only needed once the tile knows its offsets; asked for here, they
     // arrive while the tile scans and looks back
     new_u[it] = !first ? 0 : DIRECT ? (long long)slot[it] : a.tmp_u[(row0 + r) * f + gl];
+    if (gl == 0) s_cf[r] = (unsigned)c | (unsigned)__popcll(bits) << 16;
+  }
+  if (a.stat_part) {
+    unsigned long long hit_rows = 0, hit_edges = 0, host_lines = 0, bound_lines = 0;
     if (gl == 0) {
-      s_c[r] = c;
-      s_f[r] = __popcll(bits);
-      if (raw[it] & kRowHitBit) {
-        hit_rows += 1;
-        hit_edges += (unsigned)(c - ((raw[it] >> kRowHostShift) & 0xFF));
+#pragma unroll
+      for (int it = 0; it < kTileIters; ++it) {
+        if (raw[it] & kRowHitBit) {
+          hit_rows += 1;
+          hit_edges += (unsigned)((raw[it] & kRowCntMask) - ((raw[it] >> kRowHostShift) & 0xFF));
+        }
+        host_lines += (unsigned)((raw[it] >> kRowLinesShift) & kRowLinesMask);
+        bound_lines += (unsigned)((raw[it] >> kRowBoundLinesShift) & kRowBoundLinesMask);
       }
-      host_lines += (unsigned)((raw[it] >> kRowLinesShift) & kRowLinesMask);
-      bound_lines += (unsigned)((raw[it] >> kRowBoundLinesShift) & kRowBoundLinesMask);
+    }
+    hit_rows = wave_sum_u64(hit_rows);
+    hit_edges = wave_sum_u64(hit_edges);
+    host_lines = wave_sum_u64(host_lines);
+    bound_lines = wave_sum_u64(bound_lines);
+    if (lane == 0) {
+      s_hr[wave] = hit_rows;
+      s_he[wave] = hit_edges;
+      s_hl[wave] = host_lines;
+      s_hb[wave] = bound_lines;
     }
   }
   __syncthreads();
 
   // scan of the tile's rows, one thread per row
-  const int c_t = tid < TR ? s_c[tid] : 0, f_t = tid < TR ? s_f[tid] : 0;
-  const int inc_c = wave_incl_scan(c_t), inc_f = wave_incl_scan(f_t);
-  if (lane == kWave - 1) {
-    s_wc[wave] = inc_c;
-    s_wf[wave] = inc_f;
-  }
-  hit_rows = wave_sum_u64(hit_rows);
-  hit_edges = wave_sum_u64(hit_edges);
-  host_lines = wave_sum_u64(host_lines);
-  bound_lines = wave_sum_u64(bound_lines);
-  if (lane == 0) {
-    s_hr[wave] = hit_rows;
-    s_he[wave] = hit_edges;
-    s_hl[wave] = host_lines;
-    s_hb[wave] = bound_lines;
-  }
+  const unsigned cf = tid < TR ? s_cf[tid] : 0u;
+  const unsigned incl = (unsigned)wave_scan_dpp((int)cf);
+  if (lane == kWave - 1) s_w[wave] = incl;
   __syncthreads();
-  int off_c = 0, off_f = 0, tot_c = 0, tot_f = 0;
+  unsigned off = 0, tot = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
-    if (w < wave) {
-      off_c += s_wc[w];
-      off_f += s_wf[w];
-    }
-    tot_c += s_wc[w];
-    tot_f += s_wf[w];
+    if (w < wave) off += s_w[w];
+    tot += s_w[w];
   }
-  if (tid < TR) {
-    s_c[tid] = off_c + inc_c;        // inclusive edge count within the tile
-    s_f[tid] = off_f + inc_f - f_t;  // exclusive first-appearance count within the tile
-  }
-
+  const unsigned tot_c = tot & 0xFFFFu, tot_f = tot >> 16;
+  const unsigned row_cf = off + incl;  // of row tid, inclusive
+  if (tid < TR) s_cf[tid] = row_cf - (cf & 0xFFFF0000u);  // edges inclusive, first appearances exclusive
   // publish this tile, then look back over the earlier ones (first wavefront)
+  if (tid == 0)
+    __hip_atomic_store(&a.status[tile], st_pack(tile == 0 ? kStInclusive : kStAggregate, tot_f, tot_c), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   if (wave == 0) {
     long long ec = 0;
     int ef = 0;
-    if (tile == 0) {
-      if (lane == 0)
-        __hip_atomic_store(&a.status[0], st_pack(kStInclusive, (unsigned)tot_f, (unsigned)tot_c), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      if (lane == 0)
-        __hip_atomic_store(&a.status[tile], st_pack(kStAggregate, (unsigned)tot_f, (unsigned)tot_c), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+    if (tile != 0) {
       // Look back over the earlier tiles, kLookWindows x 64 status words per round trip (lane l of window k
       // reads tile j - 64 k - l), nearest first.  A window is resolved once every word nearer than its
       // nearest inclusive one (or, if it has none, every word) is published; the sum stops at the first
-      // inclusive word.
+      // inclusive word.  A lane adds its words up as they are (edges and first appearances of all tiles stay below 2^31
+      // each); the lanes' sums meet at the end.
       constexpr int kLookWindows = 4;
       long long j = (long long)tile - 1;
       unsigned polls = 0;
       bool found = false, timed_out = false;
+      unsigned sum_c = 0, sum_f = 0;
       while (!found && !timed_out) {
         unsigned long long st[kLookWindows];
 #pragma unroll
@@ -659,14 +724,10 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
               if ((st[k] >> 62) == kStInvalid)
                 st[k] = __hip_atomic_load(&a.status[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            long long pc = 0;
-            int pf = 0;
             if (lane <= first_inc && (st[k] >> 62) != kStInvalid) {
-              pc = (long long)(st[k] & 0x7FFFFFFFull);
-              pf = (int)((st[k] >> 31) & 0x7FFFFFFFull);
+              sum_c += (unsigned)(st[k] & 0x7FFFFFFFull);
+              sum_f += (unsigned)((st[k] >> 31) & 0x7FFFFFFFull);
             }
-            ec += (long long)wave_sum_u64((unsigned long long)pc);
-            ef += (int)wave_sum_u64((unsigned long long)pf);
             if (!timed_out && first_inc < kWave) found = true;
           }
         }
@@ -678,10 +739,10 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
         // so that no later kernel reads what this hop leaves behind.
         __hip_atomic_store(a.batch_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      ec = __shfl(ec, 0, kWave);
-      ef = __shfl(ef, 0, kWave);
+      ec = (long long)__builtin_amdgcn_readlane(wave_scan_dpp((int)sum_c), kWave - 1);
+      ef = __builtin_amdgcn_readlane(wave_scan_dpp((int)sum_f), kWave - 1);
       if (lane == 0)
-        __hip_atomic_store(&a.status[tile], st_pack(kStInclusive, (unsigned)(ef + tot_f), (unsigned long long)(ec + tot_c)),
+        __hip_atomic_store(&a.status[tile], st_pack(kStInclusive, (unsigned)ef + tot_f, (unsigned long long)ec + tot_c),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (lane == 0) {
@@ -692,29 +753,26 @@ __global__ __launch_bounds__(kBlock) void k_relabel_hop(RelabelArgs a) {
   __syncthreads();
   const long long ec = s_ec;
   const int ef = s_ef;
-  if (tid < TR && row0 + tid < n_rows) a.blk_indptr[row0 + tid + 1] = ec + s_c[tid];
+  if (tid < TR && row0 + tid < n_rows) a.blk_indptr[row0 + tid + 1] = ec + (row_cf & 0xFFFFu);
 
   // first appearances take the next local ids, in (row, slot) order
-  long long new_id[kTileIters];
 #pragma unroll
   for (int it = 0; it < kTileIters; ++it) {
     const int r = it * kGroups + grp;
     const bool first = (first_bits >> it) & 1u;
     const unsigned long long bits = group_bits<G>(__ballot(first), grp_in_wave);
-    new_id[it] = first ? n_rows + ef + s_f[r] + __popcll(bits & ((1ull << gl) - 1ull)) : -1;
-  }
-#pragma unroll
-  for (int it = 0; it < kTileIters; ++it)
-    if (new_id[it] >= 0) {
-      a.nodes[new_id[it]] = new_u[it];
-      entry_set_val<DIRECT>(a.table, a.shift, (unsigned)slot[it], (unsigned)new_id[it]);
+    if (first) {
+      const unsigned row = s_cf[r];
+      const long long new_id = n_rows + ef + (int)(row >> 16) + __popcll(bits & ((1ull << gl) - 1ull));
+      a.nodes[new_id] = new_u[it];
+      entry_set_val<DIRECT>(a.table, a.shift, (unsigned)slot[it], (unsigned)new_id);
       // this edge's local id is known right here: write it (the row's edges sit at its sampled slots
-      // 0 .. c-1, and s_c holds the row's inclusive edge count within the tile), and spare the edge-id pass
+      // 0 .. c-1, and s_cf holds the row's inclusive edge count within the tile), and spare the edge-id pass
       // the table look-up
-      const int r = it * kGroups + grp;
-      a.blk_src[ec + s_c[r] - (raw[it] & kRowCntMask) + gl] = (int)new_id[it];
+      a.blk_src[ec + (row & 0xFFFFu) - (raw[it] & kRowCntMask) + gl] = (int)new_id;
       a.tmp_slot[(row0 + r) * f + gl] = kSlotDone;
     }
+  }
 
   if (tid == 0) {
     if (tile == 0) a.blk_indptr[0] = 0;
@@ -755,7 +813,7 @@ struct SampleWs {
   long long* tmp_u;
   int* tmp_slot[2];  // by hop parity: a hop's slots are still read while the next hop samples
   int* row_cnt[2];
-  long long* row_memo;     // [2 * rows]: list bounds of the frontier's rows, noted for the batch's later hops
+  longlong2* row_memo;     // list bounds of the frontier's rows, noted for the batch's later hops
   unsigned long long* stat_part[DCI_MAX_HOPS];  // per hop: two words per relabel tile
 };
 
@@ -793,18 +851,21 @@ static unsigned direct_shift(int64_t num_nodes, size_t hashed_bytes) {
 static int group_for(int fanout) { return fanout <= 8 ? 8 : fanout <= 16 ? 16 : fanout <= 32 ? 32 : 64; }
 
 static int64_t tiles_for(int64_t rows, int fanout, int iters) {
-  const int64_t tr = (int64_t)(kBlock / group_for(fanout)) * iters;
+  const int64_t tr = (int64_t)(kRelabelBlock / group_for(fanout)) * iters;
   const int64_t t = (rows + tr - 1) / tr;
   return t < 1 ? 1 : t;
 }
-constexpr int kTileItersMin = 2;  // the workspace is sized for the smallest tiles
+constexpr int kTileItersMin = 1;  // the workspace is sized for the smallest tiles
 
-// Rows per lane group of a relabel tile for a frontier of up to cap_rows rows (DCI_OPT_RELABEL_TILE_ITERS overrides).
-static int tile_iters_for(const dci_ctx* ctx, int64_t cap_rows, int fanout) {
+// Rows per lane group of a relabel tile (DCI_OPT_RELABEL_TILE_ITERS overrides): the fewest that make no more than 200 tiles of the rows
+// that a frontier has about (cap_rows bounds them: seeds fill the bound, batches half or so of the next one and a fifth to a third of
+// those behind).  See kRelabelBlock for both sides.
+static int tile_iters_for(const dci_ctx* ctx, int hop, int64_t cap_rows, int fanout) {
   if (ctx->relabel_tile_iters) return ctx->relabel_tile_iters;
-  (void)cap_rows;
-  (void)fanout;
-  return kTileItersMax;
+  const int64_t rows = cap_rows / (hop < 2 ? hop + 1 : 3);
+  int iters = kTileItersMin;
+  while (iters < kTileItersMax && tiles_for(rows, fanout, iters) > 200) iters *= 2;
+  return iters;
 }
 
 static void carve_sample_ws(Arena& ar, int64_t num_nodes, const int64_t* cap_nodes, const int64_t* cap_edges,
@@ -841,7 +902,7 @@ static void carve_sample_ws(Arena& ar, int64_t num_nodes, const int64_t* cap_nod
     ws->tmp_slot[k] = ar.take<int>((size_t)max_edges);
     ws->row_cnt[k] = ar.take<int>((size_t)max_rows);
   }
-  ws->row_memo = ar.take<long long>(2 * (size_t)max_rows);
+  ws->row_memo = ar.take<longlong2>((size_t)max_rows);
   for (int32_t h = 0; h < n_hops; ++h)
     ws->stat_part[h] = ar.take<unsigned long long>(kStatPartWords * (size_t)tiles_for(cap_nodes[h], fanouts[h], kTileItersMin));
 }
@@ -889,14 +950,16 @@ static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra
   DCI_LAUNCH_CHECK(ctx);
   {
     Timed t(ctx, DCI_K_RELABEL);
-    const int iters = tile_iters_for(ctx, cap_rows, ha.fanout);
+    const int iters = tile_iters_for(ctx, ha.hop, cap_rows, ha.fanout);
     const dim3 grid_r((unsigned)tiles_for(cap_rows, ha.fanout, iters));
-    if (iters == 2)
-      hipLaunchKernelGGL((k_relabel_hop<G, 2, DIRECT>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
+    if (iters == 1)
+      hipLaunchKernelGGL((k_relabel_hop<G, 1, DIRECT>), grid_r, dim3(kRelabelBlock), 0, ctx->stream, ra);
+    else if (iters == 2)
+      hipLaunchKernelGGL((k_relabel_hop<G, 2, DIRECT>), grid_r, dim3(kRelabelBlock), 0, ctx->stream, ra);
     else if (iters == 4)
-      hipLaunchKernelGGL((k_relabel_hop<G, 4, DIRECT>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
+      hipLaunchKernelGGL((k_relabel_hop<G, 4, DIRECT>), grid_r, dim3(kRelabelBlock), 0, ctx->stream, ra);
     else
-      hipLaunchKernelGGL((k_relabel_hop<G, 8, DIRECT>), grid_r, dim3(kBlock), 0, ctx->stream, ra);
+      hipLaunchKernelGGL((k_relabel_hop<G, 8, DIRECT>), grid_r, dim3(kRelabelBlock), 0, ctx->stream, ra);
   }
   DCI_LAUNCH_CHECK(ctx);
   return DCI_OK;
@@ -945,7 +1008,6 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ha.adj_count = adj_count;
     ha.edge_count = edge_count;
     ha.prev_fanout = h > 0 ? fanouts[h - 1] : 1;
-    ha.prev_row_cnt = ws.row_cnt[(h + 1) & 1];
     ha.prev_tmp_slot = ws.tmp_slot[(h + 1) & 1];
     ha.prev_blk_indptr = h > 0 ? reinterpret_cast<const long long*>(out->blk_indptr[h - 1]) : nullptr;
     ha.prev_blk_src = h > 0 ? out->blk_src[h - 1] : nullptr;
@@ -954,6 +1016,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ha.count_lines = stats ? 1 : 0;
     ha.row_memo = ws.row_memo;
     ha.last_hop = h == n_hops - 1 ? 1 : 0;
+    ha.cap_rows = out->cap_rows[h];
     RelabelArgs ra;
     ra.counts = counts;
     ra.hop = h;
@@ -991,12 +1054,12 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     sf.n_hops = n_hops;
     for (int32_t k = 0; k < DCI_MAX_HOPS; ++k) {
       sf.part[k] = k < n_hops ? ws.stat_part[k] : nullptr;
-      sf.tile_rows[k] = k < n_hops ? (kBlock / group_for(fanouts[k])) * tile_iters_for(ctx, out->cap_rows[k], fanouts[k]) : 1;
+      sf.tile_rows[k] = k < n_hops ? (kRelabelBlock / group_for(fanouts[k])) * tile_iters_for(ctx, k, out->cap_rows[k], fanouts[k]) : 1;
     }
     Timed t(ctx, feat_count ? DCI_K_COUNT_NODES : DCI_K_WRITE_SRC);
     hipLaunchKernelGGL(ws.direct ? k_write_src<true> : k_write_src<false>, dim3(grid_for_rows(ctx, positions, kBlock)),
                        dim3(kBlock), 0, ctx->stream,
-                       (const long long*)counts, h, fanouts[h], (const int*)ws.row_cnt[h & 1],
+                       (const long long*)counts, h, fanouts[h],
                        (const int*)ws.tmp_slot[h & 1], reinterpret_cast<const long long*>(out->blk_indptr[h]),
                        (const HashEntry*)ws.table, ws.table_shift, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
                        (const unsigned*)ws.batch_flag, counts, ctx->host_flag, (const long long*)nodes, n_hops, feat_count);

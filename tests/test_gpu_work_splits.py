@@ -93,3 +93,29 @@ def test_draw_chain_at_the_edges_of_its_steps(env, fanout):
     blk = dci.Blocks(ctx, N, len(seeds), (fanout,))
     dci.dci_sample_khop(ctx, g, None, gu.dev(seeds), 3, (fanout,), 11, blk)
     gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), oracle.sample_khop(indptr, indices, seeds, 3, (fanout,), 11))
+
+
+# Tiles of the frontier scan: one row, a whole tile and one more, the last count of tiles that are numbered by their workgroup and the first
+# with tickets (16 / 17), and the line where a lane group takes two rows (200 / 201 tiles), for each width of a lane group.
+@pytest.mark.parametrize("fanout,rows_per_tile", [(2, 64), (9, 32), (17, 16), (33, 8)])
+@pytest.mark.parametrize("tiles", [0, 1, 16, 200])
+@pytest.mark.parametrize("hashed", [False, True])
+def test_tiles_of_the_frontier_scan(env, fanout, rows_per_tile, tiles, hashed):
+    dci, gu, ctx = env["dci"], env["gu"], env["ctx"]
+    N = 2_000_000 if hashed else 16_000
+    rng = np.random.default_rng(fanout + tiles)
+    degree = np.zeros(N, dtype=np.int64)
+    degree[:16_000] = rng.integers(0, 2 * fanout, 16_000)
+    indptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    indices = rng.integers(0, 16_000, indptr[-1]).astype(np.int64)
+    g = gu.make_graph(indptr, indices, None, on_device=True)
+    for extra in (0, 1):
+        n = max(1, tiles * rows_per_tile) + extra
+        seeds = rng.permutation(16_000)[:n].astype(np.int64)
+        blk = dci.Blocks(ctx, N, n, (fanout, 2))
+        stats = gu.new_stats()
+        dci.dci_sample_khop(ctx, g, None, gu.dev(seeds), extra, (fanout, 2), 5, blk, stats)
+        got = gu.blocks_to_host(ctx, blk)
+        gu.assert_blocks_equal(got, oracle.sample_khop(indptr, indices, seeds, extra, (fanout, 2), 5))
+        s = gu.stats_dict(ctx, stats)
+        assert s["edges_sampled"] == sum(got["n_edges"]) == s["adj_edge_misses"] and s["adj_node_misses"] == sum(got["n_nodes"][:2])
