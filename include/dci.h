@@ -456,7 +456,8 @@ int32_t dci_gather_forward(dci_ctx* ctx, const dci_graph* graph, const dci_cache
  * rows b*batch_size .. of `logits` (device [n_seeds, dims[n_hops]]).  A lane is a context - its own
  * stream, and a workspace that covers dci_sample_workspace_bytes and dci_sage_workspace_bytes (with
  * DCI_OPT_FUSED_INPUT: dci_gather_forward_workspace_bytes) for these sizes - with its own batch buffers (blocks sized by dci_blocks_bounds for batch_size
- * seeds; x: device [blocks->cap_nodes, F]).  Batches on different lanes run concurrently, so the
+ * seeds; x: device [blocks->cap_nodes, F]).  Where the workspace holds the sum of the two instead of the larger (dci_sample_workspace_bytes
+ * counts a little more than is needed) and stats is NULL, a batch's last sampling kernel runs beside its gather.  Batches on different lanes run concurrently, so the
  * sampling of one batch overlaps the feature loading and the model computation of others; the
  * graph, the cache, the weights and the seeds are shared and only read; `stats` (nullable) is
  * shared and updated atomically.  The result of every batch is exactly what the three calls give

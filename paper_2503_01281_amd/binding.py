@@ -494,7 +494,8 @@ class Lane:
         L = len(fanouts)
         lib = self.ctx.lib
         cap_rows = (C.c_int64 * DCI_MAX_HOPS)(*([self.blocks.cap_nodes[h] for h in range(L)] + [0] * (DCI_MAX_HOPS - L)))
-        need = max(lib.dci_sample_workspace_bytes(graph.num_nodes, batch_size, _i32_array(fanouts), L),
+        # room for both at a time lets dci_infer_batches run parts of one stage in another's launches
+        need = max(lib.dci_sample_workspace_bytes(graph.num_nodes, batch_size, _i32_array(fanouts), L) +
                    lib.dci_gather_forward_workspace_bytes(self.blocks.cap_nodes[L], cap_rows, L, _i32_array(dims)), 1 << 20)
         self.ctx.ensure_workspace(need)
 

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdci.so")
 SOURCES = ["dci_ctx.hip", "dci_sample.hip", "dci_gather.hip", "dci_sage.hip", "dci_layer.hip", "dci_fill.hip", "dci_probe.hip", "dci_pipeline.hip"]
-HEADERS = [os.path.join(CSRC, "dci_internal.h"), os.path.join(CSRC, "dci_parts.h"), os.path.join(ROOT, "include", "dci.h")]
+HEADERS = [os.path.join(CSRC, "dci_internal.h"), os.path.join(CSRC, "dci_parts.h"), os.path.join(CSRC, "dci_close.h"), os.path.join(ROOT, "include", "dci.h")]
 
 # Packed-fp32 instructions are switched off for all device code on purpose.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

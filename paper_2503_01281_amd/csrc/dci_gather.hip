@@ -12,7 +12,7 @@
 // id / remap lookups of the next two rows are issued while the current row is copied.  Rows need
 // only 4-byte alignment: gfx950 global memory takes under-aligned 16-byte accesses, and the
 // F % 4 trailing floats are moved one per lane.
-#include "dci_internal.h"
+#include "dci_close.h"
 #include "dci_parts.h"
 
 namespace dci {
@@ -122,21 +122,43 @@ struct NoSplit {
 };
 __device__ __forceinline__ void split_weights(const NoSplit&, int) {}
 
-template <int V, class Split>
+// The batch to close beside the copy: none, or one with either kind of node table.  Neither reads what the other writes, but for the
+// batch's sizes where it is void.  As a kernel of its own the closing takes 3 - 8 us of launch and latency before the copy begins.  Us a
+// pass, apart / beside: three batches of 1,001 seeds 235 / 223, 16 seeds 75.6 / 72.5, 4,096 seeds 208.5 / 206.5, eight of them on 24 M nodes
+// 2,830 / 2,775.
+struct NoClose {
+  static constexpr int wgs = 0;
+  __device__ __forceinline__ void run(int) const {}
+  __device__ __forceinline__ unsigned flag() const { return kBatchOk; }
+};
+template <bool DIRECT>
+struct Close : CloseArgs {
+  __device__ __forceinline__ void run(int block) const { (void)close_batch<DIRECT>(*this, block, wgs); }
+  __device__ __forceinline__ unsigned flag() const { return *batch_flag; }
+};
+
+template <int V, class Split, class Closing>
 __global__ __launch_bounds__(kGatherBlock) void k_gather(const long long* __restrict__ ids, long long n_max,
                                                          const long long* __restrict__ n_dev,
                                                          const int* __restrict__ remap,
                                                          const float* __restrict__ cache,
                                                          const float* __restrict__ feat, int F, int lpr_log2,
                                                          float* __restrict__ out,
-                                                         unsigned long long* __restrict__ partials, int add, Split split) {
+                                                         unsigned long long* __restrict__ partials, int add, Split split,
+                                                         Closing closing) {
   if ((int)blockIdx.x < split.wgs) {
     split_weights(split, (int)blockIdx.x);
     return;
   }
-  const int block = (int)blockIdx.x - split.wgs, n_blocks = (int)gridDim.x - split.wgs;
+  if ((int)blockIdx.x < split.wgs + closing.wgs) {
+    closing.run((int)blockIdx.x - split.wgs);
+    return;
+  }
+  const int block = (int)blockIdx.x - split.wgs - closing.wgs, n_blocks = (int)gridDim.x - split.wgs - closing.wgs;
+  const unsigned flag = closing.flag();
   long long n = n_dev ? *n_dev : n_max;
   if (n > n_max) n = n_max;
+  if (flag != kBatchOk) return;  // a void batch, whose sizes are being zeroed
   GatherCounts cnt;
   copy_rows<V>(ids, n, remap, cache, feat, F, lpr_log2, out, nullptr, block, n_blocks, cnt);
   if (partials) store_partials(cnt, partials, block, add != 0);
@@ -151,7 +173,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather(const long long* __rest
 // rest with one lane per row - 64 dependent id -> remap chains in flight per wavefront instead of one per
 // lane group, because most of these rows are only looked up - and the rows among them that missed are then
 // listed in LDS and copied a lane group per row, two rows per group in flight.
-template <int V, class Split>
+template <int V, class Split, class Closing>
 __global__ __launch_bounds__(kGatherBlock) void k_gather_select(const long long* __restrict__ ids, long long n_max,
                                                                 const long long* __restrict__ n_dev,
                                                                 const int* __restrict__ remap,
@@ -160,24 +182,30 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_select(const long long*
                                                                 float* __restrict__ out,
                                                                 unsigned long long* __restrict__ partials,
                                                                 int* __restrict__ rowref,
-                                                                const long long* __restrict__ n_dense_dev, Split split) {
+                                                                const long long* __restrict__ n_dense_dev, Split split,
+                                                                Closing closing) {
   typedef typename GVec<V>::reg reg_t;
   typedef typename GVec<V>::mem mem_t;
   if ((int)blockIdx.x < split.wgs) {
     split_weights(split, (int)blockIdx.x);
     return;
   }
-  const int block = (int)blockIdx.x - split.wgs;
-  long long n = *n_dev;
+  if ((int)blockIdx.x < split.wgs + closing.wgs) {
+    closing.run((int)blockIdx.x - split.wgs);
+    return;
+  }
+  const int block = (int)blockIdx.x - split.wgs - closing.wgs;
+  const unsigned flag = closing.flag();
+  long long n = *n_dev, n_dense = *n_dense_dev;
   if (n > n_max) n = n_max;
-  long long n_dense = *n_dense_dev;
+  if (flag != kBatchOk) return;  // a void batch, whose sizes are being zeroed
   if (n_dense > n) n_dense = n;
   GatherCounts cnt;
   // Workgroup b copies dense rows iff floor((b+1) nd / G) != floor(b nd / G): nd of the G workgroups, evenly
   // spread.  nd follows the work: 8F bytes per dense row - but no less than 2 KB, since narrow rows are bound by
   // the latency of their id -> slot -> row chain, not by their bytes - against about 160 bytes per looked-up row
   // (id, a sector of the remap, the slot note).
-  const long long G = (long long)gridDim.x - split.wgs, b = (long long)block;
+  const long long G = (long long)gridDim.x - split.wgs - closing.wgs, b = (long long)block;
   long long nd;
   {
     const double dense_bytes = (double)n_dense * (8.0 * F > 2048.0 ? 8.0 * F : 2048.0), look_bytes = (double)(n - n_dense) * 160.0;
@@ -282,7 +310,8 @@ size_t gather_partials_bytes(const dci_ctx* ctx) {
 
 int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* ids, int64_t n_max,
                       const int64_t* n_dev, float* out, uint64_t* stats, void* partials_buf, int32_t* rowref,
-                      const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials, bool fold_partials, const SplitArgs* split) {
+                      const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials, bool fold_partials, const SplitArgs* split,
+                      const CloseArgs* close) {
   const int F = g->feat_dim;
   const float* fcache = cache ? cache->feat_cache : nullptr;
   const int* remap = cache ? cache->feat_remap : nullptr;
@@ -317,28 +346,35 @@ int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, 
       blocks = blocks_for(n_dense_max, rows_per_block) + blocks_for(n_max, kGatherBlock);
       if (blocks > cap) blocks = cap;
       if (blocks < 2) blocks = 2;
-#define DCI_SELECT(V_, S_, s_)                                                                                                 \
-  hipLaunchKernelGGL((k_gather_select<V_, S_>), grid, dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max, nd_, remap, \
-                     fcache, g->feat, F, lpr_log2, out, st, rowref, dn_, s_)
-#define DCI_GATHER(V_, S_, s_)                                                                                                 \
-  hipLaunchKernelGGL((k_gather<V_, S_>), grid, dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max, nd_, remap, fcache, \
-                     g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0, s_)
-#define DCI_BY_SPLIT(WHAT_, V_)                    \
-  do {                                             \
-    if (sp.wgs) WHAT_(V_, SplitArgs, sp);          \
-    else WHAT_(V_, NoSplit, NoSplit());            \
+#define DCI_SELECT(V_, S_, s_, C_, c_)                                                                                       \
+  hipLaunchKernelGGL((k_gather_select<V_, S_, C_>), grid, dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max, nd_, \
+                     remap, fcache, g->feat, F, lpr_log2, out, st, rowref, dn_, s_, c_)
+#define DCI_GATHER(V_, S_, s_, C_, c_)                                                                                       \
+  hipLaunchKernelGGL((k_gather<V_, S_, C_>), grid, dim3(kGatherBlock), 0, ctx->stream, ids_, (long long)n_max, nd_, remap, \
+                     fcache, g->feat, F, lpr_log2, out, st, add_partials ? 1 : 0, s_, c_)
+#define DCI_BY_CLOSE(WHAT_, V_, S_, s_)                                                  \
+  do {                                                                                   \
+    if (!close) WHAT_(V_, S_, s_, NoClose, NoClose());                                   \
+    else if (close->direct) WHAT_(V_, S_, s_, Close<true>, (Close<true>{*close}));       \
+    else WHAT_(V_, S_, s_, Close<false>, (Close<false>{*close}));                        \
   } while (0)
-      const dim3 grid((unsigned)(blocks + sp.wgs));
+#define DCI_BY_SPLIT(WHAT_, V_)                           \
+  do {                                                    \
+    if (sp.wgs) DCI_BY_CLOSE(WHAT_, V_, SplitArgs, sp);   \
+    else DCI_BY_CLOSE(WHAT_, V_, NoSplit, NoSplit());     \
+  } while (0)
+      const dim3 grid((unsigned)(blocks + sp.wgs + (close ? close->wgs : 0)));
       if (V == 4) DCI_BY_SPLIT(DCI_SELECT, 4);
       else if (V == 2) DCI_BY_SPLIT(DCI_SELECT, 2);
       else DCI_BY_SPLIT(DCI_SELECT, 1);
     } else {
-      const dim3 grid((unsigned)(blocks + sp.wgs));
+      const dim3 grid((unsigned)(blocks + sp.wgs + (close ? close->wgs : 0)));
       if (V == 4) DCI_BY_SPLIT(DCI_GATHER, 4);
       else if (V == 2) DCI_BY_SPLIT(DCI_GATHER, 2);
       else DCI_BY_SPLIT(DCI_GATHER, 1);
     }
 #undef DCI_BY_SPLIT
+#undef DCI_BY_CLOSE
 #undef DCI_GATHER
 #undef DCI_SELECT
   }

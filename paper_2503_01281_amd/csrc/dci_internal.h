@@ -152,17 +152,45 @@ __global__ void k_fill_u32x4(uint4* __restrict__ p, size_t n16, uint32_t pattern
 int32_t fill_bytes(dci_ctx* ctx, void* p, size_t bytes, uint32_t pattern);
 // After a wait on the context's stream: reports (and clears) a failure that a kernel flagged.
 int32_t check_device_flag(dci_ctx* ctx);
+// What the closing workgroups of a batch do (close_batch)
+struct CloseArgs {
+  long long* counts;
+  int hop, fanout;  // of the last hop
+  const int* tmp_slot;
+  const long long* blk_indptr;
+  const void* table;
+  unsigned shift;
+  int* blk_src;
+  long long* counts_host;
+  const unsigned* batch_flag;
+  unsigned* host_flag;
+  bool direct;
+  int wgs = 0;
+};
+constexpr int kCloseBesidePerCu = 2;  // closing workgroups of another launch, at most, per compute unit
+// dci_sample_khop with its temporaries at ws_base; close (nullable): what is left to do for the batch, instead of the closing kernel
+int32_t sample_khop_in(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* seeds, int64_t n_seeds,
+                       uint64_t batch_index, const int32_t* fanouts, int32_t n_hops, uint64_t rng_seed, dci_blocks* out, uint64_t* stats,
+                       char* ws_base, size_t ws_bytes, const char* ws_name, CloseArgs* close);
+// A whole batch of dci_infer_batches without statistics, closed beside the gather.  *done = false and nothing done where the workspace
+// does not hold the sampler's temporaries beside those of the other stages, where an argument is wrong (the calls in
+// sequence then say what is), or where it would not be quicker.
+int32_t infer_joint(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* seeds, int64_t n_seeds,
+                    uint64_t batch_index, const int32_t* fanouts, int32_t n_hops, uint64_t rng_seed, dci_blocks* blocks, float* x,
+                    const int32_t* dims, int32_t model, const float* const* w_self, const float* const* w_neigh,
+                    const float* const* bias, float* logits, bool in_place, bool* done);
 // partials_buf: gather_partials_bytes(ctx) bytes of device scratch, needed when stats != NULL
 // rowref / n_dense_dev: nullptr for the plain gather; otherwise the selective form (see k_gather_select),
 // n_dense_max bounding *n_dense_dev
 // add_partials / fold_partials (plain gather only): several launches of one n_max that are folded into stats once - the
 // first starts the partial sums, later ones add to them, the last folds them
 // split (nullable): weights to be laid out as parts by workgroups of their own in the same launch
+// close (nullable): a batch to be closed by workgroups of the same launch
 struct SplitArgs;
 int32_t gather_launch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* ids,
                       int64_t n_max, const int64_t* n_dev, float* out, uint64_t* stats, void* partials_buf,
                       int32_t* rowref, const int64_t* n_dense_dev, int64_t n_dense_max, bool add_partials = false,
-                      bool fold_partials = true, const SplitArgs* split = nullptr);
+                      bool fold_partials = true, const SplitArgs* split = nullptr, const CloseArgs* close = nullptr);
 size_t gather_partials_bytes(const dci_ctx* ctx);
 // dci_gather_features' checks
 int32_t check_gather(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* node_ids, int64_t n_max, const float* out);

@@ -38,8 +38,16 @@ extern "C" int32_t dci_infer_batches(const dci_lane* lanes, int32_t n_lanes, con
     const int64_t n = lo + batch_size < n_seeds ? batch_size : n_seeds - lo;
     const dci_lane& lane = lanes[k % n_lanes];
     dci_ctx* ctx = lane.ctx;
-    int32_t rc = dci_sample_khop(ctx, graph, cache, seeds + lo, n, (uint64_t)b, fanouts, n_hops, rng_seed, lane.blocks, stats);
-    if (rc == DCI_OK && ctx->fused_input) {
+    bool done = false;
+    int32_t rc = DCI_OK;
+    if (!stats)
+      rc = dci::infer_joint(ctx, graph, cache, seeds + lo, n, (uint64_t)b, fanouts, n_hops, rng_seed, lane.blocks, lane.x, dims, model,
+                            w_self, w_neigh, bias, logits + lo * width, ctx->fused_input != 0, &done);
+    if (!done && rc == DCI_OK)
+      rc = dci_sample_khop(ctx, graph, cache, seeds + lo, n, (uint64_t)b, fanouts, n_hops, rng_seed, lane.blocks, stats);
+    if (done) {
+      // sampling, gather and forward pass are enqueued
+    } else if (rc == DCI_OK && ctx->fused_input) {
       rc = dci_gather_forward(ctx, graph, cache, lane.blocks, lane.x, n_hops, dims, model, w_self, w_neigh, bias,
                               logits + lo * width, stats);
     } else if (rc == DCI_OK && !stats) {

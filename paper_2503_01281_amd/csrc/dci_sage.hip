@@ -2185,4 +2185,38 @@ int32_t gather_all_forward(dci_ctx* ctx, const dci_graph* graph, const dci_cache
                     blocks->cap_nodes > 0 && plan.parts_first());
 }
 
+int32_t infer_joint(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* seeds, int64_t n_seeds,
+                    uint64_t batch_index, const int32_t* fanouts, int32_t n_hops, uint64_t rng_seed, dci_blocks* blocks, float* x,
+                    const int32_t* dims, int32_t model, const float* const* w_self, const float* const* w_neigh,
+                    const float* const* bias, float* logits, bool in_place, bool* done) {
+  *done = false;
+  if (n_hops < 1 || n_hops > DCI_MAX_HOPS || !blocks->nodes || blocks->n_hops != n_hops || dims[0] != graph->feat_dim || !ctx->ws) return DCI_OK;
+  if (check_gather(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, x) != DCI_OK) return DCI_OK;
+  // A copy of all rows is bound by memory, and what runs beside it adds to it: large batches are closed before it (798 k edges: 306 us a
+  // pass, beside 309).  Rows read in place leave the card to look-ups (figures at NoClose).
+  const int64_t last = blocks->cap_rows[n_hops - 1] * (int64_t)fanouts[n_hops - 1];
+  if (!in_place && last > (int64_t)kCloseBesidePerCu * ctx->num_cus * 256) return DCI_OK;
+  // the sampler's temporaries lie behind those of the stages after it
+  size_t partials_off;
+  const size_t prefix = in_place ? gather_forward_prefix_bytes(ctx, blocks->cap_nodes, &partials_off) : 0;
+  int32_t* const rowref = in_place ? reinterpret_cast<int32_t*>(ctx->ws) : nullptr;
+  const float* const feat_cache = in_place && cache ? cache->feat_cache : nullptr;
+  const size_t off = align_up(prefix + dci_sage_workspace_bytes(blocks->cap_rows, n_hops, dims));
+  const size_t need = dci_sample_khop_scratch_bytes(graph->num_nodes, n_seeds, fanouts, n_hops);
+  if (need == 0 || off + need > ctx->ws_bytes) return DCI_OK;
+  ForwardPlan plan;
+  if (plan_forward(ctx, blocks, x, n_hops, dims, model, w_self, w_neigh, bias, logits, feat_cache, prefix, &plan) != DCI_OK) return DCI_OK;
+  *done = true;
+  CloseArgs close;
+  int32_t rc = sample_khop_in(ctx, graph, cache, seeds, n_seeds, batch_index, fanouts, n_hops, rng_seed, blocks, nullptr, ctx->ws + off,
+                              ctx->ws_bytes - off, "workspace", &close);
+  if (rc != DCI_OK) return rc;
+  SplitArgs split;
+  if (plan.parts_first()) split = layers_split_args(model, 0, n_hops, plan.layers, w_self, w_neigh);
+  rc = gather_launch(ctx, graph, cache, blocks->nodes, blocks->cap_nodes, blocks->counts + n_hops, x, nullptr, nullptr, rowref,
+                     blocks->counts + (n_hops - 1), blocks->cap_rows[n_hops - 1], false, true, &split, &close);
+  if (rc != DCI_OK) return rc;
+  return forward_in(ctx, plan, blocks, x, n_hops, dims, model, w_self, w_neigh, bias, logits, rowref, feat_cache, plan.parts_first());
+}
+
 }  // namespace dci

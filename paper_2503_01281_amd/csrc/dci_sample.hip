@@ -28,13 +28,9 @@
 // position seen so far, so one atomic minimum serves both "already in the frontier" and "who came first".
 // The table is hashed (a 64-bit word per entry, node id in the high half, value in the low half) or direct
 // (a 32-bit value per node of the graph): see table_is_direct.
-#include "dci_internal.h"
+#include "dci_close.h"
 
 namespace dci {
-
-// One 64-bit word per table entry: node id in the high half, value in the low half, all ones =
-// empty.  Node ids are below 2^31, so a real entry is always smaller than the empty word.
-typedef unsigned long long HashEntry;
 
 constexpr unsigned int kTentative = 0x80000000u;
 constexpr HashEntry kEmptyEntry = ~0ull;
@@ -51,18 +47,6 @@ constexpr int kRowLinesMask = 0x7F;
 constexpr int kRowBoundLinesShift = 23;
 constexpr int kRowBoundLinesMask = 0x3;
 constexpr int kHostLineLog2 = 7;  // the host link moves 128-byte lines: smaller reads cost a whole request each
-// Batch status word (in the region that the per-batch clear fills with ones): all ones = fine; anything
-// else = a relabel tile gave up waiting for its predecessors, the batch's outputs are void.
-constexpr unsigned kBatchOk = 0xFFFFFFFFu;
-
-// The value of a slot: the low half (little endian) of a hashed table's word, or the first of the 2^shift 32-bit words
-// that a direct table has per node (its slot is the node's id).  The kind is a template parameter throughout: the kernels of
-// small batches are bound by latency, code fetch included, and with the kind as a branch at run time the hashed ones were a
-// third longer (six batches of 27 seeds 486 us, as a template 479; 485 seeds 117.2 and 115.3).
-template <bool DIRECT>
-__device__ __forceinline__ unsigned entry_val(const HashEntry* table, unsigned shift, unsigned slot) {
-  return reinterpret_cast<const unsigned*>(table)[(size_t)slot << (DIRECT ? shift : 1u)];
-}
 template <bool DIRECT>
 __device__ __forceinline__ void entry_set_val(HashEntry* table, unsigned shift, unsigned slot, unsigned v) {
   reinterpret_cast<unsigned*>(table)[(size_t)slot << (DIRECT ? shift : 1u)] = v;
@@ -138,12 +122,6 @@ __device__ __forceinline__ unsigned table_insert_min(HashEntry* table, unsigned 
     slot = slot + 1 == entries ? 0u : slot + 1;
   }
 }
-
-// tmp_slot encoding: s >= 0 a table slot whose value this edge may still own; -1 no edge at this
-// position; kSlotDone an edge whose local id the relabel kernel has already written (it was its node's first
-// appearance); any other s <= -2 the slot -2 - s of an edge that cannot be its node's first appearance.
-constexpr int kSlotDone = (int)0x80000000;
-__device__ __forceinline__ unsigned slot_of(int s) { return (unsigned)(s >= 0 ? s : -2 - s); }
 
 template <int G>
 __device__ __forceinline__ unsigned long long group_bits(unsigned long long ballot, int grp_in_wave) {
@@ -231,23 +209,6 @@ struct HopArgs {
   long long cap_rows;          // bound on the rows: what the arrays have room for
 };
 
-// blk_src of a finished hop: every edge reads the (by now final) local id of its source.
-// One thread per padded position row * fanout + slot (fewer than 2^31 of them).
-template <bool DIRECT>
-__device__ __forceinline__ void write_block_sources(long long n_rows, int fanout, const int* __restrict__ tmp_slot,
-                                                    const long long* __restrict__ blk_indptr,
-                                                    const HashEntry* table, unsigned shift,
-                                                    int* __restrict__ blk_src,
-                                                    int block, int n_blocks) {
-  const unsigned total = (unsigned)(n_rows * fanout), step = (unsigned)n_blocks * blockDim.x;
-  for (unsigned q = (unsigned)block * blockDim.x + threadIdx.x; q < total; q += step) {
-    const unsigned i = q / (unsigned)fanout;
-    const int ts = tmp_slot[q];
-    const long long first = blk_indptr[i];
-    if (ts != -1 && ts != kSlotDone) blk_src[first + (q - i * fanout)] = (int)entry_val<DIRECT>(table, shift, slot_of(ts));
-  }
-}
-
 // Closing kernel of a batch: the last hop's edge ids, and the batch sizes for the host.
 // Hit statistics of a batch: every relabel tile leaves (rows with a cache slot, edges read from the cache) in
 // its hop's array of partial sums; the closing kernel adds them up and updates the caller's counters with
@@ -261,31 +222,15 @@ struct StatFold {
 };
 
 template <bool DIRECT>
-__global__ __launch_bounds__(kBlock) void k_write_src(const long long* counts, int hop, int fanout,
-                                                      const int* tmp_slot,
-                                                      const long long* blk_indptr, const HashEntry* table,
-                                                      unsigned shift, int* blk_src, long long* counts_host, StatFold sf,
-                                                      const unsigned* batch_flag, long long* counts_rw,
-                                                      unsigned* host_flag, const long long* nodes, int n_hops,
+__global__ __launch_bounds__(kBlock) void k_write_src(CloseArgs close, StatFold sf, const long long* nodes, int n_hops,
                                                       unsigned* feat_count) {
-  if (*batch_flag != kBatchOk) {
-    // A relabel tile timed out: the batch is void.  Its sizes are zeroed so that whatever consumes the
-    // batch next (gather, forward) finds nothing to do, and the context's host flag is raised for dci_sync.
-    if (blockIdx.x == 0 && threadIdx.x < 2 * DCI_MAX_HOPS + 1) {
-      counts_rw[threadIdx.x] = 0;
-      if (counts_host) counts_host[threadIdx.x] = 0;
-      if (threadIdx.x == 0) *host_flag = 1u;
-    }
-    return;
-  }
-  write_block_sources<DIRECT>(counts[hop], fanout, tmp_slot, blk_indptr, table, shift, blk_src, (int)blockIdx.x, (int)gridDim.x);
+  if (!close_batch<DIRECT>(close, (int)blockIdx.x, (int)gridDim.x)) return;
+  const long long* const counts = close.counts;
   if (feat_count) {  // pre-sampling: one visit for every input node
     const long long n = counts[n_hops];
     for (long long i = blockIdx.x * (long long)kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
       atomicAdd(&feat_count[nodes[i]], 1u);
   }
-  if (counts_host && blockIdx.x == 0 && threadIdx.x < 2 * DCI_MAX_HOPS + 1)
-    counts_host[threadIdx.x] = counts[threadIdx.x];  // pinned host memory, visible once the stream is idle
   if (sf.stats && blockIdx.x == gridDim.x - 1) {
     __shared__ unsigned long long s_r[kBlock / kWave], s_e[kBlock / kWave];
     __shared__ unsigned long long s_l[kBlock / kWave], s_b[kBlock / kWave];
@@ -966,11 +911,12 @@ static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra
 }
 
 // Enqueues the sampling of one batch: one clear, two kernels per hop, one closing kernel.
-// `adj_count` non-null turns on the pre-sampling counters.
+// `adj_count` non-null turns on the pre-sampling counters.  left (nullable; neither counters nor statistics then): the closing is left
+// to the caller.
 static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* seeds,
                             int64_t n_seeds, uint64_t batch_index, const int32_t* fanouts, int32_t n_hops,
                             uint64_t rng_seed, const dci_blocks* out, const SampleWs& ws, uint64_t* stats,
-                            uint32_t* feat_count, uint32_t* adj_count, uint32_t* edge_count) {
+                            uint32_t* feat_count, uint32_t* adj_count, uint32_t* edge_count, CloseArgs* left = nullptr) {
   int rc;
   {
     Timed t(ctx, DCI_K_TABLE_CLEAR);
@@ -1049,6 +995,27 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
   {
     const int32_t h = n_hops - 1;
     const int64_t positions = out->cap_rows[h] * fanouts[h];
+    CloseArgs close;
+    close.counts = counts;
+    close.hop = h;
+    close.fanout = fanouts[h];
+    close.tmp_slot = ws.tmp_slot[h & 1];
+    close.blk_indptr = reinterpret_cast<const long long*>(out->blk_indptr[h]);
+    close.table = ws.table;
+    close.shift = ws.table_shift;
+    close.blk_src = out->blk_src[h];
+    close.counts_host = reinterpret_cast<long long*>(out->counts_host);
+    close.batch_flag = ws.batch_flag;
+    close.host_flag = ctx->host_flag;
+    close.direct = ws.direct;
+    close.wgs = grid_for_rows(ctx, positions, kBlock);
+    if (left) {
+      // beside other work no more workgroups than two to a compute unit: as many as for a launch of its own (eight) keep the copy from
+      // starting (a pass over 798 k edges, all rows gathered, 314 us, with two 308)
+      if (close.wgs > kCloseBesidePerCu * ctx->num_cus) close.wgs = kCloseBesidePerCu * ctx->num_cus;
+      *left = close;
+      return DCI_OK;
+    }
     StatFold sf;
     sf.stats = reinterpret_cast<unsigned long long*>(stats);
     sf.n_hops = n_hops;
@@ -1057,12 +1024,8 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
       sf.tile_rows[k] = k < n_hops ? (kRelabelBlock / group_for(fanouts[k])) * tile_iters_for(ctx, k, out->cap_rows[k], fanouts[k]) : 1;
     }
     Timed t(ctx, feat_count ? DCI_K_COUNT_NODES : DCI_K_WRITE_SRC);
-    hipLaunchKernelGGL(ws.direct ? k_write_src<true> : k_write_src<false>, dim3(grid_for_rows(ctx, positions, kBlock)),
-                       dim3(kBlock), 0, ctx->stream,
-                       (const long long*)counts, h, fanouts[h],
-                       (const int*)ws.tmp_slot[h & 1], reinterpret_cast<const long long*>(out->blk_indptr[h]),
-                       (const HashEntry*)ws.table, ws.table_shift, out->blk_src[h], reinterpret_cast<long long*>(out->counts_host), sf,
-                       (const unsigned*)ws.batch_flag, counts, ctx->host_flag, (const long long*)nodes, n_hops, feat_count);
+    hipLaunchKernelGGL(ws.direct ? k_write_src<true> : k_write_src<false>, dim3(close.wgs), dim3(kBlock), 0, ctx->stream, close, sf,
+                       (const long long*)nodes, n_hops, feat_count);
   }
   DCI_LAUNCH_CHECK(ctx);
   return DCI_OK;
@@ -1107,12 +1070,16 @@ size_t dci_sample_workspace_bytes(int64_t num_nodes, int64_t n_seeds, const int3
   return ar.off;
 }
 
-// Shared body of dci_sample_khop and dci_sample_khop_static: the two differ only in where the
-// temporaries live (`ws_base`, `ws_bytes`; `ws_name` names that memory in the error message).
-static int32_t sample_khop_in(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* seeds,
-                              int64_t n_seeds, uint64_t batch_index, const int32_t* fanouts, int32_t n_hops,
-                              uint64_t rng_seed, dci_blocks* out, uint64_t* stats, char* ws_base, size_t ws_bytes,
-                              const char* ws_name) {
+}  // extern "C"
+
+namespace dci {
+
+// Shared body of dci_sample_khop, dci_sample_khop_static and infer_joint: they differ in where the
+// temporaries live (`ws_base`, `ws_bytes`; `ws_name` names that memory in the error message) and in who closes the batch.
+int32_t sample_khop_in(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* seeds,
+                       int64_t n_seeds, uint64_t batch_index, const int32_t* fanouts, int32_t n_hops,
+                       uint64_t rng_seed, dci_blocks* out, uint64_t* stats, char* ws_base, size_t ws_bytes,
+                       const char* ws_name, CloseArgs* close) {
   int32_t rc = check_common(ctx, graph, seeds, n_seeds, fanouts, n_hops, batch_index);
   if (rc != DCI_OK) return rc;
   if ((rc = check_cache(ctx, cache)) != DCI_OK) return rc;
@@ -1152,15 +1119,19 @@ static int32_t sample_khop_in(dci_ctx* ctx, const dci_graph* graph, const dci_ca
   for (int32_t h = 0; h < n_hops; ++h) view.cap_rows[h] = cap_nodes[h];
   view.cap_nodes = cap_nodes[n_hops];
   return sample_batch(ctx, graph, cache, seeds, n_seeds, batch_index, fanouts, n_hops, rng_seed, &view, ws, stats,
-                      nullptr, nullptr, nullptr);
+                      nullptr, nullptr, nullptr, close);
 }
+
+}  // namespace dci
+
+extern "C" {
 
 int32_t dci_sample_khop(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* seeds,
                         int64_t n_seeds, uint64_t batch_index, const int32_t* fanouts, int32_t n_hops,
                         uint64_t rng_seed, dci_blocks* out, uint64_t* stats) {
   if (!ctx) return DCI_ERR_INVALID_ARG;
   return sample_khop_in(ctx, graph, cache, seeds, n_seeds, batch_index, fanouts, n_hops, rng_seed, out, stats,
-                        ctx->ws, ctx->ws_bytes, "workspace");
+                        ctx->ws, ctx->ws_bytes, "workspace", nullptr);
 }
 
 int32_t dci_sample_khop_static(dci_ctx* ctx, const dci_graph* graph, const dci_cache* cache, const int64_t* seeds,
@@ -1169,7 +1140,7 @@ int32_t dci_sample_khop_static(dci_ctx* ctx, const dci_graph* graph, const dci_c
   if (!ctx) return DCI_ERR_INVALID_ARG;
   if (!ctx->static_scratch) return fail(ctx, DCI_ERR_HIP, "the static scratch array has no address on this device");
   return sample_khop_in(ctx, graph, cache, seeds, n_seeds, batch_index, fanouts, n_hops, rng_seed, out, stats,
-                        ctx->static_scratch, (size_t)DCI_STATIC_SCRATCH_BYTES, "the static scratch array");
+                        ctx->static_scratch, (size_t)DCI_STATIC_SCRATCH_BYTES, "the static scratch array", nullptr);
 }
 
 size_t dci_sample_khop_scratch_bytes(int64_t num_nodes, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops) {

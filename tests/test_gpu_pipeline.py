@@ -6,6 +6,8 @@ CPU oracle: blocks and gathered rows bit for bit, logits to 1e-4 of the batch's 
 rows of a batch survive only until its lane takes the next one, so the sixteen batches are run twice: once
 in a single call (all logits checked, and the blocks / rows of the last batch of every lane), once four at
 a time with every lane's blocks and rows checked in between."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -161,3 +163,58 @@ def test_lanes_must_not_share(setup):
         dci.dci_infer_batches([lanes[0], lanes[0]], g, cache, setup["seeds"], B, 0, 2, w.fanouts, w.rng_seed, 0, ws, wn, bs,
                               logits)
     assert e.value.code == -1 and "share" in str(e.value)
+
+
+@pytest.mark.parametrize("fused", [0, 1])
+def test_batches_closed_beside_the_gather(setup, fused):
+    """A batch is closed beside its gather where the workspace holds both stages' temporaries and no statistics are asked for: blocks, rows and
+    logits bit for bit those of the stages in sequence (with statistics; with a workspace for one stage at a time)."""
+    dci, gu, w, g, cache, want = (setup[k] for k in ("dci", "gu", "w", "g", "cache", "want"))
+    ws, wn, bs = setup["weights"]
+    got = []
+    for way in ("beside", "statistics", "small workspace"):
+        ln = dci.Lane(g, B, w.fanouts, w.dims)
+        if way == "small workspace":
+            caps = (C.c_int64 * dci.DCI_MAX_HOPS)(*(list(ln.blocks.cap_nodes[:w.n_hops]) + [0] * (dci.DCI_MAX_HOPS - w.n_hops)))
+            lib, L = ln.ctx.lib, w.n_hops
+            arr = lambda v: (C.c_int32 * len(v))(*v)
+            need = max(lib.dci_sample_workspace_bytes(w.num_nodes, B, arr(w.fanouts), L),
+                       lib.dci_gather_forward_workspace_bytes(ln.blocks.cap_nodes[L], caps, L, arr(w.dims)))
+            small = torch.empty(need + 256, dtype=torch.uint8, device="cuda")
+            assert lib.dci_set_workspace(ln.ctx.handle, (small.data_ptr() + 255) // 256 * 256, need) == 0
+        ln.ctx.set_option(dci.DCI_OPT_FUSED_INPUT, fused)
+        logits = torch.full((w.num_seeds, w.classes), float("nan"), dtype=torch.float32, device="cuda")
+        ln.x.fill_(-5.0)
+        torch.cuda.synchronize()
+        dci.dci_infer_batches([ln], g, cache, setup["seeds"], B, 3, 2, w.fanouts, w.rng_seed, 0, ws, wn, bs, logits,
+                              gu.new_stats() if way == "statistics" else None)
+        gu.assert_blocks_equal(gu.blocks_to_host(ln.ctx, ln.blocks), want[4][0])
+        got.append((logits[3 * B:5 * B].cpu().numpy().tobytes(), ln.x.cpu().numpy().tobytes()))
+    assert got[0] == got[1] == got[2] and not np.isnan(np.frombuffer(got[0][0], dtype=np.float32)).any()
+
+
+@pytest.mark.parametrize("fused", [0, 1])
+def test_void_batch_closed_beside_the_gather(setup, fused):
+    """A relabel tile that gives up (forced from the host; every kernel still ends at once) voids the batch: sizes are zero, nothing is
+    gathered, no logits are written, the next sync reports it once, and the lane works again."""
+    dci, gu, w, g, want = (setup[k] for k in ("dci", "gu", "w", "g", "want"))
+    ws, wn, bs = setup["weights"]
+    ln = dci.Lane(g, B, w.fanouts, w.dims)
+    ln.ctx.set_option(dci.DCI_OPT_FUSED_INPUT, fused)
+    logits = torch.full((w.num_seeds, w.classes), 9.0, dtype=torch.float32, device="cuda")
+    ln.x.fill_(7.0)
+    torch.cuda.synchronize()
+    run = lambda: dci.dci_infer_batches([ln], g, setup["cache"], setup["seeds"], B, 1, 1, w.fanouts, w.rng_seed, 0, ws, wn, bs, logits)
+    ln.ctx.set_option(dci.DCI_OPT_RELABEL_SPIN_LIMIT, 200)
+    ln.ctx.set_option(dci.DCI_OPT_TEST_RELABEL_FIRST_TICKET, 1)
+    run()
+    with pytest.raises(dci.DciError) as e:
+        ln.ctx.sync()
+    assert e.value.code == -3 and "relabel scan timed out" in str(e.value)
+    assert ln.blocks.counts.cpu().numpy().tolist() == [0] * 17
+    assert bool((ln.x == 7.0).all()) and bool((logits == 9.0).all())
+    ln.ctx.set_option(dci.DCI_OPT_TEST_RELABEL_FIRST_TICKET, 0)
+    ln.ctx.set_option(dci.DCI_OPT_RELABEL_SPIN_LIMIT, 1 << 24)
+    run()
+    gu.assert_blocks_equal(gu.blocks_to_host(ln.ctx, ln.blocks), want[1][0])
+    assert bool((logits[:B] == 9.0).all()) and not bool((logits[B:2 * B] == 9.0).any())
