@@ -222,6 +222,8 @@ struct LayerPlan {
   int D, N, C;  // C: -1 not one of these kernels, 0 k_sage_layer_small, else k_sage_layer with 16 C columns per wavefront
   int64_t cap_rows;
   void* w_split;
+  int cols, rs;  // k_sage_layer: multiplying wavefronts side by side, and how many of them share columns (each takes a part of the rows)
+  int n_waves() const { return (N + 16 * C * cols - 1) / (16 * C * cols) * cols; }
 };
 // Plans every layer of a forward pass; input_apart: the input layer is not for these kernels; scratch is where the weights' parts may
 // go.  false: none of the layers is for these kernels, because an input is too narrow or the scratch too small.

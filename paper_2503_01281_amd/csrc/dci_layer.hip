@@ -3,9 +3,9 @@
 //   y = x W_self + m W_neigh + b (+ ReLU), m_i = mean / sum of x[src] over row i of the block (GCN: y = m W + b, m_i the
 //   mean over the row itself and its sources).
 //
-// A workgroup of four wavefronts makes 16 T rows by 64 C columns of y.  It walks the input columns in chunks of 64: the
-// chunk of both operands is put together in LDS (16 lanes per row, 16 bytes per lane; a row's sources are added in edge
-// order) and multiplied with the chunk's rows of the weights, a wavefront making all 16 T rows of 16 C columns.
+// A workgroup makes 16 or 32 rows by 64 to 256 columns of y.  It walks the input columns in chunks: the chunk of both operands is put
+// together in LDS (16 bytes per lane; a row's sources are added in edge order) and multiplied with the chunk's rows of the weights, a wavefront
+// making its columns of all or half of the rows.
 //
 // The products run on the bf16 matrix instructions (v_mfma_f32_16x16x32_bf16, fp32 accumulators): an fp32 number is the sum
 // of three bf16 numbers, h + m + l, without a remainder (8 + 8 + 8 bits, each part the rest rounded to nearest: |m| <= 2^-8 |x|,
@@ -22,6 +22,7 @@
 //   Numbers that the parts cannot hold (infinities, NaN, magnitudes that round up to infinity in bf16) leave infinities or
 // NaN in the accumulators they touch, and nothing else but a true overflow does.  A workgroup that finds one in its tile
 // makes the tile again with the fp32 instructions.
+#include <type_traits>
 #include "dci_internal.h"
 #include "dci_parts.h"
 
@@ -49,31 +50,61 @@ __device__ __forceinline__ f32x4 shifted(f32x4 v, int shift) {
 }
 
 // ---- layers of many rows ---------------------------------------------------------------------------
-// A workgroup makes 32 rows by 64 C columns of y.  Its input columns are walked in chunks of 64; both operands of a chunk stand
-// in LDS as parts (two buffers).  Wavefronts 4-7 put chunks together (16 lanes per row, two rows each, 16 bytes per lane),
-// wavefronts 0-3 multiply the chunk before, each by its 16 C columns of the weights, whose parts come from memory in the order
-// in which the lanes hold them.  One barrier per chunk; the chunks of a workgroup's tiles follow each other without a gap.
-//   What bounds it: asking for the sources' rows in pieces of 256 bytes (a piece that does not start on a 128-byte line touches
-// three of them), 91 of the 94 us of 32.6 k rows x 2 x 300 x 128 with 369 k sources, 128 of the 166 us of 18.6 k x 2 x 602 x 256
-// with 274 k; the aggregation alone, whole rows at a time, takes 70 and 85 there, and with the fp32 dense layer that followed
-// it 129 and 200.  The products alone take 37 and 72 us.
-//   Why this shape: wavefronts of their own for the two kinds of work, because a wavefront's vector and matrix instructions
-// take turns (one role after the other in every wavefront: 121 us where this takes 94); 32 rows, so that two workgroups fit
-// on a compute unit and the rounds of tiles are short; two rounds of loads on their way at any time (one at a time: 98 us); places for
-// as many sources as a fan-out can have, because those beyond them are read one after the other (12 k rows of 64 sources x 2 x 256 x
-// 256: 120 us, with 32 places 248; x 2 x 602 x 256: 380, 644).
-//   Two workgroups on a compute unit leave a lane 128 registers.  With 64 columns to a wavefront that is 34 too few (27 for GCN), and they
-// go to scratch memory, some of them in the loop over the chunks; 16 and 32 columns fit.
-constexpr int kLayerThreads = 512, kLayerRows = 32, kLayerChunk = 64, kLayerSlots = 64, kLayerPerCu = 2, kLayerFlags = 64;
+// A workgroup makes 32 rows by 64 to 256 columns of y, tile after tile; its input columns are walked in chunks of 128 (64), both operands of
+// a chunk as parts in LDS.  One half of the wavefronts puts chunks together (32 or 16 lanes to a row, two rows each, 16 bytes per lane), the
+// other half multiplies them, each wavefront by its 16 C columns of the weights, whose parts come from memory in the order in which the lanes
+// hold them.  The chunks of a workgroup's tiles follow each other without a gap.
+//   What bounds it: the requests for the sources' rows and, beside them on the same path, those for the weights' parts, which wait behind the
+// rows and take 20 to 30 us of the widest layers' 130 to 200, wherever they are read from.  The matrix instructions are hidden.
+//   Why this shape (us, one round of chunks of 64 columns with a barrier each, two workgroups of eight wavefronts per compute unit / this):
+//   * one workgroup of sixteen wavefronts for a compute unit and all 256 columns in it: rows are put together and weights read once where two
+//     workgroups or column groups did it twice, and a row is asked for in pieces of 512 bytes, of which those that start off a 128-byte
+//     line touch five lines for four where pieces of 256 touch three for two.  18.6 k rows x 2 x 602 x 256, 10 sources each, 164 / 136; 60 k x 2 x 128
+//     x 512, 25 sources, 235 / 195; 2 k x 2 x 256 x 256, 15 sources, 33 / 24.
+//   * a ring of three buffers (four with one operand) without barriers, so that a row with a long list holds up nothing until the ring is empty;
+//   * rows shared out in halves of tiles, so that no workgroup has more than one half more than another;
+//   * up to 64 outputs two wavefronts share columns and take a row tile each, because four would leave half of the multiplying ones idle:
+//     20 k x 2 x 96 x 64, 15 sources, 32.2 / 29.3, with 128 columns (half of them padding) 30.4;
+//   * inputs of up to 64 columns with up to 128 outputs stay with chunks of 64 and two workgroups of eight wavefronts, since half of a chunk of
+//     128 would be empty: 20 k x 2 x 64 x 64, 5 sources, 20.5 / 19.1, in the other shape 23.1; 8.7 k x 2 x 64 x 100, 15 sources, 18.9 / 19.3, 21.1;
+//   * one round of eight loads in flight per lane: eight such wavefronts to a compute unit ask for enough, and with two the registers' moves cost
+//     1 to 3 %.  Places for as many sources as a fan-out can have, because those beyond them are read one after the other (chunks of 64, 12 k
+//     rows of 64 sources x 2 x 256 x 256: 120 us, with 32 places 248).
+//   Sixteen wavefronts on a compute unit leave a lane 128 registers: 16 and 32 columns to a wavefront fit, 64 do not.
+constexpr int kLayerRows = 32, kLayerFlags = 64;
 
-struct LayerLds {
-  // [buffer][operand][k step of 32][row tile][part]: 64 lanes' fragments of 8 bf16; lane (g, r) = (l / 16, l % 16) holds
-  // columns 8g .. 8g+7 of row r, in the place (r + 4g) % 16 of its group so that the writes of a row spread over the banks
-  __attribute__((aligned(16))) unsigned char a[2][2][2][2][3][1024];
-  const float* src[kLayerRows][kLayerSlots];  // where a row's first sources are (all of them, in batches of dci_sample_khop)
-  static_assert(kLayerSlots >= DCI_MAX_FANOUT, "a list of the longest fan-out");
-  int again[kLayerFlags];                     // tiles to make again with the fp32 instructions
+// W wavefronts of either kind: chunks of 16 W columns, 4 W lanes to a row, 16 W C / RS columns of y.  Eight of each fill a compute unit
+// with one workgroup, four of each with two.  RS: wavefronts that share columns, each with 2 / RS of the row tiles.
+template <int W>
+struct LayerShape {
+  static constexpr int kThreads = 128 * W, kChunk = 16 * W, kLanes = 4 * W, kPerCu = 8 / W;
 };
+
+template <int W, bool GCN>
+struct LayerLds {
+  static constexpr int kOps = GCN ? 1 : 2, kBuffers = W == 4 ? 2 : GCN ? 4 : 3;
+  // [buffer][operand][k step of 32][row tile][part]: 64 lanes' fragments of 8 bf16; lane (g, r) = (l / 16, l % 16) holds
+  // columns 8g .. 8g+7 of row r, in the place (r + 4g + k step) % 16 of its group so that the writes of a row spread over the banks
+  __attribute__((aligned(16))) unsigned char a[kBuffers][kOps][W / 2][2][3][1024];
+  // where a row's first sources are (all of them, in batches of dci_sample_khop, but for the last eight of the longest lists in the
+  // shape that has no room for them)
+  static constexpr int kSlots = W == 8 && !GCN ? 56 : 64;
+  static_assert(kSlots % 8 == 0, "sources are read in rounds of eight");
+  const float* src[kLayerRows][kSlots];
+  int again[kLayerFlags];            // tiles to make again with the fp32 instructions
+  int full[4], free[4];              // per buffer: wavefronts that have put their part of a chunk there / are done with it, over all chunks
+};
+
+// Chunks pass from the wavefronts that put them together to those that multiply them through a ring of buffers, without a barrier: either kind
+// waits for the other only where the ring is empty or full (the workgroup's wavefronts are all on the compute unit).
+__device__ __forceinline__ void ring_wait(const int* count, int target) {
+  while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target) __builtin_amdgcn_s_sleep(1);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+__device__ __forceinline__ void ring_signal(int* count, int lane) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  if (lane == 0) (void)__hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 template <int C>
 using vec_t = float __attribute__((ext_vector_type(C)));
@@ -95,19 +126,19 @@ __device__ __forceinline__ const float* source_row(const LayerArgs& a, long long
   return r >= 0 ? a.cache + (long long)r * a.D : a.x + (long long)s * a.D;
 }
 
-// y for this lane's part of a tile: rows 4g .. 4g+3 of both row tiles, columns col .. col + C-1
-template <int C>
-__device__ __forceinline__ void store_tile(const LayerArgs& a, long long row0, int rows, int col, int g, const f32x4 (&acc)[2][C]) {
+// y for this lane's part of a tile: rows 4g .. 4g+3 of NT row tiles from the t0-th, columns col .. col + C-1
+template <int C, int NT>
+__device__ __forceinline__ void store_tile(const LayerArgs& a, long long row0, int rows, int col, int t0, int g, const f32x4 (&acc)[NT][C]) {
   const int N = a.N;
   float bias[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) bias[c] = a.bias[col + c < N ? col + c : N - 1];
   const bool whole = col + C <= N;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = 16 * t + 4 * g + r;
+      const int i = 16 * (t0 + t) + 4 * g + r;
       if (i < rows) {
         vec_t<C> v;
 #pragma unroll
@@ -129,23 +160,23 @@ __device__ __forceinline__ void store_tile(const LayerArgs& a, long long row0, i
 }
 
 // A tile with the fp32 instructions, chunk by chunk, nothing overlapped.
-template <int C, bool GCN>
-__device__ __forceinline__ void layer_tile_exact(const LayerArgs& a, LayerLds& lds, long long row0, int rows, int cg) {
-  const int tid = (int)threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15, gl = tid & 15, i = tid >> 4;
+template <int W, int C, int RS, bool GCN>
+__device__ __forceinline__ void layer_tile_exact(const LayerArgs& a, LayerLds<W, GCN>& lds, long long row0, int rows, int cg) {
+  constexpr int NT = 2 / RS, kCols = W / RS, kChunk = LayerShape<W>::kChunk, kLanes = LayerShape<W>::kLanes;
+  const int tid = (int)threadIdx.x, lane = tid & 63, g = lane >> 4, r16 = lane & 15, gl = tid & (kLanes - 1), i = tid / kLanes;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = a.D, N = a.N;
-  const int p_g = (gl & 7) >> 1;
-  const int p_slot = (gl >> 3) * 6144 + (i >> 4) * 3072 + (p_g * 16 + ((i + 4 * p_g) & 15)) * 16 + (gl & 1) * 1024;
-  const int frag = (g * 16 + ((r16 + 4 * g) & 15)) * 16;
-  const int col = (cg * 64 + (wave & 3) * 16 + r16) * C;
+  const int p_ks = gl >> 3, p_g = (gl & 7) >> 1;
+  const int p_slot = p_ks * 6144 + (i >> 4) * 3072 + (p_g * 16 + ((i + 4 * p_g + p_ks) & 15)) * 16 + (gl & 1) * 1024;
+  const int col = ((cg * kCols + wave % kCols) * 16 + r16) * C, t0 = wave / kCols % RS;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[2][C];
+  f32x4 acc[NT][C];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[t][c] = zero;
 #pragma unroll 1
-  for (int k_lo = 0; k_lo < D; k_lo += kLayerChunk) {
+  for (int k_lo = 0; k_lo < D; k_lo += kChunk) {
     const int k_col = k_lo + 4 * gl, k_ld = k_col < D - 4 ? k_col : D - 4, shift = k_col - k_ld;
     f32x4 own = zero, sum = zero;
     if (i < rows) {
@@ -157,24 +188,24 @@ __device__ __forceinline__ void layer_tile_exact(const LayerArgs& a, LayerLds& l
       if (a.mode != DCI_MODEL_SAGE_SUM && cnt != 0.f) sum = f32x4{sum.x / cnt, sum.y / cnt, sum.z / cnt, sum.w / cnt};
     }
     if (!GCN) put4<true>(&lds.a[0][0][0][0][0][0] + p_slot, shift ? shifted(own, shift) : own);
-    put4<true>(&lds.a[0][1][0][0][0][0] + p_slot, shift ? shifted(sum, shift) : sum);
+    put4<true>(&lds.a[0][GCN ? 0 : 1][0][0][0][0] + p_slot, shift ? shifted(sum, shift) : sum);
     __syncthreads();
-    if (wave < 4) {
+    if (wave < W) {
 #pragma unroll 1
-      for (int st = GCN ? 2 : 0; st < 4; ++st) {
-        const int op = st >> 1, ks = st & 1;
-        const float* W = op ? a.w_neigh : a.w_self;
+      for (int st = GCN ? W / 2 : 0; st < W; ++st) {
+        const int op = st / (W / 2), ks = st % (W / 2);
+        const float* weights = op ? a.w_neigh : a.w_self;
         float raw[8][C];  // zero past the last row, the last column past it (not stored)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
 #pragma unroll
           for (int c = 0; c < C; ++c) {
             const int k = k_lo + 32 * ks + 8 * g + j;
-            raw[j][c] = k < D ? W[(long long)k * N + (col + c < N ? col + c : N - 1)] : 0.f;
+            raw[j][c] = k < D ? weights[(long long)k * N + (col + c < N ? col + c : N - 1)] : 0.f;
           }
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const unsigned char* p = &lds.a[0][op][ks][t][0][0] + frag;
+        for (int t = 0; t < NT; ++t) {
+          const unsigned char* p = &lds.a[0][GCN ? 0 : op][ks][t0 + t][0][0] + (g * 16 + ((r16 + 4 * g + ks) & 15)) * 16;
           const f32x4 x[2] = {*reinterpret_cast<const f32x4*>(p), *reinterpret_cast<const f32x4*>(p + 1024)};
 #pragma unroll
           for (int c = 0; c < C; ++c) {
@@ -188,94 +219,111 @@ __device__ __forceinline__ void layer_tile_exact(const LayerArgs& a, LayerLds& l
     }
     __syncthreads();
   }
-  if (wave < 4) store_tile<C>(a, row0, rows, col, g, acc);
+  if (wave < W) store_tile<C, NT>(a, row0, rows, col, t0, g, acc);
 }
 
-// Multiplies one chunk.  b[0]: the parts of the chunk's first column tiles, asked for before; left there: those of the next
-// chunk (w_next; nullptr: there is none).
-template <int C, bool GCN>
-__device__ __forceinline__ void multiply_chunk(const LayerLds& lds, int buf, int lane, const char* w, size_t w_op, size_t next_ks,
-                                               const char* w_next, u32x4 (&b)[2][C < 2 ? 1 : 2][3], f32x4 (&acc)[2][C]) {
-  constexpr int kSteps = GCN ? 2 : 4, kPair = C < 2 ? 1 : 2, kPairs = C / kPair, kUnits = kSteps * kPairs;
-  typedef __attribute__((address_space(1))) const u32x4* gw_t;
+// The parts of one row tile's k step
+struct RowParts {
+  bf16x8 p[3];
+};
+template <int W, bool GCN>
+__device__ __forceinline__ RowParts row_parts(const LayerLds<W, GCN>& lds, int buf, int op, int ks, int t, int lane) {
   const int g = lane >> 4, r16 = lane & 15;
-  const int frag = (g * 16 + ((r16 + 4 * g) & 15)) * 16;
+  const unsigned char* const at = &lds.a[buf][op][ks][t][0][0] + (g * 16 + ((r16 + 4 * g + ks) & 15)) * 16;
+  RowParts r;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) r.p[p] = *reinterpret_cast<const bf16x8*>(at + p * 1024);
+  return r;
+}
+
+// Multiplies one chunk of n_ks k steps.  b[0]: the parts of the chunk's first column tiles, asked for before; left there: those of the
+// next chunk (w_next).  NT: row tiles, from the t0-th.  The rows'
+// parts are read from LDS one row tile ahead of the matrix instructions.
+template <int W, int C, bool GCN, int NT>
+__device__ __forceinline__ void multiply_chunk(const LayerLds<W, GCN>& lds, int buf, int lane, int t0, const char* w, size_t w_op, size_t w_step, int n_ks,
+                                               const char* w_next, u32x4 (&b)[2][C < 2 ? 1 : 2][3], f32x4 (&acc)[NT][C]) {
+  constexpr int kPair = C < 2 ? 1 : 2, kPairs = C / kPair, kOps = GCN ? 1 : 2, kUnits = kOps * kPairs;
+  typedef __attribute__((address_space(1))) const u32x4* gw_t;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  bf16x8 af[2][3];
+  RowParts a_next = row_parts<W, GCN>(lds, buf, 0, 0, t0, lane);
 #pragma unroll
-  for (int u = 0; u < kUnits; ++u) {
-    const int st = u / kPairs, pair = u % kPairs;
-    if (pair == 0) {
-      const int op = GCN ? 1 : st & 1, ks = GCN ? st : st >> 1;
-      const unsigned char* const p0 = &lds.a[buf][op][ks][0][0][0] + frag;
+  for (int ks = 0; ks < W / 2; ++ks) {
+    // (GCN's steps come in twos, so that the next chunk starts with b[0]: where their number is odd the last multiplies zeros with the same weights)
+    if (ks >= n_ks && !(GCN && kPairs == 1 && (ks & 1) && ks == n_ks)) break;
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int uu = 0; uu < kUnits; ++uu) {
+      const int u = ks * kUnits + uu, pair = uu % kPairs;
+      // the unit after this one: of this k step, of the next, or of the next chunk
+      const bool last = uu + 1 == kUnits;
+      const int un = last ? 0 : uu + 1, kn = last ? ks + 1 : ks;
+      {
+        const char* p = w + kn * w_step;
+        if (last && kn >= n_ks) p = GCN && kPairs == 1 && (kn & 1) ? w + ks * w_step : w_next;
+        if (!last && !GCN) p += un / kPairs * w_op;
 #pragma unroll
-        for (int p = 0; p < 3; ++p) af[t][p] = *reinterpret_cast<const bf16x8*>(p0 + t * 3072 + p * 1024);
-    }
-    {
-      const int st_n = (u + 1) / kPairs;
-      const char* p = u + 1 == kUnits ? w_next : w + (GCN ? 0 : (st_n & 1) * w_op) + ((GCN ? st_n : st_n >> 1) ? next_ks : 0);
+        for (int c = 0; c < kPair; ++c)
 #pragma unroll
-      for (int c = 0; c < kPair; ++c)
+          for (int q = 0; q < 3; ++q) b[(u + 1) & 1][c][q] = *((gw_t)(p + ((un % kPairs * kPair + c) * 3 + q) * 1024) + lane);
+      }
+      // the step's 32 products are added up from zero, h h by itself and the others smallest first, and join the running sum as
+      // one number
 #pragma unroll
-        for (int q = 0; q < 3; ++q) b[(u + 1) & 1][c][q] = *((gw_t)(p + ((((u + 1) % kPairs) * kPair + c) * 3 + q) * 1024) + lane);
-    }
-    // the step's 32 products are added up from zero, h h by itself and the others smallest first, and join the running sum as
-    // one number
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      f32x4 top[kPair], rest[kPair];
+      for (int t = 0; t < NT; ++t) {
+        const RowParts a = a_next;
+        if (t + 1 < NT) a_next = row_parts<W, GCN>(lds, buf, uu / kPairs, ks, t0 + t + 1, lane);
+        else if (kn < W / 2) a_next = row_parts<W, GCN>(lds, buf, un / kPairs, kn, t0, lane);  // (past the chunk's last step: not used)
+        f32x4 top[kPair], rest[kPair];
 #define DCI_MM(TO_, A_, P_, IN_) \
-  _Pragma("unroll") for (int c = 0; c < kPair; ++c) TO_[c] = mfma_bf16(af[t][A_], b[u & 1][c][P_], IN_)
-      DCI_MM(rest, 2, 1, zero);
-      DCI_MM(rest, 1, 2, rest[c]);
-      DCI_MM(rest, 2, 0, rest[c]);
-      DCI_MM(rest, 0, 2, rest[c]);
-      DCI_MM(rest, 1, 1, rest[c]);
-      DCI_MM(rest, 1, 0, rest[c]);
-      DCI_MM(rest, 0, 1, rest[c]);
-      DCI_MM(top, 0, 0, zero);
+  _Pragma("unroll") for (int c = 0; c < kPair; ++c) TO_[c] = mfma_bf16(a.p[A_], b[u & 1][c][P_], IN_)
+        DCI_MM(rest, 2, 1, zero);
+        DCI_MM(rest, 1, 2, rest[c]);
+        DCI_MM(rest, 2, 0, rest[c]);
+        DCI_MM(rest, 0, 2, rest[c]);
+        DCI_MM(rest, 1, 1, rest[c]);
+        DCI_MM(rest, 1, 0, rest[c]);
+        DCI_MM(rest, 0, 1, rest[c]);
+        DCI_MM(top, 0, 0, zero);
 #undef DCI_MM
 #pragma unroll
-      for (int c = 0; c < kPair; ++c) acc[t][pair * kPair + c] += top[c] + rest[c];
+        for (int c = 0; c < kPair; ++c) acc[t][pair * kPair + c] += top[c] + rest[c];
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-    __builtin_amdgcn_sched_barrier(0);
   }
-  static_assert(kUnits % 2 == 0, "the next chunk starts with b[0]");
 }
 
-template <int C, bool GCN>
-__global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
-  __shared__ LayerLds lds;
+template <int W, int C, int RS, bool GCN>
+__global__ __launch_bounds__(LayerShape<W>::kThreads, 4) void k_sage_layer(LayerArgs a) {
+  constexpr int NT = 2 / RS, kCols = W / RS, kChunk = LayerShape<W>::kChunk, kLanes = LayerShape<W>::kLanes;
+  __shared__ LayerLds<W, GCN> lds;
   const long long M = a.counts[a.hop];
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = a.D;
-  const long long row_tiles = (M + kLayerRows - 1) / kLayerRows;
-  const long long n_tiles = (row_tiles + 7) / 8 * 8 * a.n_col_groups;
-  // tile number -> column group and row tile: the column groups of a row tile run on one XCD
-  auto place = [&](long long q, int* cg) -> long long {
-    const long long j = q >> 3;
-    *cg = (int)(j % a.n_col_groups);
-    return j / a.n_col_groups * 8 + (q & 7);
-  };
+  constexpr int kSlots = LayerLds<W, GCN>::kSlots;
+  // The rows in halves of a tile (16), shared out evenly: a workgroup takes a stretch of them, two at a time.  The workgroups of the column
+  // groups of a stretch are neighbours on one XCD.
+  const int b = (int)blockIdx.x, n_wgs = (int)gridDim.x / a.n_col_groups;
+  const int cg = (b >> 3) % a.n_col_groups, wg = (b >> 3) / a.n_col_groups * 8 + (b & 7);
+  const long long n_halves = (M + 15) / 16, h_begin = wg * n_halves / n_wgs, h_end = (wg + 1) * n_halves / n_wgs;
+  constexpr int kBuffers = LayerLds<W, GCN>::kBuffers;
   if (tid < kLayerFlags) lds.again[tid] = 0;
-  const int n_chunks = (D + kLayerChunk - 1) / kLayerChunk;
+  if (tid < kBuffers) lds.full[tid] = lds.free[tid] = 0;
+  __syncthreads();
+  const int n_chunks = (D + kChunk - 1) / kChunk;
 
-  if (wave >= 4) {
-    // ---- puts the chunks together, one ahead of the others
-    const int pt = tid - 256, gl = pt & 15, grp = pt >> 4;
-    const int p_g = (gl & 7) >> 1;
-    const int p_slot = (gl >> 3) * 6144 + (p_g * 16 + ((grp + 4 * p_g) & 15)) * 16 + (gl & 1) * 8;
+  if (wave >= W) {
+    // ---- puts the chunks together, ahead of the others
+    __builtin_amdgcn_s_setprio(2);  // its loads are asked for before the others' matrix instructions are issued
+    const int pt = tid - 64 * W, gl = pt & (kLanes - 1), grp = pt / kLanes;
+    const int p_ks = gl >> 3, p_g = (gl & 7) >> 1;
+    const int p_slot = p_ks * 6144 + (p_g * 16 + ((grp + 4 * p_g + p_ks) & 15)) * 16 + (gl & 1) * 8;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    int buf = 0;
-    for (long long q = blockIdx.x; q < n_tiles; q += gridDim.x) {
-      int cg;
-      const long long rt = place(q, &cg);
-      if (rt >= row_tiles) continue;
-      const long long row0 = rt * kLayerRows;
-      const int rows = M - row0 < kLayerRows ? (int)(M - row0) : kLayerRows;
+    int buf = 0, lap = 0;  // the chunk's buffer, and how often the ring has been round
+    for (long long h = h_begin; h < h_end; h += 2) {
+      const int halves = h_end - h < 2 ? 1 : 2;
+      const long long row0 = 16 * h;
+      const int rows = M - row0 < 16 * halves ? (int)(M - row0) : 16 * halves;
       const float* own[2];
       long long e0[2];
       int deg[2];
@@ -288,37 +336,40 @@ __global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
         e0[t] = ok[t] ? a.blk_indptr[row0 + i] : 0;
         deg[t] = ok[t] ? (int)(a.blk_indptr[row0 + i + 1] - e0[t]) : 0;
       }
-      // A row's sources come in rounds of eight loads; two rounds are on their way at any time, across rows and chunks: a
-      // place is asked for again, two rounds on, as soon as it has been added.
+      // A row's sources come in rounds of eight loads, across rows and chunks; the next round is asked for as soon as one has been added.
       int rounds[2];  // of the wavefront's row with the most
+      int whole[2];   // rounds in which each of its rows has eight sources
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        int n = deg[t] < kLayerSlots ? deg[t] : kLayerSlots;
-        for (int d = 16; d < 64; d <<= 1) {
-          const int o = __shfl_xor(n, d, 64);
+        int n = deg[t] < kSlots ? deg[t] : kSlots;
+        int least = n;
+        for (int d = kLanes; d < 64; d <<= 1) {
+          const int o = __shfl_xor(n, d, 64), o_least = __shfl_xor(least, d, 64);
           n = o > n ? o : n;
+          least = o_least < least ? o_least : least;
         }
         n = __builtin_amdgcn_readfirstlane(n);
         rounds[t] = n > 8 ? (n + 7) / 8 : 1;
+        whole[t] = __builtin_amdgcn_readfirstlane(least) / 8;
       }
       // (written and read by one group of lanes; places without a source, up to the last that a round asks for, hold the row itself)
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int s = 0; s < kLayerSlots; s += 16)
-          if (s < 8 * rounds[t]) lds.src[16 * t + grp][s + gl] = s + gl < deg[t] ? source_row(a, e0[t] + s + gl) : own[t];
-      f32x4 v0[8], v1[8], own0, own1;
+        for (int s = 0; s < kSlots; s += kLanes)
+          if (s < 8 * rounds[t] && s + gl < kSlots) lds.src[16 * t + grp][s + gl] = s + gl < deg[t] ? source_row(a, e0[t] + s + gl) : own[t];
+      f32x4 v[8], own_new;
       int n_k = 0, n_t = 0, n_r = 0;  // the round to ask for next
-      auto ask = [&](f32x4 (&v)[8], f32x4& own_v) {
+      auto ask = [&]() {
         if (n_k >= n_chunks) return;
-        const int k_col = n_k * kLayerChunk + 4 * gl, k_ld = k_col < D - 4 ? k_col : D - 4;
+        const int k_col = n_k * kChunk + 4 * gl, k_ld = k_col < D - 4 ? k_col : D - 4;
         const float* const* p = &lds.src[16 * n_t + grp][8 * n_r];
-        if (n_r == 0) own_v = load4((n_t ? own[1] : own[0]) + k_ld);
+        if (n_r == 0) own_new = load4((n_t ? own[1] : own[0]) + k_ld);
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = load4(p[u] + k_ld);
         if (++n_r == (n_t ? rounds[1] : rounds[0])) {
           n_r = 0;
-          if (++n_t == 2) {
+          if (++n_t == halves) {
             n_t = 0;
             ++n_k;
           }
@@ -326,27 +377,32 @@ __global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
       };
       int k = 0, t = 0, r = 0;  // the round to add
       f32x4 sum = zero, own_v = zero;
-      auto add = [&](f32x4 (&v)[8], f32x4& own_new) {
+      auto add = [&]() {
         const int deg_t = t ? deg[1] : deg[0];
         if (r == 0) {
           own_v = own_new;
           sum = GCN ? own_v : zero;
         }
+        if (r < (t ? whole[1] : whole[0])) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const bool in = 8 * r + u < deg_t;
-          sum.x = in ? sum.x + v[u].x : sum.x;
-          sum.y = in ? sum.y + v[u].y : sum.y;
-          sum.z = in ? sum.z + v[u].z : sum.z;
-          sum.w = in ? sum.w + v[u].w : sum.w;
+          for (int u = 0; u < 8; ++u) sum += v[u];
+        } else {
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const bool in = 8 * r + u < deg_t;
+            sum.x = in ? sum.x + v[u].x : sum.x;
+            sum.y = in ? sum.y + v[u].y : sum.y;
+            sum.z = in ? sum.z + v[u].z : sum.z;
+            sum.w = in ? sum.w + v[u].w : sum.w;
+          }
         }
         asm volatile("" : "+v"(sum), "+v"(own_v));  // added here, before the places are asked for again
-        ask(v, own_new);
+        ask();
         if (++r < (t ? rounds[1] : rounds[0])) return;
         // the row's part of the chunk is complete
         r = 0;
-        const int k_col = k * kLayerChunk + 4 * gl, k_ld = k_col < D - 4 ? k_col : D - 4, shift = k_col - k_ld;
-        for (int e = kLayerSlots; e < deg_t; ++e) sum += load4(source_row(a, (t ? e0[1] : e0[0]) + e) + k_ld);
+        const int k_col = k * kChunk + 4 * gl, k_ld = k_col < D - 4 ? k_col : D - 4, shift = k_col - k_ld;
+        for (int e = kSlots; e < deg_t; ++e) sum += load4(source_row(a, (t ? e0[1] : e0[0]) + e) + k_ld);
         const float cnt = (float)deg_t + (GCN ? 1.f : 0.f);
         if (a.mode != DCI_MODEL_SAGE_SUM && cnt != 0.f) sum = f32x4{sum.x / cnt, sum.y / cnt, sum.z / cnt, sum.w / cnt};
         if (shift) {
@@ -354,22 +410,20 @@ __global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
           if (!GCN) own_v = shifted(own_v, shift);
         }
         const bool ok_t = t ? ok[1] : ok[0];
+        if (t == 0) ring_wait(&lds.free[buf], W * lap);
         if (!GCN) put4<false>(&lds.a[buf][0][0][t][0][0] + p_slot, ok_t ? own_v : zero);
-        put4<false>(&lds.a[buf][1][0][t][0][0] + p_slot, ok_t ? sum : zero);
-        if (++t < 2) return;
+        put4<false>(&lds.a[buf][GCN ? 0 : 1][0][t][0][0] + p_slot, ok_t ? sum : zero);
+        if (++t < halves) return;
         t = 0;
         ++k;
-        buf ^= 1;
-        __syncthreads();
+        ring_signal(&lds.full[buf], lane);
+        if (++buf == kBuffers) {
+          buf = 0;
+          ++lap;
+        }
       };
-      ask(v0, own0);
-      ask(v1, own1);
-      while (true) {
-        add(v0, own0);
-        if (k == n_chunks) break;
-        add(v1, own1);
-        if (k == n_chunks) break;
-      }
+      ask();
+      while (k < n_chunks) add();
     }
     __syncthreads();
   } else {
@@ -377,44 +431,44 @@ __global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
     constexpr int kPair = C < 2 ? 1 : 2;
     typedef __attribute__((address_space(1))) const u32x4* gw_t;
     // the parts of the weights: [operand][k step][column group][wavefront][tile][part][lane]
-    const size_t w_step = (size_t)a.n_col_groups * 4 * C * 3 * 1024, w_op = w_step * ((D + 31) / 32);
-    const char* const w0 = reinterpret_cast<const char*>(a.w_split) + (size_t)wave * C * 3 * 1024;
+    constexpr size_t kGroup = (size_t)kCols * C * 3 * 1024;
+    const size_t w_step = a.n_col_groups * kGroup, w_op = w_step * ((D + 31) / 32);
+    const int t0 = wave / kCols;
+    const char* const w0 = reinterpret_cast<const char*>(a.w_split) + (size_t)(wave % kCols) * C * 3 * 1024;
+    const char* const w_base = w0 + cg * kGroup;
     u32x4 b[2][kPair][3];
-    int buf = 0, it = 0;
-    bool begun = false;
-    for (long long q = blockIdx.x; q < n_tiles; q += gridDim.x, ++it) {
-      int cg;
-      const long long rt = place(q, &cg);
-      if (rt >= row_tiles) continue;
-      const char* const w_base = w0 + (size_t)cg * 4 * C * 3 * 1024;
-      if (!begun) {
+    int buf = 0, lap = 0, it = 0;
+    if (h_begin < h_end) {
 #pragma unroll
-        for (int c = 0; c < kPair; ++c)
+      for (int c = 0; c < kPair; ++c)
 #pragma unroll
-          for (int p = 0; p < 3; ++p) b[0][c][p] = *((gw_t)(w_base + (c * 3 + p) * 1024) + lane);
-        begun = true;
-      }
-      // the weights that the tile after this one starts with
-      const char* w_after = w_base;
-      if (a.n_col_groups > 1 && q + gridDim.x < n_tiles) {
-        int cg_n;
-        (void)place(q + gridDim.x, &cg_n);
-        w_after = w0 + (size_t)cg_n * 4 * C * 3 * 1024;
-      }
-      f32x4 acc[2][C];
+        for (int p = 0; p < 3; ++p) b[0][c][p] = *((gw_t)(w_base + (c * 3 + p) * 1024) + lane);
+    }
+    // a tile of which this wavefront multiplies N_ row tiles (0: it only hands the buffers back)
+    auto tile = [&](auto n_rows_, long long h) {
+      constexpr int kRowTiles = decltype(n_rows_)::value, kAcc = kRowTiles ? kRowTiles : 1;
+      f32x4 acc[kAcc][C];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < kAcc; ++t)
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int k = 0; k < n_chunks; ++k, buf ^= 1) {
-        __syncthreads();
-        const char* w = w_base + (size_t)(2 * k) * w_step;
-        // (the last chunk may have one k step of 32 only; the other multiplies zeros with the same weights)
-        multiply_chunk<C, GCN>(lds, buf, lane, w, w_op, k * kLayerChunk + 32 < D ? w_step : 0, k + 1 < n_chunks ? w + 2 * w_step : w_after, b, acc);
+      for (int k = 0; k < n_chunks; ++k) {
+        ring_wait(&lds.full[buf], W * (lap + 1));
+        const char* w = w_base + (size_t)(W / 2 * k) * w_step;
+        const int left = (D - k * kChunk + 31) / 32;
+        if (kRowTiles)
+          multiply_chunk<W, C, GCN, kAcc>(lds, buf, lane, t0, w, w_op, w_step, left < W / 2 ? left : W / 2, k + 1 < n_chunks ? w + W / 2 * w_step : w_base,
+                                          b, acc);
+        ring_signal(&lds.free[buf], lane);
+        if (++buf == kBuffers) {
+          buf = 0;
+          ++lap;
+        }
       }
+      if (!kRowTiles) return;
       bool bad = false;
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < kAcc; ++t)
 #pragma unroll
         for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -422,21 +476,24 @@ __global__ __launch_bounds__(kLayerThreads, 4) void k_sage_layer(LayerArgs a) {
             bad |= !(__builtin_fabsf(acc[t][c][r]) <= kMaxFloat);
             acc[t][c][r] *= kUnscale;
           }
-      const long long row0 = rt * kLayerRows;
-      const int rows = M - row0 < kLayerRows ? (int)(M - row0) : kLayerRows;
       if (bad) lds.again[it % kLayerFlags] = 1;
-      store_tile<C>(a, row0, rows, (cg * 64 + wave * 16 + (lane & 15)) * C, lane >> 4, acc);
+      store_tile<C, kAcc>(a, 16 * h, M - 16 * h < kLayerRows ? (int)(M - 16 * h) : kLayerRows, ((cg * kCols + wave % kCols) * 16 + (lane & 15)) * C, t0,
+                          lane >> 4, acc);
+    };
+    long long h = h_begin;
+    for (; h + 1 < h_end; h += 2, ++it) tile(std::integral_constant<int, NT>(), h);
+    if (h < h_end) {  // half a tile is left
+      if (t0 == 0) tile(std::integral_constant<int, 1>(), h);
+      else tile(std::integral_constant<int, 0>(), h);
     }
     __syncthreads();
   }
   // tiles with a number that the parts cannot hold, once more (and, past 64 tiles, those whose flag they share)
   int it = 0;
-  for (long long q = blockIdx.x; q < n_tiles; q += gridDim.x, ++it) {
-    int cg;
-    const long long rt = place(q, &cg);
-    if (rt >= row_tiles || !lds.again[it % kLayerFlags]) continue;
-    const long long row0 = rt * kLayerRows;
-    layer_tile_exact<C, GCN>(a, lds, row0, M - row0 < kLayerRows ? (int)(M - row0) : kLayerRows, cg);
+  for (long long h = h_begin; h < h_end; h += 2, ++it) {
+    if (!lds.again[it % kLayerFlags]) continue;
+    const long long row0 = 16 * h, end = 16 * h_end < M ? 16 * h_end : M;
+    layer_tile_exact<W, C, RS, GCN>(a, lds, row0, end - row0 < kLayerRows ? (int)(end - row0) : kLayerRows, cg);
   }
 }
 
@@ -631,48 +688,41 @@ __global__ __launch_bounds__(kSmallThreads) void k_sage_layer_small(LayerArgs a)
 //     79 us against 94 with aggregation, dense layer and sum of the split contraction as kernels of their own.  On either side
 //     of the line, this kernel / the other: 4,096 rows x 2 x 256 x 64 (256 workgroups), f = 5, 12.3 us / 16.8, x 100 (512) 21.8 / 17.4, x 172
 //     (768) 31.0 / 19.6; 1,024 x 2 x 100 x 256 (256), f = 10, 0.78, 2,048 x 2 x 256 x 256 (512), f = 15, 1.5.
-//   * above it, the fewest columns per wavefront that make no more than four column groups and five tiles for four compute units: 1 k rows
-//     x 2 x 256 x 512, f = 10, with 16 columns (eight groups) 20.7 us, 32 columns 21.8, 64 columns 26.5; 3.1 k (fewer than a fifth of 15,015,
-//     291 tiles) x 2 x 75 x 130 with 16 columns 15.8, 32 columns 17.6; 2 k x 2 x 300 x 320, f = 25, with 16 columns (five groups) 43.7, 32
-//     columns 36.9; 6 k x 2 x 602 x 192, f = 10, with 64 columns 56, 16 columns, which put the rows together three times in 564 tiles, 78.
+//   * above it k_sage_layer, in the shape that its width asks for (LayerPlan; figures at the kernel): 1 k rows x 2 x 256 x 512, f = 10, 24.7 us, the
+//     layer's two kernels 24.7; 3.1 k x 2 x 75 x 130, f = 8, 15.3 / 19.3; 2 k x 2 x 300 x 320, f = 25, 32.4 / 40.0; 6 k x 2 x 602 x 192, f = 10, 57.5 / 89.
+//     More than 256 outputs are two column groups or more, which put the same rows together again.
 //   * neither where lists are long: in few workgroups the lists' latency is not hidden.  With lists of more than 10,000 numbers the
 //     layer's two kernels are ahead (x 256 outputs, one kernel / the two; the two have a launch more, 1 - 2 us).  k_sage_layer_small,
 //     1,024 rows: D = 100, f = 64 0.86; D = 256, f = 25 0.93, f = 40 30.1 us / 26.3, f = 64 43 / 31; D = 300, f = 40 42 / 29; D = 602, f = 15 33.4
 //     / 31.8, f = 25 50 / 36, f = 64 106 / 55.  (Where it has two compute units for every workgroup it is only behind for more
 //     than 64 sources times pieces of 256 columns: 512 x 2 x D x 256, D = 256, f = 64 0.97; D = 300, f = 25 1.00, f = 64 1.26; D = 602, f = 25 1.16.)
-//     k_sage_layer, 2,048 rows: D = 64, f = 64 21.7 / 29.3; D = 256, f = 25 29.8 / 30.5, f = 64 49.6 / 42.6; D = 300, f = 25 35.6 / 36.1, f = 40 43.3
-//     / 40.6; D = 602, f = 25 60 / 53, f = 64 110 / 82.
-//   * where there are more tiles than that, as many columns as the layer has, up to 64, because putting a tile's rows together is
-//     what takes the time: 18.6 k x 2 x 602 x 256, f = 10, with 64 columns 166 us, 32 columns 162, 16 columns 251.
+//     k_sage_layer, 2,048 rows: D = 64, f = 64 19.0 / 19.3; D = 256, f = 25 26.6 / 34.1, f = 64 36.2 / 40.3; D = 300, f = 25 30.5 / 39.4, f = 40 32.8
+//     / 42.3; D = 602, f = 25 45 / 67, f = 64 73 / 88.
 //   * none of them where the lists are long and every column group puts the same rows together again, or rows are no whole 128-byte
-//     lines, so that a piece of 256 bytes touches three.  The aggregation reads them once and in one piece, and the dense
-//     layer follows.  18.6 k x 2 x D x N, this kernel / the two: f = 64, 602 x 256 624 us / 534, 602 x 1,024 1,668 / 832, 256 x 256
-//     0.83 of the two, 256 x 1,024 1.05; f = 25, 602 x 256 297 / 286, 602 x 1,024 691 / 575, 256 x 256 0.78, 100 x 1,024 1.08; f = 15,
-//     602 x 256 0.87, 602 x 512 0.88, 300 x 768 0.78 (60 k rows 1.03).  2 k x 2 x 602 x 256: f = 10 0.88, f = 25 1.11.
-//     Where they are even the two are taken: with four lanes they are 5 % ahead (batches of two hops, f = 10 and 25, 68 columns, 144
-//     us a batch against 151; on one lane 176 either way).  For the same reason 257 to 384 columns, a second group of 256 for less
-//     than half of its columns, are not for these kernels: three layers of 256, 300, 300 and 47 columns, 2,048 seeds, on four lanes 263 us a batch,
-//     285 with them, on one lane 305 and 297; from 100 columns 190 and 218, 225 and 230.
-constexpr int64_t kSmallReads = 10000;
+//     lines, so that a piece of 512 bytes touches five for four.  The aggregation reads them once and in one piece, and the dense
+//     layer follows.  18.6 k x 2 x D x N, this kernel / the two: f = 64, 602 x 256 509 us / 550, 602 x 1,024 1,059 / 860, 256 x 256 188 / 229,
+//     256 x 1,024 420 / 384; f = 25, 602 x 256 233 / 302, 602 x 1,024 535 / 620, 256 x 256 92 / 132, 100 x 1,024 116 / 140; f = 15, 602 x 256 166 / 235,
+//     602 x 512 235 / 366, 300 x 768 182 / 241 (60 k rows 651 / 764); 300 x 300, f = 10, 115 / 122.
+//   The lines of the last two lie where a slower form of k_sage_layer (chunks of 64 columns, column groups of 64) met the two kernels; some lists
+// beyond them would now be up to a third faster in one kernel.  They stay, because a call that crosses a line gets its products from other
+// instructions, and its results other last bits.
+constexpr int64_t kSmallReads = 10000, kFewRowsPerCu = 40;
 
 static size_t split_bytes(const LayerPlan& p, int ops) {
-  return (size_t)ops * ((p.D + 31) / 32) * ((p.N + 64 * p.C - 1) / (64 * p.C)) * 4 * p.C * 3 * 1024;
+  return (size_t)ops * ((p.D + 31) / 32) * p.n_waves() * p.C * 3 * 1024;
 }
 
-// LayerPlan::C.  rows: about what a batch has; fan: the longest list.
+// -1 not one of these kernels, 0 k_sage_layer_small, 1 k_sage_layer.  rows: about what a batch has; fan: the longest list.
 static int kernel_for(const dci_ctx* ctx, const LayerPlan& p, int64_t rows, int64_t fan) {
-  auto groups = [&](int C) -> int64_t { return (p.N + 64 * C - 1) / (64 * C); };
   const bool short_lists = fan * p.D <= kSmallReads;
-  const int64_t wgs = (rows + kSmallRows - 1) / kSmallRows * groups(1);
+  const int64_t wgs = (rows + kSmallRows - 1) / kSmallRows * ((p.N + kSmallCols - 1) / kSmallCols);
   if (p.N >= 4 && wgs <= ctx->num_cus)
     return short_lists || (2 * wgs <= ctx->num_cus && fan * ((p.D + kSmallChunk - 1) / kSmallChunk) <= 64) ? 0 : -1;
-  for (int C = 1; C <= 4; C *= 2)
-    if (groups(C) <= 4 && rows * groups(C) <= (int64_t)ctx->num_cus * kLayerRows * 5 / 4) return short_lists ? C : -1;
+  const int64_t g = (p.N + 255) / 256;
+  if (g <= 4 && rows * g <= (int64_t)ctx->num_cus * kFewRowsPerCu) return short_lists ? 1 : -1;
   if (p.N > 256 && p.N <= 384) return -1;
   const bool lines = p.D % 32 == 0;  // rows are whole 128-byte lines
-  const int C = p.N <= 64 ? 1 : p.N <= 128 ? 2 : 4;
-  const int64_t g = groups(C);
-  return lines ? (fan * (g + 1) <= 128 ? C : -1) : (fan * (g < 3 ? 3 : g) <= 60 ? C : -1);
+  return (lines ? fan * (g + 1) <= 128 : fan * (g < 3 ? 3 : g) <= 60) ? 1 : -1;
 }
 
 bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, const int32_t* dims, bool input_apart, void* scratch,
@@ -689,7 +739,13 @@ bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, co
     if (p.D < 4 || p.cap_rows < 1) return false;
     const int64_t rows = h == 0 ? p.cap_rows : h == 1 ? p.cap_rows / 2 : p.cap_rows / 5;
     p.C = l == 0 && input_apart ? -1 : kernel_for(ctx, p, rows, (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
-    if (p.C > 0) p.w_split = ar.take<char>(split_bytes(p, ops));
+    if (p.C > 0) {
+      const bool narrow = p.D <= 64 && p.N <= 128;
+      p.rs = !narrow && p.N <= 64 ? 2 : 1;
+      p.cols = narrow || p.N <= 64 ? 4 : 8;
+      p.C = p.N > (narrow ? 64 : 128) ? 2 : 1;
+      p.w_split = ar.take<char>(split_bytes(p, ops));
+    }
   }
   return ar.ok();
 }
@@ -708,6 +764,7 @@ SplitArgs layers_split_args(int32_t model, int32_t first, int32_t n_layers, cons
     sa.D[sa.n] = p.D;
     sa.N[sa.n] = p.N;
     sa.C[sa.n] = p.C;
+    sa.waves[sa.n] = p.n_waves();
     sa.ops[sa.n] = gcn ? 1 : 2;
     sa.wgs += (int)(split_bytes(p, sa.ops[sa.n]) / (4 * 3 * 1024));  // four tiles to a workgroup
     ++sa.n;
@@ -737,19 +794,22 @@ int32_t layer_launch(dci_ctx* ctx, const LayerPlan& plan, const LayerArgs& args)
     DCI_LAUNCH_CHECK(ctx);
     return DCI_OK;
   }
-  a.n_col_groups = (a.N + 64 * plan.C - 1) / (64 * plan.C);
-  const int64_t row_tiles = (plan.cap_rows + kLayerRows - 1) / kLayerRows;
-  int64_t n = (row_tiles + 7) / 8 * 8 * a.n_col_groups;
-  // (a multiple of eight: a workgroup's tiles are then all of one XCD's, and once one is past the last row tile so are those behind it,
-  // which the weights fetched ahead rely on)
-  const int64_t most = (int64_t)ctx->num_cus * kLayerPerCu / 8 * 8;
-  if (n > most) n = most > 8 ? most : 8;
-  const dim3 grid((unsigned)n);
-#define DCI_LAYER(C_) \
-  hipLaunchKernelGGL((gcn ? k_sage_layer<C_, true> : k_sage_layer<C_, false>), grid, dim3(kLayerThreads), 0, ctx->stream, a)
-  if (plan.C == 1) DCI_LAYER(1);
-  else if (plan.C == 2) DCI_LAYER(2);
-  else DCI_LAYER(4);
+  a.n_col_groups = plan.n_waves() / plan.cols;
+  const int W = plan.cols * plan.rs;
+  // one workgroup (two of the narrow shape) to a compute unit, as many for every column group, in eights for the XCDs; no more than there are
+  // halves of tiles
+  int64_t n = (int64_t)ctx->num_cus * (8 / W) / (8 * a.n_col_groups), most = ((plan.cap_rows + 15) / 16 + 7) / 8;
+  if (n > most) n = most;
+  if (n < 1) n = 1;
+  const dim3 grid((unsigned)(8 * n * a.n_col_groups));
+#define DCI_LAYER(W_, C_, RS_)                                                                                             \
+  hipLaunchKernelGGL((gcn ? k_sage_layer<W_, C_, RS_, true> : k_sage_layer<W_, C_, RS_, false>), grid, dim3(LayerShape<W_>::kThreads), 0, \
+                     ctx->stream, a)
+  if (W == 4 && plan.C == 1) DCI_LAYER(4, 1, 1);
+  else if (W == 4) DCI_LAYER(4, 2, 1);
+  else if (plan.rs == 2) DCI_LAYER(8, 1, 2);
+  else if (plan.C == 1) DCI_LAYER(8, 1, 1);
+  else DCI_LAYER(8, 2, 1);
 #undef DCI_LAYER
   DCI_LAUNCH_CHECK(ctx);
   return DCI_OK;

@@ -44,6 +44,7 @@ struct SplitArgs {
   const float* w[DCI_MAX_HOPS][2];  // self, neighbour (GCN: the one matrix in the first place)
   void* out[DCI_MAX_HOPS];
   int D[DCI_MAX_HOPS], N[DCI_MAX_HOPS], C[DCI_MAX_HOPS], ops[DCI_MAX_HOPS];
+  int waves[DCI_MAX_HOPS];  // column tiles of 16 C columns, all workgroups' together
 };
 
 // Workgroup `block` (256 threads) of SplitArgs::wgs.
@@ -54,7 +55,7 @@ __device__ __forceinline__ void split_weights(const SplitArgs& a, int block) {
   const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
   // one wavefront per tile of 32 rows by 16 columns: [operand][k step][column group and wavefront][tile]
   const int id = (block - a.first[l]) * 4 + (int)(threadIdx.x >> 6);
-  const int n32 = (D + 31) / 32, n_w = (N + 64 * C - 1) / (64 * C) * 4;
+  const int n32 = (D + 31) / 32, n_w = a.waves[l];
   const int c = id % C, w = id / C % n_w, ks = id / C / n_w % n32, op = id / C / n_w / n32;
   if (op >= a.ops[l]) return;
   const int col = (w * 16 + r16) * C + c;

@@ -115,3 +115,18 @@ def test_layer_at_the_ends_of_the_range(env, scale, M, D, N, cap):
     assert env["one kernel"]
     tiny = 2.0 ** -149 * (2 * D + 8)   # products below the smallest number are lost one by one
     assert (np.abs(got - want) <= bound + tiny).all(), np.max(np.abs(got - want) / (bound + tiny))
+
+
+@pytest.mark.parametrize("model", [0, 2])
+@pytest.mark.parametrize("M,D,N,fan", [
+    # 1,251 halves of tiles over 256 workgroups, four or five to each; the shapes' lines at 64 columns and 64 and 128 outputs
+    (20_011, 64, 64, 3), (20_011, 65, 64, 3), (20_011, 64, 65, 3), (20_011, 65, 65, 3), (20_011, 64, 128, 3), (20_011, 65, 128, 3),
+    (20_011, 64, 129, 3), (20_011, 65, 129, 3),
+    # one half more than there are workgroups; a last half of one row; three column groups and one tile's half to each
+    (4_097, 129, 100, 4), (4_097, 127, 256, 4), (8_193, 31, 41, 4), (8_193, 97, 600, 4),
+    # lists around the places for their sources
+    (3_000, 96, 100, 58), (3_000, 64, 128, 64)])
+def test_rows_shared_out_in_halves_of_tiles(env, model, M, D, N, fan):
+    got, want, bound = _run(env, M, D, N, fan, model, max(M, 9000 if fan > 4 else M), seed=M + D + N)
+    assert env["one kernel"]
+    assert (np.abs(got - want) <= bound).all(), np.max(np.abs(got - want) / bound)
