@@ -175,9 +175,9 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *          fp32 product, and 32 at a time are added).  A layer is aggregation and dense layer apart where that is faster: lists
  *          (cap_edges / cap_rows of its block) of more than 20 sources or so where input rows are not a multiple of 128 bytes, of
  *          more than 42 where the output has more than 256 columns, of more than 10000 numbers in layers of few rows; 257 to 384
- *          outputs of many rows.  An input layer of 65 to 104 columns and 256 outputs, or of 112 or
- *          128 columns and a multiple of 256 outputs above that, lists of 11 to 16 sources, at least 98304 rows by
- *          capacity, is one kernel with fp32 instructions (the default forms under DCI_OPT_INPUT_LAYER).  The whole pass
+ *          outputs of many rows.  Where that would be so for an input layer of 112 or 128
+ *          columns, a multiple of 256 outputs, lists of 11 to 16 sources and at least 98304 rows by capacity, it is
+ *          one kernel with fp32 instructions (the default form under DCI_OPT_INPUT_LAYER).  The whole pass
  *          is as with two kernels a layer where DCI_OPT_INPUT_LAYER is set, an input has fewer than four columns or the parts of
  *          the weights do not fit where the aggregated rows would be.
  *          The dense layer of two: the kernel that keeps the weights in registers when the whole contraction

@@ -225,9 +225,9 @@ struct LayerPlan {
   int cols, rs;  // k_sage_layer: multiplying wavefronts side by side, and how many of them share columns (each takes a part of the rows)
   int n_waves() const { return (N + 16 * C * cols - 1) / (16 * C * cols) * cols; }
 };
-// Plans every layer of a forward pass; input_apart: the input layer is not for these kernels; scratch is where the weights' parts may
+// Plans every layer of a forward pass; scratch is where the weights' parts may
 // go.  false: none of the layers is for these kernels, because an input is too narrow or the scratch too small.
-bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, const int32_t* dims, bool input_apart, void* scratch,
+bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, const int32_t* dims, void* scratch,
                  size_t scratch_bytes, LayerPlan* plans);
 // The parts to lay out for the layers from `first` on
 SplitArgs layers_split_args(int32_t model, int32_t first, int32_t n_layers, const LayerPlan* plans, const float* const* w_self,

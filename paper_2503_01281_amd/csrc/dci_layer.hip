@@ -725,7 +725,7 @@ static int kernel_for(const dci_ctx* ctx, const LayerPlan& p, int64_t rows, int6
   return (lines ? fan * (g + 1) <= 128 : fan * (g < 3 ? 3 : g) <= 60) ? 1 : -1;
 }
 
-bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, const int32_t* dims, bool input_apart, void* scratch,
+bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, const int32_t* dims, void* scratch,
                  size_t scratch_bytes, LayerPlan* plans) {
   const int ops = model == DCI_MODEL_GCN_AVG ? 1 : 2, n_layers = blocks->n_hops;
   Arena ar(reinterpret_cast<char*>(scratch), scratch_bytes);
@@ -738,7 +738,7 @@ bool layers_plan(const dci_ctx* ctx, const dci_blocks* blocks, int32_t model, co
     p.w_split = nullptr;
     if (p.D < 4 || p.cap_rows < 1) return false;
     const int64_t rows = h == 0 ? p.cap_rows : h == 1 ? p.cap_rows / 2 : p.cap_rows / 5;
-    p.C = l == 0 && input_apart ? -1 : kernel_for(ctx, p, rows, (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
+    p.C = kernel_for(ctx, p, rows, (blocks->cap_edges[h] + p.cap_rows - 1) / p.cap_rows);
     if (p.C > 0) {
       const bool narrow = p.D <= 64 && p.N <= 128;
       p.rs = !narrow && p.N <= 64 ? 2 : 1;

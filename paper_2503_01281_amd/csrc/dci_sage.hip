@@ -1810,20 +1810,17 @@ static int32_t plan_forward(dci_ctx* ctx, const dci_blocks* blocks, const float*
                         bias[0], n_layers == 1 ? logits : plan->ws.y[0]);
   };
   plan->input = input(feat_cache);
-  // Input layers of 65 to 104 columns and 256 outputs stay with the weights-in-registers kernel for lists of 11 to 16 sources: it moves
-  // fewer bytes (rows in one piece each), which counts when batches share the card, but its pipeline holds 16 sources and no more.
-  // Eight 4,096-seed batches of 2 x 100 x 256, 15 sources, on four lanes 1,819 us a pass, k_sage_layer 1,874; four on one lane
-  // 1,093 either way; 60 k rows x 2 x 100 x 256 with 5, 15 and 25 sources 101, 125 and 259 us, k_sage_layer 93, 144 and 199.  Input
-  // layers of 112 or 128 columns and 512 outputs or more stay with k_sage_input_tile for the same lists, since k_sage_layer puts their
-  // rows together more than once: 60 k x 2 x 128 x 512 180, 196 and 390 us, k_sage_layer 160, 211 and 268.
-  //   Where the cache's alignment rules such a kernel out for rows read in place, the layer's two kernels are taken, whose results are
+  // An input layer that k_sage_layer does not take, because it would put the rows of lists of 11 to 16 sources together too often (112 or 128
+  // columns, 1,024 outputs or more), goes to k_sage_input_tile, which does so once.  The others are faster there: 60 k rows x 2 x 100 x 256 with 5,
+  // 15 and 25 sources 79, 112 and 140 us, with the weights in registers (k_sage_input_res) 101, 125 and 259; x 2 x 128 x 512 145, 192 and 195,
+  // k_sage_input_tile 180, 196 and 390; eight 4,096-seed batches of 2 x 100 x 256, 15 sources, on four lanes 1,660 us a pass (k_sage_input_res 1,705),
+  // on one 1,860 (1,955), of 2 x 68 x 256 on one 1,735 (1,925).
+  //   Where the cache's alignment rules that kernel out for rows read in place, the layer's two kernels are taken, whose results are
   // the same to the bit where the outputs are a multiple of 256: DCI_OPT_FUSED_INPUT changes no logits.
   const int64_t fan = (blocks->cap_edges[n_layers - 1] + cap_in - 1) / cap_in;
-  const InputKernel whole = input(nullptr);
-  const bool input_here = fan > 10 && fan <= 16 && input_slabs(dims[0]) > 8 && dims[1] % kResCols == 0 &&
-                          whole == (dims[1] == kResCols ? InputKernel::Registers : InputKernel::Tiles);
-  plan->planned = ctx->linear_kernel == 0 && ctx->input_layer == 0 &&
-                  layers_plan(ctx, blocks, model, dims, input_here, plan->ws.m, plan->ws.m_bytes, plan->layers);
+  plan->planned = ctx->linear_kernel == 0 && ctx->input_layer == 0 && layers_plan(ctx, blocks, model, dims, plan->ws.m, plan->ws.m_bytes, plan->layers);
+  const bool input_here = plan->planned && plan->layers[0].C < 0 && fan > 10 && fan <= 16 && dims[1] > kResCols &&
+                          dims[1] % kResCols == 0 && input(nullptr) == InputKernel::Tiles;
   if (plan->planned && !input_here) plan->input = InputKernel::Apart;
   return DCI_OK;
 }

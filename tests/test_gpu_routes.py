@@ -183,6 +183,17 @@ def test_kernels_of_an_input_layer(env, cap, fan, D, N, kernels):
     assert _close(got, want, size, fanouts, dims)
 
 
+@pytest.mark.parametrize("model", [0, 1])
+@pytest.mark.parametrize("fan,D,N", [(10, 100, 256), (11, 68, 256), (16, 100, 256), (15, 104, 256), (16, 128, 512), (15, 112, 1024), (16, 112, 1024)])
+def test_input_layers_of_many_rows_with_11_to_16_sources(env, model, fan, D, N):
+    """At least 98,304 rows by capacity, inputs of up to 128 columns: one kernel, with three-part products but for the last, which puts its
+    rows together in one piece."""
+    fanouts, dims = (1, 1, fan), (D, N, 8, 5)
+    got, want, size, n = _forward(env, 25_000, fanouts, (100, 170, 3001, 4000), dims, model, D + N + fan)
+    assert n["mean_in"] + n["linear_in"] == 1
+    assert _close(got, want, size, fanouts, dims)
+
+
 @pytest.mark.parametrize("cap,kernels", [(8000, 1), (5000, 2)])
 def test_parts_fit_where_the_aggregated_rows_would_be_or_not(env, cap, kernels):
     """98,304 bytes of parts of 2 x 4 x 256 weights, 16 bytes to a row."""
