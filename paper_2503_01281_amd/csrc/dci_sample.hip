@@ -1,7 +1,8 @@
 // Cache-aware multi-hop neighbour sampling, mini-batch block construction and pre-sampling
 // access counting (Section II-C; Section IV; Section IV-B, first and third paragraphs).
 //
-// One batch is one clear of the batch's node table, two kernels per hop and one closing kernel:
+// One batch is one clear of the batch's node table, two kernels per hop and one closing kernel (the clear and the first hops of small batches
+// are one kernel, k_first_hops):
 //   k_sample_hop  - one lane group per frontier node (a whole wavefront for fan-outs above 32, a
 //                   half / quarter / eighth for smaller ones): read the node's list bounds from the
 //                   adjacency cache or the host CSR (a position is served by the cache iff it lies
@@ -285,9 +286,99 @@ __global__ __launch_bounds__(kBlock) void k_write_src(CloseArgs close, StatFold 
   }
 }
 
+// A hop's frontier: in the table already, the seeds, or nodes that are not in the table yet
+enum { kRegistered, kSeeds, kUnregistered };
+
+// What a frontier row reads: its list bounds and, for lane `gl` of its group, where the id at that lane's drawn position stands.
+struct RowDraw {
+  const long long* src;  // of this lane's neighbour id
+  long long start, pos;
+  bool hit, active;      // the node has a cache slot; this lane has an edge
+  int c, n_host, n_lines, n_bound_lines;  // edges; those read from the host although it has a slot; as in row_cnt
+};
+
+// A row's list: where it starts in the array that serves it, its length, how much of it the cache holds.
+struct RowBounds {
+  long long start, d, cached_len;
+  bool hit;
+};
+// b0, b1: the row's pair of bounds, in the cache's list or the graph's
+__device__ __forceinline__ RowBounds row_bounds(const HopArgs& a, long long v, bool hit, long long b0, long long b1) {
+  return RowBounds{b0, hit && v == a.partial_node ? a.partial_deg : b1 - b0, hit ? b1 - b0 : 0, hit};
+}
+__device__ __forceinline__ RowBounds noted_bounds(longlong2 memo) {
+  const long long d = memo.y & ((1ll << 62) - 1);
+  return RowBounds{memo.x, d, d, (memo.y >> 62) != 0};
+}
+__device__ __forceinline__ RowBounds look_up_bounds(const HopArgs& a, long long v) {
+  const int r = a.adj_remap ? a.adj_remap[v] : -1;
+  const long long* const p = r >= 0 ? a.c_indptr + r : a.indptr + v;
+  return row_bounds(a, v, r >= 0, p[0], p[1]);
+}
+__device__ __forceinline__ void note_bounds(const HopArgs& a, long long i, long long v, const RowBounds& b) {
+  a.row_memo[i] = longlong2{b.start, v == a.partial_node ? -1ll : (b.d | (b.hit ? (1ll << 62) : 0ll))};
+}
+
+// noted: the bounds come from a note.  Every lane of the wavefront must be active.
+template <int G>
+__device__ __forceinline__ RowDraw draw_row(const HopArgs& a, int hop, int f, bool row_ok, long long v, bool noted, const RowBounds& b, int gl,
+                                            int grp_in_wave) {
+  const long long start = b.start, d = b.d, cached_len = b.cached_len;
+  const bool hit = b.hit;
+  const long long* list = hit ? a.c_indices : a.indices;
+  const int c = d < (long long)f ? (int)d : f;
+  long long pos = gl;
+  const bool floyd = row_ok && d > (long long)f;
+  if (__ballot(floyd) != 0ull) {
+    // Slot s draws t_s below j_s + 1, j_s = d - f + s; it keeps t_s unless an earlier slot already holds that value, in which
+    // case it takes j_s.  What earlier slots hold is every earlier t, and j_k of every earlier slot k that took its own: so
+    // slot s takes j_s if an earlier t is the same, or if t_s = j_k and slot k took j_k.
+    const long long j = d - f + gl;
+    long long t = 0;
+    if (floyd && gl < f) t = (long long)uniform_below(a.k0, a.k1, v, a.batch, hop, gl, (unsigned long long)(j + 1));
+    const bool own = floyd && gl < f;
+    bool taken = earlier_equal<G>((unsigned long long)t, gl) && own;
+    const long long k = t - (d - f);
+    const bool depends = own && k >= 0 && k < gl;
+    if (__ballot(depends) != 0ull) {
+      for (;;) {
+        const unsigned long long bits = group_bits<G>(__ballot(taken), grp_in_wave);
+        const bool more = depends && !taken && ((bits >> (k & 63)) & 1ull) != 0ull;
+        if (__ballot(more) == 0ull) break;
+        taken = taken || more;
+      }
+    }
+    if (floyd) pos = taken ? j : t;
+  }
+  const bool active = row_ok && gl < c;
+  // position p of a node with a slot is served by the cache iff p < cached length (Section IV-B, third
+  // paragraph); beyond it - possible only for the one node cached in part - the host list is read
+  const bool from_host = active && hit && pos >= cached_len;
+  const int n_host = __popcll(group_bits<G>(__ballot(from_host), grp_in_wave));
+  const long long* src = from_host ? a.indices + (a.indptr[v] + pos) : list + (start + pos);
+  int n_lines = 0, n_bound_lines = 0;
+  if (a.count_lines) {
+    // Miss-path traffic of the row in the unit a host link moves (128-byte lines): the distinct lines of
+    // the neighbour ids it reads from graph->indices, and the lines its list bounds in graph->indptr lie in.
+    const bool host_read = active && (from_host || !hit);
+    if (__ballot(host_read) != 0ull) {
+      // (lanes that read nothing there have numbers of their own)
+      const unsigned long long line = host_read ? (unsigned long long)reinterpret_cast<uintptr_t>(src) >> kHostLineLog2 : ~(unsigned long long)gl;
+      const bool leader = host_read & !earlier_equal<G>(line, gl);
+      n_lines = __popcll(group_bits<G>(__ballot(leader), grp_in_wave));
+    }
+    if (row_ok && hit && n_host > 0) n_bound_lines = 1;  // the partly cached node: where its host list starts
+    if (row_ok && !hit && !noted) {  // (a noted row's bounds came from the batch's own note in HBM)
+      const uintptr_t b0 = reinterpret_cast<uintptr_t>(a.indptr + v), b1 = reinterpret_cast<uintptr_t>(a.indptr + v + 1);
+      n_bound_lines = (b0 >> kHostLineLog2) == (b1 >> kHostLineLog2) ? 1 : 2;
+    }
+  }
+  return RowDraw{src, start, pos, hit, active, c, n_host, n_lines, n_bound_lines};
+}
+
 // Phase 1 of a hop.  INIT (hop 0): row i first turns seed i into frontier entry i (final local id
 // i in the table; an atomic minimum, so it also wins against a neighbour lane that registered
-// the same node a moment earlier).  Otherwise the kernel starts by finishing the previous hop
+// the same node a moment earlier), and REGISTER (after k_first_hops) does the same with the frontier's nodes.  Otherwise the kernel starts by finishing the previous hop
 // (write_block_sources), which only needs values that are already final.
 //   Bound by the length of its chain of dependent reads, and in large frontiers by the number of random reads: the arguments are fetched
 // together; the frontier's sizes, the batch's status, the group's first node and that node's note are asked for together, before it is
@@ -298,8 +389,9 @@ struct HopRow {
   longlong2 memo;
 };
 
-template <int G, bool COUNT, bool INIT, bool DIRECT>
+template <int G, bool COUNT, int FRONTIER, bool DIRECT>
 __global__ __launch_bounds__(kBlock, 8) void k_sample_hop(HopArgs a) {
+  constexpr bool INIT = FRONTIER == kSeeds, REGISTER = FRONTIER == kUnregistered;
   const int lane = lane_id();
   const int gl = lane & (G - 1);
   const int grp_in_wave = lane / G;
@@ -350,86 +442,24 @@ __global__ __launch_bounds__(kBlock, 8) void k_sample_hop(HopArgs a) {
     const long long v = next.v;
     const longlong2 memo = next.memo;
     if (i + step < n_rows) next = read_row(i + step);
-    long long start = 0, d = 0, cached_len = 0;
-    const long long* list = a.indices;
-    bool hit = false, noted = false;
+    const bool noted = !INIT && row_ok && i < n_noted && memo.y >= 0;
+    if ((INIT || REGISTER) && row_ok && gl == 0) {
+      if (INIT) a.nodes[i] = v;
+      bool ignored;
+      (void)table_insert_min<DIRECT>(a.table, a.entries, a.shift, a.last_node, v, (unsigned)i, &ignored);
+    }
+    RowBounds b = {0, 0, 0, false};
     if (row_ok) {
-      if (INIT && gl == 0) {
-        a.nodes[i] = v;
-        bool ignored;
-        (void)table_insert_min<DIRECT>(a.table, a.entries, a.shift, a.last_node, v, (unsigned)i, &ignored);
-      }
-      noted = !INIT && i < n_noted && memo.y >= 0;
       if (noted) {
-        start = memo.x;
-        hit = (memo.y >> 62) != 0;
-        d = cached_len = memo.y & ((1ll << 62) - 1);
-        if (hit) list = a.c_indices;
+        b = noted_bounds(memo);
       } else {
-        const int r = a.adj_remap ? a.adj_remap[v] : -1;
-        hit = r >= 0;
-        if (hit) {
-          start = a.c_indptr[r];
-          cached_len = a.c_indptr[r + 1] - start;
-          d = v == a.partial_node ? a.partial_deg : cached_len;
-          list = a.c_indices;
-        } else {
-          start = a.indptr[v];
-          d = a.indptr[v + 1] - start;
-        }
-        if (!a.last_hop && gl == 0)
-          a.row_memo[i] = longlong2{start, v == a.partial_node ? -1ll : (d | (hit ? (1ll << 62) : 0ll))};
+        b = look_up_bounds(a, v);
+        if (!a.last_hop && gl == 0) note_bounds(a, i, v, b);
       }
     }
-    const int c = d < (long long)f ? (int)d : f;
-    long long pos = gl;
-    const bool floyd = row_ok && d > (long long)f;
-    if (__ballot(floyd) != 0ull) {
-      // Slot s draws t_s below j_s + 1, j_s = d - f + s; it keeps t_s unless an earlier slot already holds that value, in which
-      // case it takes j_s.  What earlier slots hold is every earlier t, and j_k of every earlier slot k that took its own: so
-      // slot s takes j_s if an earlier t is the same, or if t_s = j_k and slot k took j_k.
-      const long long j = d - f + gl;
-      long long t = 0;
-      if (floyd && gl < f) t = (long long)uniform_below(a.k0, a.k1, v, a.batch, a.hop, gl, (unsigned long long)(j + 1));
-      const bool own = floyd && gl < f;
-      bool taken = earlier_equal<G>((unsigned long long)t, gl) && own;
-      const long long k = t - (d - f);
-      const bool depends = own && k >= 0 && k < gl;
-      if (__ballot(depends) != 0ull) {
-        for (;;) {
-          const unsigned long long bits = group_bits<G>(__ballot(taken), grp_in_wave);
-          const bool more = depends && !taken && ((bits >> (k & 63)) & 1ull) != 0ull;
-          if (__ballot(more) == 0ull) break;
-          taken = taken || more;
-        }
-      }
-      if (floyd) pos = taken ? j : t;
-    }
-    const bool active = row_ok && gl < c;
-    // position p of a node with a slot is served by the cache iff p < cached length (Section IV-B, third
-    // paragraph); beyond it - possible only for the one node cached in part - the host list is read
-    const bool from_host = active && hit && pos >= cached_len;
-    const int n_host = __popcll(group_bits<G>(__ballot(from_host), grp_in_wave));
-    const long long* src = from_host ? a.indices + (a.indptr[v] + pos) : list + (start + pos);
-    int n_lines = 0, n_bound_lines = 0;
-    if (a.count_lines) {
-      // Miss-path traffic of the row in the unit a host link moves (128-byte lines): the distinct lines of
-      // the neighbour ids it reads from graph->indices, and the lines its list bounds in graph->indptr lie in.
-      const bool host_read = active && (from_host || !hit);
-      if (__ballot(host_read) != 0ull) {
-        // (lanes that read nothing there have numbers of their own)
-        const unsigned long long line = host_read ? (unsigned long long)reinterpret_cast<uintptr_t>(src) >> kHostLineLog2 : ~(unsigned long long)gl;
-        const bool leader = host_read & !earlier_equal<G>(line, gl);
-        n_lines = __popcll(group_bits<G>(__ballot(leader), grp_in_wave));
-      }
-      if (row_ok && hit && n_host > 0) n_bound_lines = 1;  // the partly cached node: where its host list starts
-      if (row_ok && !hit && !noted) {  // (a noted row's bounds came from the batch's own note in HBM)
-        const uintptr_t b0 = reinterpret_cast<uintptr_t>(a.indptr + v), b1 = reinterpret_cast<uintptr_t>(a.indptr + v + 1);
-        n_bound_lines = (b0 >> kHostLineLog2) == (b1 >> kHostLineLog2) ? 1 : 2;
-      }
-    }
-    if (active) {
-      const long long u = *(__attribute__((address_space(1))) const long long*)src;
+    const RowDraw r = draw_row<G>(a, a.hop, f, row_ok, v, noted, b, gl, grp_in_wave);
+    if (r.active) {
+      const long long u = *(__attribute__((address_space(1))) const long long*)r.src;
       const int p = (int)(i * f + gl);
       bool candidate;
       const unsigned slot =
@@ -437,17 +467,17 @@ __global__ __launch_bounds__(kBlock, 8) void k_sample_hop(HopArgs a) {
       if (!DIRECT) a.tmp_u[p] = u;  // (a direct table's slot is the id)
       a.tmp_slot[p] = candidate ? (int)slot : -2 - (int)slot;  // the relabel kernel looks at the candidates only
       if (COUNT && a.edge_count) {
-        const long long host_start = hit ? a.indptr[v] : start;
-        atomicAdd(&a.edge_count[host_start + pos], 1u);
+        const long long host_start = r.hit ? a.indptr[v] : r.start;
+        atomicAdd(&a.edge_count[host_start + r.pos], 1u);
       }
     } else if (row_ok && gl < f) {
       a.tmp_slot[(int)(i * f + gl)] = -1;  // no edge here: lets the later kernels read the slots without the row count
     }
     if (row_ok && gl == 0) {
       // the hit flag rides in bit 30 so that the relabel kernel can total the hit statistics
-      a.row_cnt[i] = c | (n_host << kRowHostShift) | (n_lines << kRowLinesShift) |
-                     (n_bound_lines << kRowBoundLinesShift) | (hit ? kRowHitBit : 0);
-      if (COUNT && c > 0) atomicAdd(&a.adj_count[v], (unsigned)c);
+      a.row_cnt[i] = r.c | (r.n_host << kRowHostShift) | (r.n_lines << kRowLinesShift) |
+                     (r.n_bound_lines << kRowBoundLinesShift) | (r.hit ? kRowHitBit : 0);
+      if (COUNT && r.c > 0) atomicAdd(&a.adj_count[v], (unsigned)r.c);
     }
   }
 }
@@ -742,6 +772,183 @@ __global__ __launch_bounds__(kRelabelBlock, 4) void k_relabel_hop(RelabelArgs a)
   }
 }
 
+// The first hops of a batch with few seeds, in one launch: the first workgroup samples and relabels them with a node table of its own in LDS
+// while the others clear the batch's table for the hops behind, the next of which puts this frontier into it (kUnregistered).
+//   Bound by the same chain of reads as a hop's two kernels (seed, slot, bounds, ids), but without their launches, the clear's and the trips
+// to the table in memory: two hops of 16 seeds take 12 us, where the clear and four kernels took 24 and the gaps between them.  A pass,
+// fan-outs 5, 10, 15, before / after: 4 seeds 63.6 / 56.1 us, 16 72.3 / 65.8, 64 (one hop) 89.4 / 86.4, 128 89.5 / 86.5; 2, 4, 8: 64 seeds 66.7 / 59.3.
+//   At most kFirstSlots slots (lanes of all rows' groups) to a hop: with 2,048, two rows to every group, one compute unit's reads take as long as
+// the launches do (256 seeds 100.5 / 100.0 us, over the host link 133.4 / 133.7, two hops 55.3 / 55.5).
+constexpr int kFirstThreads = 1024, kFirstIters = 2, kFirstSlots = 1536, kFirstEntries = 8192, kFirstNodes = kFirstEntries / 2;
+
+struct FirstArgs {
+  HopArgs a;   // what the hops have in common
+  int n_hops;  // made here, all but the batch's last at most
+  int fanout[DCI_MAX_HOPS];
+  long long* blk_indptr[DCI_MAX_HOPS];
+  int* blk_src[DCI_MAX_HOPS];
+  unsigned long long* stat_part[DCI_MAX_HOPS];  // nullptr: no statistics
+  uint4* clear;  // the region to fill with ones
+  size_t clear_n16;
+};
+
+// As table_insert_min, in LDS: at most kFirstNodes different ids come, so half of the entries stay empty.
+__device__ __forceinline__ unsigned first_insert_min(HashEntry* table, unsigned u, unsigned v) {
+  const HashEntry mine = ((HashEntry)u << 32) | v;
+  unsigned slot = (u * 0x9E3779B9u) >> 19;
+  static_assert(kFirstEntries == 1 << 13, "the hash's bits");
+  for (;;) {
+    HashEntry w = table[slot];
+    if (w == kEmptyEntry) {
+      w = atomicCAS(&table[slot], kEmptyEntry, mine);
+      if (w == kEmptyEntry) return slot;
+    }
+    if ((unsigned)(w >> 32) == u) {
+      if ((unsigned)w > v) atomicMin(&table[slot], mine);
+      return slot;
+    }
+    slot = (slot + 1) & (kFirstEntries - 1);
+  }
+}
+
+template <int G, bool COUNT>
+__global__ __launch_bounds__(kFirstThreads) void k_first_hops(FirstArgs fa) {
+  if (blockIdx.x != 0) {
+    const size_t n = (size_t)(gridDim.x - 1) * kFirstThreads;
+    for (size_t q = (size_t)(blockIdx.x - 1) * kFirstThreads + threadIdx.x; q < fa.clear_n16; q += n) fa.clear[q] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    return;
+  }
+  constexpr int kGroups = kFirstThreads / G, kRows = kGroups * kFirstIters, kWaves = kFirstThreads / kWave;
+  static_assert(kRows <= kFirstThreads && kFirstSlots <= kFirstThreads * kFirstIters, "one thread per row in the scan, a lane for every slot");
+  __shared__ HashEntry s_table[kFirstEntries];
+  __shared__ unsigned s_node[kFirstNodes];
+  __shared__ unsigned s_cf[kRows];  // edges | first appearances << 16
+  __shared__ unsigned s_w[kWaves];
+  __shared__ unsigned s_stat[kStatPartWords];
+  const HopArgs& a = fa.a;
+  const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int gl = lane & (G - 1), grp_in_wave = lane / G, grp = tid / G;
+  int n_rows = (int)a.n_seeds, n_noted = 0;
+  const long long seed = tid < n_rows ? a.seeds[tid] : 0;
+  for (int q = tid; q < kFirstEntries; q += kFirstThreads) s_table[q] = kEmptyEntry;
+  __syncthreads();
+  if (tid < n_rows) {
+    a.nodes[tid] = seed;
+    s_node[tid] = (unsigned)seed;
+    (void)first_insert_min(s_table, (unsigned)seed, (unsigned)tid);
+  }
+  if (tid == 0) a.counts[0] = n_rows;
+  for (int h = 0; h < fa.n_hops; ++h) {
+    const int f = fa.fanout[h];
+    if (tid < kStatPartWords) s_stat[tid] = 0;
+    __syncthreads();
+    // each step for all of a group's rows before the next: the reads of a step are on their way together
+    int raw[kFirstIters], look[kFirstIters];
+    unsigned slot[kFirstIters], u[kFirstIters];
+    long long v[kFirstIters], b0[kFirstIters], b1[kFirstIters];
+    RowDraw r[kFirstIters];
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it) {
+      const int i = it * kGroups + grp;
+      v[it] = s_node[i < n_rows ? i : n_rows - 1];
+      look[it] = a.adj_remap && i >= n_noted ? a.adj_remap[v[it]] : -1;
+    }
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it) {
+      const int i = it * kGroups + grp;
+      const long long* const p = i < n_noted ? &a.row_memo[i].x : look[it] >= 0 ? a.c_indptr + look[it] : a.indptr + v[it];
+      if (i < n_rows) {
+        b0[it] = p[0];
+        b1[it] = p[1];
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it) {
+      const int i = it * kGroups + grp;
+      RowBounds b = {0, 0, 0, false};
+      const bool noted = i < n_noted && b1[it] >= 0;
+      if (noted) b = noted_bounds(longlong2{b0[it], b1[it]});
+      else if (i < n_noted) b = look_up_bounds(a, v[it]);
+      else if (i < n_rows) b = row_bounds(a, v[it], look[it] >= 0, b0[it], b1[it]);
+      if (i >= n_noted && i < n_rows && gl == 0) note_bounds(a, i, v[it], b);
+      r[it] = draw_row<G>(a, h, f, i < n_rows, v[it], noted, b, gl, grp_in_wave);
+      raw[it] = r[it].c | (r[it].n_host << kRowHostShift) | (r[it].n_lines << kRowLinesShift) | (r[it].n_bound_lines << kRowBoundLinesShift) |
+                (r[it].hit ? kRowHitBit : 0);
+    }
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it)
+      if (r[it].active) u[it] = (unsigned)*(__attribute__((address_space(1))) const long long*)r[it].src;
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it) {
+      const int i = it * kGroups + grp;
+      if (r[it].active) {
+        slot[it] = first_insert_min(s_table, u[it], kTentative | (unsigned)(i * f + gl));
+        if (COUNT && a.edge_count) atomicAdd(&a.edge_count[(r[it].hit ? a.indptr[v[it]] : r[it].start) + r[it].pos], 1u);
+      }
+      if (COUNT && i < n_rows && gl == 0 && r[it].c > 0) atomicAdd(&a.adj_count[v[it]], (unsigned)r[it].c);
+    }
+    __syncthreads();
+    unsigned first_bits = 0;
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it) {
+      const int i = it * kGroups + grp, c = raw[it] & kRowCntMask;
+      const bool first = gl < c && (unsigned)s_table[slot[it]] == (kTentative | (unsigned)(i * f + gl));
+      const unsigned long long bits = group_bits<G>(__ballot(first), grp_in_wave);
+      if (first) first_bits |= 1u << it;
+      if (gl == 0) {
+        s_cf[i] = (unsigned)c | (unsigned)__popcll(bits) << 16;
+        if (fa.stat_part[h] && raw[it] != 0) {
+          if (raw[it] & kRowHitBit) {
+            atomicAdd(&s_stat[0], 1u);
+            atomicAdd(&s_stat[1], (unsigned)(c - ((raw[it] >> kRowHostShift) & 0xFF)));
+          }
+          atomicAdd(&s_stat[2], (unsigned)((raw[it] >> kRowLinesShift) & kRowLinesMask));
+          atomicAdd(&s_stat[3], (unsigned)((raw[it] >> kRowBoundLinesShift) & kRowBoundLinesMask));
+        }
+      }
+    }
+    __syncthreads();
+    const unsigned cf = tid < kRows ? s_cf[tid] : 0u;
+    const unsigned incl = (unsigned)wave_scan_dpp((int)cf);
+    if (lane == kWave - 1) s_w[wave] = incl;
+    __syncthreads();
+    unsigned off = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) off += s_w[w];
+      tot += s_w[w];
+    }
+    const unsigned row_cf = off + incl;
+    if (tid < kRows) s_cf[tid] = row_cf - cf;
+    if (tid < n_rows) fa.blk_indptr[h][tid + 1] = row_cf & 0xFFFFu;
+    if (tid == 0) {
+      fa.blk_indptr[h][0] = 0;
+      a.counts[h + 1] = n_rows + (int)(tot >> 16);
+      a.counts[DCI_MAX_HOPS + 1 + h] = tot & 0xFFFFu;
+    }
+    if (fa.stat_part[h] && tid < kStatPartWords) fa.stat_part[h][tid] = s_stat[tid];
+    __syncthreads();
+    // first appearances take the next local ids, in (row, slot) order
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it) {
+      const bool first = (first_bits >> it) & 1u;
+      const unsigned long long bits = group_bits<G>(__ballot(first), grp_in_wave);
+      if (first) {
+        const unsigned new_id = (unsigned)n_rows + (s_cf[it * kGroups + grp] >> 16) + (unsigned)__popcll(bits & ((1ull << gl) - 1ull));
+        a.nodes[new_id] = (long long)u[it];
+        s_node[new_id] = u[it];
+        reinterpret_cast<unsigned*>(s_table)[2 * slot[it]] = new_id;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kFirstIters; ++it)
+      if (gl < (raw[it] & kRowCntMask)) fa.blk_src[h][(s_cf[it * kGroups + grp] & 0xFFFFu) + gl] = (int)(unsigned)s_table[slot[it]];
+    n_noted = n_rows;
+    n_rows = __builtin_amdgcn_readfirstlane(n_rows + (int)(tot >> 16));
+  }
+}
+
 __global__ void k_add_u64(unsigned long long* p, unsigned long long v) { atomicAdd(p, v); }
 
 // ---- host side ----------------------------------------------------------------------------------
@@ -875,22 +1082,16 @@ static int grid_for_rows(const dci_ctx* ctx, int64_t rows, int groups_per_block)
   return (int)blocks;
 }
 
+// frontier: as for k_sample_hop
 template <int G, bool DIRECT>
-static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra, bool count, int64_t cap_rows) {
-  const int grid = grid_for_rows(ctx, cap_rows, kBlock / G) + (ha.hop > 0 ? ha.n_write_blocks : 0);
+static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra, bool count, int frontier, int64_t cap_rows) {
+  const int grid = grid_for_rows(ctx, cap_rows, kBlock / G) + ha.n_write_blocks;
   {
     Timed t(ctx, DCI_K_SAMPLE);
-    if (ha.hop == 0) {
-      if (count)
-        hipLaunchKernelGGL((k_sample_hop<G, true, true, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
-      else
-        hipLaunchKernelGGL((k_sample_hop<G, false, true, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
-    } else {
-      if (count)
-        hipLaunchKernelGGL((k_sample_hop<G, true, false, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
-      else
-        hipLaunchKernelGGL((k_sample_hop<G, false, false, DIRECT>), dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
-    }
+    auto* const kernel = frontier == kSeeds          ? (count ? k_sample_hop<G, true, kSeeds, DIRECT> : k_sample_hop<G, false, kSeeds, DIRECT>)
+                         : frontier == kUnregistered ? (count ? k_sample_hop<G, true, kUnregistered, DIRECT> : k_sample_hop<G, false, kUnregistered, DIRECT>)
+                                                     : (count ? k_sample_hop<G, true, kRegistered, DIRECT> : k_sample_hop<G, false, kRegistered, DIRECT>);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, ctx->stream, ha);
   }
   DCI_LAUNCH_CHECK(ctx);
   {
@@ -910,15 +1111,36 @@ static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra
   return DCI_OK;
 }
 
-// Enqueues the sampling of one batch: one clear, two kernels per hop, one closing kernel.
+template <int G>
+static void launch_first(dci_ctx* ctx, const FirstArgs& fa, bool count) {
+  const int64_t want = (int64_t)((fa.clear_n16 + kFirstThreads - 1) / kFirstThreads), most = (int64_t)ctx->num_cus * 2;
+  hipLaunchKernelGGL((count ? k_first_hops<G, true> : k_first_hops<G, false>), dim3((unsigned)(1 + (want < most ? want : most))),
+                     dim3(kFirstThreads), 0, ctx->stream, fa);
+}
+
+// How many of the batch's hops k_first_hops makes.
+static int first_hops(const dci_ctx* ctx, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, const dci_blocks* out, int* group) {
+  int n = 0, g = 8;
+  if (n_seeds < 1 || ctx->test_first_ticket != 0) return 0;
+  for (int32_t h = 0; h + 1 < n_hops; ++h) {
+    if (group_for(fanouts[h]) > g) g = group_for(fanouts[h]);
+    if (out->cap_rows[h] * g > kFirstSlots || out->cap_rows[h + 1] > kFirstNodes) break;
+    n = h + 1;
+    *group = g;
+  }
+  return n;
+}
+
+// Enqueues the sampling of one batch: one clear, two kernels per hop (or one kernel for the clear and the first hops), one closing kernel.
 // `adj_count` non-null turns on the pre-sampling counters.  left (nullable; neither counters nor statistics then): the closing is left
 // to the caller.
 static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* cache, const int64_t* seeds,
                             int64_t n_seeds, uint64_t batch_index, const int32_t* fanouts, int32_t n_hops,
                             uint64_t rng_seed, const dci_blocks* out, const SampleWs& ws, uint64_t* stats,
                             uint32_t* feat_count, uint32_t* adj_count, uint32_t* edge_count, CloseArgs* left = nullptr) {
-  int rc;
-  {
+  int rc = DCI_OK, first_group = 8;
+  const int n_first = first_hops(ctx, n_seeds, fanouts, n_hops, out, &first_group);
+  if (n_first == 0) {
     Timed t(ctx, DCI_K_TABLE_CLEAR);
     rc = fill_bytes(ctx, ws.table, ws.clear_bytes, 0xFFFFFFFFu);
   }
@@ -926,7 +1148,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
   long long* counts = reinterpret_cast<long long*>(out->counts);
   long long* nodes = reinterpret_cast<long long*>(out->nodes);
   const bool count = adj_count != nullptr;
-  for (int32_t h = 0; h < n_hops; ++h) {
+  for (int32_t h = n_first > 0 ? n_first - 1 : 0; h < n_hops; ++h) {
     HopArgs ha;
     ha.seeds = reinterpret_cast<const long long*>(seeds);
     ha.n_seeds = n_seeds;
@@ -953,16 +1175,40 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ha.last_node = (unsigned)(g->num_nodes - 1);
     ha.adj_count = adj_count;
     ha.edge_count = edge_count;
+    const bool first = h < n_first, finished = h <= n_first;  // the hop is k_first_hops'; the hop before has its edge ids
     ha.prev_fanout = h > 0 ? fanouts[h - 1] : 1;
     ha.prev_tmp_slot = ws.tmp_slot[(h + 1) & 1];
     ha.prev_blk_indptr = h > 0 ? reinterpret_cast<const long long*>(out->blk_indptr[h - 1]) : nullptr;
     ha.prev_blk_src = h > 0 ? out->blk_src[h - 1] : nullptr;
-    ha.n_write_blocks = h > 0 ? grid_for_rows(ctx, out->cap_rows[h - 1] * fanouts[h - 1], kBlock * 4) : 0;
+    ha.n_write_blocks = !finished ? grid_for_rows(ctx, out->cap_rows[h - 1] * fanouts[h - 1], kBlock * 4) : 0;
     ha.batch_flag = ws.batch_flag;
     ha.count_lines = stats ? 1 : 0;
     ha.row_memo = ws.row_memo;
     ha.last_hop = h == n_hops - 1 ? 1 : 0;
     ha.cap_rows = out->cap_rows[h];
+    if (first) {
+      FirstArgs fa;
+      fa.a = ha;
+      fa.n_hops = n_first;
+      for (int32_t k = 0; k < n_first; ++k) {
+        fa.fanout[k] = fanouts[k];
+        fa.blk_indptr[k] = reinterpret_cast<long long*>(out->blk_indptr[k]);
+        fa.blk_src[k] = out->blk_src[k];
+        fa.stat_part[k] = stats ? ws.stat_part[k] : nullptr;
+      }
+      fa.clear = reinterpret_cast<uint4*>(ws.table);
+      fa.clear_n16 = ws.clear_bytes / 16;  // (16-byte words: carve_sample_ws)
+      Timed t(ctx, DCI_K_SAMPLE);
+      switch (first_group) {
+        case 8: launch_first<8>(ctx, fa, count); break;
+        case 16: launch_first<16>(ctx, fa, count); break;
+        case 32: launch_first<32>(ctx, fa, count); break;
+        default: launch_first<64>(ctx, fa, count); break;
+      }
+      DCI_LAUNCH_CHECK(ctx);
+      continue;
+    }
+    const int frontier = h == 0 ? kSeeds : h == n_first ? kUnregistered : kRegistered;
     RelabelArgs ra;
     ra.counts = counts;
     ra.hop = h;
@@ -985,10 +1231,10 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     // runs so that the (empty) sizes get written
     const int64_t rows = out->cap_rows[h];
     switch (group_for(fanouts[h])) {
-      case 8: rc = (ws.direct ? launch_hop<8, true> : launch_hop<8, false>)(ctx, ha, ra, count, rows); break;
-      case 16: rc = (ws.direct ? launch_hop<16, true> : launch_hop<16, false>)(ctx, ha, ra, count, rows); break;
-      case 32: rc = (ws.direct ? launch_hop<32, true> : launch_hop<32, false>)(ctx, ha, ra, count, rows); break;
-      default: rc = (ws.direct ? launch_hop<64, true> : launch_hop<64, false>)(ctx, ha, ra, count, rows); break;
+      case 8: rc = (ws.direct ? launch_hop<8, true> : launch_hop<8, false>)(ctx, ha, ra, count, frontier, rows); break;
+      case 16: rc = (ws.direct ? launch_hop<16, true> : launch_hop<16, false>)(ctx, ha, ra, count, frontier, rows); break;
+      case 32: rc = (ws.direct ? launch_hop<32, true> : launch_hop<32, false>)(ctx, ha, ra, count, frontier, rows); break;
+      default: rc = (ws.direct ? launch_hop<64, true> : launch_hop<64, false>)(ctx, ha, ra, count, frontier, rows); break;
     }
     if (rc != DCI_OK) return rc;
   }
@@ -1021,7 +1267,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     sf.n_hops = n_hops;
     for (int32_t k = 0; k < DCI_MAX_HOPS; ++k) {
       sf.part[k] = k < n_hops ? ws.stat_part[k] : nullptr;
-      sf.tile_rows[k] = k < n_hops ? (kRelabelBlock / group_for(fanouts[k])) * tile_iters_for(ctx, k, out->cap_rows[k], fanouts[k]) : 1;
+      sf.tile_rows[k] = k < n_first ? kFirstThreads : k < n_hops ? (kRelabelBlock / group_for(fanouts[k])) * tile_iters_for(ctx, k, out->cap_rows[k], fanouts[k]) : 1;
     }
     Timed t(ctx, feat_count ? DCI_K_COUNT_NODES : DCI_K_WRITE_SRC);
     hipLaunchKernelGGL(ws.direct ? k_write_src<true> : k_write_src<false>, dim3(close.wgs), dim3(kBlock), 0, ctx->stream, close, sf,

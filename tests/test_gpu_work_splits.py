@@ -5,6 +5,7 @@ import torch
 
 import oracle
 import synth
+from tests.test_gpu_parity import _expected_sampler_traffic
 
 pytestmark = pytest.mark.gpu
 
@@ -119,3 +120,57 @@ def test_tiles_of_the_frontier_scan(env, fanout, rows_per_tile, tiles, hashed):
         gu.assert_blocks_equal(got, oracle.sample_khop(indptr, indices, seeds, extra, (fanout, 2), 5))
         s = gu.stats_dict(ctx, stats)
         assert s["edges_sampled"] == sum(got["n_edges"]) == s["adj_edge_misses"] and s["adj_node_misses"] == sum(got["n_nodes"][:2])
+
+
+# Batches whose first hops are one kernel: the last number of seeds and the first beyond it for each width of a lane group (1,536 slots: 192
+# rows of 8, ... 24 of 64), two and three such hops, with the hop behind them in the same batch; every kind of list (cached, not, in part).
+@pytest.mark.parametrize("n_seeds,fanouts", [(1, (1, 1)), (192, (8, 3)), (193, (8, 3)), (96, (9, 2)), (97, (9, 2)), (48, (17, 2)), (49, (32, 1)),
+                                             (24, (64, 2)), (25, (33, 2)), (16, (5, 10, 3)), (17, (5, 10, 3)), (5, (3, 3, 3, 2)), (3, (2, 40, 2)),
+                                             (127, (2, 4, 8))])
+@pytest.mark.parametrize("hashed", [False, True])
+def test_first_hops_of_small_batches(env, n_seeds, fanouts, hashed):
+    dci, gu, ctx = env["dci"], env["gu"], env["ctx"]
+    N = 400_000 if hashed else 1_500
+    rng = np.random.default_rng(n_seeds)
+    degree = np.zeros(N, dtype=np.int64)
+    degree[:1_500] = rng.integers(0, 2 * max(fanouts) + 3, 1_500)
+    degree[7] = 500  # in part in the cache
+    indptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    E = int(indptr[-1])
+    indices = np.where(rng.random(E) < 0.1, rng.integers(0, 9, E), rng.integers(0, 1_500, E)).astype(np.int64)
+    cached = np.sort(rng.permutation(np.arange(8, 1_500))[:600])
+    remap = np.full(N, -1, dtype=np.int32)
+    remap[cached], remap[7] = np.arange(600), 600
+    lists = [indices[indptr[v]:indptr[v + 1]] for v in cached] + [indices[indptr[7]:indptr[7] + 200]]
+    c_indptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    cache = gu.upload_cache(remap, c_indptr, np.concatenate(lists), np.full(N, -1), np.zeros((0, 1), dtype=np.float32), 7, 500)
+    g = gu.make_graph(indptr, indices, None)
+    blk = dci.Blocks(ctx, N, n_seeds, fanouts)
+    for batch in range(2):
+        seeds = rng.permutation(1_500)[:n_seeds].astype(np.int64)
+        seeds[0] = 7
+        want = oracle.sample_khop(indptr, indices, seeds, batch, fanouts, 3)
+        stats, plain = gu.new_stats(), gu.new_stats()
+        dci.dci_sample_khop(ctx, g, cache, gu.dev(seeds), batch, fanouts, 3, blk, stats)
+        gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), want)
+        st, n_edges = gu.stats_dict(ctx, stats), int(sum(want.n_edges))
+        rows = np.concatenate([want.nodes[:int(want.n_nodes[h])] for h in range(len(fanouts))])
+        edges = np.concatenate([np.diff(want.blk_indptr[h]) for h in range(len(fanouts))])
+        whole = (remap[rows] >= 0) & (rows != 7)
+        assert st["adj_node_hits"] == (remap[rows] >= 0).sum() and st["adj_node_misses"] == (remap[rows] < 0).sum()
+        assert edges[whole].sum() <= st["adj_edge_hits"] <= edges[whole].sum() + edges[rows == 7].sum()
+        assert st["adj_edge_hits"] + st["adj_edge_misses"] == st["edges_sampled"] == n_edges and st["input_nodes"] == len(want.nodes)
+        dci.dci_sample_khop_static(ctx, g, None, gu.dev(seeds), batch, fanouts, 3, blk, plain)
+        gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), want)
+        st = gu.stats_dict(ctx, plain)
+        none = np.full(N, -1)
+        assert (st["bytes_hbm"], st["bytes_host"], st["lines_bounds"], st["lines_ids"]) == _expected_sampler_traffic(
+            want, fanouts, indptr, none, g.indptr.data_ptr(), g.indices.data_ptr())
+    seeds = rng.permutation(1_500)[:2 * n_seeds + 1].astype(np.int64)
+    feat, adj = (torch.zeros(N, dtype=torch.int32, device="cuda") for _ in range(2))
+    edge = torch.zeros(E, dtype=torch.int32, device="cuda")
+    dci.dci_presample_count(ctx, g, None, gu.dev(seeds), n_seeds, 0, 3, 9, fanouts, 3, feat, adj, edge)
+    ctx.sync()
+    f, a, e, _ = oracle.presample_count(indptr, indices, seeds, n_seeds, 3, fanouts, 3, 9)
+    for got, counted in ((feat, f), (adj, a), (edge, e)):
+        assert np.array_equal(got.cpu().numpy().view(np.uint32), counted)
