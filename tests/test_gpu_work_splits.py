@@ -174,3 +174,37 @@ def test_first_hops_of_small_batches(env, n_seeds, fanouts, hashed):
     f, a, e, _ = oracle.presample_count(indptr, indices, seeds, n_seeds, 3, fanouts, 3, 9)
     for got, counted in ((feat, f), (adj, a), (edge, e)):
         assert np.array_equal(got.cpu().numpy().view(np.uint32), counted)
+
+
+# The selective gather's rounds of 32 to 256 looked-up rows to a workgroup, which follow from how many rows there are for its workgroups:
+# a single row, a few, many; some cached, none, all.
+@pytest.mark.parametrize("n", [1, 31, 33, 2_000, 150_000, 300_000, 600_000])
+@pytest.mark.parametrize("share", [0.3, None, 1.0])
+def test_rounds_of_the_selective_gather(env, n, share):
+    dci, gu, ctx = env["dci"], env["gu"], env["ctx"]
+    F, n_dense = 5, (n + 6) // 7
+    g_ = torch.Generator().manual_seed(n)
+    feat = torch.randn(n, F, generator=g_)
+    g = dci.Graph(torch.zeros(n + 1, dtype=torch.int64).cuda(), torch.zeros(1, dtype=torch.int64).cuda(), feat.cuda())
+    ids, remap, cache = torch.randperm(n, generator=g_), torch.full((n,), -1, dtype=torch.int32), None
+    if share is not None:
+        rows = torch.randperm(n, generator=g_)[:max(1, int(n * share))]
+        remap[rows] = torch.arange(len(rows), dtype=torch.int32)
+        cache = dci.Cache.from_arrays(torch.full((n,), -1, dtype=torch.int32).cuda(), torch.zeros(1, dtype=torch.int64).cuda(),
+                                      torch.zeros(0, dtype=torch.int64).cuda(), remap.cuda(), feat[rows].cuda())
+    blk = dci.Blocks(ctx, n, n_dense, (6,))
+    blk.counts.zero_()
+    blk.counts[0], blk.counts[1] = n_dense, n
+    blk.nodes[:n] = ids.cuda()
+    blk.blk_indptr[0].zero_()
+    x = torch.full((max(n, blk.cap_nodes[1]), F), -7.0, device="cuda")
+    w, b = torch.zeros(F, 4, device="cuda"), torch.zeros(4, device="cuda")
+    y = torch.empty(blk.cap_nodes[0], 4, device="cuda")
+    stats = gu.new_stats()
+    dci.dci_gather_forward(ctx, g, cache, blk, x, 0, [w], [w], [b], y, stats)
+    hit = remap[ids] >= 0
+    st = gu.stats_dict(ctx, stats)
+    copied = ~hit | (torch.arange(n) < n_dense)
+    assert (st["feat_hits"], st["feat_misses"], st["rows_copied"]) == (int(hit.sum()), int((~hit).sum()), int(copied.sum()))
+    got = x[:n].cpu()
+    assert torch.equal(got[copied], feat[ids][copied]) and bool((got[~copied] == -7.0).all())
