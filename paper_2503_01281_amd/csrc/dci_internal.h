@@ -47,6 +47,15 @@ namespace dci {
 constexpr int kWave = 64;
 constexpr size_t kAlign = 256;
 
+// The frontier scan numbers the tiles of a hop by tickets, so that a tile waits only for workgroups that are running already.  A hop of few
+// tiles numbers them by workgroup instead, which spares it the ticket (1 us); every tile that another one waits for must then get to run
+// whatever the others do.  Only workgroups that wait could keep it from that (all others end by themselves), so they must leave it a
+// place.  A compute unit has kRelabelPerCu places; kScansAtOnce scans may be on the card, or on the part of it that the process sees, at a
+// time, those of other processes among them (16 processes with four hardware queues each).  That makes 8 tiles with 256 compute units, and
+// with 32 of them one, which waits for nobody.
+constexpr int kRelabelPerCu = 2, kScansAtOnce = 64;
+constexpr unsigned unticketed_tiles(int num_cus) { return (unsigned)(num_cus * kRelabelPerCu / kScansAtOnce); }
+
 inline int32_t fail(dci_ctx* ctx, int32_t code, const char* fmt, ...) {
   if (ctx) {
     va_list ap;

@@ -501,10 +501,7 @@ constexpr int kTileItersMax = 8;
 // per tile / microseconds, direct table: 4 k rows (10 sources) 32 / 6.6, 64 / 6.5, 128 / 7.2, 256 / 8.7; 18 k (15) 32 / 16.2, 64 / 10.7, 128 / 8.5, 256 /
 // 9.1; 53 k (15) 64 / 25, 128 / 17.4, 256 / 13.9, and with 1,024 threads 512 / 15.8.
 constexpr int kRelabelBlock = 512;
-// Up to this many tiles are numbered by their workgroup instead of by tickets.  A tile waits for smaller numbers only, so all of them must
-// get to run; workgroups of other kernels end by themselves, and at least two of these fit on each of 256 compute units (launch bounds), so
-// 16 from each of 32 launches (more than a process has hardware queues) are on the card together.
-constexpr long long kUnticketedTiles = 16;
+static_assert(kRelabelBlock == 4 * kWave * 2, "a workgroup is two wavefronts to each of a compute unit's four SIMDs");
 constexpr unsigned long long kStInvalid = 3ull, kStAggregate = 1ull, kStInclusive = 2ull;
 // The look-back polls at most dci_ctx::relabel_spin_limit times (default 2^24: far beyond any real wait, ends a wedged launch).
 
@@ -531,10 +528,11 @@ struct RelabelArgs {
   unsigned* batch_flag;   // set to 0 by a tile that gives up; != kBatchOk on entry: do nothing
   unsigned spin_limit;    // polls of the look-back before a tile gives up
   unsigned first_ticket;  // tiles are numbered from here (0 except under the failure-handling test hook)
+  unsigned unticketed;    // up to this many tiles are numbered by their workgroup (unticketed_tiles)
 };
 
 template <int G, int kTileIters, bool DIRECT>
-__global__ __launch_bounds__(kRelabelBlock, 4) void k_relabel_hop(RelabelArgs a) {
+__global__ __launch_bounds__(kRelabelBlock, 2 * kRelabelPerCu) void k_relabel_hop(RelabelArgs a) {
   constexpr int kGroups = kRelabelBlock / G;
   constexpr int TR = kGroups * kTileIters;  // rows per tile, at most kRelabelBlock
   constexpr int kWaves = kRelabelBlock / kWave;
@@ -560,7 +558,7 @@ __global__ __launch_bounds__(kRelabelBlock, 4) void k_relabel_hop(RelabelArgs a)
   if (takers < 1) takers = 1;  // an empty frontier (or a test hook beyond it) still needs one workgroup
   if ((long long)blockIdx.x >= takers) return;
   unsigned tile = blockIdx.x + a.first_ticket;
-  if (takers > kUnticketedTiles) {
+  if (takers > (long long)a.unticketed) {
     if (tid == 0) s_tile = atomicAdd(a.ticket, 1u) + 1u + a.first_ticket;
     __syncthreads();
     tile = s_tile;
@@ -1227,6 +1225,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ra.batch_flag = ws.batch_flag;
     ra.spin_limit = ctx->relabel_spin_limit;
     ra.first_ticket = ctx->test_first_ticket;
+    ra.unticketed = unticketed_tiles(ctx->num_cus);
     // launch shapes follow the frontier bound of this call; with zero seeds one workgroup still
     // runs so that the (empty) sizes get written
     const int64_t rows = out->cap_rows[h];
