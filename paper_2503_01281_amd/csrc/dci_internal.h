@@ -232,7 +232,6 @@ struct LayerPlan {
   int64_t cap_rows;
   void* w_split;
   int cols, rs;  // k_sage_layer: multiplying wavefronts side by side, and how many of them share columns (each takes a part of the rows)
-  int n_waves() const { return (N + 16 * C * cols - 1) / (16 * C * cols) * cols; }
 };
 // Plans every layer of a forward pass; scratch is where the weights' parts may
 // go.  false: none of the layers is for these kernels, because an input is too narrow or the scratch too small.

@@ -430,15 +430,17 @@ __global__ __launch_bounds__(LayerShape<W>::kThreads, 4) void k_sage_layer(Layer
     // ---- multiplies
     constexpr int kPair = C < 2 ? 1 : 2;
     typedef __attribute__((address_space(1))) const u32x4* gw_t;
-    // the parts of the weights: [operand][k step][column group][wavefront][tile][part][lane]
-    constexpr size_t kGroup = (size_t)kCols * C * 3 * 1024;
-    const size_t w_step = a.n_col_groups * kGroup, w_op = w_step * ((D + 31) / 32);
+    // the parts of the weights: [operand][k step][wavefront, of all column groups][tile][part][lane]
+    // (wavefronts whose columns are all past the last one only hand the buffers back)
+    constexpr size_t kPieceBytes = (size_t)C * 3 * 1024;
+    const int my_wave = cg * kCols + wave % kCols;
+    const bool has_cols = my_wave * 16 * C < a.N;
+    const size_t w_step = parts_pieces(a.N, C) * kPieceBytes, w_op = w_step * ((D + 31) / 32);
     const int t0 = wave / kCols;
-    const char* const w0 = reinterpret_cast<const char*>(a.w_split) + (size_t)(wave % kCols) * C * 3 * 1024;
-    const char* const w_base = w0 + cg * kGroup;
+    const char* const w_base = reinterpret_cast<const char*>(a.w_split) + my_wave * kPieceBytes;
     u32x4 b[2][kPair][3];
     int buf = 0, lap = 0, it = 0;
-    if (h_begin < h_end) {
+    if (h_begin < h_end && has_cols) {
 #pragma unroll
       for (int c = 0; c < kPair; ++c)
 #pragma unroll
@@ -481,9 +483,12 @@ __global__ __launch_bounds__(LayerShape<W>::kThreads, 4) void k_sage_layer(Layer
                           lane >> 4, acc);
     };
     long long h = h_begin;
-    for (; h + 1 < h_end; h += 2, ++it) tile(std::integral_constant<int, NT>(), h);
+    for (; h + 1 < h_end; h += 2, ++it) {
+      if (has_cols) tile(std::integral_constant<int, NT>(), h);
+      else tile(std::integral_constant<int, 0>(), h);
+    }
     if (h < h_end) {  // half a tile is left
-      if (t0 == 0) tile(std::integral_constant<int, 1>(), h);
+      if (has_cols && t0 == 0) tile(std::integral_constant<int, 1>(), h);
       else tile(std::integral_constant<int, 0>(), h);
     }
     __syncthreads();
@@ -709,7 +714,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_sage_layer_small(LayerArgs a)
 constexpr int64_t kSmallReads = 10000, kFewRowsPerCu = 40;
 
 static size_t split_bytes(const LayerPlan& p, int ops) {
-  return (size_t)ops * ((p.D + 31) / 32) * p.n_waves() * p.C * 3 * 1024;
+  return (size_t)ops * ((p.D + 31) / 32) * parts_pieces(p.N, p.C) * p.C * 3 * 1024;
 }
 
 // -1 not one of these kernels, 0 k_sage_layer_small, 1 k_sage_layer.  rows: about what a batch has; fan: the longest list.
@@ -764,9 +769,9 @@ SplitArgs layers_split_args(int32_t model, int32_t first, int32_t n_layers, cons
     sa.D[sa.n] = p.D;
     sa.N[sa.n] = p.N;
     sa.C[sa.n] = p.C;
-    sa.waves[sa.n] = p.n_waves();
+    sa.waves[sa.n] = parts_pieces(p.N, p.C);
     sa.ops[sa.n] = gcn ? 1 : 2;
-    sa.wgs += (int)(split_bytes(p, sa.ops[sa.n]) / (4 * 3 * 1024));  // four tiles to a workgroup
+    sa.wgs += (int)((split_bytes(p, sa.ops[sa.n]) / (3 * 1024) + 3) / 4);  // four tiles to a workgroup
     ++sa.n;
   }
   return sa;
@@ -794,7 +799,7 @@ int32_t layer_launch(dci_ctx* ctx, const LayerPlan& plan, const LayerArgs& args)
     DCI_LAUNCH_CHECK(ctx);
     return DCI_OK;
   }
-  a.n_col_groups = plan.n_waves() / plan.cols;
+  a.n_col_groups = (a.N + 16 * plan.C * plan.cols - 1) / (16 * plan.C * plan.cols);
   const int W = plan.cols * plan.rs;
   // one workgroup (two of the narrow shape) to a compute unit, as many for every column group, in eights for the XCDs; no more than there are
   // halves of tiles

@@ -36,6 +36,10 @@ __device__ __forceinline__ Split2 split2(float x0, float x1) {
 // 2^104, a sum of 2^80) shows as an infinity.
 constexpr float kScale = 16777216.f, kUnscale = 1.f / (16777216.f * 16777216.f);
 
+// Pieces of 16 C columns that the parts of N columns are: whole blocks of 64 columns, and no more, whatever the number of wavefronts that
+// read them, because a layer whose parts do not fit into the scratch takes the whole pass to two kernels a layer.
+__host__ __device__ constexpr int parts_pieces(int N, int C) { return (N + 63) / 64 * 4 / C; }
+
 // The weights of a forward pass's layers as parts, in the order in which k_sage_layer's lanes hold them.
 struct SplitArgs {
   int n = 0;                 // layers
@@ -44,7 +48,7 @@ struct SplitArgs {
   const float* w[DCI_MAX_HOPS][2];  // self, neighbour (GCN: the one matrix in the first place)
   void* out[DCI_MAX_HOPS];
   int D[DCI_MAX_HOPS], N[DCI_MAX_HOPS], C[DCI_MAX_HOPS], ops[DCI_MAX_HOPS];
-  int waves[DCI_MAX_HOPS];  // column tiles of 16 C columns, all workgroups' together
+  int waves[DCI_MAX_HOPS];  // pieces of 16 C columns
 };
 
 // Workgroup `block` (256 threads) of SplitArgs::wgs.
@@ -53,7 +57,7 @@ __device__ __forceinline__ void split_weights(const SplitArgs& a, int block) {
   while (l + 1 < a.n && block >= a.first[l + 1]) ++l;
   const int D = a.D[l], N = a.N[l], C = a.C[l];
   const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
-  // one wavefront per tile of 32 rows by 16 columns: [operand][k step][column group and wavefront][tile]
+  // one wavefront per tile of 32 rows by 16 columns: [operand][k step][piece][tile]
   const int id = (block - a.first[l]) * 4 + (int)(threadIdx.x >> 6);
   const int n32 = (D + 31) / 32, n_w = a.waves[l];
   const int c = id % C, w = id / C % n_w, ks = id / C / n_w % n32, op = id / C / n_w / n32;

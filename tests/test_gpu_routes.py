@@ -202,6 +202,16 @@ def test_parts_fit_where_the_aggregated_rows_would_be_or_not(env, cap, kernels):
     assert _close(got, want, size, (3,), (4, 256))
 
 
+@pytest.mark.parametrize("cap,N,kernels", [
+    # parts of 2 x 6 x 192 weights for 130 and 192 outputs (73,728 bytes) and of 2 x 6 x 320 for 300, 24 bytes to a row; too little for all the
+    # columns that the wavefronts of a column group could have (256, 256, 512)
+    (3400, 130, 1), (2400, 130, 2), (3400, 192, 1), (2900, 192, 2), (5120, 300, 1), (4900, 300, 2)])
+def test_parts_take_whole_blocks_of_64_columns_and_no_more(env, cap, N, kernels):
+    got, want, size, n = _forward(env, cap, (3,), (cap - 100, cap), (6, N), 0, cap + N)
+    assert n["mean_in"] + n["linear_in"] == kernels
+    assert _close(got, want, size, (3,), (6, N))
+
+
 @pytest.mark.parametrize("model", [0, 2])
 @pytest.mark.parametrize("N,cap,rows", [(64, 10_000, 20_011), (100, 10_000, 20_011), (600, 10_000, 20_011),   # 16, 32, 64 columns
                                         (256, 2000, 8000), (500, 2000, 8000)])                             # 16, 32
