@@ -212,7 +212,7 @@ class Context:
             raise DciError(rc, self.lib.dci_last_error(self._h).decode())
 
     def ensure_workspace(self, nbytes: int):
-        if self._ws is None or self._ws.numel() < nbytes:
+        if self._ws is None or self._ws.numel() - 256 < nbytes:  # (256: for the alignment)
             self.sync()
             self._ws = torch.empty(int(nbytes) + 256, dtype=torch.uint8, device=self.device)
             base = self._ws.data_ptr()

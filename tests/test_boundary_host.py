@@ -99,3 +99,31 @@ def test_the_binding_has_no_fallback():
     for fn in ("binding.py", "__init__.py"):
         src = open(os.path.join(ROOT, "paper_2503_01281_amd", fn)).read()
         assert "oracle" not in src and "numpy" not in src
+
+
+def test_a_workspace_grows_for_a_need_within_its_alignment():
+    """What the library is told it has is 256 bytes less than what was allocated; a need between the two asks for a new one."""
+    import torch
+
+    import paper_2503_01281_amd as dci
+
+    class Lib:
+        told = []
+
+        def dci_sync(self, h):
+            return 0
+
+        def dci_set_workspace(self, h, base, nbytes):
+            assert base % 256 == 0
+            self.told.append(nbytes)
+            return 0
+
+        def dci_destroy(self, h):
+            pass
+
+    ctx = dci.Context.__new__(dci.Context)
+    ctx.lib, ctx._h, ctx._ws, ctx.device = Lib(), C.c_void_p(), None, torch.device("cpu")
+    for need in (1000, 1000, 999, 1001, 1256, 1257, 5000):
+        ctx.ensure_workspace(need)
+        assert Lib.told[-1] >= need
+    assert len(Lib.told) == 5 and Lib.told[0] == 1000
