@@ -494,10 +494,14 @@ class Lane:
         L = len(fanouts)
         lib = self.ctx.lib
         cap_rows = (C.c_int64 * DCI_MAX_HOPS)(*([self.blocks.cap_nodes[h] for h in range(L)] + [0] * (DCI_MAX_HOPS - L)))
-        # room for both at a time lets dci_infer_batches run parts of one stage in another's launches
-        need = max(lib.dci_sample_workspace_bytes(graph.num_nodes, batch_size, _i32_array(fanouts), L) +
-                   lib.dci_gather_forward_workspace_bytes(self.blocks.cap_nodes[L], cap_rows, L, _i32_array(dims)), 1 << 20)
-        self.ctx.ensure_workspace(need)
+        sample = lib.dci_sample_workspace_bytes(graph.num_nodes, batch_size, _i32_array(fanouts), L)
+        model = lib.dci_gather_forward_workspace_bytes(self.blocks.cap_nodes[L], cap_rows, L, _i32_array(dims))
+        # Room for both at a time lets dci_infer_batches run parts of one stage in another's launches; where the GPU has none left, room
+        # for one at a time is all that it needs.
+        try:
+            self.ctx.ensure_workspace(max(sample + model, 1 << 20))
+        except torch.OutOfMemoryError:
+            self.ctx.ensure_workspace(max(sample, model, 1 << 20))
 
 
 def dci_infer_batches(lanes: Sequence[Lane], graph: Graph, cache: Optional[Cache], seeds: torch.Tensor, batch_size: int,

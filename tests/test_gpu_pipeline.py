@@ -193,6 +193,27 @@ def test_batches_closed_beside_the_gather(setup, fused):
     assert got[0] == got[1] == got[2] and not np.isnan(np.frombuffer(got[0][0], dtype=np.float32)).any()
 
 
+def test_a_lane_without_memory_for_both_stages_takes_room_for_one(setup, monkeypatch):
+    dci, gu, w, g, want = (setup[k] for k in ("dci", "gu", "w", "g", "want"))
+    ws, wn, bs = setup["weights"]
+    asked, ensure = [], dci.Context.ensure_workspace
+
+    def full(self, nbytes):
+        asked.append(nbytes)
+        if len(asked) == 1:
+            raise torch.OutOfMemoryError("no room")
+        ensure(self, nbytes)
+
+    monkeypatch.setattr(dci.Context, "ensure_workspace", full)
+    ln = dci.Lane(g, B, w.fanouts, w.dims)
+    assert len(asked) == 2 and asked[1] < asked[0]
+    logits = torch.full((w.num_seeds, w.classes), float("nan"), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    dci.dci_infer_batches([ln], g, setup["cache"], setup["seeds"], B, 3, 1, w.fanouts, w.rng_seed, 0, ws, wn, bs, logits)
+    _check_lane(gu, ln, *want[3])
+    _check_logits(logits[3 * B:4 * B].cpu().numpy(), oracle.sage_forward(*want[3], *(setup["tiny"][k] for k in ("w_self", "w_neigh", "bias"))))
+
+
 @pytest.mark.parametrize("fused", [0, 1])
 def test_void_batch_closed_beside_the_gather(setup, fused):
     """A relabel tile that gives up (forced from the host; every kernel still ends at once) voids the batch: sizes are zero, nothing is
