@@ -210,7 +210,7 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
 #define DCI_OPT_RELABEL_SPIN_LIMIT 3
 /*   DCI_OPT_TEST_RELABEL_FIRST_TICKET  test hook for that failure path, off (0) by default: the scan numbers
  *       its tiles from this value, so the tiles below it never run or publish and the first real tile must
- *       give up.  Only accepted while the spin limit is at most 65536, so that every kernel still ends
+ *       give up (hops that one workgroup makes, the first ones of small batches, have no scan; the last hop has one).  Only accepted while the spin limit is at most 65536, so that every kernel still ends
  *       within microseconds. */
 #define DCI_OPT_TEST_RELABEL_FIRST_TICKET 4
 /*   DCI_OPT_FUSED_INPUT  how dci_infer_batches feeds the model on this context's lane: 0 (default)

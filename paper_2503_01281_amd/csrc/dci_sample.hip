@@ -1117,9 +1117,9 @@ static void launch_first(dci_ctx* ctx, const FirstArgs& fa, bool count) {
 }
 
 // How many of the batch's hops k_first_hops makes.
-static int first_hops(const dci_ctx* ctx, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, const dci_blocks* out, int* group) {
+static int first_hops(int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, const dci_blocks* out, int* group) {
   int n = 0, g = 8;
-  if (n_seeds < 1 || ctx->test_first_ticket != 0) return 0;
+  if (n_seeds < 1) return 0;
   for (int32_t h = 0; h + 1 < n_hops; ++h) {
     if (group_for(fanouts[h]) > g) g = group_for(fanouts[h]);
     if (out->cap_rows[h] * g > kFirstSlots || out->cap_rows[h + 1] > kFirstNodes) break;
@@ -1137,7 +1137,7 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
                             uint64_t rng_seed, const dci_blocks* out, const SampleWs& ws, uint64_t* stats,
                             uint32_t* feat_count, uint32_t* adj_count, uint32_t* edge_count, CloseArgs* left = nullptr) {
   int rc = DCI_OK, first_group = 8;
-  const int n_first = first_hops(ctx, n_seeds, fanouts, n_hops, out, &first_group);
+  const int n_first = first_hops(n_seeds, fanouts, n_hops, out, &first_group);
   if (n_first == 0) {
     Timed t(ctx, DCI_K_TABLE_CLEAR);
     rc = fill_bytes(ctx, ws.table, ws.clear_bytes, 0xFFFFFFFFu);

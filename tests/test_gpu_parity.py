@@ -833,7 +833,7 @@ def test_relabel_timeout_voids_the_batch_and_is_reported(env):
     and the context works again once the hook is off."""
     dci, gu, g, tiny, w = (env[k] for k in ("dci", "gu", "graph", "tiny", "w"))
     ctx = dci.Context(0, workspace_bytes=64 << 20)     # large enough for all three calls: growing it would sync
-    n = 600                                            # three scan tiles at hop 0 (256 rows each)
+    n = 600                                            # ten scan tiles at hop 0 (64 rows each)
     seeds = tiny["seeds"][:n]
     blk = dci.Blocks(ctx, w.num_nodes, n, w.fanouts)
     with pytest.raises(dci.DciError) as e:             # the hook is refused while the limit is at its default

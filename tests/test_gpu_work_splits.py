@@ -176,6 +176,34 @@ def test_first_hops_of_small_batches(env, n_seeds, fanouts, hashed):
         assert np.array_equal(got.cpu().numpy().view(np.uint32), counted)
 
 
+@pytest.mark.parametrize("n_seeds,fanouts,n_first", [(30, (3, 2), 1), (20, (5, 10, 3), 1), (16, (5, 10, 3), 2), (300, (5, 3, 2), 0)])
+def test_void_batch_behind_the_first_hops(env, n_seeds, fanouts, n_first):
+    """A tile gives up (forced from the host; every kernel still ends at once) in the first hop behind those that are one kernel."""
+    dci, gu = env["dci"], env["gu"]
+    N = 3_000
+    rng = np.random.default_rng(n_seeds)
+    indptr = np.concatenate([[0], np.cumsum(rng.integers(1, 30, N))]).astype(np.int64)
+    indices = rng.integers(0, N, indptr[-1]).astype(np.int64)
+    g, ctx = gu.make_graph(indptr, indices, None), dci.Context(0)
+    seeds = rng.permutation(N)[:n_seeds].astype(np.int64)
+    blk, stats = dci.Blocks(ctx, N, n_seeds, fanouts), gu.new_stats()
+    ctx.set_option(dci.DCI_OPT_RELABEL_SPIN_LIMIT, 200)
+    for first in (1, 40):  # 40: beyond every frontier
+        ctx.set_option(dci.DCI_OPT_TEST_RELABEL_FIRST_TICKET, first)
+        ctx.timing_enable(["table_clear", "relabel"])
+        dci.dci_sample_khop(ctx, g, None, gu.dev(seeds), 0, fanouts, 7, blk, stats)
+        with pytest.raises(dci.DciError) as e:
+            ctx.sync()
+        assert e.value.code == -3 and "relabel scan timed out" in str(e.value)
+        launches = {k: v[1] for k, v in ctx.timing_read().items()}
+        ctx.timing_enable([])
+        assert (launches["table_clear"], launches["relabel"]) == (n_first == 0, len(fanouts) - n_first)
+        assert blk.counts.cpu().numpy().tolist() == [0] * 17 and blk.counts_host.numpy().tolist() == [0] * 17 and not stats.any()
+    ctx.set_option(dci.DCI_OPT_TEST_RELABEL_FIRST_TICKET, 0)
+    dci.dci_sample_khop(ctx, g, None, gu.dev(seeds), 0, fanouts, 7, blk, stats)
+    gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), oracle.sample_khop(indptr, indices, seeds, 0, fanouts, 7))
+
+
 # The selective gather's rounds of 32 to 256 looked-up rows to a workgroup, which follow from how many rows there are for its workgroups:
 # a single row, a few, many; some cached, none, all.
 @pytest.mark.parametrize("n", [1, 31, 33, 2_000, 150_000, 300_000, 600_000])
