@@ -13,7 +13,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("variant", ["workspace", "static_scratch_and_rows_in_place"])
+@pytest.mark.parametrize("variant", ["workspace", "static_scratch_and_rows_in_place", "lane", "lane_and_rows_in_place"])
 def test_step_replays_from_a_hip_graph(tiny, variant):
     import paper_2503_01281_amd as dci
     from tests import gpu_util as gu
@@ -34,9 +34,17 @@ def test_step_replays_from_a_hip_graph(tiny, variant):
         seeds = torch.empty(w.batch_size, dtype=torch.int64, device="cuda")
         ws, wn, bs = ([gu.dev(a) for a in tiny[k]] for k in ("w_self", "w_neigh", "bias"))
         batch_index = 5
+        if variant.startswith("lane"):  # dci_infer_batches, the batch closed beside its gather
+            batch_index = 0
+            lane = dci.Lane(g, w.batch_size, w.fanouts, w.dims, stream=side)
+            ctx, blk, x = lane.ctx, lane.blocks, lane.x
+            ctx.set_option(dci.DCI_OPT_FUSED_INPUT, 0 if variant == "lane" else 1)
 
         def step():
-            if variant == "workspace":
+            if variant.startswith("lane"):
+                dci.dci_infer_batches([lane], g, cache, seeds, w.batch_size, 0, 1, w.fanouts, w.rng_seed, dci.DCI_MODEL_SAGE_MEAN,
+                                      ws, wn, bs, logits)
+            elif variant == "workspace":
                 dci.dci_sample_khop(ctx, g, cache, seeds, batch_index, w.fanouts, w.rng_seed, blk)
                 dci.dci_gather_features(ctx, g, cache, blk.nodes, blk.cap_nodes[-1], x, n_dev=blk.n_input_dev())
                 dci.dci_sage_forward(ctx, blk, x, ws, wn, bs, logits)
@@ -57,8 +65,10 @@ def test_step_replays_from_a_hip_graph(tiny, variant):
                 t.fill_(-1)
 
         seeds.copy_(all_seeds[:w.batch_size])
+        ctx.timing_enable(["write_src"])
         step()                                   # eager once: sizes the workspace before the capture
-        ctx.sync()
+        assert ctx.timing_read()["write_src"][1] == (0 if variant.startswith("lane") else 1)
+        ctx.timing_enable([])
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=side):
             step()

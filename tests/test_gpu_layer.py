@@ -108,6 +108,29 @@ def test_layer_with_numbers_that_three_parts_cannot_hold(env, model, M, D, N, ca
     assert fin.any() and (np.abs(got[fin] - want[fin]) <= bound[fin]).all()
 
 
+@pytest.mark.parametrize("model", [0, 2])
+@pytest.mark.parametrize("everywhere", [False, True])
+@pytest.mark.parametrize("D,N", [(60, 64), (60, 100), (100, 64), (100, 100), (100, 160)])
+def test_tiles_of_many_rows_made_again(env, model, everywhere, D, N):
+    """1,251 halves of tiles, two or three to a workgroup in the shapes of 64 columns of input and four or five in the others: first and
+    second whole tiles and last halves are made again, a few of them (one row in the others') or all (a weight)."""
+    M, bad = 20_011, [3, 40, 70, 130, 9_999, 20_010]
+
+    def poke(x, ws, wn):
+        for i, r in enumerate(bad):
+            x[r, (7 * i) % D] = (np.inf, -np.inf, np.nan, 1e33)[i % 4]
+        if everywhere:
+            wn[D - 1, 1] = np.inf
+    got, want, bound = _run(env, M, D, N, 3, model, M, seed=D + N, poke=poke)
+    assert env["one kernel"]
+    assert all(not np.isfinite(want[r]).all() or np.abs(want[r]).max() > 1e28 for r in bad)
+    assert (np.isnan(got) == np.isnan(want)).all()
+    inf = np.isinf(want)
+    assert (got[inf] == want[inf]).all()
+    fin = np.isfinite(want)
+    assert fin.any(axis=1).sum() > M / 2 and (np.abs(got[fin] - want[fin]) <= bound[fin]).all()
+
+
 @pytest.mark.parametrize("scale", [1e-37, 1e-30, 1e30, 1e37])
 @pytest.mark.parametrize("M,D,N,cap", [(40, 100, 64, 64), (40, 100, 256, 40000)])
 def test_layer_at_the_ends_of_the_range(env, scale, M, D, N, cap):

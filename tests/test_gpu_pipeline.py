@@ -186,11 +186,93 @@ def test_batches_closed_beside_the_gather(setup, fused):
         logits = torch.full((w.num_seeds, w.classes), float("nan"), dtype=torch.float32, device="cuda")
         ln.x.fill_(-5.0)
         torch.cuda.synchronize()
+        ln.ctx.timing_enable(["write_src"])
         dci.dci_infer_batches([ln], g, cache, setup["seeds"], B, 3, 2, w.fanouts, w.rng_seed, 0, ws, wn, bs, logits,
                               gu.new_stats() if way == "statistics" else None)
+        assert ln.ctx.timing_read()["write_src"][1] == (0 if way == "beside" else 2)
         gu.assert_blocks_equal(gu.blocks_to_host(ln.ctx, ln.blocks), want[4][0])
         got.append((logits[3 * B:5 * B].cpu().numpy().tobytes(), ln.x.cpu().numpy().tobytes()))
     assert got[0] == got[1] == got[2] and not np.isnan(np.frombuffer(got[0][0], dtype=np.float32)).any()
+
+
+# Both kinds of node table, rows of 16, 8 and 4 bytes at a time, every row cached, some, none, the three models, rows read in place or
+# gathered.
+@pytest.mark.parametrize("hashed,F,cached,model,fused", [
+    (False, 8, 0.4, 0, 1), (True, 8, 0.4, 0, 1), (True, 6, None, 1, 1), (True, 5, 1.0, 2, 1), (False, 6, 1.0, 1, 1), (False, 5, 0.4, 2, 1),
+    (False, 5, None, 2, 0), (True, 6, 0.4, 0, 0), (True, 8, 1.0, 1, 0), (False, 8, None, 0, 0)])
+def test_batches_closed_beside_every_form_of_the_gather(hashed, F, cached, model, fused):
+    import paper_2503_01281_amd as dci
+    from tests import gpu_util as gu
+    used, fanouts, batch, n_batches = 4_000, (4, 3, 6), 301, 3
+    N = 600_000 if hashed else used
+    dims = (F, 12, 9, 7)
+    rng = np.random.default_rng(F + model)
+    degree = np.zeros(N, dtype=np.int64)
+    degree[:used] = rng.integers(0, 11, used)
+    indptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    indices = rng.integers(0, used, indptr[-1]).astype(np.int64)
+    feat = rng.standard_normal((N, F)).astype(np.float32)
+    g = gu.make_graph(indptr, indices, feat)
+    cache = None
+    if cached is not None:
+        rows = np.sort(rng.permutation(N)[:int(cached * N)])
+        remap = np.full(N, -1, dtype=np.int32)
+        remap[rows] = np.arange(len(rows))
+        cache = gu.upload_cache(np.full(N, -1), np.zeros(1), np.zeros(0), remap, feat[rows])
+    seeds = rng.permutation(used)[:batch * n_batches - 50].astype(np.int64)
+    pairs = list(zip(dims, dims[1:]))
+    ws, wn = ([rng.uniform(-1, 1, p).astype(np.float32) for p in pairs] for _ in range(2))
+    bs = [rng.uniform(-1, 1, p[1]).astype(np.float32) for p in pairs]
+    out = []
+    for stats in (None, gu.new_stats()):
+        ln = dci.Lane(g, batch, fanouts, dims)
+        ln.ctx.set_option(dci.DCI_OPT_FUSED_INPUT, fused)
+        logits = torch.full((len(seeds), dims[-1]), float("nan"), dtype=torch.float32, device="cuda")
+        ln.x.fill_(-5.0)
+        seeds_dev, weights = gu.dev(seeds), [[gu.dev(a) for a in p] for p in (ws, wn, bs)]
+        if model == 2:
+            weights[0] = None
+        torch.cuda.synchronize()
+        ln.ctx.timing_enable(["write_src"])
+        dci.dci_infer_batches([ln], g, cache, seeds_dev, batch, 0, n_batches, fanouts, 17, model, *weights, logits, stats)
+        assert ln.ctx.timing_read()["write_src"][1] == (0 if stats is None else n_batches)
+        blk = gu.blocks_to_host(ln.ctx, ln.blocks)
+        gu.assert_blocks_equal(blk, oracle.sample_khop(indptr, indices, seeds[2 * batch:], 2, fanouts, 17))
+        out.append((logits.cpu().numpy(), ln.x.cpu().numpy().tobytes()))
+    assert out[0][0].tobytes() == out[1][0].tobytes() and out[0][1] == out[1][1]
+    for b in range(n_batches):
+        blk = oracle.sample_khop(indptr, indices, seeds[b * batch:(b + 1) * batch], b, fanouts, 17)
+        _check_logits(out[0][0][b * batch:(b + 1) * batch], oracle.gnn_forward(model, blk, oracle.gather(feat, blk.nodes), ws, wn, bs))
+
+
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_large_batches_of_gathered_rows_are_closed_by_a_kernel_of_their_own(beyond):
+    """More than 512 slots of the last hop for every compute unit, by their bound; rows read in place are closed beside whatever the size."""
+    import paper_2503_01281_amd as dci
+    from tests import gpu_util as gu
+    batch = torch.cuda.get_device_properties(0).multi_processor_count * 512 // 32 + beyond  # 4 rows of 8 slots to a seed
+    N, F, fanouts, dims = 20_000, 5, (3, 8), (5, 6, 4)
+    rng = np.random.default_rng(9)
+    indptr = np.concatenate([[0], np.cumsum(rng.integers(0, 20, N))]).astype(np.int64)
+    indices = rng.integers(0, N, indptr[-1]).astype(np.int64)
+    feat = rng.standard_normal((N, F)).astype(np.float32)
+    g = gu.make_graph(indptr, indices, feat, on_device=True)
+    seeds = rng.permutation(N)[:batch].astype(np.int64)
+    w = [rng.uniform(-1, 1, p).astype(np.float32) for p in zip(dims, dims[1:])]
+    b = [np.zeros(n, dtype=np.float32) for n in dims[1:]]
+    ln = dci.Lane(g, batch, fanouts, dims)
+    seeds_dev, w_dev, b_dev = gu.dev(seeds), [gu.dev(a) for a in w], [gu.dev(a) for a in b]
+    want = oracle.sample_khop(indptr, indices, seeds, 0, fanouts, 3)
+    ref = oracle.gnn_forward(0, want, oracle.gather(feat, want.nodes), w, w, b)
+    for fused in (0, 1):
+        ln.ctx.set_option(dci.DCI_OPT_FUSED_INPUT, fused)
+        logits = torch.full((batch, dims[-1]), float("nan"), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        ln.ctx.timing_enable(["write_src"])
+        dci.dci_infer_batches([ln], g, None, seeds_dev, batch, 0, 1, fanouts, 3, 0, w_dev, w_dev, b_dev, logits)
+        assert ln.ctx.timing_read()["write_src"][1] == (1 if beyond and not fused else 0)
+        gu.assert_blocks_equal(gu.blocks_to_host(ln.ctx, ln.blocks), want)
+        _check_logits(logits.cpu().numpy(), ref)
 
 
 def test_a_lane_without_memory_for_both_stages_takes_room_for_one(setup, monkeypatch):

@@ -101,9 +101,9 @@ def test_rows_read_in_place_from_an_unaligned_cache_give_the_same_logits(env, F,
         assert o.numpy().tobytes() == out[0].numpy().tobytes()
 
 
-def _forward(env, cap, fanouts, rows, dims, model, seed, deg=None):
+def _forward(env, cap, fanouts, rows, dims, model, seed, deg=None, shift=0):
     """dci_gather_forward on gathered rows: (result, 64-bit result, sum of magnitudes, launches per kernel class).  deg: list
-    lengths of the input layer's block."""
+    lengths of the input layer's block; shift: numbers that x begins beyond a 16-byte boundary."""
     dci, ctx = env["dci"], env["ctx"]
     blk, host = _blocks(env, cap, fanouts, rows, 10**7, seed)
     if deg is not None:
@@ -116,7 +116,7 @@ def _forward(env, cap, fanouts, rows, dims, model, seed, deg=None):
     feat = torch.randn(n, dims[0], generator=torch.Generator().manual_seed(seed))
     g = dci.Graph(torch.zeros(n + 1, dtype=torch.int64).cuda(), torch.zeros(1, dtype=torch.int64).cuda(), feat.cuda())
     ws, wn, bs = _weights(dims, seed + 1)
-    x = torch.zeros(blk.cap_nodes[-1], dims[0], dtype=torch.float32, device="cuda")
+    x = torch.zeros(blk.cap_nodes[-1] * dims[0] + shift, dtype=torch.float32, device="cuda")[shift:].view(-1, dims[0])
     y = torch.full((blk.cap_nodes[0], dims[-1]), float("nan"), dtype=torch.float32, device="cuda")
     ctx.timing_enable(dci.KERNEL_CLASSES)
     dci.dci_gather_forward(ctx, g, None, blk, x, model, None if model == 2 else ws, wn, bs, y)
@@ -184,14 +184,19 @@ def test_kernels_of_an_input_layer(env, cap, fan, D, N, kernels):
 
 
 @pytest.mark.parametrize("model", [0, 1])
-@pytest.mark.parametrize("fan,D,N", [(10, 100, 256), (11, 68, 256), (16, 100, 256), (15, 104, 256), (16, 128, 512), (15, 112, 1024), (16, 112, 1024)])
-def test_input_layers_of_many_rows_with_11_to_16_sources(env, model, fan, D, N):
-    """At least 98,304 rows by capacity, inputs of up to 128 columns: one kernel, with three-part products but for the last, which puts its
-    rows together in one piece."""
+@pytest.mark.parametrize("fan,D,N,tiles", [
+    (10, 100, 256, 0), (11, 68, 256, 0), (16, 100, 256, 0), (15, 104, 256, 0), (16, 128, 512, 0),
+    # rows that are no whole 128-byte lines: the lists' length times the column groups up to 60; those that are: times one more, up to 128
+    (15, 112, 1024, 0), (16, 112, 1024, 1), (12, 112, 1280, 0), (13, 112, 1280, 1), (16, 128, 1024, 0), (14, 128, 2048, 0), (15, 128, 2048, 1)])
+def test_input_layers_of_many_rows_with_11_to_16_sources(env, model, fan, D, N, tiles):
+    """At least 98,304 rows by capacity, inputs of up to 128 columns: one kernel, with three-part products, or with fp32 instructions
+    (tiles) where that one would put the rows together too often.  The latter needs rows on 16-byte boundaries: elsewhere the layer is two
+    kernels."""
     fanouts, dims = (1, 1, fan), (D, N, 8, 5)
-    got, want, size, n = _forward(env, 25_000, fanouts, (100, 170, 3001, 4000), dims, model, D + N + fan)
-    assert n["mean_in"] + n["linear_in"] == 1
-    assert _close(got, want, size, fanouts, dims)
+    for shift in (0, 1):
+        got, want, size, n = _forward(env, 25_000, fanouts, (100, 170, 3001, 4000), dims, model, D + N + fan, shift=shift)
+        assert n["mean_in"] + n["linear_in"] == (2 if tiles and shift else 1)
+        assert _close(got, want, size, fanouts, dims)
 
 
 @pytest.mark.parametrize("cap,kernels", [(8000, 1), (5000, 2)])

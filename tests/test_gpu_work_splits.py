@@ -97,7 +97,8 @@ def test_draw_chain_at_the_edges_of_its_steps(env, fanout):
 
 
 # Tiles of the frontier scan: one row, a whole tile and one more, the last count of tiles that are numbered by their workgroup and the first
-# with tickets (8 / 9), sixteen, and the line where a lane group takes two rows (200 / 201 tiles), for each width of a lane group.
+# with tickets (8 / 9), sixteen, and the line where a lane group takes two rows (200 / 201 tiles), for each width of a lane group.  With one
+# hop, which is always scanned, and with another one behind it, where few rows of the first are one workgroup's (k_first_hops).
 @pytest.mark.parametrize("fanout,rows_per_tile", [(2, 64), (9, 32), (17, 16), (33, 8)])
 @pytest.mark.parametrize("tiles", [0, 1, 8, 16, 200])
 @pytest.mark.parametrize("hashed", [False, True])
@@ -113,13 +114,30 @@ def test_tiles_of_the_frontier_scan(env, fanout, rows_per_tile, tiles, hashed):
     for extra in (0, 1):
         n = max(1, tiles * rows_per_tile) + extra
         seeds = rng.permutation(16_000)[:n].astype(np.int64)
-        blk = dci.Blocks(ctx, N, n, (fanout, 2))
-        stats = gu.new_stats()
-        dci.dci_sample_khop(ctx, g, None, gu.dev(seeds), extra, (fanout, 2), 5, blk, stats)
-        got = gu.blocks_to_host(ctx, blk)
-        gu.assert_blocks_equal(got, oracle.sample_khop(indptr, indices, seeds, extra, (fanout, 2), 5))
-        s = gu.stats_dict(ctx, stats)
-        assert s["edges_sampled"] == sum(got["n_edges"]) == s["adj_edge_misses"] and s["adj_node_misses"] == sum(got["n_nodes"][:2])
+        for fanouts in ((fanout,), (fanout, 2)):
+            blk = dci.Blocks(ctx, N, n, fanouts)
+            stats = gu.new_stats()
+            ctx.timing_enable(["relabel"])
+            dci.dci_sample_khop(ctx, g, None, gu.dev(seeds), extra, fanouts, 5, blk, stats)
+            scans = ctx.timing_read()["relabel"][1]
+            ctx.timing_enable([])
+            assert scans == len(fanouts) - _first_hops(dci, N, n, fanouts)
+            got = gu.blocks_to_host(ctx, blk)
+            gu.assert_blocks_equal(got, oracle.sample_khop(indptr, indices, seeds, extra, fanouts, 5))
+            s = gu.stats_dict(ctx, stats)
+            assert s["edges_sampled"] == sum(got["n_edges"]) == s["adj_edge_misses"] and s["adj_node_misses"] == sum(got["n_nodes"][:-1])
+
+
+def _first_hops(dci, N, n_seeds, fanouts):
+    """Hops that one workgroup makes: from the first one on, all but the last at most, while rows (by their bound) times the widest lane
+    group so far are 1,536 or fewer."""
+    n = group = 0
+    for rows, f in zip(dci.blocks_bounds(N, n_seeds, fanouts)[0], fanouts[:-1]):
+        group = max(group, next(g for g in (8, 16, 32, 64) if f <= g))
+        if rows * group > 1536:
+            break
+        n += 1
+    return n
 
 
 # Batches whose first hops are one kernel: the last number of seeds and the first beyond it for each width of a lane group (1,536 slots: 192
@@ -151,7 +169,12 @@ def test_first_hops_of_small_batches(env, n_seeds, fanouts, hashed):
         seeds[0] = 7
         want = oracle.sample_khop(indptr, indices, seeds, batch, fanouts, 3)
         stats, plain = gu.new_stats(), gu.new_stats()
+        ctx.timing_enable(["table_clear", "relabel"])
         dci.dci_sample_khop(ctx, g, cache, gu.dev(seeds), batch, fanouts, 3, blk, stats)
+        launches = {k: v[1] for k, v in ctx.timing_read().items()}
+        ctx.timing_enable([])
+        n_first = _first_hops(dci, N, n_seeds, fanouts)
+        assert (launches["table_clear"], launches["relabel"]) == (n_first == 0, len(fanouts) - n_first)
         gu.assert_blocks_equal(gu.blocks_to_host(ctx, blk), want)
         st, n_edges = gu.stats_dict(ctx, stats), int(sum(want.n_edges))
         rows = np.concatenate([want.nodes[:int(want.n_nodes[h])] for h in range(len(fanouts))])
