@@ -35,7 +35,7 @@ struct dci_ctx {
   int64_t req_nodes[DCI_MAX_HOPS + 1] = {0};
   int64_t req_edges[DCI_MAX_HOPS] = {0};
   size_t req_workspace = 0;
-  int relabel_tile_iters = 0;  // DCI_OPT_RELABEL_TILE_ITERS: 0 = by frontier size, else 2, 4 or 8 rows per lane group
+  int relabel_tile_iters = 0;  // DCI_OPT_RELABEL_TILE_ITERS: 0 = by frontier size (1, 2, 4 or 8), else 2, 4 or 8 rows per lane group
   int input_layer = 0;    // DCI_OPT_INPUT_LAYER: 0 by shape, 1 aggregation and dense layer as two kernels, 2 / 3 one kernel where the shape allows (weights in registers / 64-row tiles)
   int fused_input = 0;    // DCI_OPT_FUSED_INPUT: dci_infer_batches lets the first layer read cached rows in place
   int linear_split = 0;   // DCI_OPT_LINEAR_SPLIT: 0 = by shape, n = at most n workgroups per tile
@@ -51,9 +51,9 @@ constexpr size_t kAlign = 256;
 // tiles numbers them by workgroup instead, which spares it the ticket (1 us); every tile that another one waits for must then get to run
 // whatever the others do.  Only workgroups that wait could keep it from that (all others end by themselves), so they must leave it a
 // place.  A compute unit has kRelabelPerCu places; kScansAtOnce scans may be on the card, or on the part of it that the process sees, at a
-// time, those of other processes among them (16 processes with four hardware queues each).  That makes 8 tiles with 256 compute units, and
-// with 32 of them one, which waits for nobody.
-constexpr int kRelabelPerCu = 2, kScansAtOnce = 64;
+// time, those of other processes among them (16 processes with four hardware queues each).  That makes 16 tiles with 256 compute units, 2 with
+// 32 of them.
+constexpr int kRelabelPerCu = 4, kScansAtOnce = 64;
 constexpr unsigned unticketed_tiles(int num_cus) { return (unsigned)(num_cus * kRelabelPerCu / kScansAtOnce); }
 
 inline int32_t fail(dci_ctx* ctx, int32_t code, const char* fmt, ...) {
@@ -128,16 +128,6 @@ inline uint64_t next_pow2(uint64_t x) {
 // -- device helpers -----------------------------------------------------------------------
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
-
-__device__ __forceinline__ int wave_incl_scan(int x) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int y = __shfl_up(x, d, kWave);
-    if (lane >= d) x += y;
-  }
-  return x;
-}
 
 __device__ __forceinline__ long long wave_incl_scan64(long long x) {
   const int lane = lane_id();

@@ -532,7 +532,7 @@ struct RelabelArgs {
 };
 
 template <int G, int kTileIters, bool DIRECT>
-__global__ __launch_bounds__(kRelabelBlock, 2 * kRelabelPerCu) void k_relabel_hop(RelabelArgs a) {
+__global__ __launch_bounds__(kRelabelBlock, kTileIters < kTileItersMax ? 2 * kRelabelPerCu : 4) void k_relabel_hop(RelabelArgs a) {
   constexpr int kGroups = kRelabelBlock / G;
   constexpr int TR = kGroups * kTileIters;  // rows per tile, at most kRelabelBlock
   constexpr int kWaves = kRelabelBlock / kWave;
@@ -777,6 +777,7 @@ __global__ __launch_bounds__(kRelabelBlock, 2 * kRelabelPerCu) void k_relabel_ho
 // fan-outs 5, 10, 15, before / after: 4 seeds 63.6 / 56.1 us, 16 72.3 / 65.8, 64 (one hop) 89.4 / 86.4, 128 89.5 / 86.5; 2, 4, 8: 64 seeds 66.7 / 59.3.
 //   At most kFirstSlots slots (lanes of all rows' groups) to a hop: with 2,048, two rows to every group, one compute unit's reads take as long as
 // the launches do (256 seeds 100.5 / 100.0 us, over the host link 133.4 / 133.7, two hops 55.3 / 55.5).
+// (Every workgroup has the 83 KB of LDS that only the first needs, so the others clear one to a compute unit at a time.)
 constexpr int kFirstThreads = 1024, kFirstIters = 2, kFirstSlots = 1536, kFirstEntries = 8192, kFirstNodes = kFirstEntries / 2;
 
 struct FirstArgs {
@@ -1082,7 +1083,7 @@ static int grid_for_rows(const dci_ctx* ctx, int64_t rows, int groups_per_block)
 
 // frontier: as for k_sample_hop
 template <int G, bool DIRECT>
-static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra, bool count, int frontier, int64_t cap_rows) {
+static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, RelabelArgs& ra, bool count, int frontier, int64_t cap_rows) {
   const int grid = grid_for_rows(ctx, cap_rows, kBlock / G) + ha.n_write_blocks;
   {
     Timed t(ctx, DCI_K_SAMPLE);
@@ -1095,6 +1096,8 @@ static int32_t launch_hop(dci_ctx* ctx, const HopArgs& ha, const RelabelArgs& ra
   {
     Timed t(ctx, DCI_K_RELABEL);
     const int iters = tile_iters_for(ctx, ha.hop, cap_rows, ha.fanout);
+    // (tiles of the most rows need more registers than that many places leave, and are many: tickets, but for a single one)
+    ra.unticketed = iters < kTileItersMax ? unticketed_tiles(ctx->num_cus) : 1;
     const dim3 grid_r((unsigned)tiles_for(cap_rows, ha.fanout, iters));
     if (iters == 1)
       hipLaunchKernelGGL((k_relabel_hop<G, 1, DIRECT>), grid_r, dim3(kRelabelBlock), 0, ctx->stream, ra);
@@ -1225,7 +1228,6 @@ static int32_t sample_batch(dci_ctx* ctx, const dci_graph* g, const dci_cache* c
     ra.batch_flag = ws.batch_flag;
     ra.spin_limit = ctx->relabel_spin_limit;
     ra.first_ticket = ctx->test_first_ticket;
-    ra.unticketed = unticketed_tiles(ctx->num_cus);
     // launch shapes follow the frontier bound of this call; with zero seeds one workgroup still
     // runs so that the (empty) sizes get written
     const int64_t rows = out->cap_rows[h];

@@ -97,7 +97,7 @@ def test_draw_chain_at_the_edges_of_its_steps(env, fanout):
 
 
 # Tiles of the frontier scan: one row, a whole tile and one more, the last count of tiles that are numbered by their workgroup and the first
-# with tickets (8 / 9), sixteen, and the line where a lane group takes two rows (200 / 201 tiles), for each width of a lane group.  With one
+# with tickets (16 / 17), eight, and the line where a lane group takes two rows (200 / 201 tiles), for each width of a lane group.  With one
 # hop, which is always scanned, and with another one behind it, where few rows of the first are one workgroup's (k_first_hops).
 @pytest.mark.parametrize("fanout,rows_per_tile", [(2, 64), (9, 32), (17, 16), (33, 8)])
 @pytest.mark.parametrize("tiles", [0, 1, 8, 16, 200])

@@ -16,15 +16,15 @@ def test_tiles_without_tickets_all_have_a_place(tmp_path):
     src = tmp_path / "places.hip"
     src.write_text("""#include "dci_internal.h"
 constexpr bool places(int cus) {  // a scan of one tile waits for nobody
-  return dci::unticketed_tiles(cus) <= 1 || (int)dci::unticketed_tiles(cus) * 64 <= 2 * cus;
+  return dci::unticketed_tiles(cus) <= 1 || (int)dci::unticketed_tiles(cus) * 64 <= 4 * cus;
 }
 constexpr bool all() {
   for (int cus = 1; cus <= 512; ++cus)
     if (!places(cus)) return false;
   return true;
 }
-static_assert(all(), "16 processes of four queues each, two workgroups to a compute unit");
-static_assert(dci::kRelabelPerCu == 2 && dci::unticketed_tiles(256) == 8 && dci::unticketed_tiles(32) <= 1, "");
+static_assert(all(), "16 processes of four queues each, four workgroups to a compute unit");
+static_assert(dci::kRelabelPerCu == 4 && dci::unticketed_tiles(256) == 16 && dci::unticketed_tiles(32) == 2, "");
 """)
     r = subprocess.run([hipcc, "--cuda-host-only", "-fsyntax-only", "-std=c++17", "-x", "hip", "-I", os.path.join(ROOT, "include"),
                         "-I", build.CSRC, str(src)], capture_output=True, text=True)
