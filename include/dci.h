@@ -172,14 +172,16 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *   DCI_OPT_LINEAR_KERNEL  which kernels dci_sage_forward / dci_gnn_forward launch for a layer:
  *       0  by shape (default): aggregation and dense layer as one kernel, its products on the bf16 matrix
  *          instructions with every fp32 operand as a sum of three bf16 parts (a product by itself is rounded like an
- *          fp32 product, and 32 at a time are added).  A layer is aggregation and dense layer apart where that is faster: lists
- *          (cap_edges / cap_rows of its block) of more than 20 sources or so where input rows are not a multiple of 128 bytes, of
- *          more than 42 where the output has more than 256 columns, of more than 10000 numbers in layers of few rows; 257 to 384
- *          outputs of many rows.  Where that would be so for an input layer of 112 or 128
- *          columns, a multiple of 256 outputs, lists of 11 to 16 sources and at least 98304 rows by capacity, it is
+ *          fp32 product, and 32 at a time are added).  By rows, lists and widths a layer is aggregation and dense layer apart: with
+ *          g column groups of 256 outputs, lists (cap_edges / cap_rows of its block) of more than 60 / max(3, g) sources where input rows are
+ *          not a multiple of 128 bytes, of more than 128 / (g + 1) where they are, of more than 10000 numbers in layers of few rows; 257 to 384
+ *          outputs of many rows.  (The lines are older than the present one kernel, which would be up to a fifth faster for some layers beyond
+ *          them.)  Where that would be so for an input layer of 112 or 128 columns, a multiple of 256 outputs (1024 and more, or 2048), lists of
+ *          11 to 16 sources and at least 98304 rows by capacity, it is
  *          one kernel with fp32 instructions (the default form under DCI_OPT_INPUT_LAYER).  The whole pass
  *          is as with two kernels a layer where DCI_OPT_INPUT_LAYER is set, an input has fewer than four columns or the parts of
- *          the weights do not fit where the aggregated rows would be.
+ *          the weights (6 bytes to a weight, inputs rounded up to 32 and outputs to 64) do not fit where the aggregated rows
+ *          would be.
  *          The dense layer of two: the kernel that keeps the weights in registers when the whole contraction
  *          is at most 256 long (two operands of up to 128 columns, or GCN's one of up to 256), the input width
  *          a multiple of 4, the output width a multiple of 256 and the layer at least 98304 rows tall by
@@ -219,7 +221,7 @@ int32_t dci_last_required(const dci_ctx* ctx, int64_t* cap_nodes, int64_t* cap_e
  *       missed and those of F_{L-1}).  The logits are bit-identical either way: the sums run in the same order. */
 #define DCI_OPT_FUSED_INPUT 5
 /*   DCI_OPT_RELABEL_TILE_ITERS  rows per lane group in a tile of the frontier scan: 0 (default) chosen from
- *       the frontier's size, or 2, 4, 8.  Tuning only: the result does not depend on it. */
+ *       the frontier's size (1, 2, 4 or 8), or 2, 4, 8.  Tuning only: the result does not depend on it. */
 #define DCI_OPT_RELABEL_TILE_ITERS 6
 /*   DCI_OPT_INPUT_LAYER  how the forward pass runs its first layer (two operands of at most 128 columns, mean or
  *       sum aggregator) where DCI_OPT_LINEAR_KERNEL 0 does not make it one kernel with three-part products; 1, 2 or 3
@@ -246,12 +248,20 @@ int32_t dci_set_option(dci_ctx* ctx, int32_t option, int64_t value);
  * up the elapsed time and the number of recorded launches per class into total_ms[DCI_K_COUNT]
  * and launches[DCI_K_COUNT], and starts over.  class_mask = 0 switches timing off (the default). */
 enum {
-  DCI_K_TABLE_CLEAR = 0, /* clearing the batch's node table and scan status words   */
+  DCI_K_TABLE_CLEAR = 0, /* clearing the batch's node table and scan status words; no
+                            launch where the first hops are one kernel              */
   DCI_K_SAMPLE = 1,      /* per hop: draw positions, read neighbours, register ids
-                            (also writes the previous hop's edge local ids)        */
-  DCI_K_RELABEL = 2,     /* per hop: first appearances, row offsets, new local ids  */
-  DCI_K_WRITE_SRC = 3,   /* last hop: local id of every edge, batch sizes to host   */
-  DCI_K_GATHER = 4,      /* feature gather                                          */
+                            (also writes the previous hop's edge local ids).  The
+                            first hops of small batches are one launch of this
+                            class, with the clear and their relabelling             */
+  DCI_K_RELABEL = 2,     /* per hop but those: first appearances, row offsets, new
+                            local ids                                               */
+  DCI_K_WRITE_SRC = 3,   /* last hop: local id of every edge, batch sizes to host;
+                            no launch where dci_infer_batches closes a batch
+                            beside its gather                                       */
+  DCI_K_GATHER = 4,      /* feature gather; beside it the weights' parts, where the
+                            call goes on to the model, and in dci_infer_batches
+                            the closing of the batch                                */
   DCI_K_MEAN_IN = 5,     /* first layer (input features): neighbour mean            */
   DCI_K_LINEAR_IN = 6,   /* first layer (input features): dense layer (matrix cores), or
                             the whole layer where it is one kernel                  */

@@ -65,8 +65,11 @@ __device__ __forceinline__ f32x4 shifted(f32x4 v, int shift) {
 //   * rows shared out in halves of tiles, so that no workgroup has more than one half more than another;
 //   * up to 64 outputs two wavefronts share columns and take a row tile each, because four would leave half of the multiplying ones idle:
 //     20 k x 2 x 96 x 64, 15 sources, 32.2 / 29.3, with 128 columns (half of them padding) 30.4;
+//   * multiplying wavefronts whose columns are past the last one leave the chunks to the others: 17 k x 2 x 256 x 172, 15 sources, 59.7, with their
+//     padding multiplied 61.6;
 //   * inputs of up to 64 columns with up to 128 outputs stay with chunks of 64 and two workgroups of eight wavefronts, since half of a chunk of
-//     128 would be empty: 20 k x 2 x 64 x 64, 5 sources, 20.5 / 19.1, in the other shape 23.1; 8.7 k x 2 x 64 x 100, 15 sources, 18.9 / 19.3, 21.1;
+//     128 would be empty: 20 k x 2 x 64 x 64, 5 sources, 20.5 / 19.1, in the other shape 23.1; 8.7 k x 2 x 64 x 100, 15 sources, 18.9 / 19.3, 21.1 (8.2 k
+//     to 9 k rows are the ones that lost, 0 to 5 %; 4 k gained 9 %, 17 k 7 %);
 //   * one round of eight loads in flight per lane: eight such wavefronts to a compute unit ask for enough, and with two the registers' moves cost
 //     1 to 3 %.  Places for as many sources as a fan-out can have, because those beyond them are read one after the other (chunks of 64, 12 k
 //     rows of 64 sources x 2 x 256 x 256: 120 us, with 32 places 248).
@@ -691,26 +694,26 @@ __global__ __launch_bounds__(kSmallThreads) void k_sage_layer_small(LayerArgs a)
 //   * the one for few rows while its workgroups have a compute unit each, all of the bound taken for the rows of the seeds' block, half
 //     of it for the next one's (0.5 - 0.7 of it in batches of 256 to 1,024 seeds, fan-outs of 5 to 10) and a fifth for those behind.  Three layers of 16 - 289 rows (request of 16 seeds): a pass
 //     79 us against 94 with aggregation, dense layer and sum of the split contraction as kernels of their own.  On either side
-//     of the line, this kernel / the other: 4,096 rows x 2 x 256 x 64 (256 workgroups), f = 5, 12.3 us / 16.8, x 100 (512) 21.8 / 17.4, x 172
-//     (768) 31.0 / 19.6; 1,024 x 2 x 100 x 256 (256), f = 10, 0.78, 2,048 x 2 x 256 x 256 (512), f = 15, 1.5.
-//   * above it k_sage_layer, in the shape that its width asks for (LayerPlan; figures at the kernel): 1 k rows x 2 x 256 x 512, f = 10, 24.7 us, the
-//     layer's two kernels 24.7; 3.1 k x 2 x 75 x 130, f = 8, 15.3 / 19.3; 2 k x 2 x 300 x 320, f = 25, 32.4 / 40.0; 6 k x 2 x 602 x 192, f = 10, 57.5 / 89.
+//     of the line, this kernel / the other: 4,096 rows x 2 x 256 x 64 (256 workgroups), f = 5, 12.2 us / 19.0, x 100 (512) 22.1 / 19.8, x 172
+//     (768) 31.1 / 21.7; 1,024 x 2 x 100 x 256 (256), f = 10, 10.8 / 16.3, 2,048 x 2 x 256 x 256 (512), f = 15, 28.3 / 23.8.
+//   * above it k_sage_layer, in the shape that its width asks for (LayerPlan; figures at the kernel).  It and the layer's two kernels: 1 k rows x 2 x 256 x
+//     512, f = 10, 24.7 us / 24.8; 3.1 k x 2 x 75 x 130, f = 8, 14.9 / 19.3; 2 k x 2 x 300 x 320, f = 25, 30.8 / 32.3; 6 k x 2 x 602 x 192, f = 10, 53.9 / 77.5.
 //     More than 256 outputs are two column groups or more, which put the same rows together again.
 //   * neither where lists are long: in few workgroups the lists' latency is not hidden.  With lists of more than 10,000 numbers the
 //     layer's two kernels are ahead (x 256 outputs, one kernel / the two; the two have a launch more, 1 - 2 us).  k_sage_layer_small,
 //     1,024 rows: D = 100, f = 64 0.86; D = 256, f = 25 0.93, f = 40 30.1 us / 26.3, f = 64 43 / 31; D = 300, f = 40 42 / 29; D = 602, f = 15 33.4
 //     / 31.8, f = 25 50 / 36, f = 64 106 / 55.  (Where it has two compute units for every workgroup it is only behind for more
 //     than 64 sources times pieces of 256 columns: 512 x 2 x D x 256, D = 256, f = 64 0.97; D = 300, f = 25 1.00, f = 64 1.26; D = 602, f = 25 1.16.)
-//     k_sage_layer, 2,048 rows: D = 64, f = 64 19.0 / 19.3; D = 256, f = 25 26.6 / 34.1, f = 64 36.2 / 40.3; D = 300, f = 25 30.5 / 39.4, f = 40 32.8
-//     / 42.3; D = 602, f = 25 45 / 67, f = 64 73 / 88.
+//     k_sage_layer, 2,048 rows: D = 64, f = 64 19.3 / 18.3; D = 256, f = 25 26.0 / 27.3, f = 64 36.0 / 33.6; D = 300, f = 25 30.2 / 31.9, f = 40 32.7
+//     / 34.8; D = 602, f = 25 45 / 52, f = 64 73 / 73.
 //   * none of them where the lists are long and every column group puts the same rows together again, or rows are no whole 128-byte
 //     lines, so that a piece of 512 bytes touches five for four.  The aggregation reads them once and in one piece, and the dense
-//     layer follows.  18.6 k x 2 x D x N, this kernel / the two: f = 64, 602 x 256 509 us / 550, 602 x 1,024 1,059 / 860, 256 x 256 188 / 229,
-//     256 x 1,024 420 / 384; f = 25, 602 x 256 233 / 302, 602 x 1,024 535 / 620, 256 x 256 92 / 132, 100 x 1,024 116 / 140; f = 15, 602 x 256 166 / 235,
-//     602 x 512 235 / 366, 300 x 768 182 / 241 (60 k rows 651 / 764); 300 x 300, f = 10, 115 / 122.
-//   The lines of the last two lie where a slower form of k_sage_layer (chunks of 64 columns, column groups of 64) met the two kernels; some lists
-// beyond them would now be up to a third faster in one kernel.  They stay, because a call that crosses a line gets its products from other
-// instructions, and its results other last bits.
+//     layer follows.  18.6 k x 2 x D x N, this kernel / the two: f = 64, 602 x 256 512 us / 528, 602 x 1,024 1,051 / 815, 256 x 256 188 / 233,
+//     256 x 1,024 409 / 364; f = 25, 602 x 256 233 / 278, 602 x 1,024 526 / 571, 256 x 256 92 / 127, 100 x 1,024 114 / 130; f = 15, 602 x 256 165 / 215,
+//     602 x 512 235 / 319, 300 x 768 180 / 237 (60 k rows 653 / 752); f = 10, 300 x 300 114 / 122, 256 x 300 90 / 103.
+//   The lines of the last two lie where a slower form of k_sage_layer (chunks of 64 columns, column groups of 64) met the two kernels.  Some
+// layers beyond them, which the two kernels make, would now be faster in one: of these 602 x 256 and x 1,024, 100 x 1,024 and the last two with the
+// lists named, by 8 to 16 %, and 60 k x 2 x 100 x 256, f = 25, by 21 %.
 constexpr int64_t kSmallReads = 10000, kFewRowsPerCu = 40;
 
 static size_t split_bytes(const LayerPlan& p, int ops) {

@@ -1810,10 +1810,13 @@ static int32_t plan_forward(dci_ctx* ctx, const dci_blocks* blocks, const float*
                         bias[0], n_layers == 1 ? logits : plan->ws.y[0]);
   };
   plan->input = input(feat_cache);
-  // An input layer that k_sage_layer does not take, because it would put the rows of lists of 11 to 16 sources together too often (112 or 128
-  // columns, 1,024 outputs or more), goes to k_sage_input_tile, which does so once.  The others are faster there: 60 k rows x 2 x 100 x 256 with 5,
-  // 15 and 25 sources 79, 112 and 140 us, with the weights in registers (k_sage_input_res) 101, 125 and 259; x 2 x 128 x 512 145, 192 and 195,
-  // k_sage_input_tile 180, 196 and 390; eight 4,096-seed batches of 2 x 100 x 256, 15 sources, on four lanes 1,660 us a pass (k_sage_input_res 1,705),
+  // An input layer of 11 to 16 sources that k_sage_layer does not take, because it would put the rows together too often, goes to
+  // k_sage_input_tile, which does so once: 112 columns where sources times column groups of 256 are more than 60 (16 sources and 1,024 outputs,
+  // 13 and 1,280), 128 columns where sources times the groups and one more are more than 128 (15 and 2,048).  us, k_sage_layer / k_sage_input_tile
+  // in turn: 60 k rows x 2 x 112 x 1,024 with 11 and 15 sources 318 / 337, 320 / 341 (309 by itself), x 2 x 128 x 1,024 307 / 359, 325 / 381, x 2 x 128 x
+  // 2,048 with 13 653 / 715; 25 k rows x 2 x 112 x 1,024 126 / 158, 129 / 160, x 2 x 128 x 2,048 246 / 348.
+  // The weights-in-registers kernel is not taken beside k_sage_layer: 60 k rows x 2 x 100 x 256 with 5, 15 and 25 sources 79, 106 and 140 us, with
+  // it (k_sage_input_res) 101, 125 and 259; eight 4,096-seed batches of 2 x 100 x 256, 15 sources, on four lanes 1,660 us a pass (k_sage_input_res 1,705),
   // on one 1,860 (1,955), of 2 x 68 x 256 on one 1,735 (1,925).
   //   Where the cache's alignment rules that kernel out for rows read in place, the layer's two kernels are taken, whose results are
   // the same to the bit where the outputs are a multiple of 256: DCI_OPT_FUSED_INPUT changes no logits.
