@@ -57,3 +57,26 @@ def stats_dict(ctx, stats):
     ctx.sync()
     s = stats.cpu().numpy()
     return {k: int(s[i]) for k, i in dci.STAT.items()}
+
+
+def assert_same_without_statistics(lanes, infer, logits):
+    """infer(out, stats) is a dci_infer_batches call that has run with statistics and left `logits`.  Without them the batches are closed
+    beside their gather, rows gathered (unless there are too many) or read in place: logits and every lane's blocks bit for bit the same."""
+    want = [blocks_to_host(ln.ctx, ln.blocks) for ln in lanes]
+    for fused in (0, 1):
+        again = torch.full_like(logits, float("nan"))
+        torch.cuda.synchronize()
+        for ln in lanes:
+            ln.ctx.set_option(dci.DCI_OPT_FUSED_INPUT, fused)
+            ln.ctx.timing_enable(["write_src"])
+        infer(again, None)
+        closings = sum(ln.ctx.timing_read()["write_src"][1] for ln in lanes)
+        assert closings == 0 or not fused
+        for ln, w in zip(lanes, want):
+            ln.ctx.timing_enable([])
+            got = blocks_to_host(ln.ctx, ln.blocks)
+            for k, v in w.items():
+                assert all(np.array_equal(a, b) for a, b in zip(got[k], v)) if isinstance(v, list) else np.array_equal(got[k], v)
+        assert torch.equal(again.view(torch.int32), logits.view(torch.int32))
+    for ln in lanes:
+        ln.ctx.set_option(dci.DCI_OPT_FUSED_INPUT, 0)

@@ -114,8 +114,9 @@ def test_full_scale(name):
     logits = torch.full((w.num_seeds, w.classes), float("nan"), dtype=torch.float32, device="cuda")
     stats = gu.new_stats()
     torch.cuda.synchronize()
-    dci.dci_infer_batches(lanes, g, cache, seeds_dev, w.batch_size, first, 4, w.fanouts, w.rng_seed, 0, ws, wn, bs,
-                          logits, stats)
+    infer = lambda out, stats: dci.dci_infer_batches(lanes, g, cache, seeds_dev, w.batch_size, first, 4, w.fanouts, w.rng_seed, 0, ws, wn,
+                                                     bs, out, stats)
+    infer(logits, stats)
     for ln in lanes:
         ln.ctx.sync()
     st = gu.stats_dict(ctx, stats)
@@ -151,3 +152,4 @@ def test_full_scale(name):
                                 + F4 * (tot["nodes"] - tot["feat_hits"]))
     _log(f"{name}: feature hit rate {tot['feat_hits'] / tot['nodes']:.4f}, adjacency edge hit rate "
          f"{tot['adj_hit_edges'] / max(1, tot['edges']):.4f}, host bytes per batch {st['bytes_host'] / 4 / 1e6:.1f} MB")
+    gu.assert_same_without_statistics(lanes, infer, logits)

@@ -142,8 +142,9 @@ def test_batches_in_flight_full_size(big):
     logits = torch.full((w.num_seeds, w.classes), float("nan"), dtype=torch.float32, device="cuda")
     stats = gu.new_stats()
     torch.cuda.synchronize()
-    dci.dci_infer_batches(lanes, g, cache, seeds_dev, w.batch_size, first, count, w.fanouts, w.rng_seed, 0, ws, wn, bs,
-                          logits, stats)
+    infer = lambda out, stats: dci.dci_infer_batches(lanes, g, cache, seeds_dev, w.batch_size, first, count, w.fanouts, w.rng_seed, 0, ws, wn,
+                                                     bs, out, stats)
+    infer(logits, stats)
     for ln in lanes:
         ln.ctx.sync()
     out = logits.cpu().numpy()
@@ -165,6 +166,7 @@ def test_batches_in_flight_full_size(big):
     st = gu.stats_dict(ctx, stats)
     assert st["edges_sampled"] == edges and st["adj_edge_hits"] > 0 and st["adj_edge_misses"] > 0
     assert st["feat_hits"] > 0 and st["feat_misses"] > 0
+    gu.assert_same_without_statistics(lanes, infer, logits)
 
 
 def test_element_granular_cache_full_size(big):
