@@ -44,7 +44,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3
 THREE_PART_PEAK_TFLOPS = 2500.0 / 8  # fp32 products as eight bf16 ones (k_sage_layer)
-PIN_LIMIT_BYTES = 60 * 10**9     # the GPU machines refuse page-locked allocations beyond 64 GiB in total
+PIN_LIMIT_BYTES = 60 * 10**9     # the machines used refuse page-locked allocations beyond 64 GiB in total
 
 
 def log(*a):
@@ -120,7 +120,7 @@ def main() -> int:
     torch.cuda.set_device(0)
     t0 = time.time()
     # Placement.  The graph and the feature matrix belong in pinned host memory (zero-copy misses over the host
-    # link).  A GPU machine pins at most 64 GiB, less than the two largest workloads need (70.7 / 81.5 GB), so for
+    # link).  The machines used pin at most 64 GiB, less than the two largest workloads need (70.7 / 81.5 GB), so for
     # those the feature matrix and the list-bound array stay pinned and the neighbour-id array is placed in HBM,
     # standing in for the host tier.
     place = args.placement

@@ -1,4 +1,4 @@
-"""Helpers shared by the GPU parity tests: move synthetic inputs to the GPU machine's memory and
+"""Helpers shared by the GPU parity tests: move synthetic inputs to the GPU's or pinned memory and
 bring results back as numpy arrays."""
 import numpy as np
 import torch

@@ -1,7 +1,7 @@
 """GPU parity at the full size of the two host-resident workloads ("huge": 111 M nodes / 1.6 B edges /
 57 GB of features, "skewed": 65 M nodes / 1.8 B edges / 67 GB of features).
 
-Placement: a GPU machine pins at most 64 GiB of host memory, less than graph + features of either workload.
+Placement: the machines used pin at most 64 GiB of host memory, less than graph + features of either workload.
 The feature matrix and the list-bound array (indptr) are in pinned host memory, so feature misses and the
 list bounds of adjacency misses cross the host link as in the paper's set-up; the neighbour-id array
 (indices) is placed in HBM, standing in for the host tier (the kernels dereference the same kind of mapped
